@@ -196,8 +196,10 @@ int rov_gemm(const void *A, const void *Bm, void *C, int M, int N, int K, int dt
 /* Tile width of the bf16 matrix-core GEMM kernel (the Table 1 GEMM column's
  * MMA-bound kernel), in output columns: 0 = chosen per call from the shape (the
  * default: the width that wastes least of the last round of workgroups over the
- * compute units), or one of 128, 160, 192, 224, 256 for every later call.  The
- * result is the same sum in the same order for every width.  rov_gemm_swiglu and
+ * compute units; or a smaller tile where that is done sooner), or one of 128, 160,
+ * 192, 224, 256 for every later call.  The result is the same sum in the same order
+ * for every width; the smaller tiles keep that order too, except that from
+ * K = 2048 on they may add partial sums over k.  rov_gemm_swiglu and
  * rov_gemm_swiglu_fp8 have two tile forms: 256 forces the wide one, 128 the narrow
  * one, other values leave their choice to the shape.  For experiments
  * and tests; process-wide.  Returns the previous value, or ROV_ERR_INVALID

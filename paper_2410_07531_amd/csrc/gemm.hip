@@ -33,8 +33,10 @@
 // the flop per byte; on random data under the power limit this shape sustains
 // 4.55 PFLOP/s in a register-only loop against 4.0 for 32x32x64).
 //
-// Everything else (fp32, [K,N] weights, K not a multiple of the tile depth)
-// takes a small LDS-tiled VALU kernel that is correct for any shape.
+// Outputs too small for these tiles, fp32, [K,N] weights and other row lengths take
+// the kernels of gemm_ring.hip; what those refuse (rows of an odd number of 16-bit
+// values or of bytes, matrices beyond 32-bit offsets) takes a small LDS-tiled VALU
+// kernel that is correct for any shape.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -833,8 +835,27 @@ int launch_gemm_epilogue(const void* A, const void* Bm, void* C, const void* R, 
     const float alpha = scaleA * scaleB;
     const bool tb = transB != 0;
     const int esz = dtype == ROV_BF16 ? 2 : 1;
+    const bool wide = dtype != ROV_F32 && tb && ((size_t)K * esz) % kRowBytes == 0 && (N % 4) == 0;   // the 256-row kernels take it
 
-    if (dtype != ROV_F32 && tb && ((size_t)K * esz) % kRowBytes == 0 && (N % 4) == 0) {
+    // The tiles of gemm_ring.hip where the 256-row kernels do not apply, or leave so much of the chip idle that the
+    // smaller tile is done sooner.  A width set by rov_set_gemm_tile_cols is a 256-row tile's.
+    if ((R == nullptr || epi == EPI_ADD) && !(wide && g_tile_cols.load() != 0)) {
+        double ring_ns = 0.0;
+        const int v = ring_variant(M, N, K, dtype, transB, wide, &ring_ns);
+        if (v >= 0) {
+            bool take = !wide;
+            if (wide) {
+                // one slot (128 bytes of k) of a 256 x 32*nj tile, measured like the times in gemm_ring.hip
+                const int nj = pick_tile_cols(M, N) / 32;
+                const double slot_ns = dtype == ROV_BF16 ? 890.0 + 130.0 * (nj - 4) : 970.0 + 133.0 * (nj - 4);
+                const long long tiles = (long long)((M + BM - 1) / BM) * ((N + 32 * nj - 1) / (32 * nj));
+                take = ring_ns < gemm_tiles_ns(tiles, (int)((size_t)K * esz / kRowBytes), slot_ns);
+            }
+            if (take) return launch_gemm_ring(v, A, Bm, C, R, M, N, K, alpha, stream);
+        }
+    }
+
+    if (wide) {
         // a 256-row operand panel is addressed with 32-bit byte offsets
         if ((unsigned long long)BM * (unsigned long long)K * (unsigned long long)esz > 0xFFFFFFFFull)
             return ROV_ERR_UNSUPPORTED;

@@ -73,6 +73,13 @@ int launch_gemm_residual(const void* A, const void* Bm, void* C, const void* R, 
 enum { EPI_ADD = 0, EPI_SILU_MUL = 1 };
 int launch_gemm_epilogue(const void* A, const void* Bm, void* C, const void* R, int epi, int M, int N, int K,
                          int dtype, int transB, float scaleA, float scaleB, hipStream_t stream);
+// gemm_ring.hip: the tile of a product that is best there (an index, or -1 if it takes none of its forms) and its estimated
+// time; same_order: only tiles that add in the order of the 256-row kernels for short sums.  gemm_tiles_ns: the
+// estimate both families of tiles are compared by.
+int ring_variant(int M, int N, int K, int dtype, int transB, bool same_order, double* ns);
+int launch_gemm_ring(int variant, const void* A, const void* W, void* C, const void* R, int M, int N, int K, float alpha,
+                     hipStream_t stream);
+double gemm_tiles_ns(long long tiles, int slots, double slot_ns);
 int launch_attention(const void* Q, const void* K, const void* V, void* O, int B, int H, int Hkv,
                      int S, int d, const int64_t strides[12], int dtype, int causal, float p,
                      const uint64_t* mask, uint64_t seed, uint64_t offset, hipStream_t stream,

@@ -1,0 +1,119 @@
+"""GPU parity of the small-tile GEMM kernels (gemm_ring.hip) at the sizes where they can go wrong.
+
+Every row reaches another tile or operand form: tiles of 32 to 192 rows, k split between the waves of a
+workgroup or not, [K, N] weights, rows that start on 16 or only on 4 bytes, a last slot of k that is
+partly filled, rows and columns past the edge, output rows that take no vector store.  Reference:
+the float64 oracle on sampled rows (first, last, tile edges), all columns.
+
+Bars: bf16 and fp8 6e-3 of the result's scale (fp32 accumulation and one rounding to bf16, 2^-9, with room
+for the maximum), fp32 1e-5 (sums of at most 4096 terms of like size: sqrt(4096) * 2^-24 = 4e-6).
+"""
+import numpy as np
+import pytest
+import torch
+
+from oracle import dense as OD
+from oracle import numerics as ON
+from paper_2410_07531_amd import binding as rov
+from paper_2410_07531_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # dtype, M, N, K, transB
+    ("bf16", 100, 4096, 2048, True),     # 64 x 32, four k parts
+    ("bf16", 250, 4096, 2112, True),     # 64 x 64, two k parts, two 128-byte parts per slot, odd number of parts
+    ("bf16", 333, 4096, 2048, True),     # 128 x 64
+    ("bf16", 500, 6144, 2176, True),     # 128 x 128
+    ("bf16", 1100, 4100, 2048, True),    # 192 x 128, ragged columns
+    ("bf16", 1000, 6144, 2048, True),    # 128 x 192
+    ("bf16", 70, 1000, 448, True),       # 64 x 64, one k part
+    ("bf16", 700, 4096, 1024, True),     # 128 x 128, one k part
+    ("bf16", 1, 4, 64, True),            # smallest
+    ("bf16", 129, 65, 8, True),          # one chunk of k, odd number of columns
+    ("bf16", 333, 1001, 1000, True),     # last slot partly filled, scalar stores
+    ("bf16", 65, 130, 102, True),        # rows on 4 bytes
+    ("bf16", 64, 64, 64, False),         # [K, N]: one tile of the smallest, one slot
+    ("bf16", 257, 4096, 1032, False),    # [K, N], 128 x 64, last slot of one chunk
+    ("bf16", 1000, 1000, 72, False),     # [K, N], ragged everywhere
+    ("bf16", 900, 6144, 256, False),     # [K, N], larger tiles
+    ("bf16", 3000, 4096, 256, False),    # [K, N], 192 x 128
+    ("bf16", 130, 98, 34, False),        # [K, N], rows on 4 bytes
+    ("fp8", 100, 4096, 512, True),       # 64 x 64
+    ("fp8", 333, 4096, 640, True),       # 128 x 64
+    ("fp8", 500, 8192, 384, True),       # 128 x 128
+    ("fp8", 77, 131, 144, True),         # last slot partly filled, scalar stores
+    ("f32", 256, 256, 256, True),        # 32 x 32, four k parts
+    ("f32", 1, 1, 1, True),
+    ("f32", 1000, 1024, 260, True),      # 64 x 64, last slot of one chunk
+    ("f32", 33, 47, 131, True),          # rows on 4 bytes
+    ("f32", 700, 1025, 513, True),       # rows on 4 bytes, 64 x 64
+    ("f32", 100, 36, 68, False),         # [K, N]
+    ("f32", 1024, 1024, 64, False),      # [K, N], 64 x 64
+    ("f32", 65, 33, 35, False),          # [K, N], rows on 4 bytes
+    ("f32", 1021, 1027, 67, False),
+]
+
+
+def _operands(dtype, M, N, K, transB):
+    rng = np.random.default_rng(M * 131 + N * 17 + K)
+    a, w = wl.gemm_operands(rng, M, K, N)
+    if not transB:
+        w = np.ascontiguousarray(w.T)
+    if dtype == "fp8":
+        A = torch.from_numpy(a * np.float32(16)).to(torch.float8_e4m3fn).view(torch.uint8)
+        W = torch.from_numpy(w * np.float32(256)).to(torch.float8_e4m3fn).view(torch.uint8)
+        return A.cuda(), W.cuda(), ON.e4m3_decode(A.numpy()), ON.e4m3_decode(W.numpy())
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    A, W = torch.from_numpy(a).to(dt), torch.from_numpy(w).to(dt)
+    return A.cuda(), W.cuda(), A.float().numpy().astype(np.float64), W.float().numpy().astype(np.float64)
+
+
+@pytest.mark.parametrize("dtype,M,N,K,transB", CASES)
+def test_small_tiles_match_oracle(dtype, M, N, K, transB):
+    print("gemm ring", dtype, M, N, K, transB, flush=True)
+    if dtype != "fp8":       # what an earlier workgroup left in LDS must not reach a partly filled slot
+        dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+        nan = torch.full((512, 512), float("nan"), dtype=dt, device="cuda")
+        rov.gemm(nan, nan, transB=transB)
+    A, W, a, w = _operands(dtype, M, N, K, transB)
+    odt = torch.float32 if dtype == "f32" else torch.bfloat16
+    # a frame of known values around the result: nothing outside it is written
+    frame = torch.full((M * N + 128,), 3.0, dtype=odt, device="cuda")
+    C = frame[64:64 + M * N].view(M, N)
+    rov.gemm(A, W, C=C, transB=transB, scaleA=0.5, scaleB=4.0)
+    torch.cuda.synchronize()
+    assert bool((frame[:64] == 3.0).all()) and bool((frame[64 + M * N:] == 3.0).all())
+    rows = sorted(set(r for r in (0, 1, 31, 32, 63, 64, 127, 128, 191, 192, 255, 256, M // 2, M - 2, M - 1) if 0 <= r < M))
+    ref = 2.0 * OD.gemm(a[rows], w, transB=transB)
+    got = C[rows].float().cpu().numpy().astype(np.float64)
+    err = float(np.max(np.abs(got - ref)) / np.max(np.abs(ref)))
+    assert err <= (1e-5 if dtype == "f32" else 6e-3), err
+
+
+@pytest.mark.parametrize("dtype,M,N,K", [("bf16", 300, 2048, 1024), ("bf16", 700, 4096, 512), ("fp8", 300, 2048, 4096),
+                                         ("fp8", 520, 8192, 1024)])
+def test_unsplit_small_tiles_give_the_256_row_kernels_bits(dtype, M, N, K):
+    print("gemm ring bits", dtype, M, N, K, flush=True)
+    A, W, _, _ = _operands(dtype, M, N, K, True)
+    C = rov.gemm(A, W)
+    prev = rov.set_gemm_tile_cols(128)
+    try:
+        C2 = rov.gemm(A, W)
+        torch.cuda.synchronize()
+    finally:
+        rov.set_gemm_tile_cols(prev)
+    assert torch.equal(C.view(torch.int16), C2.view(torch.int16))
+
+
+def test_fp32_product_keeps_infinities_and_nan_in_their_rows():
+    # a non-finite operand reaches the outputs of its own row or column only
+    A = torch.ones((70, 37), device="cuda")
+    W = torch.ones((45, 37), device="cuda")
+    A[3, 36] = float("inf")
+    W[7, 0] = float("nan")
+    C = rov.gemm(A, W)
+    exp = torch.full((70, 45), 37.0, device="cuda")
+    exp[3] = float("inf")
+    exp[:, 7] = float("nan")
+    assert torch.equal(torch.nan_to_num(C, nan=-1.0), torch.nan_to_num(exp, nan=-1.0))
