@@ -94,9 +94,8 @@ __device__ __forceinline__ float half_wave_sum(float v) {
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
-constexpr int BKV = 64;   // keys per tile = one mask word per query row
-
-template <int D>
+// BKV: keys per LDS tile
+template <int D, int BKV>
 struct Tile {
     static constexpr int kKRow = D * 2;                // bytes per K row in LDS
     static constexpr int kKBytes = BKV * kKRow;
@@ -133,12 +132,13 @@ __device__ __forceinline__ int swizzle_of_row(int row) {
 // meant to run under; the kernel places its one vmcnt(0) per tile itself.  M0 (the LDS base of
 // the transfer) is a reserved register that compiled code only sets right before its own uses.
 typedef int i32x4 __attribute__((ext_vector_type(4)));
-template <int D, int NW, bool VTILE>
+template <int D, int NW, bool VTILE, int BKV>
 struct KvTileLoad {
-    static constexpr int kChunks = Tile<D>::kChunks;
+    static constexpr int kChunks = Tile<D, BKV>::kChunks;
     static constexpr int kRowsPerInst = 64 / kChunks;          // 4 (D = 128) or 8 (D = 64)
     static constexpr int kInst = BKV / kRowsPerInst;           // 16 or 8 per tile
     static constexpr int kPerWave = kInst / NW;
+    static_assert(kPerWave * NW == kInst, "every wave loads the same share");
     uint32_t off[kPerWave];
     uint32_t row_bytes;
     i32x4 rsrc;
@@ -148,7 +148,7 @@ struct KvTileLoad {
         row_bytes = (uint32_t)tok_stride * 2u;
 #pragma unroll
         for (int i = 0; i < kPerWave; ++i) {
-            const int row = (wave + NW * i) * kRowsPerInst + rl;          // 0..63
+            const int row = (wave + NW * i) * kRowsPerInst + rl;          // 0..BKV-1
             const int chunk = pc ^ swizzle_of_row<D, VTILE>(row);
             off[i] = (uint32_t)row * row_bytes + (uint32_t)chunk * 16u;
         }
@@ -189,11 +189,19 @@ __device__ __forceinline__ bf16x4 lds_read_transposed(const char* p) {
 // NW waves per workgroup, each owning NQ*32 query rows.  (NQ, NW) = (2, 4) keeps one wave per
 // SIMD with K/V fragments reused for two query tiles; (1, 8) puts two waves on every SIMD so
 // that one wave's softmax VALU work runs under the other's MFMAs.
-template <int D, int NQ, int NW, int MODE, int R = 10, int BITS = 32>
+//
+// KS > 1: the NW waves are NW / KS query tiles times KS key parts.  Of every LDS tile of 32 * KS keys
+// (64 at least) a wave takes the 32 of its part; the KS partial results of a query tile (exponent reference, row
+// sum, output) meet in LDS at the end.  A short sequence has too few query tiles for the chip - 512 tokens
+// of 32 heads are 64 workgroups of 256 rows - and its time is the walk of one wave over the keys.
+template <int D, int NQ, int NW, int KS, int MODE, int R = 10, int BITS = 32>
 __global__ __launch_bounds__(NW * 64) void attn_bf16_kernel(const AttnParams p) {
-    constexpr int BQ = NW * 32 * NQ;   // query rows per workgroup
-    using T = Tile<D>;
-    constexpr int KS = D / 16;    // k-steps of the first product
+    constexpr int QW = NW / KS;        // query tiles per workgroup
+    constexpr int BQ = QW * 32 * NQ;   // query rows per workgroup
+    constexpr int NT = KS == 1 ? 2 : 1;   // 32-key subtiles per wave and LDS tile
+    constexpr int BKV = 32 * NT * KS;     // keys per LDS tile
+    using T = Tile<D, BKV>;
+    constexpr int KSTEPS = D / 16;   // k-steps of the first product
     constexpr int DVT = D / 32;   // dv tiles of the second product
     extern __shared__ __attribute__((aligned(1024))) char lds[];
 
@@ -220,16 +228,16 @@ __global__ __launch_bounds__(NW * 64) void attn_bf16_kernel(const AttnParams p) 
     }
     const int b = bh / p.H, h = bh % p.H;
     const int hk = h / (p.H / p.Hkv);
-    const int q0 = p.q_begin + qblk * BQ + wave * (32 * NQ);
+    const int kpart = wave % KS;
+    const int q0 = p.q_begin + qblk * BQ + (wave / KS) * (32 * NQ);
     const int q_end = p.q_end;
 
     const uint16_t* Qp = (const uint16_t*)p.Q + b * p.sq[0] + h * p.sq[2];
     const uint16_t* Kp = (const uint16_t*)p.K + b * p.sk[0] + hk * p.sk[2];
     const uint16_t* Vp = (const uint16_t*)p.V + b * p.sv[0] + hk * p.sv[2];
-    uint16_t* Op = (uint16_t*)p.O + b * p.so[0] + h * p.so[2];
 
     // Q fragments (second operand of K Q^T): lane holds query ql, features 16*ks + 8*half .. +7
-    bf16x8 qf[NQ][KS];
+    bf16x8 qf[NQ][KSTEPS];
     int qrow[NQ];
 #pragma unroll
     for (int n = 0; n < NQ; ++n) {
@@ -237,7 +245,7 @@ __global__ __launch_bounds__(NW * 64) void attn_bf16_kernel(const AttnParams p) 
         qrow[n] = q;
         q = q < q_end ? q : q_end - 1;
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks)
+        for (int ks = 0; ks < KSTEPS; ++ks)
             qf[n][ks] = *reinterpret_cast<const bf16x8*>(Qp + (int64_t)q * p.sq[1] + 16 * ks + 8 * half);
     }
 
@@ -277,8 +285,8 @@ __global__ __launch_bounds__(NW * 64) void attn_bf16_kernel(const AttnParams p) 
         mtile[n] = p.mask + ((((uint64_t)b * p.H + h) * (uint32_t)p.mask_nqt + (qt - (uint32_t)p.mask_qt0)) * Tt) * 16u;
     }
 
-    KvTileLoad<D, NW, false> kload;
-    KvTileLoad<D, NW, true> vload;
+    KvTileLoad<D, NW, false, BKV> kload;
+    KvTileLoad<D, NW, true, BKV> vload;
     kload.init(Kp, p.sk[1], S, wave, lane);
     vload.init(Vp, p.sv[1], S, wave, lane);
     const uint32_t lds_base = (uint32_t)(uintptr_t)(lptr_t)lds;
@@ -314,10 +322,12 @@ __global__ __launch_bounds__(NW * 64) void attn_bf16_kernel(const AttnParams p) 
             kload.load(kv0 + BKV, lds_base + (STAGE ^ 1) * T::kStage, wave);
             vload.load(kv0 + BKV, lds_base + (STAGE ^ 1) * T::kStage + T::kKBytes, wave);
         }
-        // ---- S^T = K Q^T for 64 keys x NQ*32 queries
-        f32x16 s[2][NQ];
+        const int kvw = kv0 + kpart * (32 * NT);   // this wave's keys: [kvw, kvw + 32 * NT)
+        const char* curk = cur + kpart * (32 * NT) * T::kKRow;
+        // ---- S^T = K Q^T for 32*NT keys x NQ*32 queries
+        f32x16 s[NT][NQ];
 #pragma unroll
-        for (int t = 0; t < 2; ++t)
+        for (int t = 0; t < NT; ++t)
 #pragma unroll
             for (int n = 0; n < NQ; ++n)
 #pragma unroll
@@ -326,26 +336,26 @@ __global__ __launch_bounds__(NW * 64) void attn_bf16_kernel(const AttnParams p) 
         // groups below pin that order (3 k-steps of reads, then per k-step its MFMAs followed by
         // the reads of the k-step kAhead further on), so the LDS latency is paid once per tile
         // and not once per k-step.
-        constexpr int kAhead = 3;
-        bf16x8 kf[KS][2];
+        constexpr int kAhead = NT == 2 ? 3 : 4;
+        bf16x8 kf[KSTEPS][NT];
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks)
+        for (int ks = 0; ks < KSTEPS; ++ks)
 #pragma unroll
-            for (int t = 0; t < 2; ++t)
+            for (int t = 0; t < NT; ++t)
                 kf[ks][t] = *reinterpret_cast<const bf16x8*>(
-                    cur + (32 * t + ql) * T::kKRow + (((2 * ks + half) ^ kswz) << 4));
+                    curk + (32 * t + ql) * T::kKRow + (((2 * ks + half) ^ kswz) << 4));
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks)
+        for (int ks = 0; ks < KSTEPS; ++ks)
 #pragma unroll
-            for (int t = 0; t < 2; ++t)
+            for (int t = 0; t < NT; ++t)
 #pragma unroll
                 for (int n = 0; n < NQ; ++n)
                     s[t][n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[ks][t], qf[n][ks], s[t][n], 0, 0, 0);
-        __builtin_amdgcn_sched_group_barrier(0x100, 2 * kAhead, 0);          // DS reads
+        __builtin_amdgcn_sched_group_barrier(0x100, NT * kAhead, 0);          // DS reads
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 2 * NQ, 0);          // MFMAs of k-step ks
-            if (ks + kAhead < KS) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+        for (int ks = 0; ks < KSTEPS; ++ks) {
+            __builtin_amdgcn_sched_group_barrier(0x008, NT * NQ, 0);          // MFMAs of k-step ks
+            if (ks + kAhead < KSTEPS) __builtin_amdgcn_sched_group_barrier(0x100, NT, 0);
         }
         // nothing below moves up into the first product: a scalar load of keep words between its
         // LDS reads would turn every wait for a fragment into a wait for that load as well (the
@@ -359,30 +369,31 @@ __global__ __launch_bounds__(NW * 64) void attn_bf16_kernel(const AttnParams p) 
         // lines were pulled into L2 one tile earlier by `warm` (a vector load whose value is
         // only folded into a sink), so the scalar loads return while the row maxima and
         // exponentials are being computed.
-        uint64_t mw[NQ][2][16];
+        uint64_t mw[NQ][NT][16];
+        const uint32_t kt0 = (uint32_t)(kvw >> 5);                           // first key tile of the wave
         if (MODE == MODE_MASK) {
 #pragma unroll
             for (int n = 0; n < NQ; ++n)
 #pragma unroll
-                for (int t = 0; t < 2; ++t) {
-                    uint32_t kt = (uint32_t)(2 * jt + t);
+                for (int t = 0; t < NT; ++t) {
+                    uint32_t kt = kt0 + (uint32_t)t;
                     kt = kt < Tt ? kt : Tt - 1;
                     const const_u64_ptr wp = (const_u64_ptr)(uintptr_t)(mtile[n] + (uint64_t)kt * 16u);
 #pragma unroll
                     for (int e = 0; e < 16; ++e) mw[n][t][e] = wp[e];
                 }
             sink ^= warm;                       // the previous warm-up load has long landed
-            // 64 lanes x 4 bytes = the 32 words of the next two key tiles (16 words if the tile
-            // row has a single tile); clamped so that it never leaves this query tile's row
-            uint32_t ktn = (uint32_t)(2 * jt + 2);
-            ktn = ktn + 1 < Tt ? ktn : (Tt >= 2 ? Tt - 2 : 0);
-            warm = reinterpret_cast<const uint32_t*>(mtile[0] + (uint64_t)ktn * 16u)[lane & (Tt >= 2 ? 63 : 31)];
+            // 32 * NT lanes x 4 bytes = the words of the wave's next NT key tiles (16 words if the tile row has a
+            // single tile); clamped so that it never leaves this query tile's row
+            uint32_t ktn = kt0 + (uint32_t)(BKV / 32);
+            ktn = ktn + NT <= Tt ? ktn : (Tt >= NT ? Tt - NT : 0);
+            warm = reinterpret_cast<const uint32_t*>(mtile[0] + (uint64_t)ktn * 16u)[lane & (Tt >= NT ? 32 * NT - 1 : 31)];
         }
 
         // ---- online softmax, dropout, P^T fragments
-        bf16x8 pf[NQ][4];
-        const bool tail = kv0 + BKV > S;
-        const bool diag = p.causal && (kv0 + BKV - 1 > q0);   // some key of the tile may exceed a query
+        bf16x8 pf[NQ][2 * NT];
+        const bool tail = kvw + 32 * NT > S;
+        const bool diag = p.causal && (kvw + 32 * NT - 1 > q0);   // some key may exceed a query
 #pragma unroll
         for (int n = 0; n < NQ; ++n) {
             // the maximum is taken on the raw scores (the scale is positive) and the scale is folded
@@ -390,16 +401,16 @@ __global__ __launch_bounds__(NW * 64) void attn_bf16_kernel(const AttnParams p) 
             float mx = -INFINITY;
             if (tail || diag) {   // wave-uniform: only the tiles on the diagonal and the last one
 #pragma unroll
-                for (int t = 0; t < 2; ++t)
+                for (int t = 0; t < NT; ++t)
 #pragma unroll
                     for (int e = 0; e < 16; ++e) {
-                        const int key = kv0 + 32 * t + 8 * (e >> 2) + 4 * half + (e & 3);
+                        const int key = kvw + 32 * t + 8 * (e >> 2) + 4 * half + (e & 3);
                         const bool ok = key < S && (!p.causal || key <= qrow[n]);
                         s[t][n][e] = ok ? s[t][n][e] : -INFINITY;
                     }
             }
 #pragma unroll
-            for (int t = 0; t < 2; ++t)
+            for (int t = 0; t < NT; ++t)
 #pragma unroll
                 for (int e = 0; e < 16; ++e) mx = fmaxf(mx, s[t][n][e]);
             // the other half-wave's maximum of the same query: a lane swap in the VALU (gfx950
@@ -419,8 +430,8 @@ __global__ __launch_bounds__(NW * 64) void attn_bf16_kernel(const AttnParams p) 
             m_run[n] = m_new;
             float sum = 0.0f;
 #pragma unroll
-            for (int t = 0; t < 2; ++t) {
-                uint32_t kt = (uint32_t)(2 * jt + t);
+            for (int t = 0; t < NT; ++t) {
+                uint32_t kt = kt0 + (uint32_t)t;
                 kt = kt < Tt ? kt : Tt - 1;        // a key tile past S: its scores are -inf already
 #pragma unroll
                 for (int e = 0; e < 16; ++e) {
@@ -472,9 +483,11 @@ __global__ __launch_bounds__(NW * 64) void attn_bf16_kernel(const AttnParams p) 
 #pragma unroll
                     for (int e = 0; e < 16; ++e) o[t][n][e] *= alpha;
             }
+            // (the keep words have been waited for: V fragments may be on their way from here)
+            if (MODE == MODE_MASK) __builtin_amdgcn_sched_barrier(0);
             // k-step u = 2*t + v of the second product takes registers 8*v .. 8*v+7 of tile t
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
+            for (int u = 0; u < 2 * NT; ++u) {
                 const int t = u >> 1, v8 = (u & 1) * 8;
                 uint32_t w[4];
 #pragma unroll
@@ -484,57 +497,139 @@ __global__ __launch_bounds__(NW * 64) void attn_bf16_kernel(const AttnParams p) 
         }
 
         // ---- O^T += V^T P^T
-        const char* vt = cur + T::kKBytes;
+        // MODE_MASK: V fragments are read kAheadV fragments before the MFMA that uses them (the groups below pin
+        // that order; left to itself the compiler reads a fragment, waits for it and issues its MFMA, sixteen LDS
+        // latencies in a row).  S = 16384, 32 heads, d = 128: 4136 -> 4025 us; 4 or 6 ahead are no faster.  Without
+        // keep words the other wave of the SIMD covers those latencies and the pinned order is 0.5 % slower.
+        const char* vt = curk + T::kKBytes;
+        constexpr int kAheadV = 2;
+        bf16x8 vf[2 * NT][DVT];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
+        for (int u = 0; u < 2 * NT; ++u)
 #pragma unroll
             for (int t = 0; t < DVT; ++t) {
                 // keys 16u + 4*half + 0..3 and 16u + 8 + 4*half + 0..3 of feature 32t + lane%32
                 const bf16x4 lo = lds_read_transposed(vt + (16 * u) * T::kKRow + vt_off[t]);
                 const bf16x4 hi = lds_read_transposed(vt + (16 * u + 8) * T::kKRow + vt_off[t]);
-                const bf16x8 vf = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+                vf[u][t] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+            }
+#pragma unroll
+        for (int u = 0; u < 2 * NT; ++u)
+#pragma unroll
+            for (int t = 0; t < DVT; ++t)
 #pragma unroll
                 for (int n = 0; n < NQ; ++n)
-                    o[t][n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pf[n][u], o[t][n], 0, 0, 0);
+                    o[t][n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[u][t], pf[n][u], o[t][n], 0, 0, 0);
+        if (MODE == MODE_MASK) {
+            __builtin_amdgcn_sched_group_barrier(0x100, 2 * kAheadV, 0);
+#pragma unroll
+            for (int i = 0; i < 2 * NT * DVT; ++i) {
+                __builtin_amdgcn_sched_group_barrier(0x008, NQ, 0);
+                if (i + kAheadV < 2 * NT * DVT) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
             }
         }
     };
-    for (int jt = 0; jt < ntiles; jt += 2) {
+    // Tiles in which some query of this wave admits some key of its part; in the workgroup's others (a causal
+    // workgroup's last ones, a part beyond S) the probabilities are zero: the wave only loads its share.
+    const int key_end = p.causal ? min(S, q0 + 32 * NQ) : S;
+    const int nwave = min(ntiles, max(0, (key_end - kpart * (32 * NT) + BKV - 1) / BKV));
+    for (int jt = 0; jt < nwave; jt += 2) {
         tile_step(jt, std::integral_constant<int, 0>{});
-        if (jt + 1 < ntiles) tile_step(jt + 1, std::integral_constant<int, 1>{});
+        if (jt + 1 < nwave) tile_step(jt + 1, std::integral_constant<int, 1>{});
+    }
+    for (int jt = nwave; jt < ntiles; ++jt) {
+        __builtin_amdgcn_s_waitcnt(0x0070);
+        __syncthreads();
+        if (jt + 1 < ntiles) {
+            const uint32_t at = lds_base + (uint32_t)((jt + 1) & 1) * T::kStage;
+            kload.load((jt + 1) * BKV, at, wave);
+            vload.load((jt + 1) * BKV, at + T::kKBytes, wave);
+        }
     }
 
     // the warm-up values only have to look used (no mask pattern makes this condition true
     // for a lane id >= 64)
     if (MODE == MODE_MASK && (sink ^ warm) == 0x9E3779B9u && lane == 1000) m_run[0] = 0.0f;
 
-    // ---- normalise, scale kept entries by 1/(1-p), store O (lane: query ql, 4 consecutive dv per e/4)
-#pragma unroll
-    for (int n = 0; n < NQ; ++n) {
-        const float l = half_wave_sum(l_run[n]);
-        const float f = l > 0.0f ? p.inv_keep / l : 0.0f;
-        if (qrow[n] < q_end && p.o_fp8) {
+    // ---- normalise, scale kept entries by 1/(1-p), store O (lane: query ql, 4 consecutive dv per register group)
+    // The output's parameters are read again here: held since the kernel's start they push the scalar registers of
+    // the loop (64 of them keep words) into spills.
+    typedef const __attribute__((address_space(4))) AttnParams* params_ptr;
+    params_ptr pe = (params_ptr)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(pe));
+    const int64_t so_b = pe->so[0], so_s = pe->so[1], so_h = pe->so[2];
+    uint8_t* const Oe = (uint8_t*)pe->O;
+    const int qe = pe->q_end, o_fp8 = pe->o_fp8;
+    const float inv_keep = pe->inv_keep, o_scale = o_fp8 ? pe->o_inv_scale : 1.0f;
+    auto store_group = [&](int n, int t, int g, float c0, float c1, float c2, float c3) {
+        if (qrow[n] >= qe) return;
+        if (o_fp8) {
             // the fp8 block quantises the attention output where it is produced (strides count bytes here)
-            uint8_t* orow = (uint8_t*)p.O + b * p.so[0] + h * p.so[2] + (int64_t)qrow[n] * p.so[1];
-            const float fq = f * p.o_inv_scale;
+            uint8_t* orow = Oe + b * so_b + h * so_h + (int64_t)qrow[n] * so_s;
+            *reinterpret_cast<uint32_t*>(orow + 32 * t + 8 * g + 4 * half) = pack_e4m3x4(c0, c1, c2, c3);   // o_scale is in the factors
+        } else {
+            uint16_t* orow = (uint16_t*)Oe + b * so_b + h * so_h + (int64_t)qrow[n] * so_s;
+            *reinterpret_cast<uint2*>(orow + 32 * t + 8 * g + 4 * half) = make_uint2(pack_bf16x2(c0, c1), pack_bf16x2(c2, c3));
+        }
+    };
+    if constexpr (KS == 1) {
+#pragma unroll
+        for (int n = 0; n < NQ; ++n) {
+            const float l = half_wave_sum(l_run[n]);
+            const float f = (l > 0.0f ? inv_keep / l : 0.0f) * o_scale;
 #pragma unroll
             for (int t = 0; t < DVT; ++t)
 #pragma unroll
                 for (int g = 0; g < 4; ++g)
-                    *reinterpret_cast<uint32_t*>(orow + 32 * t + 8 * g + 4 * half) =
-                        pack_e4m3x4(o[t][n][4 * g + 0] * fq, o[t][n][4 * g + 1] * fq, o[t][n][4 * g + 2] * fq,
-                                    o[t][n][4 * g + 3] * fq);
-        } else if (qrow[n] < q_end) {
-            uint16_t* orow = Op + (int64_t)qrow[n] * p.so[1];
+                    store_group(n, t, g, o[t][n][4 * g + 0] * f, o[t][n][4 * g + 1] * f, o[t][n][4 * g + 2] * f,
+                                o[t][n][4 * g + 3] * f);
+        }
+    } else {
+        static_assert(NQ == 1, "one query tile per wave");
+        // (reference, row sum) of every part, then the outputs on a common reference; register group x = (t, g) of
+        // a query tile is added up, parts in order, and stored by part x % KS
+        constexpr int NX = DVT * 4;
+        static_assert(QW * NX * (KS - 1) * 1024 <= 2 * T::kStage && NW * 64 * 8 <= 2 * T::kStage, "partial results fit the tiles' LDS");
+        float2* ml = reinterpret_cast<float2*>(lds);
+        __syncthreads();                                  // every wave has left the K / V tiles
+        ml[wave * 64 + lane] = make_float2(m_run[0], half_wave_sum(l_run[0]));
+        __syncthreads();
+        float m_all = -INFINITY, l = 0.0f;
+        float2 part[KS];
 #pragma unroll
-            for (int t = 0; t < DVT; ++t)
+        for (int k = 0; k < KS; ++k) {
+            part[k] = ml[((wave / KS) * KS + k) * 64 + lane];
+            m_all = fmaxf(m_all, part[k].x);
+        }
+        const float m_ref = m_all == -INFINITY ? 0.0f : m_all;
 #pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    uint2 v;
-                    v.x = pack_bf16x2(o[t][n][4 * g + 0] * f, o[t][n][4 * g + 1] * f);
-                    v.y = pack_bf16x2(o[t][n][4 * g + 2] * f, o[t][n][4 * g + 3] * f);
-                    *reinterpret_cast<uint2*>(orow + 32 * t + 8 * g + 4 * half) = v;
+        for (int k = 0; k < KS; ++k) l += part[k].y * fast_exp2(part[k].x - m_ref);
+        const float f = (l > 0.0f ? inv_keep / l : 0.0f) * o_scale * fast_exp2(m_run[0] - m_ref);
+        __syncthreads();
+        char* mine = lds + (wave / KS) * NX * (KS - 1) * 1024 + lane * 16;
+#pragma unroll
+        for (int x = 0; x < NX; ++x) {
+            const int t = x >> 2, g = x & 3, own = x % KS;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[t][0][4 * g + e] *= f;
+            if (kpart != own)
+                *reinterpret_cast<float4*>(mine + (x * (KS - 1) + (kpart < own ? kpart : kpart - 1)) * 1024) =
+                    make_float4(o[t][0][4 * g], o[t][0][4 * g + 1], o[t][0][4 * g + 2], o[t][0][4 * g + 3]);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int x = 0; x < NX; ++x) {
+            const int t = x >> 2, g = x & 3, own = x % KS;
+            if (kpart == own) {
+                float c[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+                for (int k = 0; k < KS; ++k) {
+                    float4 v = make_float4(o[t][0][4 * g], o[t][0][4 * g + 1], o[t][0][4 * g + 2], o[t][0][4 * g + 3]);
+                    if (k != own) v = *reinterpret_cast<const float4*>(mine + (x * (KS - 1) + (k < own ? k : k - 1)) * 1024);
+                    c[0] += v.x; c[1] += v.y; c[2] += v.z; c[3] += v.w;
                 }
+                store_group(0, t, g, c[0], c[1], c[2], c[3]);
+            }
         }
     }
 }
@@ -664,25 +759,25 @@ __global__ __launch_bounds__(256) void attn_generic_kernel(const AttnParams p) {
     }
 }
 
-template <int D, int NQ, int NW>
+template <int D, int NQ, int NW, int KS>
 int launch_bf16(const AttnParams& prm, int mode, hipStream_t stream) {
-    const int bq = NW * 32 * NQ;
+    const int bq = NW / KS * 32 * NQ;
     AttnParams prm2 = prm;
     prm2.nq = (prm.q_end - prm.q_begin + bq - 1) / bq;
     const long long nblocks = (long long)prm2.nq * prm.H * prm.B;
     if (nblocks > 0x7FFFFFFFLL) return ROV_ERR_UNSUPPORTED;
     const dim3 grid((unsigned)nblocks), block(NW * 64);
-    const int lds_bytes = 2 * Tile<D>::kStage;   // two K/V stages
-    void (*kern)(const AttnParams) = mode == MODE_NONE ? attn_bf16_kernel<D, NQ, NW, MODE_NONE>
-                                                       : attn_bf16_kernel<D, NQ, NW, MODE_MASK>;
+    const int lds_bytes = 2 * Tile<D, KS == 1 ? 64 : 32 * KS>::kStage;   // two K/V stages
+    void (*kern)(const AttnParams) = mode == MODE_NONE ? attn_bf16_kernel<D, NQ, NW, KS, MODE_NONE>
+                                                       : attn_bf16_kernel<D, NQ, NW, KS, MODE_MASK>;
     if (mode == MODE_FUSED) {   // the round count is a compile-time constant of the fused kernel
-        if (prm.bits == 16) { if (prm.rounds != 10) return ROV_ERR_UNSUPPORTED; kern = attn_bf16_kernel<D, NQ, NW, MODE_FUSED, 10, 16>; }
-        else if (prm.bits == 8) { if (prm.rounds != 10) return ROV_ERR_UNSUPPORTED; kern = attn_bf16_kernel<D, NQ, NW, MODE_FUSED, 10, 8>; }
+        if (prm.bits == 16) { if (prm.rounds != 10) return ROV_ERR_UNSUPPORTED; kern = attn_bf16_kernel<D, NQ, NW, KS, MODE_FUSED, 10, 16>; }
+        else if (prm.bits == 8) { if (prm.rounds != 10) return ROV_ERR_UNSUPPORTED; kern = attn_bf16_kernel<D, NQ, NW, KS, MODE_FUSED, 10, 8>; }
         else switch (prm.rounds) {
-            case 10: kern = attn_bf16_kernel<D, NQ, NW, MODE_FUSED, 10>; break;
-            case 7: kern = attn_bf16_kernel<D, NQ, NW, MODE_FUSED, 7>; break;
-            case 5: kern = attn_bf16_kernel<D, NQ, NW, MODE_FUSED, 5>; break;
-            case 3: kern = attn_bf16_kernel<D, NQ, NW, MODE_FUSED, 3>; break;
+            case 10: kern = attn_bf16_kernel<D, NQ, NW, KS, MODE_FUSED, 10>; break;
+            case 7: kern = attn_bf16_kernel<D, NQ, NW, KS, MODE_FUSED, 7>; break;
+            case 5: kern = attn_bf16_kernel<D, NQ, NW, KS, MODE_FUSED, 5>; break;
+            case 3: kern = attn_bf16_kernel<D, NQ, NW, KS, MODE_FUSED, 3>; break;
             default: return ROV_ERR_INVALID;
         }
     }
@@ -693,6 +788,35 @@ int launch_bf16(const AttnParams& prm, int mode, hipStream_t stream) {
     hipLaunchKernelGGL(kern, grid, block, lds_bytes, stream, prm2);
     ROV_LAUNCH_CHECK();
     return ROV_OK;
+}
+
+// Key parts of the matrix-core kernel (1, 2 or 4: workgroups of 256, 128 or 64 query rows).  A finer split
+// fills the chip where query tiles are few and evens out causal workgroups; it re-reads K / V and merges partial results:
+// with the chip full a workgroup of 128 (64) rows takes 0.556 (0.36) of the time of one of 256 rows at d = 128, 0.54 (0.295) at
+// d = 64 (4096 and 8192 tokens, 32 heads); causal, where the diagonal's share of a workgroup shrinks with its rows,
+// 0.62 (0.42) and 0.50 (0.30).  Estimated time: rounds of one workgroup per compute unit, for causal masks the longest
+// workgroup or the average load with a tenth for its uneven end, 1.3 us of start and merge a round.
+// Measured with 256 / 128 / 64 rows, mask mode, d = 128, us: 512 tokens x 32 heads 20.5 / 14.7 / 11.4; 1500 x 32
+// 46.8 / 57.0 / 57.5, causal 44.4 / 30.2 / 39.5; 2048 x 16 causal 56.5 / 35.8 / 30.4; 4096 x 32 causal 144 / 160 / 195.
+// Only what all launches over one problem share decides, so that row ranges and modes agree bit for bit.
+int attn_key_parts(int B, int H, int S, int d, bool causal) {
+    const double ncu = device_cu_count(), walk_us = (double)S / 2048.0 * (d == 128 ? 60.0 : 35.0);
+    const double rel_full[2][2] = {{0.54, 0.295}, {0.556, 0.36}}, rel_causal[2][2] = {{0.50, 0.30}, {0.62, 0.42}};
+    int best = 1;
+    double best_us = 0.0;
+    for (int i = 0; i < 3; ++i) {
+        const int rows = 256 >> i, nq = (S + rows - 1) / rows;
+        const double n = (double)nq * B * H, rounds = ceil(n / ncu);
+        double load = rounds;
+        if (causal) {
+            load = n / ncu * 0.5 * (1.0 + 1.0 / nq);
+            load = load > 1.0 ? load + 0.1 : 1.0;
+        }
+        const double rel = i == 0 ? 1.0 : (causal ? rel_causal : rel_full)[d == 128][i - 1];
+        const double us = walk_us * rel * load + 1.3 * rounds;
+        if (i == 0 || us < best_us) { best = 1 << i; best_us = us; }
+    }
+    return best;
 }
 
 template <typename TT>
@@ -794,10 +918,17 @@ int launch_attention_rows(const void* Q, const void* K, const void* V, void* O, 
             if (!ok) return ROV_ERR_UNSUPPORTED;
         }
         if (ok) {
-            // 8 waves x 32 query rows: two waves per SIMD (measured 1.5x faster than 4 waves x 64
+            // 8 waves of 32 query rows: two waves per SIMD (measured 1.5x faster than 4 waves x 64
             // rows at S = 16384: 905 vs 602 TFLOP/s without dropout)
-            if (d == 128) return launch_bf16<128, 1, 8>(prm, mode, stream);
-            return launch_bf16<64, 1, 8>(prm, mode, stream);
+            const int ks = attn_key_parts(B, H, S, d, causal != 0);
+            if (d == 128) {
+                if (ks == 4) return launch_bf16<128, 1, 8, 4>(prm, mode, stream);
+                if (ks == 2) return launch_bf16<128, 1, 8, 2>(prm, mode, stream);
+                return launch_bf16<128, 1, 8, 1>(prm, mode, stream);
+            }
+            if (ks == 4) return launch_bf16<64, 1, 8, 4>(prm, mode, stream);
+            if (ks == 2) return launch_bf16<64, 1, 8, 2>(prm, mode, stream);
+            return launch_bf16<64, 1, 8, 1>(prm, mode, stream);
         }
     }
     if (prm.o_fp8) return ROV_ERR_UNSUPPORTED;   // the e4m3 output exists in the matrix-core kernel only
