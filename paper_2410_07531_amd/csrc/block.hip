@@ -81,40 +81,50 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const uint16_t* __restrict
 // Rotary embedding in place on the first `nheads` heads of each token row of a
 // [tokens, row_elems] buffer: pair (2t, 2t+1) of token position s is rotated by
 // s * theta^(-2t/d).  The angle is formed and reduced modulo 2*pi in double so
-// that long sequences keep fp32-accurate sines.  A thread owns four pairs (8
-// elements, 16 bytes) of one token and walks over the heads, which all turn by
-// the same angles: the sines are computed once per token, not once per head.
+// that long sequences keep fp32-accurate sines.  A workgroup owns TPB tokens: its threads
+// form the tokens' d/2 sines once, into LDS, and then walk over the rows' heads, 16 contiguous
+// bytes a thread.  Bound: 2 x 2 bytes per element from memory at many tokens (16384 x 40 heads x
+// 128: 63 us, 5.3 TB/s); at few tokens the latency of the sines, which one thread per four pairs and
+// all heads left to 32 workgroups at 512 tokens (19 us; a workgroup per token: 5 us).
+constexpr int kRopeMaxPairs = 128;
+template <int TPB>
 __global__ __launch_bounds__(256) void rope_kernel(uint16_t* __restrict__ buf, int64_t row_elems,
                                                    int S, int nheads, int d, double log2_theta,
-                                                   int64_t total_quads) {
+                                                   int64_t tokens) {
+    __shared__ float sn[TPB][kRopeMaxPairs], cs[TPB][kRopeMaxPairs];
     __builtin_amdgcn_s_setprio(3);
-    const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (idx >= total_quads) return;
-    const int quads_per_head = d / 8;
-    const int qd = (int)(idx % quads_per_head);
-    const int64_t token = idx / quads_per_head;
-    const int pos = (int)(token % S);
-    float sn[4], cs[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int t = qd * 4 + i;
+    const int64_t token0 = (int64_t)blockIdx.x * TPB;
+    const int pairs = d / 2;
+    for (int i = threadIdx.x; i < TPB * pairs; i += 256) {
+        const int tk = i / pairs, t = i - tk * pairs;
+        const int pos = (int)((token0 + tk) % S);
         const double inv_freq = exp2(-2.0 * (double)t / (double)d * log2_theta);
         double ang = (double)pos * inv_freq;
         ang -= 6.283185307179586476925 * rint(ang * 0.15915494309189533577);
-        sincosf((float)ang, &sn[i], &cs[i]);
+        sincosf((float)ang, &sn[tk][t], &cs[tk][t]);
     }
-    uint16_t* ptr = buf + token * row_elems + qd * 8;
-#pragma unroll 4
-    for (int head = 0; head < nheads; ++head, ptr += d) {
-        const uint4 v = *reinterpret_cast<const uint4*>(ptr);
-        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-        uint32_t o[4];
+    __syncthreads();
+    const int per_token = nheads * d / 8, quads_per_head = d / 8;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const float xe = lo_f(w[i]), xo = hi_f(w[i]);
-            o[i] = pack2(xe * cs[i] - xo * sn[i], xe * sn[i] + xo * cs[i]);
+    for (int tk = 0; tk < TPB; ++tk) {
+        if (token0 + tk >= tokens) return;
+        uint16_t* row = buf + (token0 + tk) * row_elems;
+#pragma unroll 4
+        for (int i = threadIdx.x; i < per_token; i += 256) {
+            const int qd = i % quads_per_head;
+            const uint4 v = *reinterpret_cast<const uint4*>(row + i * 8);
+            const float4 s4 = *reinterpret_cast<const float4*>(&sn[tk][qd * 4]);
+            const float4 c4 = *reinterpret_cast<const float4*>(&cs[tk][qd * 4]);
+            const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+            const float s[4] = {s4.x, s4.y, s4.z, s4.w}, c[4] = {c4.x, c4.y, c4.z, c4.w};
+            uint32_t o[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const float xe = lo_f(w[j]), xo = hi_f(w[j]);
+                o[j] = pack2(xe * c[j] - xo * s[j], xe * s[j] + xo * c[j]);
+            }
+            *reinterpret_cast<uint4*>(row + i * 8) = make_uint4(o[0], o[1], o[2], o[3]);
         }
-        *reinterpret_cast<uint4*>(ptr) = make_uint4(o[0], o[1], o[2], o[3]);
     }
 }
 
@@ -141,12 +151,13 @@ int launch_rmsnorm_fp8(const void* x, const void* weight, void* y8, int64_t rows
 
 int launch_rope(void* buf, int64_t tokens, int64_t row_elems, int S, int nheads, int d, float theta,
                 hipStream_t stream) {
-    if (tokens <= 0 || nheads <= 0 || (d % 8) != 0 || theta <= 0.0f) return ROV_ERR_UNSUPPORTED;
-    const int64_t quads = tokens * (d / 8);            // one thread per token and four pairs, all heads
-    const int64_t blocks = (quads + 255) / 256;
+    if (tokens <= 0 || nheads <= 0 || (d % 8) != 0 || d > 2 * kRopeMaxPairs || theta <= 0.0f) return ROV_ERR_UNSUPPORTED;
+    // four tokens a workgroup (256 threads, d/2 <= 64 sines a token) while that still fills the chip eightfold
+    const int tpb = tokens >= (int64_t)device_cu_count() * 32 ? 4 : 1;
+    const int64_t blocks = (tokens + tpb - 1) / tpb;
     if (blocks > 0x7FFFFFFF) return ROV_ERR_UNSUPPORTED;
-    hipLaunchKernelGGL(rope_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, (uint16_t*)buf,
-                       row_elems, S, nheads, d, log2((double)theta), quads);
+    hipLaunchKernelGGL(tpb == 4 ? rope_kernel<4> : rope_kernel<1>, dim3((unsigned)blocks), dim3(256), 0, stream,
+                       (uint16_t*)buf, row_elems, S, nheads, d, log2((double)theta), tokens);
     ROV_LAUNCH_CHECK();
     return ROV_OK;
 }
