@@ -24,7 +24,8 @@
 // with buffer loads that write LDS (two stages, the next tile in flight while
 // the current one is used).
 //
-// Any other case (fp32, other head dimensions) takes a small one-wave-per-row
+// fp32 with head dimensions up to 128 has a matrix-core kernel of its own (attn_f32_kernel).  Any other
+// case (other head dimensions, unaligned rows) takes a small one-wave-per-row
 // kernel that is correct for every shape.
 #include <hip/hip_runtime.h>
 
@@ -70,6 +71,7 @@ typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) void* lptr_t;
 
 __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
@@ -634,6 +636,247 @@ __global__ __launch_bounds__(NW * 64) void attn_bf16_kernel(const AttnParams p) 
     }
 }
 
+// ------------------------------------------------------------------ fp32 kernel
+// fp32, head dimension d a multiple of 8 with DP - 32 < d <= DP, on the fp32 matrix instructions (32x32x2).  Transposed like the
+// bf16 kernel (S^T = K Q^T, O^T = V^T P^T; a lane owns one query), so the score registers are the second
+// product's operand as they stand and a mask word is one register's lane predicate.  A workgroup owns 32 query
+// rows; its NW waves take every NW-th tile of 32 keys and merge their (maximum, sum, output) in LDS at the end:
+// fp32 sequences are short, and without the split a wave's walk over the keys is the whole time.  K and V
+// go straight from global memory into the operand registers (every byte is used by one wave of the workgroup
+// only); a lane's K fragment is 16 bytes of a row, a V fragment 128 contiguous bytes per half-wave.
+// Bound: matrix cores at long sequences (4 flop per score and feature at 157 TFLOP/s), one tile's chain of load,
+// product, softmax, product at short ones.  Before it the one-row-per-wave kernel below did this: 1024 tokens x 8 heads x
+// 64 features 331 us with a stored mask, now 27 (4096 tokens: 4728, 301 = 114 TFLOP/s).
+template <int DP, int NW, int MODE, int BITS>
+__global__ __launch_bounds__(NW * 64) void attn_f32_kernel(const AttnParams p) {
+    constexpr int KC = DP / 8;     // chunks of 8 features: the k range of four MFMAs
+    constexpr int DVT = DP / 32;   // feature tiles
+    extern __shared__ __attribute__((aligned(1024))) char lds[];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int ql = lane & 31, half = lane >> 5;
+    const int S = p.S, d = p.d;
+    int qblk, bh;   // all query tiles of a (batch, head) on one XCD, heaviest first when causal
+    {
+        const int pid = blockIdx.x, G = p.B * p.H;
+        if ((G & 7) == 0) {
+            const int xcd = pid & 7, j = pid >> 3, gpx = G >> 3;
+            qblk = j / gpx;
+            bh = (j % gpx) * 8 + xcd;
+        } else {
+            qblk = pid / G;
+            bh = pid % G;
+        }
+        if (p.causal) qblk = p.nq - 1 - qblk;
+    }
+    const int b = bh / p.H, h = bh % p.H;
+    const int hk = h / (p.H / p.Hkv);
+    const int q0 = p.q_begin + qblk * 32, qrow = q0 + ql;
+    const float* Qp = (const float*)p.Q + b * p.sq[0] + h * p.sq[2] + (int64_t)min(qrow, p.q_end - 1) * p.sq[1];
+    // K and V of this (batch, kv head) as buffer resources over the rows [0, S): lane offset plus tile row, no
+    // 64-bit address per register, and rows at or beyond S read as zeros
+    const uint32_t krow = (uint32_t)p.sk[1] * 4u, vrow = (uint32_t)p.sv[1] * 4u;
+    const __amdgpu_buffer_rsrc_t kres = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<float*>((const float*)p.K + b * p.sk[0] + hk * p.sk[2]), 0, (int)((uint32_t)(S - 1) * krow + (uint32_t)d * 4u), 0x00020000);
+    const __amdgpu_buffer_rsrc_t vres = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<float*>((const float*)p.V + b * p.sv[0] + hk * p.sv[2]), 0, (int)((uint32_t)(S - 1) * vrow + (uint32_t)d * 4u), 0x00020000);
+
+    // features 8c + 4*half .. +3 of the lane's row; chunks at or beyond d are zeros (an offset outside the resource)
+    f32x4 qf[KC], kf[KC];
+#pragma unroll
+    for (int c = 0; c < KC; ++c)
+        qf[c] = 8 * c < d ? *reinterpret_cast<const f32x4*>(Qp + 8 * c + 4 * half) : f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    const uint32_t koff = (uint32_t)ql * krow + (uint32_t)half * 16u;
+    auto load_k = [&](int kv0) {
+#pragma unroll
+        for (int c = 0; c < KC; ++c)
+            kf[c] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(
+                kres, koff + (8 * c < d ? 32u * c : 0x80000000u), (uint32_t)kv0 * krow, 0));
+    };
+
+    const uint32_t Tt = (uint32_t)p.W;
+    const uint32_t qt = (uint32_t)q0 >> 5;
+    const uint64_t wtile = (((uint64_t)bh * Tt + qt) * Tt) * 16u;   // words of tile (qt, 0) in the whole mask
+    const uint64_t* mtile = p.mask + (((uint64_t)bh * (uint32_t)p.mask_nqt + (qt - (uint32_t)p.mask_qt0)) * Tt) * 16u;
+
+    f32x16 o[DVT];
+#pragma unroll
+    for (int t = 0; t < DVT; ++t)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) o[t][e] = 0.0f;
+    float m_run = -INFINITY, l_run = 0.0f;
+
+    uint32_t voff[DVT];
+#pragma unroll
+    for (int t = 0; t < DVT; ++t) voff[t] = (uint32_t)(4 * half) * vrow + (uint32_t)min(32 * t + ql, d - 1) * 4u;
+    const int kv_end = p.causal ? min(S, q0 + 32) : S;
+    const int nkt = (kv_end + 31) / 32;
+    if (wave < nkt) load_k(32 * wave);
+#pragma unroll 1
+    for (int kt = wave; kt < nkt; kt += NW) {
+        const int kv0 = 32 * kt;
+        // V: register e of feature tile t is the lane's feature 32t + ql of key kv0 + 8*(e/4) + 4*half + e%4, the key
+        // of score register e.  Features beyond d repeat the last one (their outputs are not stored); keys beyond S are zeros.
+        float vf[DVT][16];
+#pragma unroll
+        for (int e = 0; e < 16; ++e)
+#pragma unroll
+            for (int t = 0; t < DVT; ++t)
+                vf[t][e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
+                    vres, voff[t], (uint32_t)(kv0 + 8 * (e >> 2) + (e & 3)) * vrow, 0));
+        uint64_t mw[16];
+        if (MODE == MODE_MASK) {
+            const const_u64_ptr wp = (const_u64_ptr)(uintptr_t)(mtile + (uint64_t)kt * 16u);
+#pragma unroll
+            for (int e = 0; e < 16; ++e) mw[e] = wp[e];
+        }
+        f32x16 s;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) s[e] = 0.0f;
+#pragma unroll
+        for (int c = 0; c < KC; ++c)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) s = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[c][e], qf[c][e], s, 0, 0, 0);
+        if (kt + NW < nkt) load_k(kv0 + 32 * NW);
+
+        const bool edge = kv0 + 32 > S || (p.causal && kv0 + 31 > q0);   // some score is not admissible
+        if (edge) {
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                const int key = kv0 + 8 * (e >> 2) + 4 * half + (e & 3);
+                s[e] = key < S && (!p.causal || key <= qrow) ? s[e] : -INFINITY;
+            }
+        }
+        float mx = s[0];
+#pragma unroll
+        for (int e = 1; e < 16; ++e) mx = fmaxf(mx, s[e]);
+        mx = half_wave_max(mx) * p.scale_log2;
+        const float m_new = fmaxf(m_run, mx);
+        const float m_safe = m_new == -INFINITY ? 0.0f : m_new;
+        const float alpha = fast_exp2(m_run - m_safe);
+        m_run = m_new;
+        float sum = 0.0f;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+            s[e] = fast_exp2(__builtin_fmaf(s[e], p.scale_log2, -m_safe));
+            sum += s[e];   // the normaliser counts dropped entries too
+        }
+        if (MODE == MODE_MASK) {
+#pragma unroll
+            for (int e = 0; e < 16; ++e) s[e] = __builtin_amdgcn_inverse_ballot_w64(mw[e]) ? s[e] : 0.0f;
+        }
+        if (MODE == MODE_FUSED) {
+            constexpr int NF = 32 / BITS, E = 4 * NF;   // fields per output word, mask words per call (see attn_bf16_kernel)
+            const uint64_t g0 = (wtile + (uint64_t)kt * 16u) / (uint32_t)E;
+#pragma unroll
+            for (int c = 0; c < 16 / E; ++c) {
+                const uint64_t n = p.offset + 64u * (g0 + (uint64_t)c) + (uint64_t)lane;
+                uint32_t x[4];
+                if (p.rounds == 10) philox4x32<10>((uint32_t)n, (uint32_t)(n >> 32), 0u, 0u, p.k0, p.k1, x);
+                else philox4x32_dyn(p.rounds, (uint32_t)n, (uint32_t)(n >> 32), 0u, 0u, p.k0, p.k1, x);
+#pragma unroll
+                for (int f = 0; f < NF; ++f)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        bool keep;
+                        if (BITS == 32) keep = x[r] <= p.t_minus_1;
+                        else keep = ((x[r] >> (BITS * f)) & ((1u << (BITS & 31)) - 1u)) < p.tb;
+                        s[E * c + 4 * f + r] = keep ? s[E * c + 4 * f + r] : 0.0f;
+                    }
+            }
+        }
+        l_run = l_run * alpha + sum;
+#pragma unroll
+        for (int t = 0; t < DVT; ++t)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) o[t][e] *= alpha;
+        // On the diagonal a probability of an inadmissible key is zero, but zero times a non-finite value is
+        // not: such a tile (never, in ordinary data) takes its keys one by one, each added where it is admissible.
+        bool finite = true;
+        if (edge) {
+#pragma unroll
+            for (int t = 0; t < DVT; ++t)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) finite = finite && fabsf(vf[t][e]) < INFINITY;
+            finite = __builtin_amdgcn_ballot_w64(!finite) == 0ull;
+        }
+        if (finite) {
+#pragma unroll
+            for (int e = 0; e < 16; ++e)
+#pragma unroll
+                for (int t = 0; t < DVT; ++t) o[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(vf[t][e], s[e], o[t], 0, 0, 0);
+        } else {
+#pragma unroll 1
+            for (int k = 0; k < 32; ++k) {
+                const int key = kv0 + k;
+                f32x16 one[DVT];
+#pragma unroll
+                for (int t = 0; t < DVT; ++t)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) one[t][e] = 0.0f;
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    const bool here = 8 * (e >> 2) + 4 * half + (e & 3) == k;
+                    const float pe = here ? s[e] : 0.0f;
+#pragma unroll
+                    for (int t = 0; t < DVT; ++t)
+                        one[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(here ? vf[t][e] : 0.0f, pe, one[t], 0, 0, 0);
+                }
+                const bool adm = key < S && (!p.causal || key <= qrow);
+#pragma unroll
+                for (int t = 0; t < DVT; ++t)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) o[t][e] += adm ? one[t][e] : 0.0f;
+            }
+        }
+    }
+
+    // the waves' partial results on a common maximum; register group x = (t, g) is added up, waves in order, and
+    // stored by wave x % NW
+    constexpr int NX = DVT * 4;
+    static_assert(NX % NW == 0 || NW % NX == 0, "groups are dealt out evenly");
+    __syncthreads();
+    float2* ml = reinterpret_cast<float2*>(lds);
+    ml[wave * 64 + lane] = make_float2(m_run, half_wave_sum(l_run));
+    __syncthreads();
+    float m_all = -INFINITY, l = 0.0f;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) m_all = fmaxf(m_all, ml[w * 64 + lane].x);
+    const float m_ref = m_all == -INFINITY ? 0.0f : m_all;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) l += ml[w * 64 + lane].y * fast_exp2(ml[w * 64 + lane].x - m_ref);
+    // (a row whose scores are all -infinity has no softmax: NaN)
+    const float norm = m_all == -INFINITY ? __uint_as_float(0x7FC00000u) : l > 0.0f ? p.inv_keep / l : 0.0f;
+    const float f = norm * fast_exp2(m_run - m_ref);
+    __syncthreads();
+#pragma unroll
+    for (int x = 0; x < NX; ++x) {
+        const int t = x >> 2, g = x & 3, own = x % NW;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[t][4 * g + e] *= f;
+        if (wave != own)
+            *reinterpret_cast<float4*>(lds + ((x * (NW - 1) + (wave < own ? wave : wave - 1)) * 64 + lane) * 16) =
+                make_float4(o[t][4 * g], o[t][4 * g + 1], o[t][4 * g + 2], o[t][4 * g + 3]);
+    }
+    __syncthreads();
+    float* orow = (float*)p.O + b * p.so[0] + h * p.so[2] + (int64_t)qrow * p.so[1];
+#pragma unroll
+    for (int x = 0; x < NX; ++x) {
+        const int t = x >> 2, g = x & 3, own = x % NW;
+        const int feat = 32 * t + 8 * g + 4 * half;
+        if (wave == own) {
+            float4 c = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+#pragma unroll
+            for (int w = 0; w < NW; ++w) {
+                float4 v = make_float4(o[t][4 * g], o[t][4 * g + 1], o[t][4 * g + 2], o[t][4 * g + 3]);
+                if (w != own) v = *reinterpret_cast<const float4*>(lds + ((x * (NW - 1) + (w < own ? w : w - 1)) * 64 + lane) * 16);
+                c.x += v.x; c.y += v.y; c.z += v.z; c.w += v.w;
+            }
+            if (qrow < p.q_end && feat < d) *reinterpret_cast<float4*>(orow + feat) = c;
+        }
+    }
+}
+
 // ------------------------------------------------------------------ generic kernel
 // One wave per query row, keys in chunks of 256 with an online softmax; any dtype / head
 // dimension up to 256.  Correct for every shape; used for fp32 and odd head dimensions.
@@ -819,6 +1062,29 @@ int attn_key_parts(int B, int H, int S, int d, bool causal) {
     return best;
 }
 
+// Waves of a workgroup of the fp32 kernel: eight at up to 64 features, four above (their registers).
+template <int DP, int NW>
+int launch_f32(const AttnParams& prm, int mode, hipStream_t stream) {
+    AttnParams prm2 = prm;
+    prm2.nq = (prm.q_end - prm.q_begin + 31) / 32;
+    const long long nblocks = (long long)prm2.nq * prm.H * prm.B;
+    if (nblocks > 0x7FFFFFFFLL) return ROV_ERR_UNSUPPORTED;
+    void (*kern)(const AttnParams) = mode == MODE_NONE   ? attn_f32_kernel<DP, NW, MODE_NONE, 32>
+                                     : mode == MODE_MASK ? attn_f32_kernel<DP, NW, MODE_MASK, 32>
+                                     : prm.bits == 32    ? attn_f32_kernel<DP, NW, MODE_FUSED, 32>
+                                     : prm.bits == 16    ? attn_f32_kernel<DP, NW, MODE_FUSED, 16>
+                                                         : attn_f32_kernel<DP, NW, MODE_FUSED, 8>;
+    const int lds_bytes = DP / 8 * (NW - 1) * 1024;
+    static_assert(DP / 8 * (NW - 1) * 1024 >= NW * 512, "the (maximum, sum) exchange fits");
+    {
+        const int rc = set_max_dynamic_lds((const void*)kern, lds_bytes);
+        if (rc != ROV_OK) return rc;
+    }
+    hipLaunchKernelGGL(kern, dim3((unsigned)nblocks), dim3(NW * 64), lds_bytes, stream, prm2);
+    ROV_LAUNCH_CHECK();
+    return ROV_OK;
+}
+
 template <typename TT>
 int launch_generic(const AttnParams& prm, int mode, hipStream_t stream) {
     const dim3 grid((unsigned)((prm.q_end - prm.q_begin + 3) / 4), (unsigned)prm.H, (unsigned)prm.B), block(256);
@@ -930,6 +1196,18 @@ int launch_attention_rows(const void* Q, const void* K, const void* V, void* O, 
             if (ks == 2) return launch_bf16<64, 1, 8, 2>(prm, mode, stream);
             return launch_bf16<64, 1, 8, 1>(prm, mode, stream);
         }
+    }
+    if (dtype == ROV_F32 && d <= 128 && d % 8 == 0) {
+        // 16-byte accesses to rows of Q, K and O
+        bool ok = aligned(Q, 16) && aligned(K, 16) && aligned(O, 16);
+        for (int i = 0; i < 12; ++i) ok = ok && (i / 3 == 2 || strides[i] % 4 == 0);
+        // K / V of one (batch, kv head) are addressed through a buffer resource: byte offsets below 2^31
+        for (int t = 4; t <= 7; t += 3)
+            ok = ok && strides[t] >= 0 && (uint64_t)(S + 31) * (uint64_t)strides[t] * 4u + 4u * (uint64_t)d < (1ull << 31);
+        if (ok && d <= 32) return launch_f32<32, 8>(prm, mode, stream);
+        if (ok && d <= 64) return launch_f32<64, 8>(prm, mode, stream);
+        if (ok && d <= 96) return launch_f32<96, 4>(prm, mode, stream);
+        if (ok) return launch_f32<128, 4>(prm, mode, stream);
     }
     if (prm.o_fp8) return ROV_ERR_UNSUPPORTED;   // the e4m3 output exists in the matrix-core kernel only
     if (dtype == ROV_BF16) return launch_generic<uint16_t>(prm, mode, stream);

@@ -1,0 +1,90 @@
+"""GPU parity of the fp32 attention kernel on the matrix instructions.
+
+Sizes at which it can go wrong: one key, one query, tiles of 32 partly filled, fewer key tiles than waves,
+head dimensions that fill a feature tile, a part of one, or several; causal and not; grouped keys; strided
+views.  Reference: the float64 oracle; bar 1e-4 of the result's scale (hardware exp2, fp32 sums).
+"""
+import numpy as np
+import pytest
+import torch
+
+from oracle import dense as OD
+from oracle import philox as OP
+from paper_2410_07531_amd import binding as rov
+from paper_2410_07531_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+TOL = 1e-4
+
+
+def _err(got, ref):
+    # (a fully dropped result is all zeros on both sides)
+    return float(np.max(np.abs(got.double().cpu().numpy() - ref)) / max(np.max(np.abs(ref)), 1e-30))
+
+
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("B,S,H,Hkv,d", [
+    (1, 1, 1, 1, 8), (1, 33, 2, 1, 32), (2, 65, 8, 4, 40), (1, 300, 4, 2, 64), (1, 97, 3, 3, 80), (1, 70, 2, 2, 96),
+    (2, 129, 2, 1, 128), (1, 100, 2, 2, 104),
+])
+def test_fp32_matches_oracle(B, S, H, Hkv, d, causal):
+    print("attn fp32", B, S, H, Hkv, d, causal, flush=True)
+    p, seed, offset = 0.2, wl.SEED, 2**32 - 200        # call numbers carry into the second counter word
+    q, k, v = wl.qkv(np.random.default_rng(S + d), B, S, H, Hkv, d)
+    Q, K, V = (torch.from_numpy(x).cuda() for x in (q, k, v))
+    keep = OP.unpack_keep(OP.dropout_mask(seed, offset, B, H, S, p), S)
+    mask = rov.dropout_mask_generate(seed, offset, B, H, S, p)
+    O = {"mask": rov.attention_fwd_dropout(Q, K, V, p, mask=mask, causal=causal),
+         "fused": rov.attention_fwd_dropout(Q, K, V, p, seed=seed, offset=offset, causal=causal),
+         "none": rov.attention_fwd_dropout(Q, K, V, 0.0, causal=causal), "rows": torch.full_like(Q, 7.0)}
+    for q0 in range(0, S, 64):
+        part = rov.dropout_mask_generate_rows(seed, offset, B, H, S, p, q0, 64)
+        rov.attention_fwd_dropout_rows(Q, K, V, p, q0, 64, O["rows"], mask_rows=part, causal=causal)
+    torch.cuda.synchronize()
+    assert torch.equal(O["mask"], O["fused"]) and torch.equal(O["mask"], O["rows"])
+    f64 = [x.astype(np.float64) for x in (q, k, v)]
+    assert _err(O["mask"], OD.attention_dropout(*f64, keep, p, causal=causal)) <= TOL
+    assert _err(O["none"], OD.attention_dropout(*f64, None, 0.0, causal=causal)) <= TOL
+
+
+@pytest.mark.parametrize("rounds,bits", [(7, 32), (3, 32), (10, 16), (10, 8)])
+def test_fp32_fused_variants_draw_the_mask_kernels_bits(rounds, bits):
+    B, S, H, d, p, seed, offset = 1, 90, 2, 64, 0.3, 77, 640
+    Q, K, V = (torch.from_numpy(x).cuda() for x in wl.qkv(np.random.default_rng(1), B, S, H, H, d))
+    if bits == 32:
+        mask = rov.dropout_mask_generate(seed, offset, B, H, S, p, rounds=rounds)
+        fused = rov.attention_fwd_dropout(Q, K, V, p, seed=seed, offset=offset, rounds=rounds)
+    else:
+        mask = rov.dropout_mask_generate_bits(seed, offset, B, H, S, p, bits)
+        fused = rov.attention_fwd_dropout(Q, K, V, p, seed=seed, offset=offset, bits=bits)
+    assert torch.equal(fused, rov.attention_fwd_dropout(Q, K, V, p, mask=mask))
+
+
+def test_fp32_strided_views():
+    # Q, K, V as slices of one projection output; a row stride that is no multiple of 4 takes the general kernel
+    B, S, H, d = 1, 70, 2, 64
+    for pad in (0, 1):
+        x = torch.randn(B, S, 3 * H * d + pad, device="cuda", generator=torch.Generator("cuda").manual_seed(5))
+        Q, K, V = (x[..., i * H * d:(i + 1) * H * d].unflatten(-1, (H, d)) for i in range(3))
+        O = torch.empty(B, S, H, d, device="cuda")
+        rov.attention_fwd_dropout(Q, K, V, 0.0, causal=True, O=O)
+        ref = OD.attention_dropout(*(t.double().cpu().numpy() for t in (Q, K, V)), None, 0.0, causal=True)
+        assert _err(O, ref) <= TOL
+
+
+def test_fp32_causal_rows_never_see_later_values():
+    # non-finite keys and values reach the rows that admit them and no other
+    B, S, H, d = 1, 96, 1, 64
+    g = torch.Generator("cuda").manual_seed(9)
+    Q, K, V = (torch.randn(B, S, H, d, device="cuda", generator=g) for _ in range(3))
+    ref = rov.attention_fwd_dropout(Q, K, V, 0.0, causal=True)
+    V2, K2 = V.clone(), K.clone()
+    V2[0, 40, 0, 3] = float("inf")
+    K2[0, 77, 0, 0] = float("nan")
+    O = rov.attention_fwd_dropout(Q, K2, V2, 0.0, causal=True)
+    torch.cuda.synchronize()
+    assert torch.allclose(O[0, :40], ref[0, :40], rtol=1e-5, atol=1e-6)
+    assert bool((O[0, 40:77, 0, 3] == float("inf")).all())
+    others = [i for i in range(d) if i != 3]
+    assert torch.allclose(O[0, 40:77, 0, others], ref[0, 40:77, 0, others], rtol=1e-5, atol=1e-6)
+    assert bool(torch.isnan(O[0, 77:]).all())
