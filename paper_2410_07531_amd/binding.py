@@ -137,22 +137,38 @@ def _check(code, what):
         raise RovError(code, what)
 
 
+# Small calls are bound by this file: pointers and handles go to ctypes as plain integers (its argtypes turn them into
+# void*), and the current stream is asked for its handle without building a Stream object (a mask call 7.6 -> 4.5 us, attention 11.1 -> 6.3).
+_raw_stream = None
+
+
 def _stream_ptr(stream):
-    if stream is None:
+    global _raw_stream
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream is None:
         import torch
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+        torch.cuda.current_stream()     # initialises the device
+        handle, device = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
+        if handle is not None and device is not None:
+            _raw_stream = lambda: handle(device())
+        else:
+            _raw_stream = lambda: torch.cuda.current_stream().cuda_stream
+    return _raw_stream()
+
+
+_dtype_codes = {}
 
 
 def _dtype_code(t):
+    code = _dtype_codes.get(t.dtype)
+    if code is not None:
+        return code
     import torch
-    if t.dtype == torch.float32:
-        return F32
-    if t.dtype == torch.bfloat16:
-        return BF16
-    if t.dtype in (torch.float8_e4m3fn, torch.uint8):
-        return FP8_E4M3
-    raise TypeError("unsupported dtype %s" % t.dtype)
+    _dtype_codes.update({torch.float32: F32, torch.bfloat16: BF16, torch.float8_e4m3fn: FP8_E4M3, torch.uint8: FP8_E4M3})
+    if t.dtype not in _dtype_codes:
+        raise TypeError("unsupported dtype %s" % t.dtype)
+    return _dtype_codes[t.dtype]
 
 
 def mask_words(B, H, S):
@@ -188,11 +204,11 @@ def set_rng_overlap_workgroups_per_cu(n):
 
 def philox_raw(seed, first_counter, ncalls, rounds=10, out=None, stream=None):
     """int32-viewed uint32 [ncalls, 4] tensor of raw Philox words (test hook)."""
-    import torch
     if out is None:
+        import torch
         out = torch.empty((int(ncalls), 4), dtype=torch.int32, device="cuda")
     _check(load().rov_philox_raw(seed & (2**64 - 1), first_counter & (2**64 - 1), int(ncalls), int(rounds),
-                                 ctypes.c_void_p(out.data_ptr()), _stream_ptr(stream)), "rov_philox_raw")
+                                 out.data_ptr(), _stream_ptr(stream)), "rov_philox_raw")
     return out
 
 
@@ -205,74 +221,74 @@ def mask_shape(B, H, S):
 def dropout_mask_generate_causal(seed, offset, B, H, S, p, out, stream=None):
     """Writes only the tiles causal attention reads (plus their chunk neighbours) into `out`."""
     _check(load().rov_dropout_mask_generate_causal(seed & (2**64 - 1), offset & (2**64 - 1), B, H, S, p,
-                                                   ctypes.c_void_p(out.data_ptr()), _stream_ptr(stream)),
+                                                   out.data_ptr(), _stream_ptr(stream)),
            "rov_dropout_mask_generate_causal")
     return out
 
 
 def dropout_mask_generate(seed, offset, B, H, S, p, out=None, rounds=None, stream=None):
     """Keep-mask words as an int64 tensor of shape mask_shape(B, H, S) (bit patterns of uint64)."""
-    import torch
     if out is None:
+        import torch
         out = torch.empty(mask_shape(B, H, S), dtype=torch.int64, device="cuda")
     L = load()
     if rounds is None:
         rc = L.rov_dropout_mask_generate(seed & (2**64 - 1), offset & (2**64 - 1), B, H, S, p,
-                                         ctypes.c_void_p(out.data_ptr()), _stream_ptr(stream))
+                                         out.data_ptr(), _stream_ptr(stream))
     else:
         rc = L.rov_dropout_mask_generate_rounds(seed & (2**64 - 1), offset & (2**64 - 1), B, H, S, p, int(rounds),
-                                                ctypes.c_void_p(out.data_ptr()), _stream_ptr(stream))
+                                                out.data_ptr(), _stream_ptr(stream))
     _check(rc, "rov_dropout_mask_generate")
     return out
 
 
 def dropout_mask_generate_bits(seed, offset, B, H, S, p, bits, out=None, stream=None):
     """Keep-mask drawn with `bits` (8, 16 or 32) random bits per element; same shape and layout."""
-    import torch
     if out is None:
+        import torch
         out = torch.empty(mask_shape(B, H, S), dtype=torch.int64, device="cuda")
     _check(load().rov_dropout_mask_generate_bits(seed & (2**64 - 1), offset & (2**64 - 1), B, H, S, p, int(bits),
-                                                 ctypes.c_void_p(out.data_ptr()), _stream_ptr(stream)),
+                                                 out.data_ptr(), _stream_ptr(stream)),
            "rov_dropout_mask_generate_bits")
     return out
 
 
 def gemm(A, Bm, C=None, transB=True, scaleA=1.0, scaleB=1.0, stream=None):
     """C = scaleA*scaleB * A @ (Bm^T if transB else Bm)."""
-    import torch
     M, K = A.shape
     N = Bm.shape[0] if transB else Bm.shape[1]
     code = _dtype_code(A)
     if C is None:
+        import torch
         C = torch.empty((M, N), dtype=torch.float32 if code == F32 else torch.bfloat16, device=A.device)
-    _check(load().rov_gemm(ctypes.c_void_p(A.data_ptr()), ctypes.c_void_p(Bm.data_ptr()),
-                           ctypes.c_void_p(C.data_ptr()), M, N, K, code, int(bool(transB)),
+    _check(load().rov_gemm(A.data_ptr(), Bm.data_ptr(),
+                           C.data_ptr(), M, N, K, code, int(bool(transB)),
                            float(scaleA), float(scaleB), _stream_ptr(stream)), "rov_gemm")
     return C
 
 
 def gemm_swiglu(A, Wg, Wu, C=None, stream=None):
     """C = silu(A @ Wg^T) * (A @ Wu^T), bf16."""
-    import torch
     M, K = A.shape
     N = Wg.shape[0]
     if C is None:
+        import torch
         C = torch.empty((M, N), dtype=torch.bfloat16, device=A.device)
-    _check(load().rov_gemm_swiglu(ctypes.c_void_p(A.data_ptr()), ctypes.c_void_p(Wg.data_ptr()),
-                                  ctypes.c_void_p(Wu.data_ptr()), ctypes.c_void_p(C.data_ptr()), M, N, K,
+    _check(load().rov_gemm_swiglu(A.data_ptr(), Wg.data_ptr(),
+                                  Wu.data_ptr(), C.data_ptr(), M, N, K,
                                   _stream_ptr(stream)), "rov_gemm_swiglu")
     return C
 
 
 def gemm_swiglu_fp8(A, Wg, Wu, scaleA, scaleWg, scaleWu, scaleC, C=None, stream=None):
     """C (e4m3 bytes) = e4m3(silu(sA sWg A Wg^T) * (sA sWu A Wu^T) / scaleC); A, Wg, Wu e4m3 bytes."""
-    import torch
     M, K = A.shape
     N = Wg.shape[0]
     if C is None:
+        import torch
         C = torch.empty((M, N), dtype=torch.uint8, device=A.device)
-    _check(load().rov_gemm_swiglu_fp8(ctypes.c_void_p(A.data_ptr()), ctypes.c_void_p(Wg.data_ptr()),
-                                      ctypes.c_void_p(Wu.data_ptr()), ctypes.c_void_p(C.data_ptr()), M, N, K,
+    _check(load().rov_gemm_swiglu_fp8(A.data_ptr(), Wg.data_ptr(),
+                                      Wu.data_ptr(), C.data_ptr(), M, N, K,
                                       float(scaleA), float(scaleWg), float(scaleWu), float(scaleC),
                                       _stream_ptr(stream)), "rov_gemm_swiglu_fp8")
     return C
@@ -287,19 +303,20 @@ def gemm_rng_fused(A, Bm, seed, offset, B, H, S, p, C=None, mask=None, stream=No
         C = torch.empty((M, N), dtype=torch.bfloat16, device=A.device)
     if mask is None:
         mask = torch.empty(mask_shape(B, H, S), dtype=torch.int64, device=A.device)
-    _check(load().rov_gemm_rng_fused(ctypes.c_void_p(A.data_ptr()), ctypes.c_void_p(Bm.data_ptr()),
-                                     ctypes.c_void_p(C.data_ptr()), M, N, K, ctypes.c_uint64(seed),
-                                     ctypes.c_uint64(offset), B, H, S, float(p), ctypes.c_void_p(mask.data_ptr()),
+    _check(load().rov_gemm_rng_fused(A.data_ptr(), Bm.data_ptr(),
+                                     C.data_ptr(), M, N, K, ctypes.c_uint64(seed),
+                                     ctypes.c_uint64(offset), B, H, S, float(p), mask.data_ptr(),
                                      _stream_ptr(stream)), "rov_gemm_rng_fused")
     return C, mask
 
 
+_I64x12 = ctypes.c_int64 * 12
+
+
 def _strides12(Q, K, V, O):
-    arr = (ctypes.c_int64 * 12)()
-    for x, t in enumerate((Q, K, V, O)):
-        assert t.stride(3) == 1, "head dimension must be contiguous"
-        arr[3 * x + 0], arr[3 * x + 1], arr[3 * x + 2] = t.stride(0), t.stride(1), t.stride(2)
-    return arr
+    q, k, v, o = Q.stride(), K.stride(), V.stride(), O.stride()
+    assert q[3] == 1 and k[3] == 1 and v[3] == 1 and o[3] == 1, "head dimension must be contiguous"
+    return _I64x12(q[0], q[1], q[2], k[0], k[1], k[2], v[0], v[1], v[2], o[0], o[1], o[2])
 
 
 def attention_fwd_dropout(Q, K, V, p, mask=None, seed=0, offset=0, causal=False, O=None, stream=None,
@@ -307,30 +324,30 @@ def attention_fwd_dropout(Q, K, V, p, mask=None, seed=0, offset=0, causal=False,
     """Q [B,S,H,d], K/V [B,S,Hkv,d] -> O [B,S,H,d]; mask=None with p>0 selects the fused variant
     (rounds: its Philox round count, 3/5/7/10, or bits: its random bits per element, 8/16/32;
     None = the 10-round, 32-bit entry point)."""
-    import torch
     B, S, H, d = Q.shape
     Hkv = K.shape[2]
     if O is None:
+        import torch
         O = torch.empty_like(Q)
     strides = _strides12(Q, K, V, O)
-    mptr = ctypes.c_void_p(mask.data_ptr()) if mask is not None else ctypes.c_void_p(0)
+    mptr = mask.data_ptr() if mask is not None else None
     if bits is not None:
         _check(load().rov_attention_fwd_dropout_bits(
-            ctypes.c_void_p(Q.data_ptr()), ctypes.c_void_p(K.data_ptr()), ctypes.c_void_p(V.data_ptr()),
-            ctypes.c_void_p(O.data_ptr()), B, H, Hkv, S, d, strides, _dtype_code(Q), int(bool(causal)),
+            Q.data_ptr(), K.data_ptr(), V.data_ptr(),
+            O.data_ptr(), B, H, Hkv, S, d, strides, _dtype_code(Q), int(bool(causal)),
             float(p), mptr, seed & (2**64 - 1), offset & (2**64 - 1), int(bits), _stream_ptr(stream)),
             "rov_attention_fwd_dropout_bits")
         return O
     if rounds is not None:
         _check(load().rov_attention_fwd_dropout_rounds(
-            ctypes.c_void_p(Q.data_ptr()), ctypes.c_void_p(K.data_ptr()), ctypes.c_void_p(V.data_ptr()),
-            ctypes.c_void_p(O.data_ptr()), B, H, Hkv, S, d, strides, _dtype_code(Q), int(bool(causal)),
+            Q.data_ptr(), K.data_ptr(), V.data_ptr(),
+            O.data_ptr(), B, H, Hkv, S, d, strides, _dtype_code(Q), int(bool(causal)),
             float(p), mptr, seed & (2**64 - 1), offset & (2**64 - 1), int(rounds), _stream_ptr(stream)),
             "rov_attention_fwd_dropout_rounds")
         return O
     _check(load().rov_attention_fwd_dropout(
-        ctypes.c_void_p(Q.data_ptr()), ctypes.c_void_p(K.data_ptr()), ctypes.c_void_p(V.data_ptr()),
-        ctypes.c_void_p(O.data_ptr()), B, H, Hkv, S, d, strides, _dtype_code(Q), int(bool(causal)), float(p),
+        Q.data_ptr(), K.data_ptr(), V.data_ptr(),
+        O.data_ptr(), B, H, Hkv, S, d, strides, _dtype_code(Q), int(bool(causal)), float(p),
         mptr, seed & (2**64 - 1), offset & (2**64 - 1), _stream_ptr(stream)), "rov_attention_fwd_dropout")
     return O
 
@@ -341,13 +358,13 @@ def mask_words_rows(B, H, S, q_begin, q_rows):
 
 def dropout_mask_generate_rows(seed, offset, B, H, S, p, q_begin, q_rows, out=None, stream=None):
     """Tile rows of query rows [q_begin, q_begin + q_rows): int64 tensor [B, H, nqt, T, 16]."""
-    import torch
     if out is None:
+        import torch
         T = (S + 31) // 32
         nqt = (min(q_begin + q_rows, S) - q_begin + 31) // 32
         out = torch.empty((B, H, nqt, T, 16), dtype=torch.int64, device="cuda")
     _check(load().rov_dropout_mask_generate_rows(seed & (2**64 - 1), offset & (2**64 - 1), B, H, S, p,
-                                                 int(q_begin), int(q_rows), ctypes.c_void_p(out.data_ptr()),
+                                                 int(q_begin), int(q_rows), out.data_ptr(),
                                                  _stream_ptr(stream)), "rov_dropout_mask_generate_rows")
     return out
 
@@ -358,10 +375,10 @@ def attention_fwd_dropout_rows(Q, K, V, p, q_begin, q_rows, O, mask_rows=None, s
     B, S, H, d = Q.shape
     Hkv = K.shape[2]
     strides = _strides12(Q, K, V, O)
-    mptr = ctypes.c_void_p(mask_rows.data_ptr()) if mask_rows is not None else ctypes.c_void_p(0)
+    mptr = mask_rows.data_ptr() if mask_rows is not None else None
     _check(load().rov_attention_fwd_dropout_rows(
-        ctypes.c_void_p(Q.data_ptr()), ctypes.c_void_p(K.data_ptr()), ctypes.c_void_p(V.data_ptr()),
-        ctypes.c_void_p(O.data_ptr()), B, H, Hkv, S, d, strides, _dtype_code(Q), int(bool(causal)), float(p),
+        Q.data_ptr(), K.data_ptr(), V.data_ptr(),
+        O.data_ptr(), B, H, Hkv, S, d, strides, _dtype_code(Q), int(bool(causal)), float(p),
         mptr, seed & (2**64 - 1), offset & (2**64 - 1), int(q_begin), int(q_rows), _stream_ptr(stream)),
         "rov_attention_fwd_dropout_rows")
     return O
@@ -371,7 +388,7 @@ def layer_step_chunked(gemm_descs, attn_desc, seed, offset, q_chunk_rows, mask_r
     arr = (GemmDesc * len(gemm_descs))(*gemm_descs)
     _check(load().rov_layer_step_chunked(arr, len(gemm_descs), ctypes.byref(attn_desc), seed & (2**64 - 1),
                                          offset & (2**64 - 1), int(q_chunk_rows),
-                                         ctypes.c_void_p(mask_ring.data_ptr()), _stream_ptr(main_stream),
+                                         mask_ring.data_ptr(), _stream_ptr(main_stream),
                                          _stream_ptr(side_stream)), "rov_layer_step_chunked")
 
 
@@ -398,7 +415,7 @@ def make_attn_desc(Q, K, V, O, p, causal=False):
 def layer_step(schedule, gemm_descs, attn_desc, seed, offset, mask, main_stream, side_stream, rounds=None,
                bits=None):
     arr = (GemmDesc * len(gemm_descs))(*gemm_descs)
-    mptr = ctypes.c_void_p(mask.data_ptr()) if mask is not None else ctypes.c_void_p(0)
+    mptr = mask.data_ptr() if mask is not None else None
     if bits is not None:
         _check(load().rov_layer_step_bits(int(schedule), arr, len(gemm_descs), ctypes.byref(attn_desc),
                                           seed & (2**64 - 1), offset & (2**64 - 1), int(bits), mptr,
@@ -446,19 +463,19 @@ def make_block_weights(w, w_scale=None):
 def block_forward(weights, x, y, cfg, schedule, seed, offset, mask, workspace, main_stream, side_stream,
                   mask_ready=False, next_mask=None):
     B, S, _ = x.shape
-    mptr = ctypes.c_void_p(mask.data_ptr()) if mask is not None else ctypes.c_void_p(0)
-    nptr = ctypes.c_void_p(next_mask.data_ptr()) if next_mask is not None else ctypes.c_void_p(0)
-    _check(load().rov_block_forward(ctypes.byref(weights), ctypes.c_void_p(x.data_ptr()),
-                                    ctypes.c_void_p(y.data_ptr()), B, S, ctypes.byref(cfg), int(schedule),
+    mptr = mask.data_ptr() if mask is not None else None
+    nptr = next_mask.data_ptr() if next_mask is not None else None
+    _check(load().rov_block_forward(ctypes.byref(weights), x.data_ptr(),
+                                    y.data_ptr(), B, S, ctypes.byref(cfg), int(schedule),
                                     seed & (2**64 - 1), offset & (2**64 - 1), int(mask_ready), mptr, nptr,
-                                    ctypes.c_void_p(workspace.data_ptr()), workspace.numel() * workspace.element_size(),
+                                    workspace.data_ptr(), workspace.numel() * workspace.element_size(),
                                     _stream_ptr(main_stream), _stream_ptr(side_stream)), "rov_block_forward")
     return y
 
 
 def mask_finish(mask, main_stream):
     """Completes and joins a mask that an OVERLAP_DEFERRED block_forward left in flight."""
-    _check(load().rov_mask_finish(ctypes.c_void_p(mask.data_ptr()), _stream_ptr(main_stream)), "rov_mask_finish")
+    _check(load().rov_mask_finish(mask.data_ptr(), _stream_ptr(main_stream)), "rov_mask_finish")
 
 
 def block_static_scratch_bytes():
@@ -469,10 +486,10 @@ def block_forward_static(weights, x, y, cfg, schedule, seed, offset, mask, main_
                          mask_ready=False, next_mask=None):
     """block_forward on the library's own static scratch (no workspace, nothing allocated)."""
     B, S, _ = x.shape
-    mptr = ctypes.c_void_p(mask.data_ptr()) if mask is not None else ctypes.c_void_p(0)
-    nptr = ctypes.c_void_p(next_mask.data_ptr()) if next_mask is not None else ctypes.c_void_p(0)
-    _check(load().rov_block_forward_static(ctypes.byref(weights), ctypes.c_void_p(x.data_ptr()),
-                                           ctypes.c_void_p(y.data_ptr()), B, S, ctypes.byref(cfg), int(schedule),
+    mptr = mask.data_ptr() if mask is not None else None
+    nptr = next_mask.data_ptr() if next_mask is not None else None
+    _check(load().rov_block_forward_static(ctypes.byref(weights), x.data_ptr(),
+                                           y.data_ptr(), B, S, ctypes.byref(cfg), int(schedule),
                                            seed & (2**64 - 1), offset & (2**64 - 1), int(mask_ready), mptr,
                                            nptr, _stream_ptr(main_stream), _stream_ptr(side_stream)),
            "rov_block_forward_static")

@@ -21,17 +21,36 @@ int record_hip_error(hipError_t e) {
 }
 
 // hipFuncAttributeMaxDynamicSharedMemorySize is a property of (device, kernel): set it the first
-// time a kernel is launched on a device and never again (the launch paths call this every time).
+// time a kernel is launched on a device and never again.  Every launch asks, so what is done is kept in a
+// table that is read without a lock (a slot is written once, after the attribute is set; two threads that race
+// on a kernel's first launch both set it); a full table only means that the attribute is set again.
 int set_max_dynamic_lds(const void* kern, int bytes) {
-    static std::mutex mu;
-    static std::vector<std::pair<int, const void*>> done;
+    constexpr unsigned kSlots = 1024;
+    struct Slot {
+        std::atomic<const void*> kern{nullptr};
+        std::atomic<int> dev{-1};
+    };
+    static Slot table[kSlots];
     int dev = 0;
     ROV_HIP_TRY(hipGetDevice(&dev));
-    std::lock_guard<std::mutex> lock(mu);
-    for (const auto& d : done)
-        if (d.first == dev && d.second == kern) return ROV_OK;
+    const unsigned h = (unsigned)(((uintptr_t)kern >> 4) * 0x9E3779B9u + (unsigned)dev * 0x85EBCA6Bu);
+    for (unsigned i = 0; i < 8; ++i) {
+        const Slot& s = table[(h + i) % kSlots];
+        const void* k = s.kern.load(std::memory_order_acquire);
+        if (k == kern && s.dev.load(std::memory_order_relaxed) == dev) return ROV_OK;
+    }
     ROV_HIP_TRY(hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, bytes));
-    done.emplace_back(dev, kern);
+    static std::mutex mu;
+    std::lock_guard<std::mutex> lock(mu);
+    for (unsigned i = 0; i < 8; ++i) {
+        Slot& s = table[(h + i) % kSlots];
+        const void* k = s.kern.load(std::memory_order_relaxed);
+        if (k == kern && s.dev.load(std::memory_order_relaxed) == dev) break;
+        if (k != nullptr) continue;
+        s.dev.store(dev, std::memory_order_relaxed);   // before the kernel: a reader that sees the kernel sees its device
+        s.kern.store(kern, std::memory_order_release);
+        break;
+    }
     return ROV_OK;
 }
 
