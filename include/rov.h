@@ -18,8 +18,8 @@
  *    schedule entry points (rov_layer_step*, rov_block_forward*) serialise their
  *    enqueue phase inside the library; the work they enqueue is ordered by the
  *    streams they are given, as usual.  The process-wide rov_set_* knobs are for
- *    experiments and are read once per call.  Masks that two launches produce
- *    together go through one of 64 work queues of the library; a queue is taken for
+ *    experiments and are read once per call.  Large masks that two launches
+ *    produce together go through one of 64 work queues of the library; a queue is taken for
  *    the duration of a call (for a mask left in flight: until it is claimed or
  *    finished) and handed out again only after the launches that used it have
  *    completed.  With all 64 taken a call returns ROV_ERR_UNSUPPORTED.
@@ -296,8 +296,8 @@ int rov_attention_fwd_dropout_rows(const void *Q, const void *K, const void *V, 
  *                         main_stream; attention(mask) on main_stream after both.
  *                         If the RNG is not done when the GEMMs end, the rest of it runs
  *                         at full speed (paper Sec. 3.3): a second RNG launch on
- *                         main_stream shares the mask's chunks with the first through a
- *                         work queue and exits at once when none are left.
+ *                         main_stream shares the mask's chunks with the first, by a split
+ *                         fixed from the sizes or, for large masks, through a work queue.
  * mask: device buffer of rov_mask_words(B,H,S) words (unused for FUSED, may be
  * NULL there).  side_stream must differ from main_stream for OVERLAP. */
 typedef struct rov_gemm_desc {

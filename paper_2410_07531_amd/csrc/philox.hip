@@ -80,15 +80,15 @@ template <int R, bool RAGGED>
 __global__ __launch_bounds__(kWavesPerBlock * 64) __attribute__((amdgpu_num_vgpr(24))) void mask_kernel(
     uint64_t* __restrict__ out, uint64_t words, uint64_t nchunks, uint64_t offset, uint32_t k0,
     uint32_t k1, uint32_t t_minus_1, uint32_t T, uint32_t Tm, uint32_t S, int lower_only, int qslot, uint64_t qper,
-    uint32_t qbatch) {
+    uint32_t qbatch, uint64_t chunk0) {
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    // qslot < 0: the grid strides over the chunks; qslot >= 0: waves pull chunks from a queue that
+    // qslot < 0: the grid strides over chunks [chunk0, nchunks); qslot >= 0: waves pull chunks from a queue that
     // another launch of this kernel may be draining too
     ChunkSource src;
     src.queues = qslot >= 0 ? g_queues[qslot] : nullptr; src.nchunks = nchunks; src.stride = (uint64_t)gridDim.x * kWavesPerBlock;
     src.per = qper; src.batch = qbatch; src.lane = lane;
-    for (bool more = src.first((uint64_t)blockIdx.x * kWavesPerBlock + wave); more; more = src.next()) {
+    for (bool more = src.first(chunk0 + (uint64_t)blockIdx.x * kWavesPerBlock + wave); more; more = src.next()) {
         const uint64_t chunk = src.cur;
         uint32_t vlo = 0u, vhi = 0u;
         uint32_t qt = 0u, kt = 0u;   // tile coordinates of the chunk's first tile
@@ -277,10 +277,13 @@ int mask_grid_cap(int grid_mode, int kernel_regs) {
 
 template <int R>
 int launch_mask_r(uint64_t* out, uint64_t words, uint64_t offset, uint32_t k0, uint32_t k1,
-                  uint32_t t_minus_1, int S, int grid_mode, int qslot, bool lower_only, hipStream_t stream) {
+                  uint32_t t_minus_1, int S, int grid_mode, int qslot, bool lower_only, uint64_t chunk0, uint64_t chunk1,
+                  hipStream_t stream) {
     const uint32_t T = (uint32_t)(((uint64_t)S + 31u) / 32u);
-    const uint64_t nchunks = (words + 63u) / 64u;
-    uint64_t blocks = (nchunks + kWavesPerBlock - 1) / kWavesPerBlock;
+    const uint64_t all = (words + 63u) / 64u;
+    const uint64_t nchunks = chunk1 < all ? chunk1 : all;   // end of the range
+    if (chunk0 >= nchunks) return ROV_OK;
+    uint64_t blocks = (nchunks - chunk0 + kWavesPerBlock - 1) / kWavesPerBlock;
     // registers per wave: 24 for 10 and 3 rounds (and every ragged variant), 25 -> 32 for 7 and 5
     const int cap = mask_grid_cap(grid_mode, ((S & 31) != 0 || R == 10 || R == 3) ? 24 : 32);
     if (blocks > (uint64_t)cap) blocks = (uint64_t)cap;
@@ -305,10 +308,10 @@ int launch_mask_r(uint64_t* out, uint64_t words, uint64_t offset, uint32_t k0, u
     queue_geometry(nchunks, &qper, &qbatch);
     if ((S & 31) == 0) {
         hipLaunchKernelGGL((mask_kernel<R, false>), grid, block, 0, stream, out, words, nchunks,
-                           offset, k0, k1, t_minus_1, T, div_magic(T), (uint32_t)S, (int)lower_only, qslot, qper, qbatch);
+                           offset, k0, k1, t_minus_1, T, div_magic(T), (uint32_t)S, (int)lower_only, qslot, qper, qbatch, chunk0);
     } else {
         hipLaunchKernelGGL((mask_kernel<R, true>), grid, block, 0, stream, out, words, nchunks,
-                           offset, k0, k1, t_minus_1, T, div_magic(T), (uint32_t)S, (int)lower_only, qslot, qper, qbatch);
+                           offset, k0, k1, t_minus_1, T, div_magic(T), (uint32_t)S, (int)lower_only, qslot, qper, qbatch, chunk0);
     }
     ROV_LAUNCH_CHECK();
     return ROV_OK;
@@ -437,7 +440,7 @@ int check_mask(int B, int H, int S, float p, int rounds, int bits, const uint64_
 }
 
 int launch_mask(uint64_t seed, uint64_t offset, int B, int H, int S, float p, int rounds,
-                uint64_t* out, hipStream_t stream, int grid_mode, int qslot, bool lower_only) {
+                uint64_t* out, hipStream_t stream, int grid_mode, int qslot, bool lower_only, uint64_t chunk0, uint64_t chunk1) {
     if (qslot >= kQueueSlots) return ROV_ERR_INVALID;
     {
         const int rc = check_mask(B, H, S, p, rounds, 32, out);
@@ -449,10 +452,10 @@ int launch_mask(uint64_t seed, uint64_t offset, int B, int H, int S, float p, in
     const uint64_t words = (uint64_t)B * (uint64_t)H * T * T * 16u;
     const uint32_t k0 = (uint32_t)seed, k1 = (uint32_t)(seed >> 32);
     switch (rounds) {
-        case 10: return launch_mask_r<10>(out, words, offset, k0, k1, tm1, S, grid_mode, qslot, lower_only, stream);
-        case 7: return launch_mask_r<7>(out, words, offset, k0, k1, tm1, S, grid_mode, qslot, lower_only, stream);
-        case 5: return launch_mask_r<5>(out, words, offset, k0, k1, tm1, S, grid_mode, qslot, lower_only, stream);
-        case 3: return launch_mask_r<3>(out, words, offset, k0, k1, tm1, S, grid_mode, qslot, lower_only, stream);
+        case 10: return launch_mask_r<10>(out, words, offset, k0, k1, tm1, S, grid_mode, qslot, lower_only, chunk0, chunk1, stream);
+        case 7: return launch_mask_r<7>(out, words, offset, k0, k1, tm1, S, grid_mode, qslot, lower_only, chunk0, chunk1, stream);
+        case 5: return launch_mask_r<5>(out, words, offset, k0, k1, tm1, S, grid_mode, qslot, lower_only, chunk0, chunk1, stream);
+        case 3: return launch_mask_r<3>(out, words, offset, k0, k1, tm1, S, grid_mode, qslot, lower_only, chunk0, chunk1, stream);
         default: return ROV_ERR_INVALID;
     }
 }

@@ -53,9 +53,10 @@ int mask_queue_release(int slot, hipStream_t stream);
 int mask_queue_device_ptr(int slot, void** ptr);
 void mask_queue_geometry(uint64_t nchunks, uint64_t* per, uint32_t* batch);
 // lower_only: write only what causal attention reads (tiles with key tile <= query tile).
+// chunk0, chunk1: only the 64-word chunks [chunk0, chunk1) of the mask (without a queue).
 int launch_mask(uint64_t seed, uint64_t offset, int B, int H, int S, float p, int rounds,
                 uint64_t* out, hipStream_t stream, int grid_mode = MASK_GRID_FULL, int qslot = -1,
-                bool lower_only = false);
+                bool lower_only = false, uint64_t chunk0 = 0, uint64_t chunk1 = ~0ull);
 
 // Same layout with `bits` (8, 16 or 32) random bits per element; grid stride, no work queue.
 int launch_mask_bits(uint64_t seed, uint64_t offset, int B, int H, int S, float p, int bits, uint64_t* out,

@@ -82,11 +82,19 @@ struct SideStream {
     }
 };
 
+// How a mask is shared between the small grid beside the GEMMs and the full-size launch behind them: by work queue
+// `qslot`, or, with qslot < 0, the small grid makes the 64-word chunks [0, rest) and the other launch those from `rest` on
+// (none if the mask has no more).
+struct MaskSplit {
+    int qslot = -1;
+    uint64_t rest = ~0ull;
+};
+
 // Masks left in flight by ROV_SCHED_OVERLAP_DEFERRED calls, keyed by their buffer: what the
 // following block needs in order to finish and join them (guarded by g_sched_mu).
 struct InFlightMask {
     hipStream_t ss;
-    int qslot;              // work queue the small grid pulls from (-1: plain launch, nothing to help with)
+    MaskSplit split;        // between the small grid on the side stream and the launch that finishes the mask
     uint64_t seed, offset;
     int B, H, S, causal;
     float p;
@@ -132,26 +140,53 @@ int t_gemm(const void* A, const void* Bm, void* C, const void* R, int M, int N, 
     });
 }
 
+// The mask, on one stream (MASK_GRID_FULL) or one of the two launches of a split: MASK_GRID_BESIDE the small grid,
+// MASK_GRID_HELPER the launch that makes the rest at full speed.  An empty share launches nothing.
 int t_mask(uint64_t seed, uint64_t offset, int B, int H, int S, float p, uint64_t* out, hipStream_t st,
-           int grid_mode, int qslot, bool lower_only, int rounds = 10, int bits = 32) {
+           int grid_mode, const MaskSplit& split, bool lower_only, int rounds = 10, int bits = 32) {
+    uint64_t chunk0 = 0, chunk1 = ~0ull;
+    int grid = grid_mode;
+    if (split.qslot < 0 && grid_mode == MASK_GRID_BESIDE) {
+        chunk1 = split.rest;
+    } else if (split.qslot < 0 && grid_mode == MASK_GRID_HELPER) {
+        chunk0 = split.rest;
+        grid = MASK_GRID_FULL;
+    }
+    if (chunk0 >= chunk1 || chunk0 >= (rov_mask_words(B, H, S) + 63u) / 64u) return ROV_OK;
     return traced(grid_mode == MASK_GRID_HELPER ? ROV_TRACE_RNG_HELPER : ROV_TRACE_RNG, st, [&] {
-        if (bits != 32) return launch_mask_bits(seed, offset, B, H, S, p, bits, out, st, grid_mode);
-        return launch_mask(seed, offset, B, H, S, p, rounds, out, st, grid_mode, qslot, lower_only);
+        if (bits != 32) return launch_mask_bits(seed, offset, B, H, S, p, bits, out, st, grid);
+        return launch_mask(seed, offset, B, H, S, p, rounds, out, st, grid, split.qslot, lower_only, chunk0, chunk1);
     });
 }
 
 // Will the small RNG grid finish while the GEMMs beside it run?  Then the plain launch is enough;
-// otherwise the mask goes through a work queue and a helper launch finishes it after the GEMMs.
+// otherwise a second launch finishes the mask after the GEMMs.
 // The rates are this chip's measured ones with both kernels running: 1.16 PFLOP/s for the bf16
 // GEMMs and 2.55 for fp8 (12 % and 8 % below their stand-alone rates; 30 TFLOP/s for the fp32
 // kernel), 0.335 T Philox calls/s for the three-waves-per-SIMD grid beside them (0.44 of the
-// stand-alone kernel).  A wrong guess costs time (an empty helper launch, about 10 us, or an RNG
-// tail at the small grid's rate), never correctness.
+// stand-alone kernel).  A wrong guess costs time, never correctness.
+double beside_gemm_seconds(double gemm_flop, int dtype) {
+    return gemm_flop / (dtype == ROV_F32 ? 30e12 : (dtype == ROV_FP8_E4M3 ? 2.55e15 : 1.16e15));
+}
 bool rng_fits_beside(double gemm_flop, int dtype, double rng_calls) {
-    const double rate = dtype == ROV_F32 ? 30e12 : (dtype == ROV_FP8_E4M3 ? 2.55e15 : 1.16e15);
-    const double t_gemm = gemm_flop / rate;
-    const double t_rng = rng_calls / 0.335e12;
-    return t_rng < 0.9 * t_gemm;
+    return rng_calls / 0.335e12 < 0.9 * beside_gemm_seconds(gemm_flop, dtype);
+}
+
+// The split of a mask that is generated beside GEMMs of gemm_flop.  Large masks go through a work queue (reset on `ms`, to
+// be released there), which evens out what the estimate misses; but its waves pop eight chunks at a time (an atomic on
+// memory shared by eight L2s costs about as much as a chunk), and a mask that gives each of the 11000 waves of the two
+// launches less than two batches ends with most of them idle.  Such a mask is split beforehand: the small grid gets
+// what it does in the GEMMs' time at the 0.295 T calls/s it was measured at beside all four GEMMs of the S = 16384 block,
+// or nothing if that is too little to pay for its launch.  Two blocks, queue / fixed split, us: 16 heads x 3000 tokens
+// 621 / 546, 16 x 1200 271 / 233, 32 x 2000 1830 / 1806, 32 x 4096 3237 / 3219; 16 x 8192 causal 1282 / 1349, 32 x 16384
+// 23877 / 24041.
+int plan_split(double gemm_flop, int dtype, double rng_calls, int B, int H, int S, hipStream_t ms, MaskSplit* split) {
+    const uint64_t chunks = (rov_mask_words(B, H, S) + 63u) / 64u;
+    if (rng_fits_beside(gemm_flop, dtype, rng_calls)) return ROV_OK;
+    if (chunks >= (uint64_t)device_cu_count() * (8 + 3) * 4 * 8 * 2) return mask_queue_acquire(ms, &split->qslot);
+    const double share = beside_gemm_seconds(gemm_flop, dtype) * 0.295e12 / rng_calls;
+    split->rest = share < 0.03 ? 0 : share >= 1.0 ? chunks : (uint64_t)(share * (double)chunks);
+    return ROV_OK;
 }
 
 double gemm_flop(int M, int N, int K) { return 2.0 * (double)M * (double)N * (double)K; }
@@ -250,7 +285,7 @@ int layer_step_impl(int schedule, const rov_gemm_desc* gemms, int n_gemms, const
 
     std::lock_guard<std::mutex> sched_lock(g_sched_mu);
     SideStream side;
-    int qslot = -1;
+    MaskSplit split;
     const bool overlap = schedule == ROV_SCHED_OVERLAP && need_mask;
     if (overlap) {
         int rc = get_events(&side.ev);
@@ -264,9 +299,9 @@ int layer_step_impl(int schedule, const rov_gemm_desc* gemms, int n_gemms, const
             if (gemms[i].dtype == ROV_F32 || (gemms[i].dtype == ROV_BF16 && slowest != ROV_F32)) slowest = gemms[i].dtype;
         }
         const double calls = (double)rov_mask_philox_calls(attn->B, attn->H, attn->S) * (attn->causal ? 0.5 : 1.0);
-        // (cost per call ~ rounds; the narrower kernels have no work-queue form and simply run on)
-        if (bits == 32 && !rng_fits_beside(flop, slowest, calls * (0.25 + 0.075 * rounds))) {
-            rc = mask_queue_acquire(ms, &qslot);   // reset here: ordered before both RNG launches
+        // (cost per call ~ rounds; the narrower kernels take no range and simply run on)
+        if (bits == 32) {
+            rc = plan_split(flop, slowest, calls * (0.25 + 0.075 * rounds), attn->B, attn->H, attn->S, ms, &split);
             if (rc != ROV_OK) return rc;
         }
         // the mask buffer may still be read by work already queued on the main stream
@@ -285,7 +320,7 @@ int layer_step_impl(int schedule, const rov_gemm_desc* gemms, int n_gemms, const
             rc = run_gemm(0);
             if (rc != ROV_OK) return rc;
         }
-        rc = t_mask(seed, offset, attn->B, attn->H, attn->S, attn->p, mask, ss, MASK_GRID_BESIDE, qslot,
+        rc = t_mask(seed, offset, attn->B, attn->H, attn->S, attn->p, mask, ss, MASK_GRID_BESIDE, split,
                     attn->causal != 0, rounds, bits);
         if (rc != ROV_OK) return rc;
         rc = side.mark();
@@ -294,16 +329,13 @@ int layer_step_impl(int schedule, const rov_gemm_desc* gemms, int n_gemms, const
             rc = run_gemm(i);
             if (rc != ROV_OK) return rc;
         }
-        // whatever the small grid has not produced when the GEMMs end is finished at full speed
-        // (paper Sec. 3.3); waves of this launch leave at once if the queue is already empty
-        if (qslot >= 0) {
-            rc = t_mask(seed, offset, attn->B, attn->H, attn->S, attn->p, mask, ms, MASK_GRID_HELPER, qslot,
-                        attn->causal != 0, rounds, bits);
-            if (rc != ROV_OK) return rc;
-        }
+        // what the small grid was not given is made at full speed (paper Sec. 3.3)
+        rc = t_mask(seed, offset, attn->B, attn->H, attn->S, attn->p, mask, ms, MASK_GRID_HELPER, split,
+                    attn->causal != 0, rounds, bits);
+        if (rc != ROV_OK) return rc;
         rc = side.join();
         if (rc != ROV_OK) return rc;
-        rc = mask_queue_release(qslot, ms);
+        rc = mask_queue_release(split.qslot, ms);
         if (rc != ROV_OK) return rc;
     } else {
         for (int i = 0; i < n_gemms; ++i) {
@@ -311,7 +343,7 @@ int layer_step_impl(int schedule, const rov_gemm_desc* gemms, int n_gemms, const
             if (rc != ROV_OK) return rc;
         }
         if (need_mask) {
-            rc = t_mask(seed, offset, attn->B, attn->H, attn->S, attn->p, mask, ms, MASK_GRID_FULL, -1,
+            rc = t_mask(seed, offset, attn->B, attn->H, attn->S, attn->p, mask, ms, MASK_GRID_FULL, split,
                         attn->causal != 0, rounds, bits);
             if (rc != ROV_OK) return rc;
         }
@@ -634,11 +666,14 @@ int block_forward_impl(const rov_block_weights* w, const void* x, void* y, int B
     if (next_mask != nullptr && g_in_flight.count(next_mask) != 0) return ROV_ERR_INVALID;
 
     // this block's own mask, if nobody produced it yet
-    int qslot = -1;
+    int qslot = -1;                    // hybrid: work queue of a range of rows
+    MaskSplit own;                     // of the block's own mask
     const double mask_calls = (double)rov_mask_philox_calls(B, H, S) * (cfg->causal ? 0.5 : 1.0);
+    const double qkv_flop = gemm_flop((int)T, qkv_n, hidden);
     if (use_mask && !mask_ready && overlap) {
-        if (!rng_fits_beside(gemm_flop((int)((int64_t)B * S), (cfg->H + 2 * cfg->Hkv) * cfg->d, cfg->hidden), dt,
-                             mask_calls))
+        if (R == S)
+            ROV_STEP(plan_split(qkv_flop, dt, mask_calls, B, H, S, ms, &own));
+        else if (!rng_fits_beside(qkv_flop, dt, mask_calls))
             ROV_STEP(mask_queue_acquire(ms, &qslot));
     }
     ROV_STEP(traced(ROV_TRACE_GLUE, ms, [&] {
@@ -662,29 +697,29 @@ int block_forward_impl(const rov_block_weights* w, const void* x, void* y, int B
                     return launch_mask_rows(seed, offset, B, H, S, cfg->p, 0, R, mask, ms, MASK_GRID_HELPER, qslot);
                 }));
         } else if (overlap) {
-            ROV_STEP(t_mask(seed, offset, B, H, S, cfg->p, mask, ss, MASK_GRID_BESIDE, qslot, cfg->causal != 0));
+            ROV_STEP(t_mask(seed, offset, B, H, S, cfg->p, mask, ss, MASK_GRID_BESIDE, own, cfg->causal != 0));
             ROV_STEP(side.mark());
-            if (qslot >= 0)
-                ROV_STEP(t_mask(seed, offset, B, H, S, cfg->p, mask, ms, MASK_GRID_HELPER, qslot, cfg->causal != 0));
+            ROV_STEP(t_mask(seed, offset, B, H, S, cfg->p, mask, ms, MASK_GRID_HELPER, own, cfg->causal != 0));
         } else {
-            ROV_STEP(t_mask(seed, offset, B, H, S, cfg->p, mask, ms, MASK_GRID_FULL, -1, cfg->causal != 0));
+            ROV_STEP(t_mask(seed, offset, B, H, S, cfg->p, mask, ms, MASK_GRID_FULL, own, cfg->causal != 0));
         }
     }
-    if (in_flight && fl.qslot >= 0)
-        // what the small grid (running since the previous block) has not produced by the end of this
-        // block's QKV GEMM is finished at full speed (paper Sec. 3.3)
-        ROV_STEP(t_mask(seed, offset, B, H, S, cfg->p, mask, ms, MASK_GRID_HELPER, fl.qslot, cfg->causal != 0));
+    if (in_flight)
+        // what the small grid (running since the previous block) was not given is made at full speed behind this
+        // block's QKV GEMM (paper Sec. 3.3)
+        ROV_STEP(t_mask(seed, offset, B, H, S, cfg->p, mask, ms, MASK_GRID_HELPER, fl.split, cfg->causal != 0));
     ROV_STEP(traced(ROV_TRACE_GLUE, ms, [&] {   // q heads then k heads
         return launch_rope(qkv, T, qkv_n, S, H + Hkv, d, cfg->rope_theta, ms);
     }));
     if (use_mask && !mask_ready && overlap) {
         ROV_STEP(side.join());
         ROV_STEP(mask_queue_release(qslot, ms));
+        ROV_STEP(mask_queue_release(own.qslot, ms));
     }
     if (in_flight) {
         ROV_STEP(side.mark());    // everything queued on the side stream so far, the RNG grid included
         ROV_STEP(side.join());
-        ROV_STEP(mask_queue_release(fl.qslot, ms));
+        ROV_STEP(mask_queue_release(fl.split.qslot, ms));
     }
 
     if (hybrid && R < S) {
@@ -709,13 +744,14 @@ int block_forward_impl(const rov_block_weights* w, const void* x, void* y, int B
 
     // the next layer's mask runs beside this block's remaining GEMMs (it would compete with
     // attention for VALU issue, so it starts once attention is done)
-    int qslot_next = -1;
+    MaskSplit next;
     const bool run_ahead = overlap && next_mask != nullptr && R > 0;
     if (run_ahead) {
         const double rest = gemm_flop((int)T, hidden, H * d) + 2.0 * gemm_flop((int)T, ffn, hidden) +
                             gemm_flop((int)T, hidden, ffn);
-        // (hybrid with R < S: the rows were chosen to fit, no queue and no helper launch)
-        if (R == S && !rng_fits_beside(rest, dt, mask_calls)) ROV_STEP(mask_queue_acquire(ms, &qslot_next));
+        // (hybrid with R < S: the rows were chosen to fit, no helper launch; left in flight: the next block's QKV
+        // product, of this block's sizes, hosts the RNG too)
+        if (R == S) ROV_STEP(plan_split(rest + (defer ? qkv_flop : 0.0), dt, mask_calls, B, H, S, ms, &next));
         ROV_STEP(side.fork());
     }
     ROV_STEP(t_gemm(att_out, w->wo, x2, x, (int)T, hidden, H * d, dt, 1, sa1, sw_o, ms));
@@ -727,7 +763,7 @@ int block_forward_impl(const rov_block_weights* w, const void* x, void* y, int B
             }));
         else
             ROV_STEP(t_mask(seed, offset + rov_mask_philox_calls(B, H, S), B, H, S, cfg->p, next_mask, ss,
-                            MASK_GRID_BESIDE, qslot_next, cfg->causal != 0));
+                            MASK_GRID_BESIDE, next, cfg->causal != 0));
         ROV_STEP(side.mark());
     }
     ROV_STEP(traced(ROV_TRACE_GLUE, ms, [&] {
@@ -743,16 +779,16 @@ int block_forward_impl(const rov_block_weights* w, const void* x, void* y, int B
     ROV_STEP(t_gemm(u, w->wd, y, x2, (int)T, hidden, ffn, dt, 1, sa3, sw_d, ms));
     if (run_ahead && defer && R == S) {
         // left in flight: the following block (mask_ready == ROV_MASK_IN_FLIGHT) helps and joins
-        g_in_flight[next_mask] = InFlightMask{ss, qslot_next, seed, offset + rov_mask_philox_calls(B, H, S), B, H, S,
+        g_in_flight[next_mask] = InFlightMask{ss, next, seed, offset + rov_mask_philox_calls(B, H, S), B, H, S,
                                               cfg->causal != 0, cfg->p};
         side.open = false;
     } else if (run_ahead) {
-        // what is left of the next mask when the last GEMM ends is finished at full speed
-        if (qslot_next >= 0)
+        // what is left of the next mask is made at full speed behind the last GEMM
+        if (R == S)
             ROV_STEP(t_mask(seed, offset + rov_mask_philox_calls(B, H, S), B, H, S, cfg->p, next_mask, ms,
-                            MASK_GRID_HELPER, qslot_next, cfg->causal != 0));
+                            MASK_GRID_HELPER, next, cfg->causal != 0));
         ROV_STEP(side.join());
-        ROV_STEP(mask_queue_release(qslot_next, ms));
+        ROV_STEP(mask_queue_release(next.qslot, ms));
     }
 #undef ROV_STEP
     return ROV_OK;
@@ -769,7 +805,7 @@ int mask_finish_impl(uint64_t* mask, void* main_stream) {
     const InFlightMask fl = it->second;
     hipStream_t ms = (hipStream_t)main_stream;
     if (ms == fl.ss) return ROV_ERR_INVALID;
-    if (fl.qslot >= 0) {
+    {
         const int rc0 = check_mask(fl.B, fl.H, fl.S, fl.p, 10, 32, mask);
         if (rc0 != ROV_OK) return rc0;
     }
@@ -780,15 +816,13 @@ int mask_finish_impl(uint64_t* mask, void* main_stream) {
     side.ss = fl.ss;
     g_in_flight.erase(it);
     side.open = true;   // an early return below still joins
-    if (fl.qslot >= 0) {
-        rc = t_mask(fl.seed, fl.offset, fl.B, fl.H, fl.S, fl.p, mask, ms, MASK_GRID_HELPER, fl.qslot, fl.causal != 0);
-        if (rc != ROV_OK) return rc;
-    }
+    rc = t_mask(fl.seed, fl.offset, fl.B, fl.H, fl.S, fl.p, mask, ms, MASK_GRID_HELPER, fl.split, fl.causal != 0);
+    if (rc != ROV_OK) return rc;
     rc = side.mark();
     if (rc != ROV_OK) return rc;
     rc = side.join();
     if (rc != ROV_OK) return rc;
-    return mask_queue_release(fl.qslot, ms);
+    return mask_queue_release(fl.split.qslot, ms);
 }
 
 // Scratch of rov_block_forward_static: the block's intermediate tensors (normed activations, QKV,
