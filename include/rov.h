@@ -200,8 +200,8 @@ int rov_gemm(const void *A, const void *Bm, void *C, int M, int N, int K, int dt
  * 192, 224, 256 for every later call.  The result is the same sum in the same order
  * for every width; the smaller tiles keep that order too, except that from
  * K = 2048 on they may add partial sums over k.  rov_gemm_swiglu and
- * rov_gemm_swiglu_fp8 have two tile forms: 256 forces the wide one, 128 the narrow
- * one, other values leave their choice to the shape.  For experiments
+ * rov_gemm_swiglu_fp8 have five tile forms: 256 forces the widest, 128 the narrowest,
+ * other values leave their choice to the shape.  For experiments
  * and tests; process-wide.  Returns the previous value, or ROV_ERR_INVALID
  * (nothing changed) for any other argument. */
 int rov_set_gemm_tile_cols(int cols);

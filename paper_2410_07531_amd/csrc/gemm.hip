@@ -197,10 +197,13 @@ __device__ __forceinline__ void epilogue_combine(int epi, uint2 r, float& c0, fl
 // The tile of workgroup blockIdx.x, computed by the workgroup's waves 0-3 (`wave`; `lane` = lane
 // in the wave).  Its barriers are workgroup barriers: 1 + 2*(K*2/128) of them for bf16, 1 + K/128
 // for fp8, whatever the tile; any other wave of the workgroup has to arrive at as many.
-// DUAL (SwiGLU, bf16): the tile's weight rows are, per wave, 8*NJ rows of Wt (the gate
-// projection) followed by the same 8*NJ rows of Wt2 (the up projection); the epilogue writes
-// silu(gate) * up for those 8*NJ output columns, both still in fp32, so the gate projection is
-// neither stored nor read back and the activation panel is fetched once for the two products.
+// DUAL (SwiGLU): the tile's weight rows are rows of Wt (the gate projection) and the same rows of Wt2 (the up
+// projection); the epilogue writes silu(gate) * up for those 16*NJ output columns, both still in fp32, so the gate
+// projection is neither stored nor read back and the activation panel is fetched once for the two products.
+// With 8 or 4 blocks per wave these are, per wave, 8*NJ gate rows followed by 8*NJ up rows.  With 5, 6 or 7 every
+// 16-row block is 8 gate rows followed by 8 up rows, and gate and up of an output meet across the half-waves by a
+// lane swap that serves two activation blocks at once (the swaps make that form 1 % slower at 8 blocks, so 8 and 4 keep
+// theirs).
 // OUT8 (dual form only): the result is written as OCP e4m3 bytes, out_inv * silu(alpha * gate) *
 // (alpha2 * up) rounded to the nearest code, the SwiGLU output of the fp8 block quantised where it
 // is produced; C then points at bytes.
@@ -210,8 +213,8 @@ __device__ __forceinline__ void gemm_tile(const char* __restrict__ A, const char
                                           const uint16_t* __restrict__ R, int M, int N, int K, float alpha,
                                           int tiles_m, int tiles_n, int epi, char* lds, const int lane,
                                           const int wave, float alpha2 = 1.0f, float out_inv = 1.0f) {
-    static_assert(!DUAL || NJ == 8 || NJ == 4, "dual form: 8 or 4 weight blocks per wave");
     static_assert(!OUT8 || DUAL, "e4m3 output exists in the dual form only");
+    constexpr bool MIXED = DUAL && NJ % 4 != 0;   // gate and up rows in every weight block
     const int wm = wave >> 1, wn = wave & 1;
 
     // XCD-aware tile id: workgroup ids are dealt round-robin to the 8 XCDs; give each XCD a
@@ -278,8 +281,10 @@ __device__ __forceinline__ void gemm_tile(const char* __restrict__ A, const char
         const int row = (wave + 4 * j) * 8 + (lane >> 3);
         const int chunk = (lane & 7) ^ swz(row);
         const int ra = row < rows_a ? row : rows_a - 1;   // rows past the edge are never stored
-        // dual: LDS rows [16*NJ*h, +8*NJ) are gate rows of output columns 8*NJ*h .., the next 8*NJ the up rows
-        const int wcol = DUAL ? (row / (16 * NJ)) * (8 * NJ) + row % (8 * NJ) : row;
+        // dual: LDS rows [16*NJ*h, +8*NJ) are gate rows of output columns 8*NJ*h .., the next 8*NJ the up rows;
+        // mixed: LDS rows [16*b, +8) are gate rows of output columns 8*b .., the next 8 the up rows
+        const int wcol = MIXED ? (row >> 4) * 8 + (row & 7)
+                               : DUAL ? (row / (16 * NJ)) * (8 * NJ) + row % (8 * NJ) : row;
         const int rw = wcol < rows_w ? wcol : rows_w - 1;
         voff_a[j] = (uint32_t)((size_t)ra * ld_bytes) + (uint32_t)(chunk * 16);
         if (j < NJ) voff_w[j] = (uint32_t)((size_t)rw * ld_bytes) + (uint32_t)(chunk * 16);
@@ -301,8 +306,9 @@ __device__ __forceinline__ void gemm_tile(const char* __restrict__ A, const char
         return r;
     };
     const i32x4 rsrc_a = make_rsrc(a_panel, (size_t)rows_a * ld_bytes);
-    const i32x4 rsrc_w = make_rsrc(w_panel, (size_t)rows_w * ld_bytes);
-    const i32x4 rsrc_w2 = DUAL ? make_rsrc(Wt2 + (size_t)n0 * ld_bytes, (size_t)rows_w * ld_bytes) : rsrc_w;
+    // (mixed: a load fills 8 rows, row block wave + 4*j, so odd waves load the up rows)
+    const i32x4 rsrc_w = make_rsrc(MIXED && (wave & 1) ? Wt2 + (size_t)n0 * ld_bytes : w_panel, (size_t)rows_w * ld_bytes);
+    const i32x4 rsrc_w2 = DUAL && !MIXED ? make_rsrc(Wt2 + (size_t)n0 * ld_bytes, (size_t)rows_w * ld_bytes) : rsrc_w;
     const uint32_t lds_base = (uint32_t)(uintptr_t)(lptr_t)lds;
 
     // Load instruction q (0..7 = A row blocks, 8..7+NJ = W row blocks) of slot-step `step` into the
@@ -323,7 +329,7 @@ __device__ __forceinline__ void gemm_tile(const char* __restrict__ A, const char
             const uint32_t dst = slot + (uint32_t)(BM * kRow + (wave + 4 * (q - 8)) * 1024);
             // dual: row block wave + 4*(q-8) holds up rows iff it lies in the second half of its wave's
             // 2*NJ row blocks; with NJ = 8 or 4 that does not depend on the wave
-            const bool up = DUAL && (4 * (q - 8)) % (2 * NJ) >= NJ;
+            const bool up = DUAL && !MIXED && (4 * (q - 8)) % (2 * NJ) >= NJ;
             asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
                          :: "s"(dst), "v"(voff_w[q - 8]), "s"(up ? rsrc_w2 : rsrc_w), "s"(koff) : "memory");
         }
@@ -474,30 +480,53 @@ __device__ __forceinline__ void gemm_tile(const char* __restrict__ A, const char
     const int mrow = lane & 15;
     const int nsub = (lane >> 4) * 4;
     if constexpr (DUAL) {
+        auto store4 = [&](int m, int n, const float (&o)[4]) {
+            if (m >= M || n >= N) return;
+            if constexpr (OUT8) {
+                *reinterpret_cast<uint32_t*>(reinterpret_cast<uint8_t*>(C) + (size_t)m * N + n) =
+                    pack_e4m3x4(o[0] * out_inv, o[1] * out_inv, o[2] * out_inv, o[3] * out_inv);
+            } else {
+                uint2 v;
+                v.x = pack_bf16x2(o[0], o[1]);
+                v.y = pack_bf16x2(o[2], o[3]);
+                *reinterpret_cast<uint2*>(C + (size_t)m * N + n) = v;
+            }
+        };
+        const float alpha_up = OUT8 ? alpha2 : alpha;
+        if constexpr (!MIXED) {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const int m = m0 + wm * 128 + i * 16 + mrow;
-            __builtin_amdgcn_sched_barrier(0);
+            for (int i = 0; i < 8; ++i) {
+                __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int j = 0; j < NJ / 2; ++j) {
-                const int n = n0 + wn * 8 * NJ + j * 16 + nsub;
-                float o[4];
+                for (int j = 0; j < NJ / 2; ++j) {
+                    float o[4];
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const float gte = alpha * acc_read(acc[j][i][e]);
-                    const float upv = (DUAL && OUT8 ? alpha2 : alpha) * acc_read(acc[j + NJ / 2][i][e]);
-                    o[e] = gte / (1.0f + __expf(-gte)) * upv;
-                }
-                if (m < M && n < N) {
-                    if constexpr (OUT8) {
-                        *reinterpret_cast<uint32_t*>(reinterpret_cast<uint8_t*>(C) + (size_t)m * N + n) =
-                            pack_e4m3x4(o[0] * out_inv, o[1] * out_inv, o[2] * out_inv, o[3] * out_inv);
-                    } else {
-                        uint2 v;
-                        v.x = pack_bf16x2(o[0], o[1]);
-                        v.y = pack_bf16x2(o[2], o[3]);
-                        *reinterpret_cast<uint2*>(C + (size_t)m * N + n) = v;
+                    for (int e = 0; e < 4; ++e) {
+                        const float gte = alpha * acc_read(acc[j][i][e]);
+                        const float upv = alpha_up * acc_read(acc[j + NJ / 2][i][e]);
+                        o[e] = gte / (1.0f + __expf(-gte)) * upv;
                     }
+                    store4(m0 + wm * 128 + i * 16 + mrow, n0 + wn * 8 * NJ + j * 16 + nsub, o);
+                }
+            }
+        } else {
+            // lanes 0-31 hold the gate values of their row and four columns, lanes 32-63 the up values of the same; after
+            // the swap lanes 0-31 have both of activation block i, lanes 32-63 both of block i + 1
+#pragma unroll
+            for (int i = 0; i < 8; i += 2) {
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int j = 0; j < NJ; ++j) {
+                    float o[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const auto gu = __builtin_amdgcn_permlane32_swap(__float_as_uint(acc_read(acc[j][i][e])),
+                                                                         __float_as_uint(acc_read(acc[j][i + 1][e])), false, false);
+                        const float gte = alpha * __uint_as_float(gu[0]);
+                        const float upv = alpha_up * __uint_as_float(gu[1]);
+                        o[e] = gte / (1.0f + __expf(-gte)) * upv;
+                    }
+                    store4(m0 + wm * 128 + (i + (lane >> 5)) * 16 + mrow, n0 + (wn * NJ + j) * 8 + ((lane >> 4) & 1) * 4, o);
                 }
             }
         }
@@ -653,6 +682,30 @@ __global__ __launch_bounds__(512, 1) void gemm_rng_kernel(const char* __restrict
     }
 }
 
+// Weight blocks per wave (tiles of 16 * blocks output columns) of the dual kernels for `slots` slots of k: the one with
+// the smallest estimated time, the widest on ties; slot_ns: one slot with four blocks, each further one block_ns more
+// (measured at 2000 and 16384 x 14336 x 4096, all tiles forced in turn).  Seven blocks make 14336 columns 128 tiles, full
+// rounds for few tile rows: us with 8 / 7 blocks at 2000 rows 364 / 356 (bf16), 236 / 217 (fp8), at 4096 676 / 699, 415 / 421;
+// 3000 x 2816 x 1024 54.6 with 8, 42.6 with 5; 128 x 14336 x 4096 88 with 8, 77 with 4.  Where the widest needs one round
+// a narrower tile has to promise 5 %: the compute units that the widest leaves free there run the mask kernel beside
+// it (bf16 block of 512 tokens 600 with 8, 603 with 7; the fp8 product of it alone 68 and 64).
+// rov_set_gemm_tile_cols: 256 forces the widest tile, 128 the narrowest.
+int pick_dual_blocks(int M, int N, int slots, double slot_ns, double block_ns) {
+    const int forced = g_tile_cols.load();
+    if (forced == 256) return 8;
+    if (forced == 128) return 4;
+    const long long tiles_m = (M + BM - 1) / BM;
+    const double bar = tiles_m * ((N + 127) / 128) <= device_cu_count() ? 0.95 : 1.0;
+    int best = 8;
+    double widest_ns = 0.0, best_ns = 0.0;
+    for (int nj = 8; nj >= 4; --nj) {
+        const double t = gemm_tiles_ns(tiles_m * ((N + 16 * nj - 1) / (16 * nj)), slots, slot_ns + block_ns * (nj - 4));
+        if (nj == 8) { widest_ns = best_ns = t; }
+        else if (t < best_ns && t < bar * widest_ns) { best = nj; best_ns = t; }
+    }
+    return best;
+}
+
 }  // namespace
 
 int check_gemm_swiglu(const void* A, const void* Wg, const void* Wu, const void* C, int M, int N, int K) {
@@ -671,18 +724,13 @@ int launch_gemm_swiglu(const void* A, const void* Wg, const void* Wu, void* C, i
         const int rc = check_gemm_swiglu(A, Wg, Wu, C, M, N, K);
         if (rc != ROV_OK) return rc;
     }
-    // 128 or 64 output columns per tile (8 or 4 weight blocks per wave, half gate, half up).  The
-    // narrow tile takes 0.67 of the wide tile's time for half of its work (measured on
-    // 2048...8192 x 14336 x 4096), so it is chosen only where it saves more than a third of the rounds
-    const long long tiles_m = (M + BM - 1) / BM, ncu = device_cu_count();
-    const long long t8 = tiles_m * ((N + 127) / 128), t4 = tiles_m * ((N + 63) / 64);
-    const int forced = g_tile_cols.load();    // rov_set_gemm_tile_cols: 256 forces the wide tile, 128 the narrow one
-    const bool wide = forced == 256 ? true : forced == 128 ? false
-                                                           : ((t8 + ncu - 1) / ncu) * 3 <= ((t4 + ncu - 1) / ncu) * 2;
-    const long long T = wide ? t8 : t4;
+    const int nj = pick_dual_blocks(M, N, (int)((size_t)K * 2 / kRowBytes), 1040.0, 110.0);
+    const long long tiles_m = (M + BM - 1) / BM, T = tiles_m * ((N + 16 * nj - 1) / (16 * nj));
     if (T > 0x7FFFFFFFLL) return ROV_ERR_UNSUPPORTED;
     typedef void (*kern_t)(const char*, const char*, const char*, uint16_t*, int, int, int, int, int);
-    const kern_t kern = wide ? (kern_t)gemm_swiglu_kernel<8> : (kern_t)gemm_swiglu_kernel<4>;
+    static const kern_t kerns[5] = {gemm_swiglu_kernel<4>, gemm_swiglu_kernel<5>, gemm_swiglu_kernel<6>,
+                                    gemm_swiglu_kernel<7>, gemm_swiglu_kernel<8>};
+    const kern_t kern = kerns[nj - 4];
     {
         const int rc = set_max_dynamic_lds((const void*)kern, kLdsBytes);
         if (rc != ROV_OK) return rc;
@@ -728,14 +776,13 @@ int launch_gemm_swiglu_fp8(const void* A, const void* Wg, const void* Wu, void* 
         const int rc = check_gemm_swiglu_fp8(A, Wg, Wu, C, M, N, K, scaleC);
         if (rc != ROV_OK) return rc;
     }
-    const long long tiles_m = (M + BM - 1) / BM, ncu = device_cu_count();
-    const long long t8 = tiles_m * ((N + 127) / 128), t4 = tiles_m * ((N + 63) / 64);
-    const int forced = g_tile_cols.load();
-    const bool wide = forced == 256 ? true : forced == 128 ? false
-                                                           : ((t8 + ncu - 1) / ncu) * 3 <= ((t4 + ncu - 1) / ncu) * 2;
-    const long long T = wide ? t8 : t4;
+    const int nj = pick_dual_blocks(M, N, K / kRowBytes, 1150.0, 172.0);
+    const long long tiles_m = (M + BM - 1) / BM, T = tiles_m * ((N + 16 * nj - 1) / (16 * nj));
+    if (T > 0x7FFFFFFFLL) return ROV_ERR_UNSUPPORTED;
     typedef void (*kern_t)(const char*, const char*, const char*, uint8_t*, int, int, int, int, int, float, float, float);
-    const kern_t kern = wide ? (kern_t)gemm_swiglu_fp8_kernel<8> : (kern_t)gemm_swiglu_fp8_kernel<4>;
+    static const kern_t kerns[5] = {gemm_swiglu_fp8_kernel<4>, gemm_swiglu_fp8_kernel<5>, gemm_swiglu_fp8_kernel<6>,
+                                    gemm_swiglu_fp8_kernel<7>, gemm_swiglu_fp8_kernel<8>};
+    const kern_t kern = kerns[nj - 4];
     {
         const int rc = set_max_dynamic_lds((const void*)kern, kLdsBytes);
         if (rc != ROV_OK) return rc;

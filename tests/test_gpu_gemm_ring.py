@@ -117,3 +117,30 @@ def test_fp32_product_keeps_infinities_and_nan_in_their_rows():
     exp[3] = float("inf")
     exp[:, 7] = float("nan")
     assert torch.equal(torch.nan_to_num(C, nan=-1.0), torch.nan_to_num(exp, nan=-1.0))
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "fp8"])
+@pytest.mark.parametrize("M,N,K", [
+    (300, 14336, 128),       # seven weight blocks a wave, ragged rows
+    (2900, 2820, 1024),      # five, ragged columns (last tile: 4 of 80)
+    (2900, 2816, 128),       # five or six
+    (2304, 3300, 256),       # nine tile rows
+    (70, 4, 128),            # one tile, four columns
+])
+def test_dual_tiles_of_every_width_give_the_same_bits(dtype, M, N, K):
+    # the width chosen from the shape against the widest and the narrowest (whose parity has its own tests)
+    print("dual", dtype, M, N, K, flush=True)
+    A, Wg, _, _ = _operands(dtype, M, N, K, True)
+    g = torch.Generator("cuda").manual_seed(N)
+    Wu = Wg[torch.randperm(N, device="cuda", generator=g)].contiguous()
+    run = (lambda: rov.gemm_swiglu(A, Wg, Wu)) if dtype == "bf16" else (lambda: rov.gemm_swiglu_fp8(A, Wg, Wu, 1 / 16, 1 / 64, 1 / 64, 0.25))
+    got = {}
+    for cols in (0, 256, 128):
+        prev = rov.set_gemm_tile_cols(cols)
+        try:
+            got[cols] = run()
+            torch.cuda.synchronize()
+        finally:
+            rov.set_gemm_tile_cols(prev)
+    assert torch.equal(got[0], got[256]) and torch.equal(got[0], got[128])
+    assert got[0].float().abs().max() > 0
