@@ -674,7 +674,9 @@ __global__ __launch_bounds__(NW * 64) void attn_f32_kernel(const AttnParams p) {
     const int q0 = p.q_begin + qblk * 32, qrow = q0 + ql;
     const float* Qp = (const float*)p.Q + b * p.sq[0] + h * p.sq[2] + (int64_t)min(qrow, p.q_end - 1) * p.sq[1];
     // K and V of this (batch, kv head) as buffer resources over the rows [0, S): lane offset plus tile row, no
-    // 64-bit address per register, and rows at or beyond S read as zeros
+    // 64-bit address per register, and rows at or beyond S read as zeros.  The check compares the lane offset with
+    // what the scalar offset leaves of the size, so the scalar offset itself stays within the size: a tile's first row for
+    // K, no row beyond the last for V (vlast).
     const uint32_t krow = (uint32_t)p.sk[1] * 4u, vrow = (uint32_t)p.sv[1] * 4u;
     const __amdgpu_buffer_rsrc_t kres = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<float*>((const float*)p.K + b * p.sk[0] + hk * p.sk[2]), 0, (int)((uint32_t)(S - 1) * krow + (uint32_t)d * 4u), 0x00020000);
@@ -709,6 +711,7 @@ __global__ __launch_bounds__(NW * 64) void attn_f32_kernel(const AttnParams p) {
     uint32_t voff[DVT];
 #pragma unroll
     for (int t = 0; t < DVT; ++t) voff[t] = (uint32_t)(4 * half) * vrow + (uint32_t)min(32 * t + ql, d - 1) * 4u;
+    const uint32_t vlast = (uint32_t)(S - 1) * vrow;
     const int kv_end = p.causal ? min(S, q0 + 32) : S;
     const int nkt = (kv_end + 31) / 32;
     if (wave < nkt) load_k(32 * wave);
@@ -716,14 +719,15 @@ __global__ __launch_bounds__(NW * 64) void attn_f32_kernel(const AttnParams p) {
     for (int kt = wave; kt < nkt; kt += NW) {
         const int kv0 = 32 * kt;
         // V: register e of feature tile t is the lane's feature 32t + ql of key kv0 + 8*(e/4) + 4*half + e%4, the key
-        // of score register e.  Features beyond d repeat the last one (their outputs are not stored); keys beyond S are zeros.
+        // of score register e.  Features beyond d repeat the last one (their outputs are not stored); keys beyond S are the
+        // last key's values or zeros, under probabilities of zero.
         float vf[DVT][16];
 #pragma unroll
         for (int e = 0; e < 16; ++e)
 #pragma unroll
             for (int t = 0; t < DVT; ++t)
                 vf[t][e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
-                    vres, voff[t], (uint32_t)(kv0 + 8 * (e >> 2) + (e & 3)) * vrow, 0));
+                    vres, voff[t], min((uint32_t)kv0 * vrow + (uint32_t)(8 * (e >> 2) + (e & 3)) * vrow, vlast), 0));
         uint64_t mw[16];
         if (MODE == MODE_MASK) {
             const const_u64_ptr wp = (const_u64_ptr)(uintptr_t)(mtile + (uint64_t)kt * 16u);

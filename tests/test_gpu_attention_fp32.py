@@ -88,3 +88,22 @@ def test_fp32_causal_rows_never_see_later_values():
     others = [i for i in range(d) if i != 3]
     assert torch.allclose(O[0, 40:77, 0, others], ref[0, 40:77, 0, others], rtol=1e-5, atol=1e-6)
     assert bool(torch.isnan(O[0, 77:]).all())
+
+
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("S,d", [(1, 8), (33, 40), (60, 64), (97, 128)])
+def test_fp32_rows_behind_the_last_key_are_not_part_of_the_result(S, d, causal):
+    # K and V end inside a tile of 32 keys and what lies behind them in memory is NaN: the loads stay in the rows
+    # [0, S) (the row of a load is clamped to the last one, the rest is outside its buffer's range)
+    print("attn fp32 rows behind", S, d, causal, flush=True)
+    g = torch.Generator("cuda").manual_seed(S)
+    buf = [torch.full((1, S + 40, 2, d), float("nan"), device="cuda") for _ in range(3)]
+    Q, K, V = (x[:, :S] for x in buf)
+    for x in (Q, K, V):
+        x.copy_(torch.randn(1, S, 2, d, device="cuda", generator=g))
+    frame = torch.full((1, S + 40, 2, d), 7.0, device="cuda")
+    rov.attention_fwd_dropout(Q, K, V, 0.0, causal=causal, O=frame[:, :S])
+    torch.cuda.synchronize()
+    ref = OD.attention_dropout(*(t.double().cpu().numpy() for t in (Q, K, V)), None, 0.0, causal=causal)
+    assert _err(frame[:, :S], ref) <= TOL
+    assert bool((frame[:, S:] == 7.0).all())
