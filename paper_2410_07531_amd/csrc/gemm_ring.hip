@@ -206,12 +206,13 @@ __global__ __launch_bounds__(64 * WM * WN * KS) void gemm_ring_kernel(const Ring
     int f_slot = 0, f_st = kstart, f_left = ns;
     auto next_fill = [&]() {
         f_slot = f_slot + 1 == STAGES ? 0 : f_slot + 1;
-        f_st = f_st + 1 == ns ? 0 : f_st + 1;
         --f_left;
+        f_st = f_left <= 0 || f_st + 1 == ns ? 0 : f_st + 1;
     };
     // Inline assembly: the compiler's wait-count pass cannot tell these LDS writes from the fragment reads;
     // the kernel places its vmcnt waits itself.  M0 is only set by compiled code right before its own uses.
-    // Past the end of the walk the range is empty: no memory access, and the counter's arithmetic holds.
+    // Past the end of the walk the range is empty and the scalar offset zero (the check takes it off the size):
+    // no memory access, and the counter's arithmetic holds.
     auto issue = [&](int q) {
         const int q1 = q % L1;
         const bool is_w = q1 >= LA;

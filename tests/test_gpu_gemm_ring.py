@@ -91,6 +91,28 @@ def test_small_tiles_match_oracle(dtype, M, N, K, transB):
     assert err <= (1e-5 if dtype == "f32" else 6e-3), err
 
 
+@pytest.mark.parametrize("dtype,M,N,K,transB", [
+    ("bf16", 70, 36, 64, True), ("bf16", 333, 4096, 2112, True), ("bf16", 65, 130, 102, True), ("bf16", 257, 264, 72, False),
+    ("fp8", 77, 131, 144, True), ("f32", 33, 36, 36, True), ("f32", 33, 47, 131, True), ("f32", 65, 36, 68, False),
+])
+def test_memory_behind_the_operands_is_not_part_of_the_result(dtype, M, N, K, transB):
+    # rows past the edge, the partly filled last slot and the loads issued past the end of the walk over k (all of them,
+    # where the ring has more slots than the sum) lie outside the operands' ranges: NaN behind A and W changes nothing
+    print("gemm ring behind", dtype, M, N, K, transB, flush=True)
+    A, W, _, _ = _operands(dtype, M, N, K, transB)
+
+    def framed(t, fill):
+        buf = torch.full((t.numel() + 64 * K + 4096,), fill, dtype=t.dtype, device="cuda")
+        buf[:t.numel()] = t.flatten()
+        return buf[:t.numel()].view(t.shape)
+
+    nan = 0x7F if dtype == "fp8" else float("nan")
+    C = rov.gemm(framed(A, nan), framed(W, nan), transB=transB)
+    C0 = rov.gemm(framed(A, 0), framed(W, 0), transB=transB)
+    torch.cuda.synchronize()
+    assert bool(torch.isfinite(C.float()).all()) and torch.equal(C, C0)
+
+
 @pytest.mark.parametrize("dtype,M,N,K", [("bf16", 300, 2048, 1024), ("bf16", 700, 4096, 512), ("fp8", 300, 2048, 4096),
                                          ("fp8", 520, 8192, 1024)])
 def test_unsplit_small_tiles_give_the_256_row_kernels_bits(dtype, M, N, K):
