@@ -193,22 +193,38 @@ int rov_valu_probe(int kind, int iters, int workgroups, uint64_t *out, void *str
 int rov_gemm(const void *A, const void *Bm, void *C, int M, int N, int K, int dtype, int transB,
              float scaleA, float scaleB, void *stream);
 
-/* Tile width of the bf16 matrix-core GEMM kernel (the Table 1 GEMM column's
- * MMA-bound kernel), in output columns: 0 = chosen per call from the shape (the
- * default: the width that wastes least of the last round of workgroups over the
- * compute units; or a smaller tile where that is done sooner), or one of 128, 160,
- * 192, 224, 256 for every later call.  The result is the same sum in the same order
- * for every width; the smaller tiles keep that order too, except that from
- * K = 2048 on they may add partial sums over k.  rov_gemm_swiglu and
- * rov_gemm_swiglu_fp8 have five tile forms: 256 forces the widest, 128 the narrowest,
- * other values leave their choice to the shape.  For experiments
+/* Tile width of the 256-row matrix-core GEMM kernels (the Table 1 GEMM column's
+ * MMA-bound kernels, bf16 and fp8), in output columns: 0 = chosen per call from the
+ * shape (the default: the width that wastes least of the last round of workgroups over
+ * the compute units; or a kernel with smaller tiles where that is done sooner, see
+ * rov_gemm_tile), or one of 128, 160, 192, 224, 256 for every later call that these
+ * kernels can take.  The result is the same sum in the same order for every one of these
+ * widths, whatever M and N; the smaller tiles keep that order too below K = 2048 and
+ * from there on may add partial sums over k, so that with 0 the last bit of a result
+ * can depend on M and N.  rov_gemm_swiglu and rov_gemm_swiglu_fp8 have the same five
+ * forms, with half as many columns of either product.  For experiments
  * and tests; process-wide.  Returns the previous value, or ROV_ERR_INVALID
  * (nothing changed) for any other argument. */
 int rov_set_gemm_tile_cols(int cols);
-/* The tile width the matrix-core kernel uses for an M x N output with the
+/* The tile width the 256-row kernels use for an M x N output with the
  * current setting (host-side rule, no device work): 128..256, or
- * ROV_ERR_INVALID for M <= 0 or N <= 0. */
+ * ROV_ERR_INVALID for M <= 0 or N <= 0.  Whether rov_gemm runs one of them for
+ * a product depends on K, the data type and the layout too: rov_gemm_tile. */
 int rov_gemm_tile_cols(int M, int N);
+/* The kernel that rov_gemm runs for a product with the current setting (host-side rule,
+ * no device work): ROV_GEMM_256_ROWS, ROV_GEMM_SMALL_TILES (short products, [K,N]
+ * weights, fp32, rows off 128 bytes) or ROV_GEMM_ANY_SHAPE (vector units; what the
+ * others do not take), or the error code of such a call with aligned operands.
+ * tile (host): rows and columns of its tile, parts of k that the waves of a workgroup
+ * add up, bytes of an operand that a lane loads at once. */
+#define ROV_GEMM_256_ROWS 0
+#define ROV_GEMM_SMALL_TILES 1
+#define ROV_GEMM_ANY_SHAPE 2
+int rov_gemm_tile(int M, int N, int K, int dtype, int transB, int tile[4]);
+/* Output columns of a tile of rov_gemm_swiglu (dtype ROV_BF16) or rov_gemm_swiglu_fp8
+ * (ROV_FP8_E4M3) with the current setting, 64..128 (host-side rule), or the error code of
+ * such a call with aligned operands. */
+int rov_gemm_swiglu_tile_cols(int M, int N, int K, int dtype);
 
 /* C[M,N] = silu(A Wg^T) * (A Wu^T), bf16 operands and result, fp32 accumulation: the gate and
  * up projections of the block's SwiGLU feed-forward (Fig. 2's FC1 in its Llama form) as one
@@ -258,6 +274,13 @@ int rov_attention_fwd_dropout(const void *Q, const void *K, const void *V, void 
                               int B, int H, int Hkv, int S, int d, const int64_t strides[12],
                               int dtype, int causal, float p, const uint64_t *mask,
                               uint64_t seed, uint64_t offset, void *stream);
+
+/* How the matrix-core attention kernels share the keys of a query tile between waves (host-side
+ * rule, no device work): the number of waves, 1, 2 or 4 for bf16 with d = 64 or 128 and 4 or 8 for
+ * fp32 with d <= 128 a multiple of 8; 0 where the one-row-per-wave kernel for any shape runs (also for
+ * rows off 16 bytes, which this function does not see).  The same for every range of rows of a
+ * problem, every mode and every stream.  ROV_ERR_INVALID for other arguments. */
+int rov_attention_key_parts(int B, int H, int S, int d, int dtype, int causal);
 
 /* Same with a selectable Philox round count for the fused variant (paper Sec. 5.2): with
  * mask == NULL and p > 0 the kernel draws the bits of
@@ -325,6 +348,12 @@ typedef struct rov_attn_desc {
 int rov_layer_step(int schedule, const rov_gemm_desc *gemms, int n_gemms, const rov_attn_desc *attn,
                    uint64_t seed, uint64_t offset, uint64_t *mask, void *main_stream,
                    void *side_stream);
+
+/* How an overlap schedule shares a mask beside GEMMs of gemm_flop operations in `dtype` (host-side
+ * rule, no device work): the number of 64-word chunks, (rov_mask_words + 63) / 64 in all, that the grid
+ * on side_stream makes, the launch behind the GEMMs making the rest; -1: the two share a work queue;
+ * -2: invalid arguments. */
+int64_t rov_overlap_mask_chunks(double gemm_flop, int dtype, int B, int H, int S, int causal, int rounds);
 
 /* rov_layer_step with a selectable Philox round count (paper Sec. 5.2: fewer rounds shrink both
  * the stand-alone RNG kernel and the fused attention kernel, and with them what the overlap

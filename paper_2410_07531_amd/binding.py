@@ -76,6 +76,10 @@ SIGNATURES = {
     "rov_set_rng_max_workgroups": (_i, [_i]),
     "rov_set_gemm_tile_cols": (_i, [_i]),
     "rov_gemm_tile_cols": (_i, [_i, _i]),
+    "rov_gemm_tile": (_i, [_i, _i, _i, _i, _i, ctypes.POINTER(ctypes.c_int)]),
+    "rov_gemm_swiglu_tile_cols": (_i, [_i, _i, _i, _i]),
+    "rov_attention_key_parts": (_i, [_i, _i, _i, _i, _i, _i]),
+    "rov_overlap_mask_chunks": (ctypes.c_int64, [ctypes.c_double, _i, _i, _i, _i, _i, _i]),
     "rov_set_rng_overlap_workgroups_per_cu": (_i, [_i]),
     "rov_trace_enable": (_i, [_i]),
     "rov_trace_read": (_i, [ctypes.POINTER(ctypes.c_int), ctypes.POINTER(ctypes.c_float), _i,
@@ -196,6 +200,40 @@ def set_gemm_tile_cols(cols):
 
 def gemm_tile_cols(M, N):
     return int(load().rov_gemm_tile_cols(int(M), int(N)))
+
+
+GEMM_256_ROWS, GEMM_SMALL_TILES, GEMM_ANY_SHAPE = 0, 1, 2
+
+
+def gemm_tile(M, N, K, dtype, transB=True):
+    """(kernel, rows, columns, parts of k, bytes of a lane's load) of the product rov_gemm would run."""
+    t = (ctypes.c_int * 4)()
+    kernel = load().rov_gemm_tile(M, N, K, dtype, int(bool(transB)), t)
+    if kernel < 0:
+        raise RovError(kernel, "rov_gemm_tile")
+    return (kernel,) + tuple(t)
+
+
+def gemm_swiglu_tile_cols(M, N, K, dtype):
+    r = load().rov_gemm_swiglu_tile_cols(M, N, K, dtype)
+    if r < 0:
+        raise RovError(r, "rov_gemm_swiglu_tile_cols")
+    return r
+
+
+def attention_key_parts(B, H, S, d, dtype, causal):
+    r = load().rov_attention_key_parts(B, H, S, d, dtype, int(bool(causal)))
+    if r < 0:
+        raise RovError(r, "rov_attention_key_parts")
+    return r
+
+
+def overlap_mask_chunks(gemm_flop, dtype, B, H, S, causal=False, rounds=10):
+    """Chunks of the mask that the grid beside the GEMMs makes; -1: a work queue."""
+    r = load().rov_overlap_mask_chunks(float(gemm_flop), dtype, B, H, S, int(bool(causal)), rounds)
+    if r < -1:
+        raise RovError(ERR_INVALID, "rov_overlap_mask_chunks")
+    return r
 
 
 def set_rng_overlap_workgroups_per_cu(n):

@@ -1066,7 +1066,10 @@ int attn_key_parts(int B, int H, int S, int d, bool causal) {
     return best;
 }
 
-// Waves of a workgroup of the fp32 kernel: eight at up to 64 features, four above (their registers).
+// Waves of a workgroup of the fp32 kernel: eight at up to 64 features, four above (their registers); 0: a head dimension
+// that it does not take.
+int attn_f32_waves(int d) { return d % 8 != 0 || d > 128 ? 0 : d <= 64 ? 8 : 4; }
+
 template <int DP, int NW>
 int launch_f32(const AttnParams& prm, int mode, hipStream_t stream) {
     AttnParams prm2 = prm;
@@ -1201,7 +1204,7 @@ int launch_attention_rows(const void* Q, const void* K, const void* V, void* O, 
             return launch_bf16<64, 1, 8, 1>(prm, mode, stream);
         }
     }
-    if (dtype == ROV_F32 && d <= 128 && d % 8 == 0) {
+    if (dtype == ROV_F32 && attn_f32_waves(d) != 0) {
         // 16-byte accesses to rows of Q, K and O
         bool ok = aligned(Q, 16) && aligned(K, 16) && aligned(O, 16);
         for (int i = 0; i < 12; ++i) ok = ok && (i / 3 == 2 || strides[i] % 4 == 0);
@@ -1219,6 +1222,13 @@ int launch_attention_rows(const void* Q, const void* K, const void* V, void* O, 
 }
 
 }  // namespace rov
+
+extern "C" int rov_attention_key_parts(int B, int H, int S, int d, int dtype, int causal) {
+    if (B <= 0 || H <= 0 || S <= 0 || d <= 0 || d > 256) return ROV_ERR_INVALID;
+    if (dtype != ROV_F32 && dtype != ROV_BF16) return ROV_ERR_INVALID;
+    if (dtype == ROV_F32) return rov::attn_f32_waves(d);
+    return d == 64 || d == 128 ? rov::attn_key_parts(B, H, S, d, causal != 0) : 0;
+}
 
 extern "C" int rov_attention_fwd_dropout_rows(const void* Q, const void* K, const void* V, void* O, int B,
                                               int H, int Hkv, int S, int d, const int64_t strides[12],

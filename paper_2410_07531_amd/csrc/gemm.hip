@@ -689,11 +689,10 @@ __global__ __launch_bounds__(512, 1) void gemm_rng_kernel(const char* __restrict
 // 3000 x 2816 x 1024 54.6 with 8, 42.6 with 5; 128 x 14336 x 4096 88 with 8, 77 with 4.  Where the widest needs one round
 // a narrower tile has to promise 5 %: the compute units that the widest leaves free there run the mask kernel beside
 // it (bf16 block of 512 tokens 600 with 8, 603 with 7; the fp8 product of it alone 68 and 64).
-// rov_set_gemm_tile_cols: 256 forces the widest tile, 128 the narrowest.
+// rov_set_gemm_tile_cols forces the tile of as many blocks: half its columns of either product.
 int pick_dual_blocks(int M, int N, int slots, double slot_ns, double block_ns) {
     const int forced = g_tile_cols.load();
-    if (forced == 256) return 8;
-    if (forced == 128) return 4;
+    if (forced != 0) return forced / 32;
     const long long tiles_m = (M + BM - 1) / BM;
     const double bar = tiles_m * ((N + 127) / 128) <= device_cu_count() ? 0.95 : 1.0;
     int best = 8;
@@ -704,6 +703,10 @@ int pick_dual_blocks(int M, int N, int slots, double slot_ns, double block_ns) {
         else if (t < best_ns && t < bar * widest_ns) { best = nj; best_ns = t; }
     }
     return best;
+}
+int dual_blocks(int M, int N, int K, int dtype) {
+    return dtype == ROV_BF16 ? pick_dual_blocks(M, N, (int)((size_t)K * 2 / kRowBytes), 1040.0, 110.0)
+                             : pick_dual_blocks(M, N, K / kRowBytes, 1150.0, 172.0);
 }
 
 }  // namespace
@@ -724,7 +727,7 @@ int launch_gemm_swiglu(const void* A, const void* Wg, const void* Wu, void* C, i
         const int rc = check_gemm_swiglu(A, Wg, Wu, C, M, N, K);
         if (rc != ROV_OK) return rc;
     }
-    const int nj = pick_dual_blocks(M, N, (int)((size_t)K * 2 / kRowBytes), 1040.0, 110.0);
+    const int nj = dual_blocks(M, N, K, ROV_BF16);
     const long long tiles_m = (M + BM - 1) / BM, T = tiles_m * ((N + 16 * nj - 1) / (16 * nj));
     if (T > 0x7FFFFFFFLL) return ROV_ERR_UNSUPPORTED;
     typedef void (*kern_t)(const char*, const char*, const char*, uint16_t*, int, int, int, int, int);
@@ -776,7 +779,7 @@ int launch_gemm_swiglu_fp8(const void* A, const void* Wg, const void* Wu, void* 
         const int rc = check_gemm_swiglu_fp8(A, Wg, Wu, C, M, N, K, scaleC);
         if (rc != ROV_OK) return rc;
     }
-    const int nj = pick_dual_blocks(M, N, K / kRowBytes, 1150.0, 172.0);
+    const int nj = dual_blocks(M, N, K, ROV_FP8_E4M3);
     const long long tiles_m = (M + BM - 1) / BM, T = tiles_m * ((N + 16 * nj - 1) / (16 * nj));
     if (T > 0x7FFFFFFFLL) return ROV_ERR_UNSUPPORTED;
     typedef void (*kern_t)(const char*, const char*, const char*, uint8_t*, int, int, int, int, int, float, float, float);
@@ -824,11 +827,8 @@ int launch_gemm_rng(const void* A, const void* Bm, void* C, int M, int N, int K,
 
 // Tile width (output columns, 32*nj) for an M x N product.  The workgroups run in rounds of one per
 // compute unit; a tile costs about nj + 1 units (its A panel does not shrink with it), so the width
-// with the smallest rounds x (nj + 1) is taken, the widest on ties; a width set through
-// rov_set_gemm_tile_cols overrides the rule.
-int pick_tile_cols(int M, int N) {
-    const int forced = g_tile_cols.load();
-    if (forced != 0) return forced;
+// with the smallest rounds x (nj + 1) is taken, the widest on ties.
+int best_tile_cols(int M, int N) {
     const long long tiles_m = (M + BM - 1) / BM, ncu = device_cu_count();
     long long best = -1;
     int nj = 8;
@@ -838,6 +838,33 @@ int pick_tile_cols(int M, int N) {
         if (best < 0 || cost < best) { best = cost; nj = c; }
     }
     return 32 * nj;
+}
+
+// The kernel of a product: the tiles of gemm_ring.hip where the 256-row kernels do not apply, or leave so much of the
+// chip idle that the smaller tile is done sooner.  A width set by rov_set_gemm_tile_cols is a 256-row tile's.
+// ring: the epilogue is one that the small tiles have (none, or the residual).
+struct GemmChoice {
+    int kernel, variant, cols;   // ROV_GEMM_*, index of a small tile, width of a 256-row tile
+};
+GemmChoice choose_gemm(int M, int N, int K, int dtype, int transB, bool ring) {
+    const int esz = dtype == ROV_BF16 ? 2 : 1;
+    const bool wide = dtype != ROV_F32 && transB != 0 && ((size_t)K * esz) % kRowBytes == 0 && (N % 4) == 0;
+    const int forced = g_tile_cols.load();
+    const int cols = wide ? (forced != 0 ? forced : best_tile_cols(M, N)) : 0;
+    if (ring && !(wide && forced != 0)) {
+        double ring_ns = 0.0;
+        const int v = ring_variant(M, N, K, dtype, transB, wide, &ring_ns);
+        if (v >= 0 && !wide) return {ROV_GEMM_SMALL_TILES, v, 0};
+        if (v >= 0) {
+            // one slot (128 bytes of k) of a 256 x 32*nj tile, measured like the times in gemm_ring.hip
+            const int nj = cols / 32;
+            const double slot_ns = dtype == ROV_BF16 ? 890.0 + 130.0 * (nj - 4) : 970.0 + 133.0 * (nj - 4);
+            const long long tiles = (long long)((M + BM - 1) / BM) * ((N + cols - 1) / cols);
+            if (ring_ns < gemm_tiles_ns(tiles, (int)((size_t)K * esz / kRowBytes), slot_ns))
+                return {ROV_GEMM_SMALL_TILES, v, 0};
+        }
+    }
+    return {wide ? ROV_GEMM_256_ROWS : ROV_GEMM_ANY_SHAPE, -1, cols};
 }
 
 int launch_gemm(const void* A, const void* Bm, void* C, int M, int N, int K, int dtype, int transB,
@@ -882,32 +909,16 @@ int launch_gemm_epilogue(const void* A, const void* Bm, void* C, const void* R, 
     const float alpha = scaleA * scaleB;
     const bool tb = transB != 0;
     const int esz = dtype == ROV_BF16 ? 2 : 1;
-    const bool wide = dtype != ROV_F32 && tb && ((size_t)K * esz) % kRowBytes == 0 && (N % 4) == 0;   // the 256-row kernels take it
+    const GemmChoice choice = choose_gemm(M, N, K, dtype, transB, R == nullptr || epi == EPI_ADD);
+    if (choice.kernel == ROV_GEMM_SMALL_TILES)
+        return launch_gemm_ring(choice.variant, A, Bm, C, R, M, N, K, alpha, stream);
 
-    // The tiles of gemm_ring.hip where the 256-row kernels do not apply, or leave so much of the chip idle that the
-    // smaller tile is done sooner.  A width set by rov_set_gemm_tile_cols is a 256-row tile's.
-    if ((R == nullptr || epi == EPI_ADD) && !(wide && g_tile_cols.load() != 0)) {
-        double ring_ns = 0.0;
-        const int v = ring_variant(M, N, K, dtype, transB, wide, &ring_ns);
-        if (v >= 0) {
-            bool take = !wide;
-            if (wide) {
-                // one slot (128 bytes of k) of a 256 x 32*nj tile, measured like the times in gemm_ring.hip
-                const int nj = pick_tile_cols(M, N) / 32;
-                const double slot_ns = dtype == ROV_BF16 ? 890.0 + 130.0 * (nj - 4) : 970.0 + 133.0 * (nj - 4);
-                const long long tiles = (long long)((M + BM - 1) / BM) * ((N + 32 * nj - 1) / (32 * nj));
-                take = ring_ns < gemm_tiles_ns(tiles, (int)((size_t)K * esz / kRowBytes), slot_ns);
-            }
-            if (take) return launch_gemm_ring(v, A, Bm, C, R, M, N, K, alpha, stream);
-        }
-    }
-
-    if (wide) {
+    if (choice.kernel == ROV_GEMM_256_ROWS) {
         // a 256-row operand panel is addressed with 32-bit byte offsets
         if ((unsigned long long)BM * (unsigned long long)K * (unsigned long long)esz > 0xFFFFFFFFull)
             return ROV_ERR_UNSUPPORTED;
         const int tiles_m = (M + BM - 1) / BM;
-        const int nj = pick_tile_cols(M, N) / 32;
+        const int nj = choice.cols / 32;
         const int tiles_n = (N + 32 * nj - 1) / (32 * nj);
         const long long T = (long long)tiles_m * tiles_n;
         if (T > 0x7FFFFFFFLL) return ROV_ERR_UNSUPPORTED;
@@ -962,7 +973,33 @@ int launch_gemm_epilogue(const void* A, const void* Bm, void* C, const void* R, 
 
 extern "C" int rov_gemm_tile_cols(int M, int N) {
     if (M <= 0 || N <= 0) return ROV_ERR_INVALID;
-    return rov::pick_tile_cols(M, N);
+    const int forced = rov::g_tile_cols.load();
+    return forced != 0 ? forced : rov::best_tile_cols(M, N);
+}
+
+extern "C" int rov_gemm_tile(int M, int N, int K, int dtype, int transB, int tile[4]) {
+    if (tile == nullptr) return ROV_ERR_INVALID;
+    const void* const any = (const void*)(uintptr_t)16;   // an aligned operand, never dereferenced
+    const int rc = rov::check_gemm(any, any, any, nullptr, rov::EPI_ADD, M, N, K, dtype, transB);
+    if (rc != ROV_OK) return rc;
+    const rov::GemmChoice c = rov::choose_gemm(M, N, K, dtype, transB, true);
+    if (c.kernel == ROV_GEMM_SMALL_TILES) {
+        rov::ring_variant_tile(c.variant, tile);
+    } else {
+        tile[0] = c.kernel == ROV_GEMM_256_ROWS ? 256 : 64;
+        tile[1] = c.kernel == ROV_GEMM_256_ROWS ? c.cols : 64;
+        tile[2] = 1;
+        tile[3] = c.kernel == ROV_GEMM_256_ROWS ? 16 : dtype == ROV_F32 ? 4 : dtype == ROV_BF16 ? 2 : 1;
+    }
+    return c.kernel;
+}
+
+extern "C" int rov_gemm_swiglu_tile_cols(int M, int N, int K, int dtype) {
+    const void* const any = (const void*)(uintptr_t)16;
+    if (dtype != ROV_BF16 && dtype != ROV_FP8_E4M3) return ROV_ERR_INVALID;
+    const int rc = dtype == ROV_BF16 ? rov::check_gemm_swiglu(any, any, any, any, M, N, K)
+                                     : rov::check_gemm_swiglu_fp8(any, any, any, any, M, N, K, 1.0f);
+    return rc != ROV_OK ? rc : 16 * rov::dual_blocks(M, N, K, dtype);
 }
 
 extern "C" int rov_set_gemm_tile_cols(int cols) {

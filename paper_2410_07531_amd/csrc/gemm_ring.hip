@@ -546,6 +546,11 @@ int ring_variant(int M, int N, int K, int dtype, int transB, bool same_order, do
     return best;
 }
 
+void ring_variant_tile(int variant, int tile[4]) {
+    const RingVariant& r = kRing[variant];
+    tile[0] = r.bm; tile[1] = r.bn; tile[2] = r.kparts; tile[3] = r.vec;
+}
+
 int launch_gemm_ring(int variant, const void* A, const void* W, void* C, const void* R, int M, int N, int K, float alpha,
                      hipStream_t stream) {
     if (variant < 0 || variant >= kRingVariants) return ROV_ERR_INVALID;

@@ -180,13 +180,23 @@ bool rng_fits_beside(double gemm_flop, int dtype, double rng_calls) {
 // or nothing if that is too little to pay for its launch.  Two blocks, queue / fixed split, us: 16 heads x 3000 tokens
 // 621 / 546, 16 x 1200 271 / 233, 32 x 2000 1830 / 1806, 32 x 4096 3237 / 3219; 16 x 8192 causal 1282 / 1349, 32 x 16384
 // 23877 / 24041.
-int plan_split(double gemm_flop, int dtype, double rng_calls, int B, int H, int S, hipStream_t ms, MaskSplit* split) {
+// split_chunks: the chunks of the small grid's share, all of them where the whole mask fits beside the GEMMs, -1 for a queue.
+int64_t split_chunks(double gemm_flop, int dtype, double rng_calls, int B, int H, int S) {
     const uint64_t chunks = (rov_mask_words(B, H, S) + 63u) / 64u;
-    if (rng_fits_beside(gemm_flop, dtype, rng_calls)) return ROV_OK;
-    if (chunks >= (uint64_t)device_cu_count() * (8 + 3) * 4 * 8 * 2) return mask_queue_acquire(ms, &split->qslot);
+    if (rng_fits_beside(gemm_flop, dtype, rng_calls)) return (int64_t)chunks;
+    if (chunks >= (uint64_t)device_cu_count() * (8 + 3) * 4 * 8 * 2) return -1;
     const double share = beside_gemm_seconds(gemm_flop, dtype) * 0.295e12 / rng_calls;
-    split->rest = share < 0.03 ? 0 : share >= 1.0 ? chunks : (uint64_t)(share * (double)chunks);
+    return share < 0.03 ? 0 : share >= 1.0 ? (int64_t)chunks : (int64_t)(share * (double)chunks);
+}
+int plan_split(double gemm_flop, int dtype, double rng_calls, int B, int H, int S, hipStream_t ms, MaskSplit* split) {
+    const int64_t n = split_chunks(gemm_flop, dtype, rng_calls, B, H, S);
+    if (n < 0) return mask_queue_acquire(ms, &split->qslot);
+    split->rest = (uint64_t)n;
     return ROV_OK;
+}
+// The measure of a mask's cost that the estimates take: its Philox calls, fewer when causal; cost per call ~ rounds.
+double mask_cost(int B, int H, int S, int causal, int rounds) {
+    return (double)rov_mask_philox_calls(B, H, S) * (causal ? 0.5 : 1.0) * (0.25 + 0.075 * rounds);
 }
 
 double gemm_flop(int M, int N, int K) { return 2.0 * (double)M * (double)N * (double)K; }
@@ -298,10 +308,10 @@ int layer_step_impl(int schedule, const rov_gemm_desc* gemms, int n_gemms, const
             flop += gemm_flop(gemms[i].M, gemms[i].N, gemms[i].K);
             if (gemms[i].dtype == ROV_F32 || (gemms[i].dtype == ROV_BF16 && slowest != ROV_F32)) slowest = gemms[i].dtype;
         }
-        const double calls = (double)rov_mask_philox_calls(attn->B, attn->H, attn->S) * (attn->causal ? 0.5 : 1.0);
-        // (cost per call ~ rounds; the narrower kernels take no range and simply run on)
+        // (the narrower kernels take no range and simply run on)
         if (bits == 32) {
-            rc = plan_split(flop, slowest, calls * (0.25 + 0.075 * rounds), attn->B, attn->H, attn->S, ms, &split);
+            rc = plan_split(flop, slowest, mask_cost(attn->B, attn->H, attn->S, attn->causal, rounds), attn->B, attn->H,
+                            attn->S, ms, &split);
             if (rc != ROV_OK) return rc;
         }
         // the mask buffer may still be read by work already queued on the main stream
@@ -530,6 +540,12 @@ extern "C" int rov_layer_step_chunked(const rov_gemm_desc* gemms, int n_gemms, c
     return ROV_OK;
 }
 
+extern "C" int64_t rov_overlap_mask_chunks(double gemm_flop, int dtype, int B, int H, int S, int causal, int rounds) {
+    if (!(gemm_flop >= 0.0) || (dtype != ROV_F32 && dtype != ROV_BF16 && dtype != ROV_FP8_E4M3)) return -2;
+    if (B <= 0 || H <= 0 || S <= 0 || (rounds != 10 && rounds != 7 && rounds != 5 && rounds != 3)) return -2;
+    return rov::split_chunks(gemm_flop, dtype, rov::mask_cost(B, H, S, causal, rounds), B, H, S);
+}
+
 extern "C" size_t rov_block_workspace_bytes(const rov_block_cfg* cfg, int B, int S, int schedule) {
     (void)schedule;
     rov::BlockLayout L;
@@ -668,7 +684,7 @@ int block_forward_impl(const rov_block_weights* w, const void* x, void* y, int B
     // this block's own mask, if nobody produced it yet
     int qslot = -1;                    // hybrid: work queue of a range of rows
     MaskSplit own;                     // of the block's own mask
-    const double mask_calls = (double)rov_mask_philox_calls(B, H, S) * (cfg->causal ? 0.5 : 1.0);
+    const double mask_calls = mask_cost(B, H, S, cfg->causal, 10);
     const double qkv_flop = gemm_flop((int)T, qkv_n, hidden);
     if (use_mask && !mask_ready && overlap) {
         if (R == S)

@@ -59,6 +59,39 @@ def test_gemm_tile_width_rule():
     assert binding.gemm_tile_cols(8192, 8192) == 256
 
 
+def test_kernel_choice_queries():
+    # host logic: what the launches choose, so that a test can assert the kernel that it means to reach
+    B = binding
+    assert B.gemm_tile(16384, 14336, 4096, B.BF16) == (B.GEMM_256_ROWS, 256, 256, 1, 16)
+    assert B.gemm_tile(333, 4096, 2048, B.BF16) == (B.GEMM_SMALL_TILES, 128, 64, 2, 16)
+    assert B.gemm_tile(65, 130, 102, B.BF16) == (B.GEMM_SMALL_TILES, 64, 64, 2, 4)
+    assert B.gemm_tile(77, 130, 101, B.BF16) == (B.GEMM_ANY_SHAPE, 64, 64, 1, 2)      # rows off 4 bytes
+    assert B.gemm_tile(256, 256, 256, B.FP8_E4M3, transB=False)[0] == B.GEMM_ANY_SHAPE
+    for cols in (128, 160, 192, 224, 256):
+        prev = B.set_gemm_tile_cols(cols)
+        try:
+            assert B.gemm_tile(333, 4096, 2048, B.BF16) == (B.GEMM_256_ROWS, 256, cols, 1, 16)
+            assert B.gemm_swiglu_tile_cols(333, 4096, 2048, B.FP8_E4M3) == cols // 2
+        finally:
+            B.set_gemm_tile_cols(prev)
+    assert B.gemm_swiglu_tile_cols(2000, 14336, 4096, B.BF16) == 112
+    for bad in ((0, 4, 4, B.BF16), (4, 4, 4, 7)):
+        try:
+            B.gemm_tile(*bad)
+            assert False
+        except B.RovError as e:
+            assert e.code == B.ERR_INVALID
+    assert B.attention_key_parts(1, 32, 16384, 128, B.BF16, False) == 1
+    assert B.attention_key_parts(1, 2, 128, 64, B.BF16, True) == 4
+    assert [B.attention_key_parts(1, 2, 128, d, B.F32, False) for d in (40, 64, 128, 100, 136)] == [8, 8, 4, 0, 0]
+    assert B.attention_key_parts(1, 2, 128, 96, B.BF16, False) == 0
+    chunks = lambda H, S: (B.mask_words(1, H, S) + 63) // 64
+    assert B.overlap_mask_chunks(0.0, B.BF16, 1, 8, 512) == 0
+    assert B.overlap_mask_chunks(1e15, B.BF16, 1, 32, 16384) == chunks(32, 16384)
+    assert B.overlap_mask_chunks(1e9, B.BF16, 1, 32, 16384) == -1
+    assert 0 < B.overlap_mask_chunks(4e9, B.BF16, 1, 8, 1024) < chunks(8, 1024)
+
+
 def test_no_oracle_on_the_product_path():
     # the package must never import the oracle (and the oracle never the package)
     pkg = os.path.join(ROOT, "paper_2410_07531_amd")
