@@ -490,12 +490,15 @@ def main():
                 "unit": "TFLOP/s", "frac": flops / ms / 1e9 / PEAK_BF16_TFLOPS, "traffic": TRAFFIC[key]}
 
     def tn_label(M, N, K):
-        # the launch picks the tile width per shape; ask the library which instantiation it runs
-        return "gemm_tn_kernel<%d, false> %dx%dx%d (RNG co-running)" % (rov.gemm_tile_cols(M, N) // 32, M, N, K)
+        # the launch picks the kernel and its tile per shape; ask the library what it runs
+        kernel, rows, cols = rov.gemm_tile(M, N, K, rov.BF16)[:3]
+        name = "gemm_tn_kernel<%d, false>" % (cols // 32) if kernel == rov.GEMM_256_ROWS else "gemm_ring_kernel (tile %dx%d)" % (rows, cols)
+        return "%s %dx%dx%d (RNG co-running)" % (name, M, N, K)
 
     T_tok = B * S
     roofline_by_kernel = {
-        "gemm_swiglu": mfma_roofline("gemm_swiglu_kernel<8> (gate and up projections, SwiGLU in the accumulators; RNG co-running)",
+        "gemm_swiglu": mfma_roofline("gemm_swiglu_kernel<%d> (gate and up projections, SwiGLU in the accumulators; RNG co-running)"
+                                     % (rov.gemm_swiglu_tile_cols(T_tok, ffn_, hidden_, rov.BF16) // 16),
                                      blk.gemm_flops["swiglu"], g_ovl[2], "gemm_swiglu"),
         "gemm_down": mfma_roofline(tn_label(T_tok, hidden_, ffn_), blk.gemm_flops["down"], g_ovl[3], "gemm_down"),
         "gemm_qkv": mfma_roofline(tn_label(T_tok, (H + 2 * Hkv) * d, hidden_), blk.gemm_flops["qkv"], g_ovl[0], "gemm_qkv"),

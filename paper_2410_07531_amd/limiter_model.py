@@ -126,6 +126,29 @@ def gemm_tile_cols(chip: Chip, M: int, N: int) -> int:
     return cols
 
 
+def dual_tile_blocks(chip: Chip, M: int, N: int, K: int, esz: int = 2) -> int:
+    """Weight blocks per wave (tiles of 256 x 16*blocks output columns) the library's launch picks for the
+    SwiGLU form: the smallest of its time estimates (rounds of measured slot times, shorter where a round leaves
+    compute units idle, 1.5 us a round), the widest on ties; 5 % has to be promised where the widest needs one round."""
+    tiles_m, slots = -(-M // 256), K * esz // 128
+    slot_ns, block_ns = (1040.0, 110.0) if esz == 2 else (1150.0, 172.0)
+
+    def estimate(nj: int) -> float:
+        tiles = tiles_m * -(-N // (16 * nj))
+        rounds = -(-tiles // chip.cus)
+        use = tiles / float(rounds * chip.cus)
+        return rounds * (slots * (slot_ns + block_ns * (nj - 4)) * (0.73 + 0.27 * use) + 1500.0)
+
+    bar = 0.95 if tiles_m * -(-N // 128) <= chip.cus else 1.0
+    widest = best = estimate(8)
+    blocks = 8
+    for nj in range(7, 3, -1):
+        t = estimate(nj)
+        if t < best and t < bar * widest:
+            best, blocks = t, nj
+    return blocks
+
+
 def t_gemm(chip: Chip, M: int, N: int, K: int, esz: int = 2, dual: bool = False) -> Dict[str, float]:
     """GEMM (paper Table 1, GEMM column: MMA math first, L2 read bandwidth second), from the tile
     kernel's counts.  A workgroup (one wave per SIMD) walks K in slot-steps of 128 bytes per row;
@@ -134,12 +157,13 @@ def t_gemm(chip: Chip, M: int, N: int, K: int, esz: int = 2, dual: bool = False)
     workgroup moves (256 + 32 nj) rows x 128 bytes from L2 to LDS.  Workgroups run in rounds of one
     per compute unit; a round ends with its output leaving the chip in one burst.
     dual: the SwiGLU form (gate and up projections in one tile of half the output width; N counts
-    the output columns)."""
+    the output columns).
+    It prices the 256-row kernels.  Products that leave much of the chip idle under them (the layers of this
+    repository's workloads below 2048 tokens) run smaller tiles and take less than this: the library's
+    rov_gemm_tile tells which."""
     if dual:
-        tiles_m, cu = -(-M // 256), chip.cus
-        t8, t4 = tiles_m * -(-N // 128), tiles_m * -(-N // 64)
-        nj = 8 if -(-t8 // cu) * 3 <= -(-t4 // cu) * 2 else 4      # the launch's rule for the dual tile
-        tiles, out_cols = (t8 if nj == 8 else t4), 16 * nj
+        nj = dual_tile_blocks(chip, M, N, K, esz)
+        tiles, out_cols = -(-M // 256) * -(-N // (16 * nj)), 16 * nj
     else:
         cols = gemm_tile_cols(chip, M, N)
         nj = cols // 32

@@ -49,6 +49,15 @@ def test_gemm_tile_width_rule():
     for M in (1, 256, 300, 2048, 4096, 8192, 16384):
         for N in range(4, 20000, 364):
             assert binding.gemm_tile_cols(M, N) == LM.gemm_tile_cols(LM.MI355X, M, N), (M, N)
+    for esz, dt in ((2, binding.BF16), (1, binding.FP8_E4M3)):
+        for M in (1, 70, 300, 949, 2000, 2048, 2900, 4096, 16384):
+            for N in (4, 300, 2816, 2820, 8192, 14336, 28672):
+                for K in (128, 1024, 4096):
+                    assert binding.gemm_swiglu_tile_cols(M, N, K, dt) == 16 * LM.dual_tile_blocks(LM.MI355X, M, N, K, esz), (M, N, K, dt)
+    # what the model prices as a 256-row kernel is one, in the workloads that it is applied to
+    for S in (2048, 4096, 8192, 16384, 32768):
+        for N, K in ((6144, 4096), (4096, 4096), (4096, 14336)):
+            assert binding.gemm_tile(S, N, K, binding.BF16)[:3] == (binding.GEMM_256_ROWS, 256, LM.gemm_tile_cols(LM.MI355X, S, N))
     L = binding.load()
     assert L.rov_gemm_tile_cols(0, 8) == binding.ERR_INVALID and L.rov_gemm_tile_cols(8, -1) == binding.ERR_INVALID
     prev = binding.set_gemm_tile_cols(160)
