@@ -1040,27 +1040,30 @@ int launch_bf16(const AttnParams& prm, int mode, hipStream_t stream) {
 // Key parts of the matrix-core kernel (1, 2 or 4: workgroups of 256, 128 or 64 query rows).  A finer split
 // fills the chip where query tiles are few and evens out causal workgroups; it re-reads K / V and merges partial results:
 // with the chip full a workgroup of 128 (64) rows takes 0.556 (0.36) of the time of one of 256 rows at d = 128, 0.54 (0.295) at
-// d = 64 (4096 and 8192 tokens, 32 heads); causal, where the diagonal's share of a workgroup shrinks with its rows,
-// 0.62 (0.42) and 0.50 (0.30).  Estimated time: rounds of one workgroup per compute unit, for causal masks the longest
-// workgroup or the average load with a tenth for its uneven end, 1.3 us of start and merge a round.
-// Measured with 256 / 128 / 64 rows, mask mode, d = 128, us: 512 tokens x 32 heads 20.5 / 14.7 / 11.4; 1500 x 32
-// 46.8 / 57.0 / 57.5, causal 44.4 / 30.2 / 39.5; 2048 x 16 causal 56.5 / 35.8 / 30.4; 4096 x 32 causal 144 / 160 / 195.
+// d = 64 (4096 and 8192 tokens, 32 heads).  Estimated time: rounds of one workgroup per compute unit and 1.3 us of start and
+// merge each.  Causal: the longest workgroup, or the average load and `uneven` of a workgroup more, since the last ones do
+// not end together (two share a compute unit at d = 64), if that is longer; these constants are fitted to all three forms
+// at 4 to 128 heads of 128 to 8192 tokens, so that the choice is nowhere there more than 1 % slower than 256 rows, without dropout
+// and with a stored mask (and mostly within 2 % of the best of the three).
+// Measured with 256 / 128 / 64 rows, mask mode, us: d = 128, 512 tokens x 32 heads 20.5 / 14.7 / 11.4; 1500 x 32
+// 46.8 / 57.0 / 57.5; causal 2048 x 16 55.6 / 36.5 / 31.4, 512 x 64 20.6 / 15.5 / 18.2, 6000 x 16 169 / 173 / 195; d = 64, causal
+// 2048 x 32 43.5 / 31.5 / 31.1, 2048 x 64 56.4 / 49.7 / 58.6, 8192 x 64 636 / 681 / 774.  (Bits drawn in the kernel: the last one
+// 1357 / 1168 / 1248: the unsplit form's 160 registers leave room for one workgroup per compute unit only.  It follows the
+// others' choice.)
 // Only what all launches over one problem share decides, so that row ranges and modes agree bit for bit.
 int attn_key_parts(int B, int H, int S, int d, bool causal) {
-    const double ncu = device_cu_count(), walk_us = (double)S / 2048.0 * (d == 128 ? 60.0 : 35.0);
-    const double rel_full[2][2] = {{0.54, 0.295}, {0.556, 0.36}}, rel_causal[2][2] = {{0.50, 0.30}, {0.62, 0.42}};
+    struct Cost { double walk_us, rel[3], uneven, round_us; };
+    static const Cost full[2] = {{35.0, {1.0, 0.54, 0.295}, 0.0, 1.3}, {60.0, {1.0, 0.556, 0.36}, 0.0, 1.3}};
+    static const Cost lower[2] = {{35.0, {1.0, 0.61, 0.36}, 0.6, 0.8}, {60.0, {1.0, 0.65, 0.40}, 0.3, 4.0}};
+    const Cost& c = (causal ? lower : full)[d == 128];
+    const double ncu = device_cu_count(), walk_us = (double)S / 2048.0 * c.walk_us;
     int best = 1;
     double best_us = 0.0;
     for (int i = 0; i < 3; ++i) {
         const int rows = 256 >> i, nq = (S + rows - 1) / rows;
         const double n = (double)nq * B * H, rounds = ceil(n / ncu);
-        double load = rounds;
-        if (causal) {
-            load = n / ncu * 0.5 * (1.0 + 1.0 / nq);
-            load = load > 1.0 ? load + 0.1 : 1.0;
-        }
-        const double rel = i == 0 ? 1.0 : (causal ? rel_causal : rel_full)[d == 128][i - 1];
-        const double us = walk_us * rel * load + 1.3 * rounds;
+        const double load = causal ? fmax(1.0, n / ncu * 0.5 * (1.0 + 1.0 / nq) + c.uneven) : rounds;
+        const double us = walk_us * c.rel[i] * load + c.round_us * rounds;
         if (i == 0 || us < best_us) { best = 1 << i; best_us = us; }
     }
     return best;

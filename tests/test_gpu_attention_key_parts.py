@@ -1,8 +1,8 @@
 """GPU parity of the matrix-core attention kernel where its workgroups split the keys between waves.
 
 Short sequences, few heads and causal masks take workgroups of 128 or 64 query rows whose waves share the
-keys and merge their partial results; larger problems take 256 rows and no split.  The sizes reach every split at
-both head dimensions, key parts that lie beyond the sequence, row tiles past its end and causal parts without a
+keys and merge their partial results; larger problems take 256 rows and no split.  The rows reach every split at
+both head dimensions, causal and not, and assert which one they reach; among them are key parts that lie beyond the sequence, row tiles past its end and causal parts without a
 single admissible key.  Reference: the float64 oracle on sampled rows; bar 2e-2 of the result's scale as for
 every bf16 attention test (probabilities rounded to bf16, 2^-9, one rounding of the result).
 """
@@ -22,19 +22,24 @@ def _f64(t):
     return t.float().cpu().numpy().astype(np.float64)
 
 
-@pytest.mark.parametrize("B,S,H,Hkv,d,causal", [
-    (1, 33, 2, 1, 128, True),        # 64 rows a workgroup; the second row tile has one row, two key parts none
-    (1, 33, 2, 1, 64, False),
-    (2, 130, 3, 3, 128, False),      # a second LDS tile with two keys
-    (1, 257, 4, 2, 64, True),        # ragged, third LDS tile with one key
-    (1, 700, 24, 8, 128, False),     # 128 rows
-    (1, 1100, 24, 8, 128, True),     # 128 rows, causal
-    (2, 1025, 16, 4, 64, True),      # 64 rows, causal, one row past a tile
-    (1, 1500, 24, 8, 64, False),     # 256 rows
-    (2, 2048, 24, 8, 128, True),     # 256 rows, causal: waves that leave the walk early
+@pytest.mark.parametrize("B,S,H,Hkv,d,causal,parts", [
+    (1, 33, 2, 1, 128, True, 4),     # 64 rows a workgroup; the second row tile has one row, two key parts none
+    (1, 33, 2, 1, 64, False, 4),
+    (2, 130, 3, 3, 128, False, 4),   # a second LDS tile with two keys
+    (1, 257, 4, 2, 64, True, 4),     # ragged, third LDS tile with one key
+    (1, 700, 24, 8, 128, False, 2),  # 128 rows
+    (1, 1001, 32, 8, 64, False, 2),
+    (2, 1025, 16, 4, 128, True, 2),  # causal, one row past a tile
+    (2, 1000, 32, 8, 64, True, 2),
+    (2, 1025, 16, 4, 64, True, 4),
+    (1, 1500, 24, 8, 128, False, 1),  # 256 rows
+    (1, 2001, 32, 8, 64, False, 1),
+    (2, 2048, 24, 8, 128, True, 1),  # causal: waves that leave the walk early
+    (4, 1279, 32, 8, 64, True, 1),
 ])
-def test_split_keys_match_oracle_and_agree(B, S, H, Hkv, d, causal):
-    print("attention key parts", B, S, H, Hkv, d, causal, flush=True)
+def test_split_keys_match_oracle_and_agree(B, S, H, Hkv, d, causal, parts):
+    print("attention key parts", B, S, H, Hkv, d, causal, parts, flush=True)
+    assert rov.attention_key_parts(B, H, S, d, rov.BF16, causal) == parts
     p, seed, offset = 0.1, wl.SEED, 96
     rng = np.random.default_rng(S + d)
     Q, K, V = (torch.from_numpy(x).bfloat16().cuda() for x in wl.qkv(rng, B, S, H, Hkv, d))
