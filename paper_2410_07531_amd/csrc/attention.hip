@@ -1062,6 +1062,7 @@ int attn_key_parts(int B, int H, int S, int d, bool causal) {
     for (int i = 0; i < 3; ++i) {
         const int rows = 256 >> i, nq = (S + rows - 1) / rows;
         const double n = (double)nq * B * H, rounds = ceil(n / ncu);
+        if (i > 0 && n > 0x7FFFFFFF) break;   // more workgroups than a grid holds (with 256 rows: refused)
         const double load = causal ? fmax(1.0, n / ncu * 0.5 * (1.0 + 1.0 / nq) + c.uneven) : rounds;
         const double us = walk_us * c.rel[i] * load + c.round_us * rounds;
         if (i == 0 || us < best_us) { best = 1 << i; best_us = us; }
@@ -1070,8 +1071,11 @@ int attn_key_parts(int B, int H, int S, int d, bool causal) {
 }
 
 // Waves of a workgroup of the fp32 kernel: eight at up to 64 features, four above (their registers); 0: a head dimension
-// that it does not take.
-int attn_f32_waves(int d) { return d % 8 != 0 || d > 128 ? 0 : d <= 64 ? 8 : 4; }
+// that it does not take, or more workgroups than a grid holds (the whole problem's, so that row ranges agree with it).
+int attn_f32_waves(int B, int H, int S, int d) {
+    if (d % 8 != 0 || d > 128 || ((long long)S + 31) / 32 * H * B > 0x7FFFFFFFLL) return 0;
+    return d <= 64 ? 8 : 4;
+}
 
 template <int DP, int NW>
 int launch_f32(const AttnParams& prm, int mode, hipStream_t stream) {
@@ -1207,7 +1211,7 @@ int launch_attention_rows(const void* Q, const void* K, const void* V, void* O, 
             return launch_bf16<64, 1, 8, 1>(prm, mode, stream);
         }
     }
-    if (dtype == ROV_F32 && attn_f32_waves(d) != 0) {
+    if (dtype == ROV_F32 && attn_f32_waves(B, H, S, d) != 0) {
         // 16-byte accesses to rows of Q, K and O
         bool ok = aligned(Q, 16) && aligned(K, 16) && aligned(O, 16);
         for (int i = 0; i < 12; ++i) ok = ok && (i / 3 == 2 || strides[i] % 4 == 0);
@@ -1229,7 +1233,7 @@ int launch_attention_rows(const void* Q, const void* K, const void* V, void* O, 
 extern "C" int rov_attention_key_parts(int B, int H, int S, int d, int dtype, int causal) {
     if (B <= 0 || H <= 0 || S <= 0 || d <= 0 || d > 256) return ROV_ERR_INVALID;
     if (dtype != ROV_F32 && dtype != ROV_BF16) return ROV_ERR_INVALID;
-    if (dtype == ROV_F32) return rov::attn_f32_waves(d);
+    if (dtype == ROV_F32) return rov::attn_f32_waves(B, H, S, d);
     return d == 64 || d == 128 ? rov::attn_key_parts(B, H, S, d, causal != 0) : 0;
 }
 

@@ -114,6 +114,17 @@ def test_key_parts_leave_full_chips_alone():
     assert parts(1, 32, 2048, 128) == 2 and parts(1, 32, 4096, 64) == 2
 
 
+def test_key_parts_never_ask_for_more_workgroups_than_a_grid_holds():
+    # 2^30 (batch, head) pairs (views with zero strides) fit the grid with 256 rows a workgroup or one row a wave, which
+    # is what such calls are accepted for, but not with the 32, 64 or 128 rows of the finer forms
+    B = H = 32768
+    assert binding.attention_key_parts(B, H, 64, 64, binding.F32, False) == 0
+    assert binding.attention_key_parts(B, H, 32, 64, binding.F32, False) == 8
+    for d in (64, 128):
+        for causal in (False, True):
+            assert binding.attention_key_parts(B, H, 256, d, binding.BF16, causal) == 1
+
+
 def test_no_oracle_on_the_product_path():
     # the package must never import the oracle (and the oracle never the package)
     pkg = os.path.join(ROOT, "paper_2410_07531_amd")
