@@ -101,6 +101,21 @@ def test_kernel_choice_queries():
     assert 0 < B.overlap_mask_chunks(4e9, B.BF16, 1, 8, 1024) < chunks(8, 1024)
 
 
+def test_small_tile_cases_reach_every_form():
+    # every row of the small-tile GEMM's parity test names the tile that it reaches (the test asserts it); together they are
+    # all the forms that the launch chooses from
+    import test_gpu_gemm_ring as T
+    seen = set()
+    for dtype, M, N, K, transB, tile in T.CASES:
+        assert binding.gemm_tile(M, N, K, T.DTYPES[dtype], transB) == (binding.GEMM_SMALL_TILES,) + tile, (dtype, M, N, K)
+        seen.add((dtype, transB) + tile)
+    src = open(os.path.join(ROOT, "paper_2410_07531_amd", "csrc", "gemm_ring.hip")).read()
+    table = re.findall(r"^\s*\{ROV_(BF16|FP8_E4M3|F32), (\d), (\d+), (\d), (\d+), (\d+), ", src, flags=re.M)
+    forms = {({"BF16": "bf16", "FP8_E4M3": "fp8", "F32": "f32"}[t], kn == "0", int(bm), int(bn), int(ks), int(vec))
+             for t, kn, vec, ks, bm, bn in table}
+    assert len(forms) == len(table) == 25 and seen == forms, seen ^ forms
+
+
 def test_key_parts_leave_full_chips_alone():
     # causal problems that fill the chip take workgroups of 256 rows: with two key parts these shapes were measured 2 to 20 %
     # slower (stored mask and no dropout); and short ones keep their split

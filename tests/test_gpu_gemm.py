@@ -37,8 +37,8 @@ def _rel_err(got, ref):
     (2304, 256, 192, True),      # 9 tile rows over 3 slots: every cyclic start of the k walk, wrapping
     (300, 520, 192, True),       # ragged M and N (N % 4 == 0): MFMA kernel with clamped edges
     (1, 4, 64, True),            # degenerate sizes on the MFMA path
-    (77, 130, 100, True),        # N % 4 != 0, K % 64 != 0: generic kernel
-    (130, 96, 72, False),        # [K, N] weights: generic kernel
+    (77, 130, 100, True),        # N % 4 != 0, K % 64 != 0: small tiles, rows on 4 bytes
+    (130, 96, 72, False),        # [K, N] weights: small tiles
 ])
 def test_gemm_bf16_matches_oracle(M, N, K, transB):
     print("gemm bf16", M, N, K, transB, flush=True)
@@ -51,6 +51,39 @@ def test_gemm_bf16_matches_oracle(M, N, K, transB):
     ref = OD.gemm(_f64(A), _f64(W), transB=transB)
     err = _rel_err(_f64(C), ref)
     assert err <= BF16_TOL and err <= BF16_EXPECTED, err
+
+
+@pytest.mark.parametrize("dtype,M,N,K,transB", [
+    ("bf16", 7, 13, 17, True), ("bf16", 130, 70, 333, True), ("bf16", 65, 131, 35, False), ("bf16", 130, 99, 64, False),
+    ("fp8", 70, 36, 133, True), ("fp8", 70, 36, 64, False), ("fp8", 65, 67, 130, False),
+    # fp32 with operand rows (or a [K, N] matrix with the last slot's overhang) beyond 32-bit byte offsets
+    ("f32", 2, 3, 5700000, True), ("f32", 3, 8400000, 2, False),
+])
+def test_gemm_any_shape_kernel_matches_oracle(dtype, M, N, K, transB):
+    # what no matrix-core kernel takes: rows of an odd number of 16-bit values, fp8 rows off 16 bytes and fp8 [K, N].
+    # Operands in sixteenths up to 1: products are multiples of 2^-8, and these sums of them stay below 2^16, exact in fp32
+    # in any order (of the longest sum one term in 64 is not zero)
+    print("gemm any shape", dtype, M, N, K, transB, flush=True)
+    dt = {"bf16": rov.BF16, "fp8": rov.FP8_E4M3, "f32": rov.F32}[dtype]
+    assert rov.gemm_tile(M, N, K, dt, transB)[0] == rov.GEMM_ANY_SHAPE
+    g = torch.Generator().manual_seed(M + N + K)
+    a = torch.randint(-16, 17, (M, K), generator=g).float() / 16
+    w = torch.randint(-16, 17, (N, K) if transB else (K, N), generator=g).float() / 16
+    if K > 1 << 20:
+        a[:, (torch.arange(K) % 64) != 5] = 0.0
+    if dtype == "fp8":
+        A, W = (x.to(torch.float8_e4m3fn).view(torch.uint8).cuda() for x in (a, w))
+        a, w = (x.to(torch.float8_e4m3fn).float() for x in (a, w))
+    else:
+        A, W = (x.to(torch.bfloat16 if dtype == "bf16" else torch.float32).cuda() for x in (a, w))
+    odt = torch.float32 if dtype == "f32" else torch.bfloat16
+    frame = torch.full((M * N + 128,), 3.0, dtype=odt, device="cuda")
+    C = frame[64:64 + M * N].view(M, N)
+    rov.gemm(A, W, C=C, transB=transB, scaleA=0.5, scaleB=4.0)
+    torch.cuda.synchronize()
+    ref = 2.0 * (a.double() @ (w.double().T if transB else w.double()))
+    assert torch.equal(C.cpu(), ref.to(odt))
+    assert bool((frame[:64] == 3.0).all()) and bool((frame[64 + M * N:] == 3.0).all())
 
 
 @pytest.mark.parametrize("cols", [128, 160, 192, 224, 256])
@@ -84,7 +117,7 @@ def test_gemm_bf16_every_tile_width(cols):
     (2304, 192, 128),       # nine tile rows (every k start), narrow output
     (512, 4096, 256),       # 64 tiles of 128 columns
 ])
-@pytest.mark.parametrize("form", [0, 128, 256])       # the launch's choice, the narrow tile, the wide tile
+@pytest.mark.parametrize("form", [0, 128, 160, 192, 224, 256])       # the launch's choice, every tile from the narrowest
 def test_gemm_swiglu_matches_oracle(M, N, K, form):
     # silu(A Wg^T) * (A Wu^T) from the dual product: the oracle's two products and its silu
     print("gemm swiglu", M, N, K, form, flush=True)
@@ -95,6 +128,7 @@ def test_gemm_swiglu_matches_oracle(M, N, K, form):
     A, Wg, Wu = _to_dev(a, torch.bfloat16), _to_dev(wg, torch.bfloat16), _to_dev(wu, torch.bfloat16)
     prev = rov.set_gemm_tile_cols(form)
     try:
+        assert form == 0 or rov.gemm_swiglu_tile_cols(M, N, K, rov.BF16) == form // 2
         C = rov.gemm_swiglu(A, Wg, Wu)
         torch.cuda.synchronize()
     finally:
@@ -304,7 +338,7 @@ def test_gemm_fp8_llama70b_qkv_sampled():
     (300, 72, 384),         # fewer columns than one wave's half of a 64-column tile
     (512, 4096, 256),       # 64 tiles of 128 columns
 ])
-@pytest.mark.parametrize("form", [128, 256])          # the narrow and the wide tile
+@pytest.mark.parametrize("form", [128, 160, 192, 224, 256])          # every tile
 def test_gemm_swiglu_fp8_codes_match_oracle(M, N, K, form):
     # e4m3( silu(sA sWg A Wg^T) * (sA sWu A Wu^T) / sC ): the codes the kernel writes against the
     # oracle's nearest-code choice on the float64 value.  The kernel takes the decision on its own
@@ -325,6 +359,7 @@ def test_gemm_swiglu_fp8_codes_match_oracle(M, N, K, form):
     sc = float(np.float32(np.max(np.abs(v)) / 600.0))          # the largest values saturate at 448
     prev = rov.set_gemm_tile_cols(form)
     try:
+        assert rov.gemm_swiglu_tile_cols(M, N, K, rov.FP8_E4M3) == form // 2
         C = rov.gemm_swiglu_fp8(Aq.cuda(), Gq.cuda(), Uq.cuda(), sa, sg, su, sc)
         torch.cuda.synchronize()
     finally:

@@ -1,6 +1,6 @@
 """GPU parity of the small-tile GEMM kernels (gemm_ring.hip) at the sizes where they can go wrong.
 
-Every row reaches another tile or operand form: tiles of 32 to 192 rows, k split between the waves of a
+The rows reach every tile and operand form, and assert which one: tiles of 32 to 192 rows, k split between the waves of a
 workgroup or not, [K, N] weights, rows that start on 16 or only on 4 bytes, a last slot of k that is
 partly filled, rows and columns past the edge, output rows that take no vector store.  Reference:
 the float64 oracle on sampled rows (first, last, tile edges), all columns.
@@ -20,38 +20,39 @@ from paper_2410_07531_amd import workloads as wl
 pytestmark = pytest.mark.gpu
 
 CASES = [
-    # dtype, M, N, K, transB
-    ("bf16", 100, 4096, 2048, True),     # 64 x 32, four k parts
-    ("bf16", 250, 4096, 2112, True),     # 64 x 64, two k parts, two 128-byte parts per slot, odd number of parts
-    ("bf16", 333, 4096, 2048, True),     # 128 x 64
-    ("bf16", 500, 6144, 2176, True),     # 128 x 128
-    ("bf16", 1100, 4100, 2048, True),    # 192 x 128, ragged columns
-    ("bf16", 1000, 6144, 2048, True),    # 128 x 192
-    ("bf16", 70, 1000, 448, True),       # 64 x 64, one k part
-    ("bf16", 700, 4096, 1024, True),     # 128 x 128, one k part
-    ("bf16", 1, 4, 64, True),            # smallest
-    ("bf16", 129, 65, 8, True),          # one chunk of k, odd number of columns
-    ("bf16", 333, 1001, 1000, True),     # last slot partly filled, scalar stores
-    ("bf16", 65, 130, 102, True),        # rows on 4 bytes
-    ("bf16", 64, 64, 64, False),         # [K, N]: one tile of the smallest, one slot
-    ("bf16", 257, 4096, 1032, False),    # [K, N], 128 x 64, last slot of one chunk
-    ("bf16", 1000, 1000, 72, False),     # [K, N], ragged everywhere
-    ("bf16", 900, 6144, 256, False),     # [K, N], larger tiles
-    ("bf16", 3000, 4096, 256, False),    # [K, N], 192 x 128
-    ("bf16", 130, 98, 34, False),        # [K, N], rows on 4 bytes
-    ("fp8", 100, 4096, 512, True),       # 64 x 64
-    ("fp8", 333, 4096, 640, True),       # 128 x 64
-    ("fp8", 500, 8192, 384, True),       # 128 x 128
-    ("fp8", 77, 131, 144, True),         # last slot partly filled, scalar stores
-    ("f32", 256, 256, 256, True),        # 32 x 32, four k parts
-    ("f32", 1, 1, 1, True),
-    ("f32", 1000, 1024, 260, True),      # 64 x 64, last slot of one chunk
-    ("f32", 33, 47, 131, True),          # rows on 4 bytes
-    ("f32", 700, 1025, 513, True),       # rows on 4 bytes, 64 x 64
-    ("f32", 100, 36, 68, False),         # [K, N]
-    ("f32", 1024, 1024, 64, False),      # [K, N], 64 x 64
-    ("f32", 65, 33, 35, False),          # [K, N], rows on 4 bytes
-    ("f32", 1021, 1027, 67, False),
+    # dtype, M, N, K, transB; the tile: rows, columns, parts of k, bytes of a lane's load
+    ("bf16", 100, 4096, 2048, True, (64, 32, 4, 16)),
+    ("bf16", 250, 4096, 2112, True, (64, 64, 2, 16)),   # two 128-byte parts per slot, odd number of parts
+    ("bf16", 333, 4096, 2048, True, (128, 64, 2, 16)),
+    ("bf16", 500, 6144, 2176, True, (128, 128, 2, 16)),
+    ("bf16", 1100, 4100, 2048, True, (192, 128, 2, 16)),   # ragged columns
+    ("bf16", 1000, 6144, 2048, True, (128, 192, 2, 16)),
+    ("bf16", 70, 1000, 448, True, (64, 64, 1, 16)),
+    ("bf16", 700, 4096, 1024, True, (128, 128, 1, 16)),
+    ("bf16", 1, 4, 64, True, (64, 64, 1, 16)),   # smallest
+    ("bf16", 129, 65, 8, True, (64, 32, 4, 16)),   # one chunk of k, odd number of columns
+    ("bf16", 333, 1001, 1000, True, (64, 32, 4, 16)),   # last slot partly filled, scalar stores
+    ("bf16", 65, 130, 102, True, (64, 64, 2, 4)),
+    ("bf16", 64, 64, 64, False, (64, 64, 4, 16)),   # one tile, one slot
+    ("bf16", 257, 4096, 1032, False, (128, 64, 2, 16)),   # last slot of one chunk
+    ("bf16", 1000, 1000, 72, False, (64, 64, 4, 16)),   # ragged everywhere
+    ("bf16", 900, 4096, 264, False, (128, 128, 2, 16)),   # last slot of one chunk
+    ("bf16", 900, 6144, 256, False, (192, 128, 2, 16)),
+    ("bf16", 3000, 4096, 256, False, (192, 128, 2, 16)),
+    ("bf16", 130, 98, 34, False, (64, 64, 2, 4)),
+    ("fp8", 100, 4096, 512, True, (64, 64, 1, 16)),
+    ("fp8", 333, 4096, 640, True, (128, 64, 1, 16)),
+    ("fp8", 500, 8192, 384, True, (128, 128, 1, 16)),
+    ("fp8", 77, 131, 144, True, (64, 64, 1, 16)),   # last slot partly filled, scalar stores
+    ("f32", 256, 256, 256, True, (32, 32, 4, 16)),
+    ("f32", 1, 1, 1, True, (32, 32, 4, 4)),   # smallest
+    ("f32", 1000, 1024, 260, True, (64, 64, 2, 16)),   # last slot of one chunk
+    ("f32", 33, 47, 131, True, (32, 32, 4, 4)),
+    ("f32", 700, 1025, 513, True, (64, 64, 2, 4)),
+    ("f32", 100, 36, 68, False, (32, 32, 4, 16)),
+    ("f32", 1024, 1024, 64, False, (64, 64, 2, 16)),
+    ("f32", 65, 33, 35, False, (32, 32, 4, 4)),
+    ("f32", 1021, 1027, 67, False, (64, 64, 2, 4)),
 ]
 
 
@@ -69,9 +70,13 @@ def _operands(dtype, M, N, K, transB):
     return A.cuda(), W.cuda(), A.float().numpy().astype(np.float64), W.float().numpy().astype(np.float64)
 
 
-@pytest.mark.parametrize("dtype,M,N,K,transB", CASES)
-def test_small_tiles_match_oracle(dtype, M, N, K, transB):
-    print("gemm ring", dtype, M, N, K, transB, flush=True)
+DTYPES = {"bf16": rov.BF16, "fp8": rov.FP8_E4M3, "f32": rov.F32}
+
+
+@pytest.mark.parametrize("dtype,M,N,K,transB,tile", CASES)
+def test_small_tiles_match_oracle(dtype, M, N, K, transB, tile):
+    print("gemm ring", dtype, M, N, K, transB, tile, flush=True)
+    assert rov.gemm_tile(M, N, K, DTYPES[dtype], transB) == (rov.GEMM_SMALL_TILES,) + tile
     if dtype != "fp8":       # what an earlier workgroup left in LDS must not reach a partly filled slot
         dt = torch.bfloat16 if dtype == "bf16" else torch.float32
         nan = torch.full((512, 512), float("nan"), dtype=dt, device="cuda")
@@ -113,19 +118,49 @@ def test_memory_behind_the_operands_is_not_part_of_the_result(dtype, M, N, K, tr
     assert bool(torch.isfinite(C.float()).all()) and torch.equal(C, C0)
 
 
-@pytest.mark.parametrize("dtype,M,N,K", [("bf16", 300, 2048, 1024), ("bf16", 700, 4096, 512), ("fp8", 300, 2048, 4096),
-                                         ("fp8", 520, 8192, 1024)])
-def test_unsplit_small_tiles_give_the_256_row_kernels_bits(dtype, M, N, K):
-    print("gemm ring bits", dtype, M, N, K, flush=True)
+@pytest.mark.parametrize("dtype,M,N,K,tile", [
+    ("bf16", 300, 2048, 1024, (64, 64)), ("bf16", 700, 4096, 512, (128, 128)),
+    ("fp8", 300, 2048, 4096, (64, 64)), ("fp8", 333, 4096, 640, (128, 64)), ("fp8", 500, 8192, 384, (128, 128)),
+])
+def test_unsplit_small_tiles_give_the_256_row_kernels_bits(dtype, M, N, K, tile):
+    print("gemm ring bits", dtype, M, N, K, tile, flush=True)
+    assert rov.gemm_tile(M, N, K, DTYPES[dtype])[:4] == (rov.GEMM_SMALL_TILES,) + tile + (1,)
     A, W, _, _ = _operands(dtype, M, N, K, True)
     C = rov.gemm(A, W)
     prev = rov.set_gemm_tile_cols(128)
     try:
+        assert rov.gemm_tile(M, N, K, DTYPES[dtype])[0] == rov.GEMM_256_ROWS
         C2 = rov.gemm(A, W)
         torch.cuda.synchronize()
     finally:
         rov.set_gemm_tile_cols(prev)
     assert torch.equal(C.view(torch.int16), C2.view(torch.int16))
+
+
+def test_long_sums_have_the_same_bits_at_every_forced_width():
+    # from K = 2048 on the small tiles may add partial sums over k: the default product is then another rounding of the same
+    # sum, while the forced widths keep one order, whatever M is
+    M, N, K = 333, 4096, 4096
+    assert rov.gemm_tile(M, N, K, rov.BF16) == (rov.GEMM_SMALL_TILES, 128, 64, 2, 16)
+    A, W, _, _ = _operands("bf16", M, N, K, True)
+    got = {}
+    for cols in (0, 128, 160, 192, 224, 256):
+        prev = rov.set_gemm_tile_cols(cols)
+        try:
+            got[cols] = rov.gemm(A, W)
+            if cols == 256:
+                part = rov.gemm(A[:100], W)
+        finally:
+            rov.set_gemm_tile_cols(prev)
+    torch.cuda.synchronize()
+    for cols in (160, 192, 224, 256):
+        assert torch.equal(got[cols], got[128]), cols
+    assert torch.equal(part, got[128][:100])
+    # fp32 sums of 4096 terms in two orders: 4e-6 of the scale apart (see above) and then rounded to bf16, so that a few
+    # results on the edge between two neighbours differ by one of 2^-8
+    far = (got[0].float() - got[128].float()).abs()
+    assert float((far > 0).float().mean()) < 0.02
+    assert bool((far <= 2.0 ** -7 * got[128].float().abs() + 1e-5 * got[128].float().abs().max()).all())
 
 
 def test_fp32_product_keeps_infinities_and_nan_in_their_rows():
@@ -143,26 +178,28 @@ def test_fp32_product_keeps_infinities_and_nan_in_their_rows():
 
 @pytest.mark.parametrize("dtype", ["bf16", "fp8"])
 @pytest.mark.parametrize("M,N,K", [
-    (300, 14336, 128),       # seven weight blocks a wave, ragged rows
-    (2900, 2820, 1024),      # five, ragged columns (last tile: 4 of 80)
-    (2900, 2816, 128),       # five or six
-    (2304, 3300, 256),       # nine tile rows
-    (70, 4, 128),            # one tile, four columns
+    (300, 14336, 128),       # ragged rows
+    (2900, 2820, 1024),      # ragged columns (five blocks: last tile 20 of 80)
+    (2304, 3300, 256),       # nine tile rows: every start of the walk over k
+    (70, 4, 128),            # one tile, four columns: fewer than one block
+    (257, 60, 256),          # fewer columns than one wave's half of any tile
 ])
 def test_dual_tiles_of_every_width_give_the_same_bits(dtype, M, N, K):
-    # the width chosen from the shape against the widest and the narrowest (whose parity has its own tests)
+    # every width forced, and the one chosen from the shape, against the widest (whose parity has its own tests)
     print("dual", dtype, M, N, K, flush=True)
     A, Wg, _, _ = _operands(dtype, M, N, K, True)
     g = torch.Generator("cuda").manual_seed(N)
     Wu = Wg[torch.randperm(N, device="cuda", generator=g)].contiguous()
     run = (lambda: rov.gemm_swiglu(A, Wg, Wu)) if dtype == "bf16" else (lambda: rov.gemm_swiglu_fp8(A, Wg, Wu, 1 / 16, 1 / 64, 1 / 64, 0.25))
     got = {}
-    for cols in (0, 256, 128):
+    for cols in (0, 128, 160, 192, 224, 256):
         prev = rov.set_gemm_tile_cols(cols)
         try:
+            assert cols == 0 or rov.gemm_swiglu_tile_cols(M, N, K, DTYPES[dtype]) == cols // 2
             got[cols] = run()
             torch.cuda.synchronize()
         finally:
             rov.set_gemm_tile_cols(prev)
-    assert torch.equal(got[0], got[256]) and torch.equal(got[0], got[128])
-    assert got[0].float().abs().max() > 0
+    for cols in (0, 128, 160, 192, 224):
+        assert torch.equal(got[cols], got[256]), cols
+    assert got[256].float().abs().max() > 0

@@ -159,12 +159,12 @@ def test_layer_step_replays_from_a_captured_graph(sched):
 def test_layer_step_overlap_from_two_host_threads():
     # two host threads enqueue overlap steps at the same time, each on its own pair of streams with its own
     # buffers and seed (ctypes releases the interpreter lock during the calls).  The library serialises the
-    # enqueue phase of its schedule entry points and shares one set of fork / join events and the work-queue
-    # slots between them: every thread must end with the oracle's mask for its seed and with the outputs a
+    # enqueue phase of its schedule entry points and shares one set of fork / join events between them (and the work-queue
+    # slots of larger masks: test_gpu_mask_queue.py): every thread must end with the oracle's mask for its seed and with the outputs a
     # single-threaded run gives, bit for bit.
     import threading
     B, H, Hkv, d = 1, 4, 2, 128
-    cases = [dict(S=512, gemm=(256, 128, 256), seed=wl.SEED),            # RNG outlasts the GEMM: work queue + helper launch
+    cases = [dict(S=512, gemm=(256, 128, 256), seed=wl.SEED),            # RNG outlasts the GEMM: split, helper launch
              dict(S=256, gemm=(1024, 512, 1024), seed=wl.SEED + 77)]     # RNG fits beside the GEMM: plain launch
     p, reps = 0.1, 12
     for i, c in enumerate(cases):
@@ -637,8 +637,8 @@ def test_block_forward_fp8_error_paths():
 
 
 @pytest.mark.parametrize("causal", [False, True])
-@pytest.mark.parametrize("force_queue", [False, True])
-def test_block_forward_deferred_join_over_three_layers(causal, force_queue):
+@pytest.mark.parametrize("tiny_grid", [False, True])
+def test_block_forward_deferred_join_over_three_layers(causal, tiny_grid):
     # a stack of blocks on one stream pair: every block leaves the next layer's mask in flight
     # (ROV_SCHED_OVERLAP_DEFERRED) and the following one finishes and joins it beside its QKV GEMM
     # (mask_ready = ROV_MASK_IN_FLIGHT).  Outputs and masks are those of the sequential schedule.
@@ -650,8 +650,9 @@ def test_block_forward_deferred_join_over_three_layers(causal, force_queue):
     ws = torch.empty(rov.block_workspace_bytes(cfg, B, S, 0), dtype=torch.uint8, device="cuda")
     main, side = torch.cuda.Stream(), torch.cuda.Stream()
     calls = rov.mask_philox_calls(B, H, S)
-    # (a tiny RNG grid cannot finish beside the GEMMs: the work queue and the helper launch are used)
-    prev = rov.set_rng_max_workgroups(1) if force_queue else None
+    # (masks of this size are split between the two RNG launches beforehand; with a grid of one workgroup for either of
+    # them each runs on for long.  The work queue: test_gpu_mask_queue.py)
+    prev = rov.set_rng_max_workgroups(1) if tiny_grid else None
     try:
         y_seq = []
         m = torch.zeros(rov.mask_shape(B, H, S), dtype=torch.int64, device="cuda")
@@ -673,7 +674,7 @@ def test_block_forward_deferred_join_over_three_layers(causal, force_queue):
                           mask_ready=rov.MASK_IN_FLIGHT, next_mask=None)
         torch.cuda.synchronize()
     finally:
-        if force_queue:
+        if tiny_grid:
             rov.set_rng_max_workgroups(prev)
     for layer in range(3):
         assert torch.equal(ys[layer], y_seq[layer]), layer
@@ -697,8 +698,8 @@ def test_block_forward_deferred_join_over_three_layers(causal, force_queue):
     assert bool((y == 5.0).all())
 
 
-@pytest.mark.parametrize("force_queue", [False, True])
-def test_mask_finish_completes_a_mask_left_in_flight(force_queue):
+@pytest.mark.parametrize("tiny_grid", [False, True])
+def test_mask_finish_completes_a_mask_left_in_flight(tiny_grid):
     # the last block of a stack called with ROV_SCHED_OVERLAP_DEFERRED leaves a mask that no block will
     # claim: while it is in flight every other use of the buffer is refused; rov_mask_finish completes it
     # (bit-exact against the oracle) and gives the buffer back
@@ -713,9 +714,10 @@ def test_mask_finish_completes_a_mask_left_in_flight(force_queue):
     masks = [torch.full(rov.mask_shape(B, H, S), 0x2AAAAAAAAAAAAAAA, dtype=torch.int64, device="cuda") for _ in range(2)]
     y = torch.zeros_like(x)
     torch.cuda.synchronize()
-    prev = rov.set_rng_max_workgroups(1) if force_queue else None
+    # (a fixed split, with one workgroup for either launch; the work queue: test_gpu_mask_queue.py)
+    prev = rov.set_rng_max_workgroups(1) if tiny_grid else None
     try:
-        print("mask_finish: deferred block", force_queue, flush=True)
+        print("mask_finish: deferred block", tiny_grid, flush=True)
         rov.block_forward(weights, x, y, cfg, rov.SCHED_OVERLAP_DEFERRED, seed, offset, masks[0], ws, main, side,
                           mask_ready=rov.MASK_NOT_READY, next_mask=masks[1])
         # in flight: not usable as a ready mask, not as a target, and only finishable once
@@ -739,7 +741,7 @@ def test_mask_finish_completes_a_mask_left_in_flight(force_queue):
             rov.mask_finish(masks[0], main)            # never was in flight
         main.synchronize()                             # the main stream alone: it has joined the side stream
     finally:
-        if force_queue:
+        if tiny_grid:
             rov.set_rng_max_workgroups(prev)
     assert bool((y2 == 5.0).all())
     assert np.array_equal(masks[1].cpu().numpy().view(np.uint64), OP.dropout_mask(seed, offset + calls, B, H, S, p))
