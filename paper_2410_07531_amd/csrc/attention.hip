@@ -883,7 +883,8 @@ __global__ __launch_bounds__(NW * 64) void attn_f32_kernel(const AttnParams p) {
 
 // ------------------------------------------------------------------ generic kernel
 // One wave per query row, keys in chunks of 256 with an online softmax; any dtype / head
-// dimension up to 256.  Correct for every shape; used for fp32 and odd head dimensions.
+// dimension up to 256.  Correct for every shape; used for the head dimensions, strides and alignments that
+// the two kernels above do not take.
 template <typename TT>
 __device__ __forceinline__ float ld(const TT* p);
 template <>

@@ -34,9 +34,9 @@
 // 4.55 PFLOP/s in a register-only loop against 4.0 for 32x32x64).
 //
 // Outputs too small for these tiles, fp32, [K,N] weights and other row lengths take
-// the kernels of gemm_ring.hip; what those refuse (rows of an odd number of 16-bit
-// values or of bytes, matrices beyond 32-bit offsets) takes a small LDS-tiled VALU
-// kernel that is correct for any shape.
+// the kernels of gemm_ring.hip; what those refuse (bf16 rows of an odd number of values,
+// fp8 rows off 16 bytes, fp8 [K,N] weights, operands beyond 32-bit offsets) takes a small
+// LDS-tiled VALU kernel that is correct for any shape.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 

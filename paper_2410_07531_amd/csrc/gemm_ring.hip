@@ -6,7 +6,7 @@
 // 128-byte slot of k has to travel L2 -> LDS (about 43 bytes per clock and compute unit) at a
 // latency of one to two microseconds.  So
 //   - tiles are small enough that the launch covers the 256 compute units, and
-//   - operands go through a ring of STAGES LDS slots (up to 144 KiB in flight per compute unit),
+//   - operands go through a ring of STAGES LDS slots (up to 160 KiB of them per compute unit),
 //     filled by buffer loads that write LDS, loaded STAGES slots ahead.
 // One barrier per slot: when a wave arrives there it has read the slot it is working on into
 // registers and its own loads of the next slot have landed.  The fragments of a unit of k (one MFMA
@@ -23,8 +23,8 @@
 // Per element the sum runs over k in the order of the 256-row kernels (same MFMA, same cyclic start),
 // so for bf16 and fp8 with KS == 1 the result is theirs bit for bit.
 //
-// Measured at 333 x 4096 x 4096 bf16: 21.5 us (256-row kernel 54); [K, N] weights 1024 x 4096 x 4096: 40 us
-// (generic VALU kernel 800); fp32 1024^3: 23 us (184), 2048 x 4096 x 4096: 510 us = 135 TFLOP/s of the
+// Measured at 333 x 4096 x 4096 bf16: 20 us (256-row kernel 52.5); [K, N] weights 1024 x 4096 x 4096: 37 us
+// (generic VALU kernel 799); fp32 1024^3: 23 us (184), 2048 x 4096 x 4096: 510 us = 135 TFLOP/s of the
 // 157 the fp32 matrix instructions reach (1470).
 #include <hip/hip_runtime.h>
 #include <stdint.h>

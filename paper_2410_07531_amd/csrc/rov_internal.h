@@ -39,8 +39,8 @@ void trace_end(int slot, hipStream_t st);
 // Launchers used across translation units (all asynchronous on `stream`).
 // Grid of the RNG kernel: alone on the device; a small persistent grid meant to run beside a
 // GEMM (overlap schedules); or a device-filling persistent grid that helps such a small grid
-// finish, launched where the GEMMs end (the full-speed tail of the RNG, paper Sec. 3.3).  The last two share the mask through a work queue:
-// qslot >= 0 (from mask_queue_acquire, which resets the slot on the given stream; it must be
+// finish, launched where the GEMMs end (the full-speed tail of the RNG, paper Sec. 3.3).  The last two share a mask through a work queue
+// (smaller masks by ranges of chunks, see launch_mask): qslot >= 0 (from mask_queue_acquire, which resets the slot on the given stream; it must be
 // ordered before both launches) makes the waves pull 64-word chunks from that queue, so each
 // chunk is produced by whichever launch gets to it first.  qslot < 0: static striding.
 enum { MASK_GRID_FULL = 0, MASK_GRID_BESIDE = 1, MASK_GRID_HELPER = 2 };

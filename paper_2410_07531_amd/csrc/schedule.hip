@@ -164,7 +164,8 @@ int t_mask(uint64_t seed, uint64_t offset, int B, int H, int S, float p, uint64_
 // The rates are this chip's measured ones with both kernels running: 1.16 PFLOP/s for the bf16
 // GEMMs and 2.55 for fp8 (12 % and 8 % below their stand-alone rates; 120 TFLOP/s for the fp32
 // kernels), 0.335 T Philox calls/s for the three-waves-per-SIMD grid beside them (0.44 of the
-// stand-alone kernel).  A wrong guess costs time, never correctness.
+// stand-alone kernel).  They are those of products that fill the chip: short ones run at half of that and less, so there the
+// small grid gets less than it could do.  A wrong guess costs time, never correctness.
 double beside_gemm_seconds(double gemm_flop, int dtype) {
     return gemm_flop / (dtype == ROV_F32 ? 120e12 : (dtype == ROV_FP8_E4M3 ? 2.55e15 : 1.16e15));
 }
