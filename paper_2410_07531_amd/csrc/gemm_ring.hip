@@ -466,7 +466,10 @@ int launch_ring(const void* A, const void* W, void* C, const void* R, int M, int
 
 // ------------------------------------------------------------------ choice of the tile
 // One row per instantiation: what it takes, its tile, and the time of one slot (128 bytes of k; 256 compute units
-// busy) in nanoseconds, measured on one box with K = 4096 at 128 to 1024 workgroups.  Register counts leave room
+// busy) in nanoseconds, measured with K = 4096 at 128 to 1024 workgroups; for bf16 and fp8 [N, K] weights, where the 256-row
+// kernels compete, adjusted so that none of 622 products of either type for which all forms were timed (16 to 4096 rows, 256 to
+// 14336 columns, K of 512 to 14336) runs more than 2 % slower than with the 256-row kernel: fp8 128 x 64 at 280 chose this
+// form where it was up to 28 % slower (700 x 8192 x 8192 68 us against 53, 300 x 14336 x 4096 36.5 against 30.5).  Register counts leave room
 // for three 24-register RNG waves on every SIMD (a 256 x 128 tile with eight waves, 250 registers each, was up to
 // 8 % faster than the 256-row kernel at 2048 x 4096 x 4096, but its workgroups could not be placed beside an RNG
 // grid that arrived first).
@@ -481,9 +484,9 @@ const RingVariant kRing[] = {
     {ROV_BF16, 0, 16, 4, 64, 32, 125.f, launch_ring<ROV_BF16, 4, 2, 1, 1, 4, 2, false, 16, 5>},
     {ROV_BF16, 0, 16, 2, 64, 64, 165.f, launch_ring<ROV_BF16, 2, 2, 2, 2, 2, 2, false, 16, 4>},
     {ROV_BF16, 0, 16, 2, 128, 64, 275.f, launch_ring<ROV_BF16, 4, 2, 2, 2, 2, 2, false, 16, 3>},
-    {ROV_BF16, 0, 16, 2, 128, 128, 455.f, launch_ring<ROV_BF16, 4, 4, 2, 2, 2, 1, false, 16, 4>},
-    {ROV_BF16, 0, 16, 2, 192, 128, 660.f, launch_ring<ROV_BF16, 6, 4, 2, 2, 2, 1, false, 16, 4>},
-    {ROV_BF16, 0, 16, 2, 128, 192, 660.f, launch_ring<ROV_BF16, 4, 6, 2, 2, 2, 1, false, 16, 4>},
+    {ROV_BF16, 0, 16, 2, 128, 128, 490.f, launch_ring<ROV_BF16, 4, 4, 2, 2, 2, 1, false, 16, 4>},
+    {ROV_BF16, 0, 16, 2, 192, 128, 700.f, launch_ring<ROV_BF16, 6, 4, 2, 2, 2, 1, false, 16, 4>},
+    {ROV_BF16, 0, 16, 2, 128, 192, 700.f, launch_ring<ROV_BF16, 4, 6, 2, 2, 2, 1, false, 16, 4>},
     {ROV_BF16, 0, 16, 1, 64, 64, 190.f, launch_ring<ROV_BF16, 2, 2, 2, 2, 1, 1, false, 16, 4>},
     {ROV_BF16, 0, 16, 1, 128, 128, 520.f, launch_ring<ROV_BF16, 4, 4, 2, 2, 1, 1, false, 16, 4>},
     {ROV_BF16, 0, 4, 2, 64, 64, 260.f, launch_ring<ROV_BF16, 2, 2, 2, 2, 2, 1, false, 4, 4>},
@@ -492,9 +495,9 @@ const RingVariant kRing[] = {
     {ROV_BF16, 1, 16, 2, 128, 128, 510.f, launch_ring<ROV_BF16, 4, 4, 2, 2, 2, 1, true, 16, 4>},
     {ROV_BF16, 1, 16, 2, 192, 128, 700.f, launch_ring<ROV_BF16, 6, 4, 2, 2, 2, 1, true, 16, 4>},
     {ROV_BF16, 1, 4, 2, 64, 64, 260.f, launch_ring<ROV_BF16, 2, 2, 2, 2, 2, 1, true, 4, 4>},
-    {ROV_FP8_E4M3, 0, 16, 1, 64, 64, 165.f, launch_ring<ROV_FP8_E4M3, 2, 2, 2, 2, 1, 1, false, 16, 4>},
-    {ROV_FP8_E4M3, 0, 16, 1, 128, 64, 280.f, launch_ring<ROV_FP8_E4M3, 2, 2, 4, 2, 1, 1, false, 16, 6>},
-    {ROV_FP8_E4M3, 0, 16, 1, 128, 128, 500.f, launch_ring<ROV_FP8_E4M3, 4, 2, 2, 4, 1, 1, false, 16, 4>},
+    {ROV_FP8_E4M3, 0, 16, 1, 64, 64, 172.f, launch_ring<ROV_FP8_E4M3, 2, 2, 2, 2, 1, 1, false, 16, 4>},
+    {ROV_FP8_E4M3, 0, 16, 1, 128, 64, 315.f, launch_ring<ROV_FP8_E4M3, 2, 2, 4, 2, 1, 1, false, 16, 6>},
+    {ROV_FP8_E4M3, 0, 16, 1, 128, 128, 530.f, launch_ring<ROV_FP8_E4M3, 4, 2, 2, 4, 1, 1, false, 16, 4>},
     {ROV_F32, 0, 16, 4, 32, 32, 142.f, launch_ring<ROV_F32, 1, 1, 1, 1, 4, 1, false, 16, 8>},
     {ROV_F32, 0, 16, 2, 64, 64, 500.f, launch_ring<ROV_F32, 1, 1, 2, 2, 2, 1, false, 16, 4>},
     {ROV_F32, 0, 4, 4, 32, 32, 200.f, launch_ring<ROV_F32, 1, 1, 1, 1, 4, 1, false, 4, 4>},
