@@ -129,6 +129,19 @@ def test_small_tiles_only_where_they_are_sooner():
         assert B.gemm_tile(M, N, K, dt)[0] == B.GEMM_SMALL_TILES, (dt, M, N, K)
 
 
+def test_very_short_sums_take_the_any_shape_kernel():
+    # sums of a few terms into large outputs were measured up to twice as slow with the small tiles; longer ones and small
+    # outputs are theirs
+    B = binding
+    for dt, M, N, K, tb in ((B.BF16, 1500, 4098, 2, True), (B.BF16, 6000, 4096, 2, False), (B.BF16, 6000, 4098, 24, True),
+                            (B.BF16, 1500, 4098, 30, False), (B.F32, 1500, 4098, 30, True), (B.F32, 6000, 4096, 16, True),
+                            (B.F32, 6000, 4098, 62, False), (B.F32, 1500, 1001, 32, True)):
+        assert B.gemm_tile(M, N, K, dt, tb)[0] == B.GEMM_ANY_SHAPE, (dt, M, N, K, tb)
+    for dt, M, N, K, tb in ((B.BF16, 1500, 4098, 102, True), (B.BF16, 1500, 1000, 30, False), (B.BF16, 6000, 1000, 8, True),
+                            (B.F32, 200, 1000, 40, True), (B.F32, 1500, 1000, 102, False), (B.F32, 6000, 4098, 200, True)):
+        assert B.gemm_tile(M, N, K, dt, tb)[0] == B.GEMM_SMALL_TILES, (dt, M, N, K, tb)
+
+
 def test_key_parts_leave_full_chips_alone():
     # causal problems that fill the chip take workgroups of 256 rows: with two key parts these shapes were measured 2 to 20 %
     # slower (stored mask and no dropout); and short ones keep their split

@@ -56,11 +56,14 @@ def test_gemm_bf16_matches_oracle(M, N, K, transB):
 @pytest.mark.parametrize("dtype,M,N,K,transB", [
     ("bf16", 7, 13, 17, True), ("bf16", 130, 70, 333, True), ("bf16", 65, 131, 35, False), ("bf16", 130, 99, 64, False),
     ("fp8", 70, 36, 133, True), ("fp8", 70, 36, 64, False), ("fp8", 65, 67, 130, False),
+    # very short sums into large outputs, which the small tiles could take
+    ("bf16", 1500, 4098, 8, True), ("bf16", 1500, 4098, 30, False), ("f32", 1500, 1001, 16, False), ("f32", 700, 4099, 24, True),
     # fp32 with operand rows (or a [K, N] matrix with the last slot's overhang) beyond 32-bit byte offsets
     ("f32", 2, 3, 5700000, True), ("f32", 3, 8400000, 2, False),
 ])
 def test_gemm_any_shape_kernel_matches_oracle(dtype, M, N, K, transB):
-    # what no matrix-core kernel takes: rows of an odd number of 16-bit values, fp8 rows off 16 bytes and fp8 [K, N].
+    # what no matrix-core kernel takes: rows of an odd number of 16-bit values, fp8 rows off 16 bytes and fp8 [K, N]; and what
+    # this kernel does sooner.
     # Operands in sixteenths up to 1: products are multiples of 2^-8, and these sums of them stay below 2^16, exact in fp32
     # in any order (of the longest sum one term in 64 is not zero)
     print("gemm any shape", dtype, M, N, K, transB, flush=True)
