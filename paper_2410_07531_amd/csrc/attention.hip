@@ -1071,10 +1071,20 @@ int attn_key_parts(int B, int H, int S, int d, bool causal) {
     return best;
 }
 
-// Waves of a workgroup of the fp32 kernel: eight at up to 64 features, four above (their registers); 0: a head dimension
-// that it does not take, or more workgroups than a grid holds (the whole problem's, so that row ranges agree with it).
+// Waves of a workgroup of the fp32 kernel: eight at up to 64 features, four above (their registers); 0: the one-row-per-wave
+// kernel runs, for a head dimension that this one does not take, for more workgroups than a grid holds, or because it is done
+// sooner.  That is so for a few rows: its waves have one key a lane, where the matrix kernel is one chain of load, 32-key
+// products and merge whatever S is.  Both times in us, fitted to 3360 problems of 1 to 96 tokens, 1 to 512 heads and 8 to 128
+// features (one row a wave / matrix kernel, no dropout, d = 128: 1 head x 33 tokens 7.9 / 11.0, 32 x 16 6.4 / 10.2, 32 x 64 15.3 / 10.7,
+// 512 x 8 9.4 / 19.1, 512 x 32 63 / 20; d = 64: 1 x 33 5.4 / 7.3, 32 x 33 6.7 / 8.0, 32 x 64 9.2 / 7.3).
+// Only what all launches over one problem share decides, so that row ranges and modes agree.
 int attn_f32_waves(int B, int H, int S, int d) {
-    if (d % 8 != 0 || d > 128 || ((long long)S + 31) / 32 * H * B > 0x7FFFFFFFLL) return 0;
+    const double heads = (double)B * H, tiles = ceil(S / 32.0) * heads;
+    if (d % 8 != 0 || d > 128 || tiles > 0x7FFFFFFF) return 0;
+    const double f = d <= 64 ? 1.0 : 2.0;
+    const double row_us = 2.5 + 0.06 * f * S + 1e-3 * heads * S * f * (1.0 + 0.01 * S);
+    const double mfma_us = (4.0 + 0.06 * ((d + 31) / 32 * 32)) * (0.2 + 0.8 * ceil(tiles / device_cu_count()));
+    if (S <= 64 && row_us < mfma_us) return 0;   // (beyond 64 tokens a lane has a second key)
     return d <= 64 ? 8 : 4;
 }
 

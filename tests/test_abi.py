@@ -155,12 +155,22 @@ def test_key_parts_leave_full_chips_alone():
     assert parts(1, 32, 2048, 128) == 2 and parts(1, 32, 4096, 64) == 2
 
 
+def test_fp32_attention_of_a_few_rows_takes_a_row_a_wave():
+    # measured 1.2 to 3 times as fast as the matrix kernel for a few rows, and slower where there are many
+    waves = lambda heads, S, d: binding.attention_key_parts(1, heads, S, d, binding.F32, False)
+    for heads, S, d in ((1, 1, 8), (1, 16, 64), (1, 33, 128), (8, 32, 96), (32, 16, 128), (128, 8, 64), (512, 8, 128), (512, 4, 32)):
+        assert waves(heads, S, d) == 0, (heads, S, d)
+    for heads, S, d in ((1, 65, 8), (2, 128, 64), (32, 64, 128), (128, 48, 64), (512, 32, 128), (512, 33, 64), (32, 56, 96)):
+        assert waves(heads, S, d) == (8 if d <= 64 else 4), (heads, S, d)
+
+
 def test_key_parts_never_ask_for_more_workgroups_than_a_grid_holds():
     # 2^30 (batch, head) pairs (views with zero strides) fit the grid with 256 rows a workgroup or one row a wave, which
     # is what such calls are accepted for, but not with the 32, 64 or 128 rows of the finer forms
     B = H = 32768
     assert binding.attention_key_parts(B, H, 64, 64, binding.F32, False) == 0
     assert binding.attention_key_parts(B, H, 32, 64, binding.F32, False) == 8
+    assert binding.attention_key_parts(B // 4, H, 96, 64, binding.F32, False) == 8
     for d in (64, 128):
         for causal in (False, True):
             assert binding.attention_key_parts(B, H, 256, d, binding.BF16, causal) == 1

@@ -1,8 +1,8 @@
-"""GPU parity of the fp32 attention kernel on the matrix instructions.
+"""GPU parity of fp32 attention: the kernel on the matrix instructions and, for a few rows, the one-row-per-wave kernel.
 
-Sizes at which it can go wrong: one key, one query, tiles of 32 partly filled, fewer key tiles than waves,
+Sizes at which the former can go wrong: tiles of 32 partly filled, fewer key tiles than waves,
 head dimensions that fill a feature tile, a part of one, or several; causal and not; grouped keys; strided
-views.  Reference: the float64 oracle; bar 1e-4 of the result's scale (hardware exp2, fp32 sums).
+views.  The rows assert which of the two they reach.  Reference: the float64 oracle; bar 1e-4 of the result's scale (hardware exp2, fp32 sums).
 """
 import numpy as np
 import pytest
@@ -23,12 +23,14 @@ def _err(got, ref):
 
 
 @pytest.mark.parametrize("causal", [False, True])
-@pytest.mark.parametrize("B,S,H,Hkv,d", [
-    (1, 1, 1, 1, 8), (1, 33, 2, 1, 32), (2, 65, 8, 4, 40), (1, 300, 4, 2, 64), (1, 97, 3, 3, 80), (1, 70, 2, 2, 96),
-    (2, 129, 2, 1, 128), (1, 100, 2, 2, 104),
+@pytest.mark.parametrize("B,S,H,Hkv,d,waves", [
+    (1, 1, 1, 1, 8, 0), (1, 33, 2, 1, 32, 0), (1, 40, 2, 2, 128, 0),       # few rows: one row a wave
+    (8, 20, 64, 16, 8, 8), (4, 33, 16, 4, 32, 8), (8, 32, 32, 32, 128, 4),  # one or two key tiles, many heads
+    (2, 65, 8, 4, 40, 8), (1, 300, 4, 2, 64, 8), (1, 97, 3, 3, 80, 4), (1, 70, 2, 2, 96, 4), (2, 129, 2, 1, 128, 4), (1, 100, 2, 2, 104, 4),
 ])
-def test_fp32_matches_oracle(B, S, H, Hkv, d, causal):
+def test_fp32_matches_oracle(B, S, H, Hkv, d, waves, causal):
     print("attn fp32", B, S, H, Hkv, d, causal, flush=True)
+    assert rov.attention_key_parts(B, H, S, d, rov.F32, causal) == waves
     p, seed, offset = 0.2, wl.SEED, 2**32 - 200        # call numbers carry into the second counter word
     q, k, v = wl.qkv(np.random.default_rng(S + d), B, S, H, Hkv, d)
     Q, K, V = (torch.from_numpy(x).cuda() for x in (q, k, v))
@@ -75,6 +77,7 @@ def test_fp32_strided_views():
 def test_fp32_causal_rows_never_see_later_values():
     # non-finite keys and values reach the rows that admit them and no other
     B, S, H, d = 1, 96, 1, 64
+    assert rov.attention_key_parts(B, H, S, d, rov.F32, True) == 8
     g = torch.Generator("cuda").manual_seed(9)
     Q, K, V = (torch.randn(B, S, H, d, device="cuda", generator=g) for _ in range(3))
     ref = rov.attention_fwd_dropout(Q, K, V, 0.0, causal=True)
@@ -91,17 +94,18 @@ def test_fp32_causal_rows_never_see_later_values():
 
 
 @pytest.mark.parametrize("causal", [False, True])
-@pytest.mark.parametrize("S,d", [(1, 8), (33, 40), (60, 64), (97, 128)])
-def test_fp32_rows_behind_the_last_key_are_not_part_of_the_result(S, d, causal):
+@pytest.mark.parametrize("S,H,d", [(1, 1, 8), (20, 256, 8), (33, 128, 40), (60, 128, 64), (97, 2, 128)])
+def test_fp32_rows_behind_the_last_key_are_not_part_of_the_result(S, H, d, causal):
     # K and V end inside a tile of 32 keys and what lies behind them in memory is NaN: the loads stay in the rows
     # [0, S) (the row of a load is clamped to the last one, the rest is outside its buffer's range)
-    print("attn fp32 rows behind", S, d, causal, flush=True)
+    print("attn fp32 rows behind", S, H, d, causal, flush=True)
+    assert (rov.attention_key_parts(1, H, S, d, rov.F32, causal) != 0) == (S > 1)
     g = torch.Generator("cuda").manual_seed(S)
-    buf = [torch.full((1, S + 40, 2, d), float("nan"), device="cuda") for _ in range(3)]
+    buf = [torch.full((1, S + 40, H, d), float("nan"), device="cuda") for _ in range(3)]
     Q, K, V = (x[:, :S] for x in buf)
     for x in (Q, K, V):
-        x.copy_(torch.randn(1, S, 2, d, device="cuda", generator=g))
-    frame = torch.full((1, S + 40, 2, d), 7.0, device="cuda")
+        x.copy_(torch.randn(1, S, H, d, device="cuda", generator=g))
+    frame = torch.full((1, S + 40, H, d), 7.0, device="cuda")
     rov.attention_fwd_dropout(Q, K, V, 0.0, causal=causal, O=frame[:, :S])
     torch.cuda.synchronize()
     ref = OD.attention_dropout(*(t.double().cpu().numpy() for t in (Q, K, V)), None, 0.0, causal=causal)
