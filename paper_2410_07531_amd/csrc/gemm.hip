@@ -840,17 +840,17 @@ int best_tile_cols(int M, int N) {
     return 32 * nj;
 }
 
-// Is a sum of at most 128 terms, bf16 or fp32, done sooner by the any-shape kernel?  Its 64 x 64 tiles pay per 16 terms; the
+// Is a sum of at most 128 terms done sooner by the any-shape kernel?  Its 64 x 64 tiles pay per 16 terms; the
 // small tiles move whole slots of k and then pay for the output, more so where columns are not stored four at a time (c[1]) and
-// where rows start on 4 bytes (c[2]).  Both estimates in us, fitted to 1120 products of 1 to 6000 rows and 2 to 4098 columns.  Any
+// where rows start on 4 bytes (c[2]).  Both estimates in us, fitted to 1120 products of 1 to 6000 rows and 2 to 4098 columns (fp8: bf16's, but for the output).  Any
 // shape / small tiles, us: bf16 1500 x 4098 x 2 12 / 27, 6000 x 4098 x 40 54 / 63, x 72 84 / 63; fp32 1500 x 4098 x 30
 // 21 / 35, 6000 x 4096 x 16 40 / 55, x 48 66 / 67, x 96 105 / 79.
 bool any_shape_sooner(int M, int N, int K, int dtype, int vec) {
-    if (K > 128 || dtype == ROV_FP8_E4M3 || (double)M * (double)N < 5e5) return false;   // (small outputs: at launch cost either way)
+    if (K > 128 || (double)M * (double)N < 5e5) return false;   // (small outputs: at launch cost either way)
     const bool f32 = dtype == ROV_F32;
     const double tiles = (double)((M + 63) / 64) * (double)((N + 63) / 64), out = 1e-6 * (double)M * (double)N;
     const double any_us = fmax(1.8, 2.1e-3 * tiles + 1.3) * ((K + 15) / 16) + 3.7 + (f32 ? 4.6e-3 : 2.25e-3) * tiles;
-    const double c[4] = {f32 ? 1.78 : 0.85, f32 ? 1.43 : 1.36, f32 ? 0.84 : 1.20, f32 ? 0.013 : 0.0};
+    const double c[4] = {f32 ? 1.78 : dtype == ROV_BF16 ? 0.85 : 1.15, f32 ? 1.43 : 1.36, f32 ? 0.84 : 1.20, f32 ? 0.013 : 0.0};
     const double small_us = (f32 ? 5.3 : 4.4) + out * (c[0] + (N % 4 != 0 ? c[1] : 0.0) + (vec < 16 ? c[2] : 0.0) + c[3] * K);
     return any_us < 1.05 * small_us;   // (the estimates scatter by 7 and 9 %)
 }

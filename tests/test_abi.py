@@ -135,10 +135,12 @@ def test_very_short_sums_take_the_any_shape_kernel():
     B = binding
     for dt, M, N, K, tb in ((B.BF16, 1500, 4098, 2, True), (B.BF16, 6000, 4096, 2, False), (B.BF16, 6000, 4098, 24, True),
                             (B.BF16, 1500, 4098, 30, False), (B.F32, 1500, 4098, 30, True), (B.F32, 6000, 4096, 16, True),
-                            (B.F32, 6000, 4098, 62, False), (B.F32, 1500, 1001, 32, True)):
+                            (B.F32, 6000, 4098, 62, False), (B.F32, 1500, 1001, 32, True),
+                            (B.FP8_E4M3, 6000, 1001, 16, True), (B.FP8_E4M3, 1500, 4096, 16, True)):
         assert B.gemm_tile(M, N, K, dt, tb)[0] == B.GEMM_ANY_SHAPE, (dt, M, N, K, tb)
     for dt, M, N, K, tb in ((B.BF16, 1500, 4098, 102, True), (B.BF16, 1500, 1000, 30, False), (B.BF16, 6000, 1000, 8, True),
-                            (B.F32, 200, 1000, 40, True), (B.F32, 1500, 1000, 102, False), (B.F32, 6000, 4098, 200, True)):
+                            (B.F32, 200, 1000, 40, True), (B.F32, 1500, 1000, 102, False), (B.F32, 6000, 4098, 200, True),
+                            (B.FP8_E4M3, 6000, 1001, 48, True), (B.FP8_E4M3, 1500, 4096, 112, True)):
         assert B.gemm_tile(M, N, K, dt, tb)[0] == B.GEMM_SMALL_TILES, (dt, M, N, K, tb)
 
 
