@@ -214,7 +214,7 @@ int rov_gemm_tile_cols(int M, int N);
 /* The kernel that rov_gemm runs for a product with the current setting (host-side rule,
  * no device work): ROV_GEMM_256_ROWS, ROV_GEMM_SMALL_TILES (short products, [K,N]
  * weights, fp32, rows off 128 bytes) or ROV_GEMM_ANY_SHAPE (vector units; what the
- * others do not take), or the error code of such a call with aligned operands.
+ * others do not take, and very short sums), or the error code of such a call with aligned operands.
  * tile (host): rows and columns of its tile, parts of k that the waves of a workgroup
  * add up, bytes of an operand that a lane loads at once. */
 #define ROV_GEMM_256_ROWS 0
@@ -277,8 +277,8 @@ int rov_attention_fwd_dropout(const void *Q, const void *K, const void *V, void 
 
 /* How the matrix-core attention kernels share the keys of a query tile between waves (host-side
  * rule, no device work): the number of waves, 1, 2 or 4 for bf16 with d = 64 or 128 and 4 or 8 for
- * fp32 with d <= 128 a multiple of 8; 0 where the one-row-per-wave kernel for any shape runs (also for
- * rows off 16 bytes, which this function does not see).  The same for every range of rows of a
+ * fp32 with d <= 128 a multiple of 8; 0 where the one-row-per-wave kernel runs (any other head dimension, and
+ * fp32 problems of a few rows; also rows off 16 bytes, which this function does not see).  The same for every range of rows of a
  * problem, every mode and every stream.  ROV_ERR_INVALID for other arguments. */
 int rov_attention_key_parts(int B, int H, int S, int d, int dtype, int causal);
 

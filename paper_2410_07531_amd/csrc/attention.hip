@@ -25,7 +25,7 @@
 // the current one is used).
 //
 // fp32 with head dimensions up to 128 has a matrix-core kernel of its own (attn_f32_kernel).  Any other
-// case (other head dimensions, unaligned rows) takes a small one-wave-per-row
+// case (other head dimensions, unaligned rows, fp32 problems of a few rows) takes a small one-wave-per-row
 // kernel that is correct for every shape.
 #include <hip/hip_runtime.h>
 
@@ -884,7 +884,7 @@ __global__ __launch_bounds__(NW * 64) void attn_f32_kernel(const AttnParams p) {
 // ------------------------------------------------------------------ generic kernel
 // One wave per query row, keys in chunks of 256 with an online softmax; any dtype / head
 // dimension up to 256.  Correct for every shape; used for the head dimensions, strides and alignments that
-// the two kernels above do not take.
+// the two kernels above do not take, and for a few rows of fp32 (attn_f32_waves).
 template <typename TT>
 __device__ __forceinline__ float ld(const TT* p);
 template <>

@@ -91,7 +91,7 @@ template <int TPB>
 __global__ __launch_bounds__(256) void rope_kernel(uint16_t* __restrict__ buf, int64_t row_elems,
                                                    int S, int nheads, int d, double log2_theta,
                                                    int64_t tokens) {
-    __shared__ float sn[TPB][kRopeMaxPairs], cs[TPB][kRopeMaxPairs];
+    __shared__ __attribute__((aligned(16))) float sn[TPB][kRopeMaxPairs], cs[TPB][kRopeMaxPairs];   // (read 16 bytes at a time)
     __builtin_amdgcn_s_setprio(3);
     const int64_t token0 = (int64_t)blockIdx.x * TPB;
     const int pairs = d / 2;

@@ -78,3 +78,22 @@ def test_key_parts_with_scores_far_apart():
     O = rov.attention_fwd_dropout(Q, K, V, 0.0)
     ref = OD.attention_dropout(_f64(Q), _f64(K), _f64(V), None, 0.0, causal=False)
     assert np.max(np.abs(_f64(O) - ref)) / np.max(np.abs(ref)) <= 2e-2
+
+
+@pytest.mark.parametrize("mode", ["mask", "fused", "none"])
+def test_split_keys_repeat_bit_for_bit(mode):
+    # the parts are merged in a fixed order: repeated calls, on other streams and beside other work too, give the same bits
+    B, S, H, Hkv, d, causal, p = 2, 1000, 16, 4, 64, True, 0.1
+    assert rov.attention_key_parts(B, H, S, d, rov.BF16, causal) == 4
+    Q, K, V = (torch.from_numpy(x).bfloat16().cuda() for x in wl.qkv(np.random.default_rng(4), B, S, H, Hkv, d))
+    mask = rov.dropout_mask_generate(wl.SEED, 96, B, H, S, p)
+    kw = dict(p=0.0) if mode == "none" else dict(p=p, mask=mask if mode == "mask" else None, seed=wl.SEED, offset=96)
+    ref = rov.attention_fwd_dropout(Q, K, V, causal=causal, **kw)
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in range(3)]
+    outs = [torch.full_like(Q, 7.0) for _ in range(24)]
+    torch.cuda.synchronize()
+    for i, O in enumerate(outs):
+        rov.attention_fwd_dropout(Q, K, V, causal=causal, O=O, stream=streams[i % 3], **kw)
+    torch.cuda.synchronize()
+    assert all(torch.equal(O, ref) for O in outs)

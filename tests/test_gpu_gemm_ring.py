@@ -203,3 +203,18 @@ def test_dual_tiles_of_every_width_give_the_same_bits(dtype, M, N, K):
     for cols in (0, 128, 160, 192, 224):
         assert torch.equal(got[cols], got[256]), cols
     assert got[256].float().abs().max() > 0
+
+
+@pytest.mark.parametrize("dtype,M,N,K,transB", [("bf16", 333, 4096, 4096, True), ("bf16", 1000, 1000, 2056, False),
+                                                ("f32", 256, 256, 1000, True), ("fp8", 333, 4096, 640, True)])
+def test_split_sums_repeat_bit_for_bit(dtype, M, N, K, transB):
+    # the parts of k are added in a fixed order: repeated calls, on other streams and beside other work too, give the same bits
+    A, W, _, _ = _operands(dtype, M, N, K, transB)
+    ref = rov.gemm(A, W, transB=transB)
+    streams = [torch.cuda.Stream() for _ in range(3)]
+    outs = [torch.full_like(ref, 7.0) for _ in range(24)]
+    torch.cuda.synchronize()
+    for i, C in enumerate(outs):
+        rov.gemm(A, W, C=C, transB=transB, stream=streams[i % 3])
+    torch.cuda.synchronize()
+    assert all(torch.equal(C, ref) for C in outs)
