@@ -216,7 +216,7 @@ int rov_gemm_tile_cols(int M, int N);
  * weights, fp32, rows off 128 bytes) or ROV_GEMM_ANY_SHAPE (vector units; what the
  * others do not take, and very short sums), or the error code of such a call with aligned operands.
  * tile (host): rows and columns of its tile, parts of k that the waves of a workgroup
- * add up, bytes of an operand that a lane loads at once. */
+ * add up, bytes that the operands' rows start on (the widest of 16, 4, 2, 1 that it uses). */
 #define ROV_GEMM_256_ROWS 0
 #define ROV_GEMM_SMALL_TILES 1
 #define ROV_GEMM_ANY_SHAPE 2

@@ -12,7 +12,8 @@
 // registers and its own loads of the next slot have landed.  The fragments of a unit of k (one MFMA
 // depth, see Traits) are read while the MFMAs of the unit before it run.
 //
-// A load instruction fills 64 lanes x 16 bytes (x 4 bytes where rows do not start on 16: VEC) of LDS, and keeps
+// A load instruction fills 64 lanes x 16 bytes of LDS, whether rows start on 16 bytes or on 4 (VEC: what the end of a
+// row takes with it is cleared, see clear_tail; a load of 4 bytes a lane costs its wave as much and moves a quarter), and keeps
 // its wave from issuing for 20 to 50 clocks; with one wave per SIMD the matrix pipe idles meanwhile.
 // KS > 1: the waves of a workgroup share one output tile and split each slot's k between them (with SUB
 // 128-byte parts per slot where a slot of one part has too few units to split); the partial sums meet in
@@ -24,7 +25,7 @@
 // so for bf16 and fp8 with KS == 1 the result is theirs bit for bit.
 //
 // Measured at 333 x 4096 x 4096 bf16: 20 us (256-row kernel 52.5); [K, N] weights 1024 x 4096 x 4096: 37 us
-// (generic VALU kernel 799); fp32 1024^3: 23 us (184), 2048 x 4096 x 4096: 510 us = 135 TFLOP/s of the
+// (generic VALU kernel 799); fp32 72 x 2922 x 747: 10.3 us (with loads of 4 bytes a lane 15.6); fp32 1024^3: 23 us (184), 2048 x 4096 x 4096: 510 us = 135 TFLOP/s of the
 // 157 the fp32 matrix instructions reach (1470).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -42,6 +43,9 @@ typedef int i32x8 __attribute__((ext_vector_type(8)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef int i32x2 __attribute__((ext_vector_type(2)));
+typedef i32x2 i32x2_u __attribute__((aligned(4)));   // stored to rows that start on 4 bytes
+typedef f32x4 f32x4_u __attribute__((aligned(4)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -117,7 +121,7 @@ __device__ __forceinline__ int ring_swizzle(int row) {
 }
 
 // TM x TN MFMA blocks per wave, WM x WN waves over the tile, KS of them over k.  KN: W is [K, N].
-// VEC: bytes per lane of an operand load, 16 where every row starts on 16 bytes, else 4.
+// VEC: alignment of the operands' rows, 16 or 4 bytes (loads are 16 bytes a lane either way: a buffer load needs 4).
 template <int DT, int TM, int TN, int WM, int WN, int KS, int SUB, bool KN, int VEC, int STAGES>
 __global__ __launch_bounds__(64 * WM * WN * KS) void gemm_ring_kernel(const RingParams p) {
     using TR = Traits<DT>;
@@ -126,10 +130,12 @@ __global__ __launch_bounds__(64 * WM * WN * KS) void gemm_ring_kernel(const Ring
     constexpr int KR1 = kSlotRow / ESZ, KR = SUB * KR1;      // k per part, per slot
     constexpr int WROWB = KN ? BN * ESZ : kSlotRow;          // bytes per LDS row of the W tile
     constexpr int kPart = (BM + BN) * kSlotRow, kSlot = SUB * kPart;
-    constexpr int LA = BM * kSlotRow / (64 * VEC) / NW, LW = BN * kSlotRow / (64 * VEC) / NW, L1 = LA + LW, L = SUB * L1;
+    constexpr int QA = BM * kSlotRow / 1024, QP = (BM + BN) * kSlotRow / 1024;   // loads (1 KiB each) of A, of a part
+    constexpr int L = SUB * QP / NW;                         // loads per wave and slot
     constexpr int UW = SUB * TR::UNITS / KS;                 // units of k per wave and slot
     constexpr int MU = TM * TN;
-    static_assert(LA * NW * 64 * VEC == BM * kSlotRow && LW * NW * 64 * VEC == BN * kSlotRow, "every wave loads the same share");
+    static_assert(L * NW == SUB * QP, "every wave loads the same share");
+    static_assert(VEC == 16 || VEC == 4, "alignment of the rows");
     static_assert(UW * KS == SUB * TR::UNITS && (UW == 1 || UW % 2 == 0), "fragment buffers alternate");
     static_assert((STAGES - 2) * L <= 63, "loads in flight fit the counter");
     static_assert(!KN || DT != ROV_FP8_E4M3, "fp8 weights are [N, K]");
@@ -178,24 +184,31 @@ __global__ __launch_bounds__(64 * WM * WN * KS) void gemm_ring_kernel(const Ring
     i32x4 rsrc_w = make_rsrc(KN ? p.W + (size_t)n0 * ESZ : p.W + (size_t)n0 * ld_w, bytes_w);
     const uint32_t lds_base = (uint32_t)(uintptr_t)(lptr_t)lds;
 
-    // Load q of this wave (0..LA-1: A, then W) fills 64 * VEC consecutive LDS bytes.  voff: the lane's byte
-    // offset from the panel's start at slot 0; kl: its position in the slot's k (the row for a [K, N] tile).
+    // Load q of this wave is load q * NW + wave of the slot: part by part, A's rows, then W's, 1 KiB of LDS each (a load whose
+    // operand differs between the waves selects its resource).  voff: the lane's byte offset from the panel's start at
+    // slot 0; lane_k: its position in the slot's k (the row for a [K, N] tile).
     // Rows past the edge and, in the last slot, k >= K lie outside the resource and read as zeros.
     uint32_t voff[L];
-    auto lds_at = [&](int q1) { return ((q1 < LA ? q1 : q1 - LA) * NW + wave) * 64 * VEC; };   // in the operand's part
+    // (all waves' loads q in one part, or of one operand: known when compiled)
+    auto load_part = [&](int q) { return q * NW / QP == (q * NW + NW - 1) / QP ? q * NW / QP : (q * NW + wave) / QP; };
+    auto load_in_part = [&](int q) { return q * NW - load_part(q) * QP + wave; };
+    auto load_is_w = [&](int q) {
+        const int first = q * NW % QP, last = first + NW - 1;
+        return last < QA ? false : first >= QA && last < QP ? true : load_in_part(q) >= QA;
+    };
+    auto lds_at = [&](int q) { return (load_in_part(q) - (load_is_w(q) ? QA : 0)) * 1024; };   // in the operand's part
     auto lane_k = [&](int q) {
-        const int q1 = q % L1, sub = q / L1;
-        const bool krow = KN && q1 >= LA;
-        const int b = lds_at(q1) + lane * VEC, row = b / (krow ? WROWB : kSlotRow), pos = b % (krow ? WROWB : kSlotRow);
-        return sub * KR1 + (krow ? row : (((pos >> 4) ^ ring_swizzle<false, kSlotRow, DT>(row)) * 16 + (pos & 15)) / ESZ);
+        const bool krow = KN && load_is_w(q);
+        const int b = lds_at(q) + lane * 16, row = b / (krow ? WROWB : kSlotRow), pos = b % (krow ? WROWB : kSlotRow);
+        return load_part(q) * KR1 + (krow ? row : ((pos >> 4) ^ ring_swizzle<false, kSlotRow, DT>(row)) * 16 / ESZ);
     };
 #pragma unroll
     for (int q = 0; q < L; ++q) {
-        const int q1 = q % L1, sub = q / L1;
-        const bool is_w = q1 >= LA, krow = KN && is_w;
-        const int b = lds_at(q1) + lane * VEC, row = b / (krow ? WROWB : kSlotRow), pos = b % (krow ? WROWB : kSlotRow);
+        const int sub = load_part(q);
+        const bool is_w = load_is_w(q), krow = KN && is_w;
+        const int b = lds_at(q) + lane * 16, row = b / (krow ? WROWB : kSlotRow), pos = b % (krow ? WROWB : kSlotRow);
         const int sw = krow ? ring_swizzle<true, WROWB, DT>(row) : ring_swizzle<false, kSlotRow, DT>(row);
-        const uint32_t col = (uint32_t)(((pos >> 4) ^ sw) * 16 + (pos & 15));
+        const uint32_t col = (uint32_t)(((pos >> 4) ^ sw) * 16);
         const bool ok = is_w ? (KN || row < rows_w) : row < rows_a;
         const uint32_t at = krow ? (uint32_t)(sub * KR1 + row) * ld_w + col
                                  : (uint32_t)row * (is_w ? ld_w : ld_a) + (uint32_t)(sub * kSlotRow) + col;
@@ -214,9 +227,8 @@ __global__ __launch_bounds__(64 * WM * WN * KS) void gemm_ring_kernel(const Ring
     // Past the end of the walk the range is empty and the scalar offset zero (the check takes it off the size):
     // no memory access, and the counter's arithmetic holds.
     auto issue = [&](int q) {
-        const int q1 = q % L1;
-        const bool is_w = q1 >= LA;
-        const uint32_t dst = lds_base + (uint32_t)(f_slot * kSlot + (q / L1) * kPart + (is_w ? BM * kSlotRow : 0) + lds_at(q1));
+        const bool is_w = load_is_w(q);
+        const uint32_t dst = lds_base + (uint32_t)(f_slot * kSlot + (q * NW + wave) * 1024);
         i32x4 rs = is_w ? rsrc_w : rsrc_a;
         rs[2] = f_left > 0 ? rs[2] : 0;
         uint32_t vo = voff[q];
@@ -225,12 +237,8 @@ __global__ __launch_bounds__(64 * WM * WN * KS) void gemm_ring_kernel(const Ring
         const int sdst = __builtin_amdgcn_readfirstlane((int)dst), sso = __builtin_amdgcn_readfirstlane((int)so);
 #pragma unroll
         for (int e = 0; e < 4; ++e) rs[e] = __builtin_amdgcn_readfirstlane(rs[e]);   // (kept in scalar registers)
-        if constexpr (VEC == 16)
-            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-                         :: "s"(sdst), "v"(vo), "s"(rs), "s"(sso) : "memory");
-        else
-            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, %3 offen lds"
-                         :: "s"(sdst), "v"(vo), "s"(rs), "s"(sso) : "memory");
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+                     :: "s"(sdst), "v"(vo), "s"(rs), "s"(sso) : "memory");
     };
 
     // fragments
@@ -281,6 +289,20 @@ __global__ __launch_bounds__(64 * WM * WN * KS) void gemm_ring_kernel(const Ring
         }
     };
 
+    // Rows that start on 4 bytes: the 16 bytes that hold the end of a row go on into the next row (the last row's are cut
+    // off by the resource, which is checked dword by dword).  Their part beyond k is cleared once the last slot of k has
+    // landed, in both operands, so that no product sees a value that is not the row's ([K, N]: W's rows beyond k are zeros).
+    auto clear_tail = [&](int at_slot) {
+        const int kb = krem % KR1 * ESZ;                     // bytes of the part that k ends in
+        if ((kb & 15) == 0) return;
+        for (int r = threadIdx.x; r < (KN ? BM : BM + BN); r += 64 * NW) {
+            char* const c = lds + at_slot * kSlot + krem / KR1 * kPart + r * kSlotRow +
+                            (((kb >> 4) ^ ring_swizzle<false, kSlotRow, DT>(r < BM ? r : r - BM)) << 4);
+            for (int e = kb & 15; e < 16; e += 4) *reinterpret_cast<uint32_t*>(c + e) = 0u;
+        }
+        __syncthreads();
+    };
+
     typename TR::acc_t acc[TN][TM];
 #pragma unroll
     for (int j = 0; j < TN; ++j)
@@ -302,6 +324,8 @@ __global__ __launch_bounds__(64 * WM * WN * KS) void gemm_ring_kernel(const Ring
     }
     wait_loads(std::integral_constant<int, (STAGES - 1) * L <= 63 ? (STAGES - 1) * L : 63>{});
     __syncthreads();
+    int c_st = kstart;                                       // position on the walk of the slot being read (VEC == 4)
+    if (VEC == 4 && c_st == ns - 1) clear_tail(0);
     read_units(0, 0, 0);
 
     // The loads that refill the slot released by a barrier (in the last unit of a slot's k) go out one per few
@@ -334,6 +358,10 @@ __global__ __launch_bounds__(64 * WM * WN * KS) void gemm_ring_kernel(const Ring
         wait_loads(std::integral_constant<int, (STAGES - 2) * L>{});
         __syncthreads();
         slot = slot + 1 == STAGES ? 0 : slot + 1;
+        if (VEC == 4) {
+            c_st = c_st + 1 == ns ? 0 : c_st + 1;
+            if (c_st == ns - 1) clear_tail(slot);            // (past the walk's end: the slot is not used any more)
+        }
         read_units(slot, 0, (UW + PAR) & 1);
         __builtin_amdgcn_sched_barrier(0);
         mfmas((UW - 1 + PAR) & 1, 0);
@@ -368,8 +396,9 @@ __global__ __launch_bounds__(64 * WM * WN * KS) void gemm_ring_kernel(const Ring
     wait_loads(std::integral_constant<int, 0>{});   // no LDS load may outlive the loop
 
     // Block (i, j), register group g: the lane holds row fr of the block's A rows and four consecutive output
-    // columns.
-    auto store4 = [&](int i, int j, int g, float c0, float c1, float c2, float c3) {
+    // columns.  WHOLE: every row starts on four values, and its columns come in whole groups of four.
+    auto store4 = [&](auto whole, int i, int j, int g, float c0, float c1, float c2, float c3) __attribute__((always_inline)) {
+        constexpr bool WHOLE = decltype(whole)::value;
         const int m = m0 + (wm * TM + i) * MB + fr;
         const int n = n0 + (wn * TN + j) * MB + (MB == 32 ? 8 * g : 0) + 4 * fc;
         if (m >= M || n >= N) return;
@@ -377,16 +406,19 @@ __global__ __launch_bounds__(64 * WM * WN * KS) void gemm_ring_kernel(const Ring
         const size_t at = (size_t)m * N + n;
         if constexpr (DT == ROV_F32) {
             float* out = (float*)p.C + at;
-            if ((N & 3) == 0) {
+            if (WHOLE) {
                 *reinterpret_cast<float4*>(out) = make_float4(c[0], c[1], c[2], c[3]);
+            } else if (n + 3 < N) {   // (a row starts on any 4 bytes)
+                f32x4 v = {c[0], c[1], c[2], c[3]};
+                *reinterpret_cast<f32x4_u*>(out) = v;
             } else {
 #pragma unroll
-                for (int e = 0; e < 4; ++e)
+                for (int e = 0; e < 3; ++e)
                     if (n + e < N) out[e] = c[e];
             }
         } else {
             uint16_t* out = (uint16_t*)p.C + at;
-            if ((N & 3) == 0) {
+            if (WHOLE) {
                 if (p.R != nullptr) {
                     const uint2 r = *reinterpret_cast<const uint2*>(p.R + at);
                     c[0] += __uint_as_float(r.x << 16);
@@ -395,6 +427,9 @@ __global__ __launch_bounds__(64 * WM * WN * KS) void gemm_ring_kernel(const Ring
                     c[3] += __uint_as_float(r.y & 0xFFFF0000u);
                 }
                 *reinterpret_cast<uint2*>(out) = make_uint2(pack_bf16x2(c[0], c[1]), pack_bf16x2(c[2], c[3]));
+            } else if ((N & 1) == 0 && n + 3 < N) {   // rows on 4 bytes
+                i32x2 v = {(int)pack_bf16x2(c[0], c[1]), (int)pack_bf16x2(c[2], c[3])};
+                *reinterpret_cast<i32x2_u*>(out) = v;
             } else {
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
@@ -403,44 +438,48 @@ __global__ __launch_bounds__(64 * WM * WN * KS) void gemm_ring_kernel(const Ring
         }
     };
     constexpr int GR = ACC / 4;                               // register groups per block
-    if constexpr (KS == 1) {
+    auto finish = [&](auto whole) __attribute__((always_inline)) {
+        if constexpr (KS == 1) {
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
+            for (int i = 0; i < TM; ++i)
 #pragma unroll
-            for (int j = 0; j < TN; ++j)
+                for (int j = 0; j < TN; ++j)
 #pragma unroll
-                for (int g = 0; g < GR; ++g)
-                    store4(i, j, g, acc[j][i][4 * g], acc[j][i][4 * g + 1], acc[j][i][4 * g + 2], acc[j][i][4 * g + 3]);
-    } else {
-        // Register group x of the tile wave is finished by its k part x % KS: the others hand it their sums through
-        // LDS, [tile wave][group][part] of 64 x 16 bytes, and the parts are added in order.
-        constexpr int NG = TM * TN * GR;
-        static_assert(WM * WN * NG * (KS - 1) * 1024 <= STAGES * kSlot, "partial sums fit the ring");
-        char* mine = lds + (size_t)(wm * WN + wn) * NG * (KS - 1) * 1024 + lane * 16;
-        __syncthreads();                                      // every wave has left the ring
+                    for (int g = 0; g < GR; ++g)
+                        store4(whole, i, j, g, acc[j][i][4 * g], acc[j][i][4 * g + 1], acc[j][i][4 * g + 2], acc[j][i][4 * g + 3]);
+        } else {
+            // Register group x of the tile wave is finished by its k part x % KS: the others hand it their sums through
+            // LDS, [tile wave][group][part] of 64 x 16 bytes, and the parts are added in order.
+            constexpr int NG = TM * TN * GR;
+            static_assert(WM * WN * NG * (KS - 1) * 1024 <= STAGES * kSlot, "partial sums fit the ring");
+            char* mine = lds + (size_t)(wm * WN + wn) * NG * (KS - 1) * 1024 + lane * 16;
+            __syncthreads();                                  // every wave has left the ring
 #pragma unroll
-        for (int x = 0; x < NG; ++x) {
-            const int j = x / GR / TM, i = x / GR % TM, g = x % GR, own = x % KS;
-            if (ks != own)
-                *reinterpret_cast<float4*>(mine + (x * (KS - 1) + (ks < own ? ks : ks - 1)) * 1024) =
-                    make_float4(acc[j][i][4 * g], acc[j][i][4 * g + 1], acc[j][i][4 * g + 2], acc[j][i][4 * g + 3]);
-        }
-        __syncthreads();
+            for (int x = 0; x < NG; ++x) {
+                const int j = x / GR / TM, i = x / GR % TM, g = x % GR, own = x % KS;
+                if (ks != own)
+                    *reinterpret_cast<float4*>(mine + (x * (KS - 1) + (ks < own ? ks : ks - 1)) * 1024) =
+                        make_float4(acc[j][i][4 * g], acc[j][i][4 * g + 1], acc[j][i][4 * g + 2], acc[j][i][4 * g + 3]);
+            }
+            __syncthreads();
 #pragma unroll
-        for (int x = 0; x < NG; ++x) {
-            const int j = x / GR / TM, i = x / GR % TM, g = x % GR, own = x % KS;
-            if (ks == own) {
-                float c[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+            for (int x = 0; x < NG; ++x) {
+                const int j = x / GR / TM, i = x / GR % TM, g = x % GR, own = x % KS;
+                if (ks == own) {
+                    float c[4] = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-                for (int k = 0; k < KS; ++k) {
-                    float4 v = make_float4(acc[j][i][4 * g], acc[j][i][4 * g + 1], acc[j][i][4 * g + 2], acc[j][i][4 * g + 3]);
-                    if (k != own) v = *reinterpret_cast<const float4*>(mine + (x * (KS - 1) + (k < own ? k : k - 1)) * 1024);
-                    c[0] += v.x; c[1] += v.y; c[2] += v.z; c[3] += v.w;
+                    for (int k = 0; k < KS; ++k) {
+                        float4 v = make_float4(acc[j][i][4 * g], acc[j][i][4 * g + 1], acc[j][i][4 * g + 2], acc[j][i][4 * g + 3]);
+                        if (k != own) v = *reinterpret_cast<const float4*>(mine + (x * (KS - 1) + (k < own ? k : k - 1)) * 1024);
+                        c[0] += v.x; c[1] += v.y; c[2] += v.z; c[3] += v.w;
+                    }
+                    store4(whole, i, j, g, c[0], c[1], c[2], c[3]);
                 }
-                store4(i, j, g, c[0], c[1], c[2], c[3]);
             }
         }
-    }
+    };
+    if ((N & 3) == 0) finish(std::true_type{});
+    else finish(std::false_type{});
 }
 
 template <int DT, int TM, int TN, int WM, int WN, int KS, int SUB, bool KN, int VEC, int STAGES>
@@ -464,24 +503,40 @@ int launch_ring(const void* A, const void* W, void* C, const void* R, int M, int
     return ROV_OK;
 }
 
+// The ring's depth by the product.  A long walk over k by one workgroup per compute unit wants every slot that LDS holds (64 x 32
+// tiles, 128 x 4096 x 14336: five slots 34.5 us, three 39.5).  Several rounds of tiles, or a walk that ends soon, want the
+// fewest, so that a second workgroup shares the compute unit and works while the first fills its ring or stores (three slots against five,
+// 64 x 32: 1.04 to 1.2 times as fast below K = 2048, 304 x 1024 x 2048 0.98; 1.2 to 1.5 with more tiles than compute units; [K, N] 128 x 64, three against six:
+// 1.02 to 1.15 and 1.15 to 1.28).
+template <int DT, int TM, int TN, int WM, int WN, int KS, int SUB, bool KN, int VEC, int DEEP, int FEW>
+int launch_ring_depth(const void* A, const void* W, void* C, const void* R, int M, int N, int K, float alpha, hipStream_t stream) {
+    constexpr int BM = Traits<DT>::MB * TM * WM, BN = Traits<DT>::MB * TN * WN;
+    const long long tiles = (long long)((M + BM - 1) / BM) * ((N + BN - 1) / BN);
+    if (tiles <= device_cu_count() && (long long)K * Traits<DT>::ESZ >= 32 * kSlotRow)
+        return launch_ring<DT, TM, TN, WM, WN, KS, SUB, KN, VEC, DEEP>(A, W, C, R, M, N, K, alpha, stream);
+    return launch_ring<DT, TM, TN, WM, WN, KS, SUB, KN, VEC, FEW>(A, W, C, R, M, N, K, alpha, stream);
+}
+
 // ------------------------------------------------------------------ choice of the tile
 // One row per instantiation: what it takes, its tile, and the time of one slot (128 bytes of k; 256 compute units
 // busy) in nanoseconds, measured with K = 4096 at 128 to 1024 workgroups; for bf16 and fp8 [N, K] weights, where the 256-row
 // kernels compete, adjusted so that none of 622 products of either type for which all forms were timed (16 to 4096 rows, 256 to
 // 14336 columns, K of 512 to 14336) runs more than 2 % slower than with the 256-row kernel: fp8 128 x 64 at 280 chose this
-// form where it was up to 28 % slower (700 x 8192 x 8192 68 us against 53, 300 x 14336 x 4096 36.5 against 30.5).  Register counts leave room
+// form where it was up to 28 % slower (700 x 8192 x 8192 68 us against 53, 300 x 14336 x 4096 36.5 against 30.5).  fp32 and rows on
+// 4 bytes, which have no other matrix-core kernel, are fitted to 200 to 300 products of each kind instead: the choice is under 1 % above
+// the best form on average.  Register counts leave room
 // for three 24-register RNG waves on every SIMD (a 256 x 128 tile with eight waves, 250 registers each, was up to
 // 8 % faster than the 256-row kernel at 2048 x 4096 x 4096, but its workgroups could not be placed beside an RNG
 // grid that arrived first).
 struct RingVariant {
-    int dtype, kn, vec, kparts;
+    int dtype, kn, vec, kparts;   // vec: bytes that the operands' rows start on
     int bm, bn;
     float slot_ns;
     int (*launch)(const void*, const void*, void*, const void*, int, int, int, float, hipStream_t);
 };
 const RingVariant kRing[] = {
     //                                                                TM TN WM WN KS SUB KN   VEC ST
-    {ROV_BF16, 0, 16, 4, 64, 32, 125.f, launch_ring<ROV_BF16, 4, 2, 1, 1, 4, 2, false, 16, 5>},
+    {ROV_BF16, 0, 16, 4, 64, 32, 125.f, launch_ring_depth<ROV_BF16, 4, 2, 1, 1, 4, 2, false, 16, 5, 3>},
     {ROV_BF16, 0, 16, 2, 64, 64, 165.f, launch_ring<ROV_BF16, 2, 2, 2, 2, 2, 2, false, 16, 4>},
     {ROV_BF16, 0, 16, 2, 128, 64, 275.f, launch_ring<ROV_BF16, 4, 2, 2, 2, 2, 2, false, 16, 3>},
     {ROV_BF16, 0, 16, 2, 128, 128, 490.f, launch_ring<ROV_BF16, 4, 4, 2, 2, 2, 1, false, 16, 4>},
@@ -489,25 +544,44 @@ const RingVariant kRing[] = {
     {ROV_BF16, 0, 16, 2, 128, 192, 700.f, launch_ring<ROV_BF16, 4, 6, 2, 2, 2, 1, false, 16, 4>},
     {ROV_BF16, 0, 16, 1, 64, 64, 190.f, launch_ring<ROV_BF16, 2, 2, 2, 2, 1, 1, false, 16, 4>},
     {ROV_BF16, 0, 16, 1, 128, 128, 520.f, launch_ring<ROV_BF16, 4, 4, 2, 2, 1, 1, false, 16, 4>},
-    {ROV_BF16, 0, 4, 2, 64, 64, 260.f, launch_ring<ROV_BF16, 2, 2, 2, 2, 2, 1, false, 4, 4>},
+    {ROV_BF16, 0, 4, 2, 64, 64, 355.f, launch_ring<ROV_BF16, 2, 2, 2, 2, 2, 1, false, 4, 4>},
     {ROV_BF16, 1, 16, 4, 64, 64, 190.f, launch_ring<ROV_BF16, 4, 2, 1, 2, 4, 2, true, 16, 4>},
-    {ROV_BF16, 1, 16, 2, 128, 64, 305.f, launch_ring<ROV_BF16, 4, 2, 2, 2, 2, 1, true, 16, 6>},
+    {ROV_BF16, 1, 16, 2, 128, 64, 305.f, launch_ring_depth<ROV_BF16, 4, 2, 2, 2, 2, 1, true, 16, 6, 3>},
     {ROV_BF16, 1, 16, 2, 128, 128, 510.f, launch_ring<ROV_BF16, 4, 4, 2, 2, 2, 1, true, 16, 4>},
     {ROV_BF16, 1, 16, 2, 192, 128, 700.f, launch_ring<ROV_BF16, 6, 4, 2, 2, 2, 1, true, 16, 4>},
-    {ROV_BF16, 1, 4, 2, 64, 64, 260.f, launch_ring<ROV_BF16, 2, 2, 2, 2, 2, 1, true, 4, 4>},
+    {ROV_BF16, 1, 4, 2, 64, 64, 355.f, launch_ring<ROV_BF16, 2, 2, 2, 2, 2, 1, true, 4, 4>},
     {ROV_FP8_E4M3, 0, 16, 1, 64, 64, 172.f, launch_ring<ROV_FP8_E4M3, 2, 2, 2, 2, 1, 1, false, 16, 4>},
     {ROV_FP8_E4M3, 0, 16, 1, 128, 64, 315.f, launch_ring<ROV_FP8_E4M3, 2, 2, 4, 2, 1, 1, false, 16, 6>},
     {ROV_FP8_E4M3, 0, 16, 1, 128, 128, 530.f, launch_ring<ROV_FP8_E4M3, 4, 2, 2, 4, 1, 1, false, 16, 4>},
-    {ROV_F32, 0, 16, 4, 32, 32, 142.f, launch_ring<ROV_F32, 1, 1, 1, 1, 4, 1, false, 16, 8>},
-    {ROV_F32, 0, 16, 2, 64, 64, 500.f, launch_ring<ROV_F32, 1, 1, 2, 2, 2, 1, false, 16, 4>},
-    {ROV_F32, 0, 4, 4, 32, 32, 200.f, launch_ring<ROV_F32, 1, 1, 1, 1, 4, 1, false, 4, 4>},
-    {ROV_F32, 0, 4, 2, 64, 64, 650.f, launch_ring<ROV_F32, 1, 1, 2, 2, 2, 1, false, 4, 4>},
-    {ROV_F32, 1, 16, 4, 32, 32, 150.f, launch_ring<ROV_F32, 1, 1, 1, 1, 4, 1, true, 16, 8>},
-    {ROV_F32, 1, 16, 2, 64, 64, 520.f, launch_ring<ROV_F32, 1, 1, 2, 2, 2, 1, true, 16, 4>},
-    {ROV_F32, 1, 4, 4, 32, 32, 200.f, launch_ring<ROV_F32, 1, 1, 1, 1, 4, 1, true, 4, 4>},
-    {ROV_F32, 1, 4, 2, 64, 64, 600.f, launch_ring<ROV_F32, 1, 1, 2, 2, 2, 1, true, 4, 4>},
+    {ROV_F32, 0, 16, 4, 32, 32, 153.f, launch_ring<ROV_F32, 1, 1, 1, 1, 4, 1, false, 16, 4>},
+    {ROV_F32, 0, 16, 2, 64, 64, 715.f, launch_ring<ROV_F32, 1, 1, 2, 2, 2, 1, false, 16, 3>},
+    {ROV_F32, 0, 4, 4, 32, 32, 131.f, launch_ring<ROV_F32, 1, 1, 1, 1, 4, 1, false, 4, 4>},
+    {ROV_F32, 0, 4, 2, 64, 64, 534.f, launch_ring<ROV_F32, 1, 1, 2, 2, 2, 1, false, 4, 4>},
+    {ROV_F32, 1, 16, 4, 32, 32, 144.f, launch_ring<ROV_F32, 1, 1, 1, 1, 4, 1, true, 16, 4>},
+    {ROV_F32, 1, 16, 2, 64, 64, 715.f, launch_ring<ROV_F32, 1, 1, 2, 2, 2, 1, true, 16, 3>},
+    {ROV_F32, 1, 4, 4, 32, 32, 180.f, launch_ring<ROV_F32, 1, 1, 1, 1, 4, 1, true, 4, 4>},
+    {ROV_F32, 1, 4, 2, 64, 64, 730.f, launch_ring<ROV_F32, 1, 1, 2, 2, 2, 1, true, 4, 4>},
 };
 constexpr int kRingVariants = (int)(sizeof(kRing) / sizeof(kRing[0]));
+
+// bf16 products whose rows start on 4 bytes only: with 16-byte loads there too (see VEC) they take the larger tiles as well, from
+// kRow4Slots slots of k on (shorter sums are the output's time: the 64 x 64 tiles above).  Slot times fitted, with those of the 4-byte rows
+// above, to 300 products of either layout (32 to 6000 rows, 32 to 8000 columns, K of 2 to 14336): the choice is 0.4 % (0.7 % [K, N]) above the best
+// form on average, 15 % at worst.  With 4-byte loads and 64 x 64 tiles alone the same products took 1.56 (1.48) times as long:
+// 770 x 4090 x 14336 [K, N] 274 -> 107 us, 1000 x 2002 x 2002 28 -> 19, 200 x 1000 x 4090 26 -> 11.
+constexpr int kRow4Slots = 8;
+const RingVariant kRingRow4[] = {
+    {ROV_BF16, 0, /* rows on */ 4, 4, 64, 32, 245.f, launch_ring_depth<ROV_BF16, 4, 2, 1, 1, 4, 2, false, 4, 5, 3>},
+    {ROV_BF16, 0, /* rows on */ 4, 2, 128, 64, 545.f, launch_ring<ROV_BF16, 4, 2, 2, 2, 2, 2, false, 4, 3>},
+    {ROV_BF16, 0, /* rows on */ 4, 2, 128, 128, 869.f, launch_ring<ROV_BF16, 4, 4, 2, 2, 2, 1, false, 4, 4>},
+    {ROV_BF16, 0, /* rows on */ 4, 2, 192, 128, 1130.f, launch_ring<ROV_BF16, 6, 4, 2, 2, 2, 1, false, 4, 4>},
+    {ROV_BF16, 1, /* rows on */ 4, 4, 64, 64, 340.f, launch_ring<ROV_BF16, 4, 2, 1, 2, 4, 2, true, 4, 4>},
+    {ROV_BF16, 1, /* rows on */ 4, 2, 128, 64, 575.f, launch_ring_depth<ROV_BF16, 4, 2, 2, 2, 2, 1, true, 4, 6, 3>},
+    {ROV_BF16, 1, /* rows on */ 4, 2, 128, 128, 750.f, launch_ring<ROV_BF16, 4, 4, 2, 2, 2, 1, true, 4, 4>},
+    {ROV_BF16, 1, /* rows on */ 4, 2, 192, 128, 1016.f, launch_ring<ROV_BF16, 6, 4, 2, 2, 2, 1, true, 4, 4>},
+};
+constexpr int kRingAll = kRingVariants + (int)(sizeof(kRingRow4) / sizeof(kRingRow4[0]));
+inline const RingVariant& ring_form(int v) { return v < kRingVariants ? kRing[v] : kRingRow4[v - kRingVariants]; }
 
 }  // namespace
 
@@ -537,8 +611,8 @@ int ring_variant(int M, int N, int K, int dtype, int transB, bool same_order, do
     const bool split = !same_order || K >= 2048;
     int best = -1;
     double best_ns = 0.0;
-    for (int v = 0; v < kRingVariants; ++v) {
-        const RingVariant& r = kRing[v];
+    for (int v = 0; v < (slots >= kRow4Slots ? kRingAll : kRingVariants); ++v) {
+        const RingVariant& r = ring_form(v);
         if (r.dtype != dtype || (r.kn != 0) != kn || r.vec != vec || (r.kparts > 1 && !split)) continue;
         const long long tiles = (long long)((M + r.bm - 1) / r.bm) * ((N + r.bn - 1) / r.bn);
         if (tiles > 0x7FFFFFFFLL) continue;
@@ -550,13 +624,13 @@ int ring_variant(int M, int N, int K, int dtype, int transB, bool same_order, do
 }
 
 void ring_variant_tile(int variant, int tile[4]) {
-    const RingVariant& r = kRing[variant];
+    const RingVariant& r = ring_form(variant);
     tile[0] = r.bm; tile[1] = r.bn; tile[2] = r.kparts; tile[3] = r.vec;
 }
 
 int launch_gemm_ring(int variant, const void* A, const void* W, void* C, const void* R, int M, int N, int K, float alpha,
                      hipStream_t stream) {
-    if (variant < 0 || variant >= kRingVariants) return ROV_ERR_INVALID;
-    return kRing[variant].launch(A, W, C, R, M, N, K, alpha, stream);
+    if (variant < 0 || variant >= kRingAll) return ROV_ERR_INVALID;
+    return ring_form(variant).launch(A, W, C, R, M, N, K, alpha, stream);
 }
 }  // namespace rov

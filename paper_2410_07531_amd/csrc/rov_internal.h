@@ -78,7 +78,7 @@ int launch_gemm_epilogue(const void* A, const void* Bm, void* C, const void* R, 
 // time; same_order: only tiles that add in the order of the 256-row kernels for short sums.  gemm_tiles_ns: the
 // estimate both families of tiles are compared by.
 int ring_variant(int M, int N, int K, int dtype, int transB, bool same_order, double* ns);
-void ring_variant_tile(int variant, int tile[4]);   // rows, columns, k parts, bytes of a lane's load
+void ring_variant_tile(int variant, int tile[4]);   // rows, columns, k parts, bytes that rows start on
 int launch_gemm_ring(int variant, const void* A, const void* W, void* C, const void* R, int M, int N, int K, float alpha,
                      hipStream_t stream);
 double gemm_tiles_ns(long long tiles, int slots, double slot_ns);
