@@ -209,7 +209,7 @@ int rov_set_gemm_tile_cols(int cols);
 /* The tile width the 256-row kernels use for an M x N output with the
  * current setting (host-side rule, no device work): 128..256, or
  * ROV_ERR_INVALID for M <= 0 or N <= 0.  Whether rov_gemm runs one of them for
- * a product depends on K, the data type and the layout too: rov_gemm_tile. */
+ * a product, and the width for K off a multiple of 64, depends on K, the data type and the layout too: rov_gemm_tile. */
 int rov_gemm_tile_cols(int M, int N);
 /* The kernel that rov_gemm runs for a product with the current setting (host-side rule,
  * no device work): ROV_GEMM_256_ROWS, ROV_GEMM_SMALL_TILES (short products, [K,N]

@@ -206,7 +206,7 @@ GEMM_256_ROWS, GEMM_SMALL_TILES, GEMM_ANY_SHAPE = 0, 1, 2
 
 
 def gemm_tile(M, N, K, dtype, transB=True):
-    """(kernel, rows, columns, parts of k, bytes of a lane's load) of the product rov_gemm would run."""
+    """(kernel, rows, columns, parts of k, bytes that rows start on) of the product rov_gemm would run."""
     t = (ctypes.c_int * 4)()
     kernel = load().rov_gemm_tile(M, N, K, dtype, int(bool(transB)), t)
     if kernel < 0:

@@ -33,6 +33,7 @@
 // the flop per byte; on random data under the power limit this shape sustains
 // 4.55 PFLOP/s in a register-only loop against 4.0 for 32x32x64).
 //
+// bf16 rows of any multiple of 16 bytes, and any number of columns, take the same kernel in its RAGGED form (gemm_tile).
 // Outputs too small for these tiles, fp32, [K,N] weights and other row lengths take
 // the kernels of gemm_ring.hip; very short sums (any_shape_sooner) and what those refuse (bf16 rows of an odd number of values,
 // fp8 rows off 16 bytes, fp8 [K,N] weights, operands beyond 32-bit offsets) takes a small
@@ -152,6 +153,8 @@ typedef __attribute__((address_space(3))) void* lptr_t;
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef int i32x8 __attribute__((ext_vector_type(8)));
+typedef int i32x2 __attribute__((ext_vector_type(2)));
+typedef i32x2 i32x2_u __attribute__((aligned(4)));   // stored to rows that start on 4 bytes
 
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
@@ -207,13 +210,16 @@ __device__ __forceinline__ void epilogue_combine(int epi, uint2 r, float& c0, fl
 // OUT8 (dual form only): the result is written as OCP e4m3 bytes, out_inv * silu(alpha * gate) *
 // (alpha2 * up) rounded to the nearest code, the SwiGLU output of the fp8 block quantised where it
 // is produced; C then points at bytes.
-template <int NJ, bool FP8, bool DUAL = false, bool OUT8 = false>
+// RAGGED: rows of any multiple of 16 bytes (k ends inside the last slot: its lanes beyond k are aimed outside the operands,
+// one select a load, and read zeros) and any number of output columns.
+template <int NJ, bool FP8, bool DUAL = false, bool OUT8 = false, bool RAGGED = false>
 __device__ __forceinline__ void gemm_tile(const char* __restrict__ A, const char* __restrict__ Wt,
                                           const char* __restrict__ Wt2, uint16_t* __restrict__ C,
                                           const uint16_t* __restrict__ R, int M, int N, int K, float alpha,
                                           int tiles_m, int tiles_n, int epi, char* lds, const int lane,
                                           const int wave, float alpha2 = 1.0f, float out_inv = 1.0f) {
     static_assert(!OUT8 || DUAL, "e4m3 output exists in the dual form only");
+    static_assert(!RAGGED || (!FP8 && !DUAL), "rows off 128 bytes: the plain bf16 product only");
     constexpr bool MIXED = DUAL && NJ % 4 != 0;   // gate and up rows in every weight block
     const int wm = wave >> 1, wn = wave & 1;
 
@@ -272,7 +278,7 @@ __device__ __forceinline__ void gemm_tile(const char* __restrict__ A, const char
     // Loads: wave w issues row blocks (8 rows) w, w+4, ... of each operand: 8 + NJ instructions
     // per slot.  Lane L fills physical chunk L%8 of row L/8, i.e. fetches logical chunk (L%8) ^ swz(row).
     const size_t ld_bytes = (size_t)K * ESZ;
-    const int ns = (int)(ld_bytes / kRow);            // slots to walk
+    const int ns = (int)((ld_bytes + (RAGGED ? kRow - 1 : 0)) / kRow);   // slots to walk
     const int rows_a = M - m0 < BM ? M - m0 : BM;
     const int rows_w = N - n0 < BNT ? N - n0 : BNT;
     uint32_t voff_a[8], voff_w[NJ];
@@ -310,6 +316,8 @@ __device__ __forceinline__ void gemm_tile(const char* __restrict__ A, const char
     const i32x4 rsrc_w = make_rsrc(MIXED && (wave & 1) ? Wt2 + (size_t)n0 * ld_bytes : w_panel, (size_t)rows_w * ld_bytes);
     const i32x4 rsrc_w2 = DUAL && !MIXED ? make_rsrc(Wt2 + (size_t)n0 * ld_bytes, (size_t)rows_w * ld_bytes) : rsrc_w;
     const uint32_t lds_base = (uint32_t)(uintptr_t)(lptr_t)lds;
+    // RAGGED: does the lane's chunk (the same in every load: row / 2 % 8 does not depend on j) lie beyond k in the last slot?
+    const bool beyond_k = RAGGED && ((lane & 7) ^ swz(wave * 8 + (lane >> 3))) * 16 >= (int)(ld_bytes - (size_t)(ns - 1) * kRow);
 
     // Load instruction q (0..7 = A row blocks, 8..7+NJ = W row blocks) of slot-step `step` into the
     // slot at LDS byte address `slot`.  Inline assembly, so that the compiler's wait-count pass does
@@ -323,15 +331,17 @@ __device__ __forceinline__ void gemm_tile(const char* __restrict__ A, const char
         const int koff = st * kRow;
         if (q < 8) {
             const uint32_t dst = slot + (uint32_t)((wave + 4 * q) * 1024);
+            const uint32_t vo = RAGGED && st == ns - 1 && beyond_k ? (uint32_t)rsrc_a[2] : voff_a[q];
             asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-                         :: "s"(dst), "v"(voff_a[q]), "s"(rsrc_a), "s"(koff) : "memory");
+                         :: "s"(dst), "v"(vo), "s"(rsrc_a), "s"(koff) : "memory");
         } else {
             const uint32_t dst = slot + (uint32_t)(BM * kRow + (wave + 4 * (q - 8)) * 1024);
             // dual: row block wave + 4*(q-8) holds up rows iff it lies in the second half of its wave's
             // 2*NJ row blocks; with NJ = 8 or 4 that does not depend on the wave
             const bool up = DUAL && !MIXED && (4 * (q - 8)) % (2 * NJ) >= NJ;
+            const uint32_t vo = RAGGED && st == ns - 1 && beyond_k ? (uint32_t)rsrc_w[2] : voff_w[q - 8];
             asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-                         :: "s"(dst), "v"(voff_w[q - 8]), "s"(up ? rsrc_w2 : rsrc_w), "s"(koff) : "memory");
+                         :: "s"(dst), "v"(vo), "s"(up ? rsrc_w2 : rsrc_w), "s"(koff) : "memory");
         }
     };
 
@@ -544,12 +554,12 @@ __device__ __forceinline__ void gemm_tile(const char* __restrict__ A, const char
             if (m < M && n < N) dst[j] = *reinterpret_cast<const uint2*>(R + (size_t)m * N + n);
         }
     };
-    if (R != nullptr) load_side(0, rv[0]);
+    if (!RAGGED && R != nullptr) load_side(0, rv[0]);
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
         const int m = m0 + wm * 128 + i * 16 + mrow;
         __builtin_amdgcn_sched_barrier(0);
-        if (R != nullptr && i + 1 < 8) load_side(i + 1, rv[(i + 1) & 1]);
+        if (!RAGGED && R != nullptr && i + 1 < 8) load_side(i + 1, rv[(i + 1) & 1]);
 #pragma unroll
         for (int j = 0; j < NJ; ++j) {
             const int n = n0 + wn * 16 * NJ + j * 16 + nsub;
@@ -558,17 +568,28 @@ __device__ __forceinline__ void gemm_tile(const char* __restrict__ A, const char
             float c2 = alpha * acc_read(acc[j][i][2]);
             float c3 = alpha * acc_read(acc[j][i][3]);
             if (m < M && n < N) {
-                if (R != nullptr) epilogue_combine(epi, rv[i & 1][j], c0, c1, c2, c3);
+                if (!RAGGED && R != nullptr) epilogue_combine(epi, rv[i & 1][j], c0, c1, c2, c3);
                 uint2 v;
                 v.x = pack_bf16x2(c0, c1);
                 v.y = pack_bf16x2(c2, c3);
-                *reinterpret_cast<uint2*>(C + (size_t)m * N + n) = v;
+                uint16_t* const out = C + (size_t)m * N + n;
+                if constexpr (!RAGGED) {
+                    *reinterpret_cast<uint2*>(out) = v;
+                } else if ((N & 1) == 0 && n + 3 < N) {   // rows on 4 bytes
+                    const i32x2 u = {(int)v.x, (int)v.y};
+                    *reinterpret_cast<i32x2_u*>(out) = u;
+                } else {
+                    const uint32_t h[4] = {v.x & 0xFFFFu, v.x >> 16, v.y & 0xFFFFu, v.y >> 16};
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (n + e < N) out[e] = (uint16_t)h[e];
+                }
             }
         }
     }
 }
 
-template <int NJ, bool FP8 = false>
+template <int NJ, bool FP8 = false, bool RAGGED = false>
 __global__ __launch_bounds__(256, 1) void gemm_tn_kernel(const char* __restrict__ A,
                                                          const char* __restrict__ Wt,
                                                          uint16_t* __restrict__ C,
@@ -578,7 +599,7 @@ __global__ __launch_bounds__(256, 1) void gemm_tn_kernel(const char* __restrict_
     // Co-resident RNG waves only need the VALU issue slots this kernel leaves idle; raise this
     // wave's issue priority so that they never delay its MFMA / LDS instruction stream.
     __builtin_amdgcn_s_setprio(3);
-    gemm_tile<NJ, FP8>(A, Wt, nullptr, C, R, M, N, K, alpha, tiles_m, tiles_n, epi, lds, threadIdx.x & 63,
+    gemm_tile<NJ, FP8, false, false, RAGGED>(A, Wt, nullptr, C, R, M, N, K, alpha, tiles_m, tiles_n, epi, lds, threadIdx.x & 63,
                        __builtin_amdgcn_readfirstlane(threadIdx.x >> 6));
 }
 
@@ -827,14 +848,15 @@ int launch_gemm_rng(const void* A, const void* Bm, void* C, int M, int N, int K,
 
 // Tile width (output columns, 32*nj) for an M x N product.  The workgroups run in rounds of one per
 // compute unit; a tile costs about nj + 1 units (its A panel does not shrink with it), so the width
-// with the smallest rounds x (nj + 1) is taken, the widest on ties.
-int best_tile_cols(int M, int N) {
+// with the smallest rounds x (nj + 1) is taken, the widest on ties.  Rows off 128 bytes (K % 64 != 0) cost a second line a load, and the
+// A panel counts more: nj + 3 (6935 x 8514 x 5960 640 us with 192 columns, 563 with 256).
+int best_tile_cols(int M, int N, int fixed = 1) {
     const long long tiles_m = (M + BM - 1) / BM, ncu = device_cu_count();
     long long best = -1;
     int nj = 8;
     for (int c = 8; c >= 4; --c) {
         const long long t = tiles_m * ((N + 32 * c - 1) / (32 * c));
-        const long long cost = ((t + ncu - 1) / ncu) * (c + 1);
+        const long long cost = ((t + ncu - 1) / ncu) * (c + fixed);
         if (best < 0 || cost < best) { best = cost; nj = c; }
     }
     return 32 * nj;
@@ -855,6 +877,19 @@ bool any_shape_sooner(int M, int N, int K, int dtype, int vec) {
     return any_us < 1.05 * small_us;   // (the estimates scatter by 7 and 9 %)
 }
 
+// Products that the 256-row kernel takes in its form for rows off 128 bytes (RAGGED): bf16 [N, K] operands whose rows start on 16 bytes.
+bool ragged_rows(int M, int N, int K, int dtype, int transB) {
+    return dtype == ROV_BF16 && transB != 0 && K % 8 == 0 && (unsigned long long)BM * (unsigned long long)K * 2ull + 1024 <= 0xFFFFFFFFull &&
+           (long long)((M + BM - 1) / BM) * ((N + 127) / 128) <= 0x7FFFFFFFLL;
+}
+// Its time by the 256-row tiles' slot times, against the small tiles' estimate: over 220 products (64 to 9000 rows, 200 to 14336
+// columns, K of 130 to 14336) none was slower than with small tiles alone, and 60 up to a third faster: us 6935 x 8514 x 5960 817 -> 563,
+// 5398 x 6144 x 4088 306 -> 235, 7296 x 4090 x 4096 215 -> 188, 6798 x 14336 x 1000 285 -> 203.
+double ragged_rows_ns(int M, int N, int K, int cols) {
+    const long long tiles = (long long)((M + BM - 1) / BM) * ((N + cols - 1) / cols);
+    return gemm_tiles_ns(tiles, (int)(((size_t)K * 2 + kRowBytes - 1) / kRowBytes), 890.0 + 130.0 * (cols / 32 - 4));
+}
+
 // The kernel of a product: the tiles of gemm_ring.hip where the 256-row kernels do not apply, or leave so much of the
 // chip idle that the smaller tile is done sooner.  A width set by rov_set_gemm_tile_cols is a 256-row tile's.
 // ring: the epilogue is one that the small tiles have (none, or the residual).
@@ -864,15 +899,19 @@ struct GemmChoice {
 GemmChoice choose_gemm(int M, int N, int K, int dtype, int transB, bool ring) {
     const int esz = dtype == ROV_BF16 ? 2 : 1;
     const bool wide = dtype != ROV_F32 && transB != 0 && ((size_t)K * esz) % kRowBytes == 0 && (N % 4) == 0;
+    const bool ragged = !wide && ragged_rows(M, N, K, dtype, transB) && ring;
     const int forced = g_tile_cols.load();
-    const int cols = wide ? (forced != 0 ? forced : best_tile_cols(M, N)) : 0;
+    const int cols = wide || ragged ? (forced != 0 ? forced : best_tile_cols(M, N, K % 64 != 0 ? 3 : 1)) : 0;
+    if (ragged && forced != 0) return {ROV_GEMM_256_ROWS, -1, cols};
     if (ring && !(wide && forced != 0)) {
         double ring_ns = 0.0;
         const int v = ring_variant(M, N, K, dtype, transB, wide, &ring_ns);
         if (v >= 0 && !wide) {
             int tile[4];
             ring_variant_tile(v, tile);
-            return any_shape_sooner(M, N, K, dtype, tile[3]) ? GemmChoice{ROV_GEMM_ANY_SHAPE, -1, 0} : GemmChoice{ROV_GEMM_SMALL_TILES, v, 0};
+            if (any_shape_sooner(M, N, K, dtype, tile[3])) return {ROV_GEMM_ANY_SHAPE, -1, 0};
+            if (ragged && ragged_rows_ns(M, N, K, cols) < ring_ns) return {ROV_GEMM_256_ROWS, -1, cols};
+            return {ROV_GEMM_SMALL_TILES, v, 0};
         }
         if (v >= 0) {
             // one slot (128 bytes of k) of a 256 x 32*nj tile, measured like the times in gemm_ring.hip
@@ -942,11 +981,13 @@ int launch_gemm_epilogue(const void* A, const void* Bm, void* C, const void* R, 
         const long long T = (long long)tiles_m * tiles_n;
         if (T > 0x7FFFFFFFLL) return ROV_ERR_UNSUPPORTED;
         typedef void (*kern_t)(const char*, const char*, uint16_t*, const uint16_t*, int, int, int, float, int, int, int);
-        static const kern_t kerns[10] = {gemm_tn_kernel<4>,       gemm_tn_kernel<5>,       gemm_tn_kernel<6>,
+        static const kern_t kerns[15] = {gemm_tn_kernel<4>,       gemm_tn_kernel<5>,       gemm_tn_kernel<6>,
                                          gemm_tn_kernel<7>,       gemm_tn_kernel<8>,       gemm_tn_kernel<4, true>,
                                          gemm_tn_kernel<5, true>, gemm_tn_kernel<6, true>, gemm_tn_kernel<7, true>,
-                                         gemm_tn_kernel<8, true>};
-        const int ki = nj - 4 + (esz == 2 ? 0 : 5);
+                                         gemm_tn_kernel<8, true>, gemm_tn_kernel<4, false, true>, gemm_tn_kernel<5, false, true>,
+                                         gemm_tn_kernel<6, false, true>, gemm_tn_kernel<7, false, true>, gemm_tn_kernel<8, false, true>};
+        const bool whole = ((size_t)K * esz) % kRowBytes == 0 && (N % 4) == 0;
+        const int ki = nj - 4 + (esz != 2 ? 5 : whole ? 0 : 10);
         const kern_t kern = kerns[ki];
         {
             const int rc = set_max_dynamic_lds((const void*)kern, kLdsBytes);
