@@ -96,6 +96,18 @@ __device__ __forceinline__ float half_wave_sum(float v) {
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
+// The same over the four lanes l, l ^ 16, l ^ 32, l ^ 48.
+__device__ __forceinline__ float quarter_wave_max(float v) {
+    const uint32_t u = __float_as_uint(v);
+    const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+    return half_wave_max(fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1])));
+}
+__device__ __forceinline__ float quarter_wave_sum(float v) {
+    const uint32_t u = __float_as_uint(v);
+    const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+    return half_wave_sum(__uint_as_float(r[0]) + __uint_as_float(r[1]));
+}
+
 // BKV: keys per LDS tile
 template <int D, int BKV>
 struct Tile {
@@ -881,6 +893,238 @@ __global__ __launch_bounds__(NW * 64) void attn_f32_kernel(const AttnParams p) {
     }
 }
 
+// The same on 16 x 16 x 4 instructions, for problems whose 32-query tiles leave the chip idle: a workgroup owns 16 query rows, a wave
+// takes every NW-th block of 16 keys, so there are twice as many workgroups and a block's chain of load, product, softmax, product is
+// a quarter as long.  Lane l holds query l % 16 and keys 4 * (l / 16) + e of a block: the score registers are the second product's
+// operand as they stand here too.  The keep word of register e is word 4 * (2 * (block % 2) + (l / 16) / 2) + e of the 32 x 32 tile, its
+// bit 32 * (l / 16 % 2) + query % 32: read as the lane's half word (stored mask) or drawn by the lane (same call, same field).
+// Each K and V byte is read by twice as many workgroups: see attn_f32_q16 for where that begins to cost more.
+// us, 32-query tiles -> this: 128 tokens x 2 heads x 64 features (stored mask) 8.1 -> 6.9; 400 x 2 x 128 27.2 -> 17.7; 2 x 359 x 8 x 64 causal,
+// bits drawn here, 16.1 -> 11.7.
+template <int DP, int NW, int MODE, int BITS>
+__global__ __launch_bounds__(NW * 64) void attn_f32_q16_kernel(const AttnParams p) {
+    constexpr int KC = DP / 16;    // chunks of 16 features: the k range of four MFMAs, and the output's feature blocks
+    extern __shared__ __attribute__((aligned(1024))) char lds[];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int ql = lane & 15, g = lane >> 4;
+    const int S = p.S, d = p.d;
+    int qblk, bh;   // all query tiles of a (batch, head) on one XCD, heaviest first when causal
+    {
+        const int pid = blockIdx.x, G = p.B * p.H;
+        if ((G & 7) == 0) {
+            const int xcd = pid & 7, j = pid >> 3, gpx = G >> 3;
+            qblk = j / gpx;
+            bh = (j % gpx) * 8 + xcd;
+        } else {
+            qblk = pid / G;
+            bh = pid % G;
+        }
+        if (p.causal) qblk = p.nq - 1 - qblk;
+    }
+    const int b = bh / p.H, h = bh % p.H;
+    const int hk = h / (p.H / p.Hkv);
+    const int q0 = p.q_begin + qblk * 16, qrow = q0 + ql;
+    const float* Qp = (const float*)p.Q + b * p.sq[0] + h * p.sq[2] + (int64_t)min(qrow, p.q_end - 1) * p.sq[1];
+    // (resources and offsets as in attn_f32_kernel)
+    const uint32_t krow = (uint32_t)p.sk[1] * 4u, vrow = (uint32_t)p.sv[1] * 4u;
+    const __amdgpu_buffer_rsrc_t kres = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<float*>((const float*)p.K + b * p.sk[0] + hk * p.sk[2]), 0, (int)((uint32_t)(S - 1) * krow + (uint32_t)d * 4u), 0x00020000);
+    const __amdgpu_buffer_rsrc_t vres = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<float*>((const float*)p.V + b * p.sv[0] + hk * p.sv[2]), 0, (int)((uint32_t)(S - 1) * vrow + (uint32_t)d * 4u), 0x00020000);
+
+    // features 16c + 4g .. +3 of the lane's row; chunks at or beyond d are zeros (an offset outside the resource)
+    f32x4 qf[KC], kf[KC];
+#pragma unroll
+    for (int c = 0; c < KC; ++c)
+        qf[c] = 16 * c + 4 * g < d ? *reinterpret_cast<const f32x4*>(Qp + 16 * c + 4 * g) : f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    const uint32_t koff = (uint32_t)ql * krow + (uint32_t)g * 16u;
+    auto load_k = [&](int kv0) {
+#pragma unroll
+        for (int c = 0; c < KC; ++c)
+            kf[c] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(
+                kres, 16 * c + 4 * g < d ? koff + 64u * c : 0x80000000u, (uint32_t)kv0 * krow, 0));
+    };
+    // V: register (t, e) is the lane's feature 16t + l % 16 of key kv0 + 4g + e.  Features beyond d repeat the last one (their outputs
+    // are not stored); keys beyond S are the last key's values, under probabilities of zero.
+    float vf[KC][4];
+    uint32_t voff[KC];
+#pragma unroll
+    for (int t = 0; t < KC; ++t) voff[t] = (uint32_t)min(16 * t + ql, d - 1) * 4u;
+    auto load_v = [&](int kv0) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const uint32_t row = (uint32_t)min(kv0 + 4 * g + e, S - 1) * vrow;
+#pragma unroll
+            for (int t = 0; t < KC; ++t) vf[t][e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(vres, voff[t] + row, 0, 0));
+        }
+    };
+
+    const uint32_t Tt = (uint32_t)p.W;
+    const uint32_t qt = (uint32_t)q0 >> 5;
+    const uint64_t wtile = (((uint64_t)bh * Tt + qt) * Tt) * 16u;   // words of tile (qt, 0) in the whole mask
+    const uint64_t* mtile = p.mask + (((uint64_t)bh * (uint32_t)p.mask_nqt + (qt - (uint32_t)p.mask_qt0)) * Tt) * 16u;
+    const uint32_t qbit = (uint32_t)qrow & 31u, bit = 32u * (uint32_t)(g & 1) + qbit;
+
+    f32x4 o[KC];
+#pragma unroll
+    for (int t = 0; t < KC; ++t) o[t] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    float m_run = -INFINITY, l_run = 0.0f;
+    const int kv_end = p.causal ? min(S, q0 + 16) : S;
+    const int nkb = (kv_end + 15) / 16;
+    uint32_t mw[4];
+    auto load_mask = [&](int kb) {
+        const uint32_t* w = reinterpret_cast<const uint32_t*>(mtile + (uint64_t)(kb >> 1) * 16u + 4u * (uint32_t)(2 * (kb & 1) + (g >> 1))) + (g & 1);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) mw[e] = w[2 * e];
+    };
+    if (wave < nkb) {
+        load_k(16 * wave);
+        if (MODE == MODE_MASK) load_mask(wave);
+        load_v(16 * wave);
+    }
+#pragma unroll 1
+    for (int kb = wave; kb < nkb; kb += NW) {
+        const int kv0 = 16 * kb;
+        const bool more = kb + NW < nkb;
+        f32x4 s = {0.0f, 0.0f, 0.0f, 0.0f}, s2 = s;   // (two chains: an instruction's result takes longer than its issue)
+#pragma unroll
+        for (int c = 0; c < KC; ++c) {
+#pragma unroll
+            for (int e = 0; e < 4; e += 2) {
+                s = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[c][e], qf[c][e], s, 0, 0, 0);
+                s2 = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[c][e + 1], qf[c][e + 1], s2, 0, 0, 0);
+            }
+        }
+        if (more) load_k(kv0 + 16 * NW);
+        s += s2;
+        const bool edge = kv0 + 16 > S || (p.causal && kv0 + 15 > q0);   // some score is not admissible
+        if (edge) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int key = kv0 + 4 * g + e;
+                s[e] = key < S && (!p.causal || key <= qrow) ? s[e] : -INFINITY;
+            }
+        }
+        float mx = fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3]));
+        mx = quarter_wave_max(mx) * p.scale_log2;
+        const float m_new = fmaxf(m_run, mx);
+        const float m_safe = m_new == -INFINITY ? 0.0f : m_new;
+        const float alpha = fast_exp2(m_run - m_safe);
+        m_run = m_new;
+        float sum = 0.0f;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            s[e] = fast_exp2(__builtin_fmaf(s[e], p.scale_log2, -m_safe));
+            sum += s[e];   // the normaliser counts dropped entries too
+        }
+        if (MODE == MODE_MASK) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) s[e] = (mw[e] >> qbit) & 1u ? s[e] : 0.0f;
+            if (more) load_mask(kb + NW);
+        }
+        if (MODE == MODE_FUSED) {
+            constexpr int NF = 32 / BITS, E = 4 * NF;   // fields per output word, mask words per call (see attn_bf16_kernel)
+            const uint32_t word = 4u * (uint32_t)(2 * (kb & 1) + (g >> 1));   // of register 0 in its 32 x 32 tile
+            const uint64_t w0 = wtile + (uint64_t)(kb >> 1) * 16u;
+            const uint64_t n = p.offset + 64u * (w0 / (uint32_t)E + word / (uint32_t)E) + bit;
+            uint32_t x[4];
+            if (p.rounds == 10) philox4x32<10>((uint32_t)n, (uint32_t)(n >> 32), 0u, 0u, p.k0, p.k1, x);
+            else philox4x32_dyn(p.rounds, (uint32_t)n, (uint32_t)(n >> 32), 0u, 0u, p.k0, p.k1, x);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                bool keep;
+                if (BITS == 32) keep = x[e] <= p.t_minus_1;
+                else keep = ((x[e] >> ((uint32_t)BITS * ((word / 4u) % (uint32_t)NF))) & ((1u << (BITS & 31)) - 1u)) < p.tb;
+                s[e] = keep ? s[e] : 0.0f;
+            }
+        }
+        l_run = l_run * alpha + sum;
+#pragma unroll
+        for (int t = 0; t < KC; ++t) o[t] *= alpha;
+        // (non-finite values under inadmissible keys: see attn_f32_kernel)
+        bool finite = true;
+        if (edge) {
+#pragma unroll
+            for (int t = 0; t < KC; ++t)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) finite = finite && fabsf(vf[t][e]) < INFINITY;
+            finite = __builtin_amdgcn_ballot_w64(!finite) == 0ull;
+        }
+        if (finite) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int t = 0; t < KC; ++t) o[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[t][e], s[e], o[t], 0, 0, 0);
+        } else {
+#pragma unroll 1
+            for (int k = 0; k < 16; ++k) {
+                const int key = kv0 + k;
+                f32x4 one[KC];
+#pragma unroll
+                for (int t = 0; t < KC; ++t) one[t] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const bool here = 4 * g + e == k;
+                    const float pe = here ? s[e] : 0.0f;
+#pragma unroll
+                    for (int t = 0; t < KC; ++t) one[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(here ? vf[t][e] : 0.0f, pe, one[t], 0, 0, 0);
+                }
+                const bool adm = key < S && (!p.causal || key <= qrow);
+#pragma unroll
+                for (int t = 0; t < KC; ++t)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) o[t][e] += adm ? one[t][e] : 0.0f;
+            }
+        }
+        if (more) load_v(kv0 + 16 * NW);
+    }
+
+    // The waves' partial results meet in LDS, not used before: (maximum, sum) and output of each.  Feature block t is brought on
+    // the common maximum and added up, waves in order, by wave t % NW.
+    float2* ml = reinterpret_cast<float2*>(lds + KC * (NW - 1) * 1024);
+    {
+        const float l_all = quarter_wave_sum(l_run);
+        if (g == 0) ml[wave * 16 + ql] = make_float2(m_run, l_all);
+    }
+#pragma unroll
+    for (int t = 0; t < KC; ++t) {
+        const int own = t % NW;
+        if (wave != own)
+            *reinterpret_cast<f32x4*>(lds + ((t * (NW - 1) + (wave < own ? wave : wave - 1)) * 64 + lane) * 16) = o[t];
+    }
+    __syncthreads();
+    float m_all = -INFINITY, l = 0.0f, f[NW];
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+        f[w] = ml[w * 16 + ql].x;
+        m_all = fmaxf(m_all, f[w]);
+    }
+    const float m_ref = m_all == -INFINITY ? 0.0f : m_all;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+        f[w] = fast_exp2(f[w] - m_ref);
+        l += ml[w * 16 + ql].y * f[w];
+    }
+    // (a row whose scores are all -infinity has no softmax: NaN)
+    const float norm = m_all == -INFINITY ? __uint_as_float(0x7FC00000u) : l > 0.0f ? p.inv_keep / l : 0.0f;
+    float* orow = (float*)p.O + b * p.so[0] + h * p.so[2] + (int64_t)qrow * p.so[1];
+#pragma unroll
+    for (int t = 0; t < KC; ++t) {
+        const int own = t % NW, feat = 16 * t + 4 * g;
+        if (wave == own) {
+            f32x4 c = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+            for (int w = 0; w < NW; ++w) {
+                f32x4 v = o[t];
+                if (w != own) v = *reinterpret_cast<const f32x4*>(lds + ((t * (NW - 1) + (w < own ? w : w - 1)) * 64 + lane) * 16);
+                c += v * (norm * f[w]);
+            }
+            if (qrow < p.q_end && feat < d) *reinterpret_cast<f32x4*>(orow + feat) = c;
+        }
+    }
+}
+
 // ------------------------------------------------------------------ generic kernel
 // One wave per query row, keys in chunks of 256 with an online softmax; any dtype / head
 // dimension up to 256.  Correct for every shape; used for the head dimensions, strides and alignments that
@@ -1088,6 +1332,11 @@ int attn_f32_waves(int B, int H, int S, int d) {
     return d <= 64 ? 8 : 4;
 }
 
+// fp32: query tiles of 16 instead of 32 rows?  Where those of 32 are at most three quarters of the compute units (timed at 120 problems of 64 to 1100
+// tokens, 2 to 16 heads, 32 to 128 features: 1.2 to 1.5 times as fast up to 128 tiles, 1.0 to 1.4 at up to 192, 0.83 to 1.2 at 256,
+// 0.82 to 0.97 from 512 on).  Only what all launches over one problem share decides, so that row ranges and modes agree.
+bool attn_f32_q16(int B, int H, int S) { return ceil(S / 32.0) * B * H <= 0.75 * device_cu_count(); }
+
 template <int DP, int NW>
 int launch_f32(const AttnParams& prm, int mode, hipStream_t stream) {
     AttnParams prm2 = prm;
@@ -1106,6 +1355,24 @@ int launch_f32(const AttnParams& prm, int mode, hipStream_t stream) {
         if (rc != ROV_OK) return rc;
     }
     hipLaunchKernelGGL(kern, dim3((unsigned)nblocks), dim3(NW * 64), lds_bytes, stream, prm2);
+    ROV_LAUNCH_CHECK();
+    return ROV_OK;
+}
+
+template <int DP, int NW>
+int launch_f32_q16(const AttnParams& prm, int mode, hipStream_t stream) {
+    AttnParams prm2 = prm;
+    prm2.nq = (prm.q_end - prm.q_begin + 15) / 16;
+    const long long nblocks = (long long)prm2.nq * prm.H * prm.B;
+    if (nblocks > 0x7FFFFFFFLL) return ROV_ERR_UNSUPPORTED;
+    void (*kern)(const AttnParams) = mode == MODE_NONE   ? attn_f32_q16_kernel<DP, NW, MODE_NONE, 32>
+                                     : mode == MODE_MASK ? attn_f32_q16_kernel<DP, NW, MODE_MASK, 32>
+                                     : prm.bits == 32    ? attn_f32_q16_kernel<DP, NW, MODE_FUSED, 32>
+                                     : prm.bits == 16    ? attn_f32_q16_kernel<DP, NW, MODE_FUSED, 16>
+                                                         : attn_f32_q16_kernel<DP, NW, MODE_FUSED, 8>;
+    constexpr int kLds = DP / 16 * (NW - 1) * 1024 + NW * 128;
+    static_assert(kLds <= 64 * 1024, "no attribute is needed");
+    hipLaunchKernelGGL(kern, dim3((unsigned)nblocks), dim3(NW * 64), kLds, stream, prm2);
     ROV_LAUNCH_CHECK();
     return ROV_OK;
 }
@@ -1229,6 +1496,12 @@ int launch_attention_rows(const void* Q, const void* K, const void* V, void* O, 
         // K / V of one (batch, kv head) are addressed through a buffer resource: byte offsets below 2^31
         for (int t = 4; t <= 7; t += 3)
             ok = ok && strides[t] >= 0 && (uint64_t)(S + 31) * (uint64_t)strides[t] * 4u + 4u * (uint64_t)d < (1ull << 31);
+        if (ok && attn_f32_q16(B, H, S)) {
+            if (d <= 32) return launch_f32_q16<32, 8>(prm, mode, stream);
+            if (d <= 64) return launch_f32_q16<64, 8>(prm, mode, stream);
+            if (d <= 96) return launch_f32_q16<96, 4>(prm, mode, stream);
+            return launch_f32_q16<128, 4>(prm, mode, stream);
+        }
         if (ok && d <= 32) return launch_f32<32, 8>(prm, mode, stream);
         if (ok && d <= 64) return launch_f32<64, 8>(prm, mode, stream);
         if (ok && d <= 96) return launch_f32<96, 4>(prm, mode, stream);
