@@ -38,9 +38,9 @@ PEAK_FP8_TFLOPS = 5000.0        # dense fp8 MFMA (published)
 PEAK_INT32_LANE_OPS = 256 * 4 * 32 * 2.4e9 / 1e12      # 78.6 T lane-instructions/s
 # Philox4x32-10 call, counted two ways: algorithmic 32-bit results (20 wide multiplies x 2 halves,
 # 40 two-input xors, 4 compares) and VALU instructions the kernel issues per call (18 v_mad_u64_u32,
-# 15 v_bitop3, 4 v_xor, 4 v_cmp, 8 v_writelane, 1 v_add; SQ_INSTS_VALU reads 50.7 per wave-call)
+# 15 v_bitop3, 4 v_xor, 4 v_cmp, 4 v_mov_b64, 1 v_add; SQ_INSTS_VALU reads 46.5 per wave-call)
 INT32_RESULTS_PER_CALL = 84
-VALU_INSTS_PER_CALL = 50.7
+VALU_INSTS_PER_CALL = 46.5
 # Memory traffic per launch at this workload from rocprofv3 --pmc FETCH_SIZE and WRITE_SIZE (KiB per dispatch), as
 # bytes.  Calibration on a 1 GiB device copy in the same run: WRITE_SIZE reads 1048576 KiB (x1.00), FETCH_SIZE
 # 524311 KiB (x2.00: requests wider than 64 bytes are counted as 64).  The keep words reach attention through
@@ -55,11 +55,10 @@ TRAFFIC = {"attention_mask": (2 * 1114234 + 1049119 + 131077) * _KIB,     # K/V/
            "gemm_down": (2 * 1456557 + 131110) * _KIB,
            "gemm_qkv": (2 * 611749 + 196773) * _KIB,
            "gemm_o": (2 * 408145 + 131110) * _KIB}
-# VALU occupancy of the stand-alone mask kernel from rocprofv3 --pmc: SQ_ACTIVE_INST_VALU (1698234368, in units
-# of four cycles) x 4 / (4 SIMDs x SQ_BUSY_CU_CYCLES 1691193071): the share of SIMD cycles in which a VALU
-# instruction is in flight.  SQ_INSTS_VALU reads 1698103296 = 50.6 per wave-call, and GRBM_GUI_ACTIVE gives
-# 2.27 GHz, i.e. one wave-instruction per 4.05 cycles per SIMD.
-RNG_VALU_BUSY_COUNTER = 1698234368 / 1691193071
+# VALU occupancy of the stand-alone mask kernel from rocprofv3 --pmc: SQ_ACTIVE_INST_VALU (1561919488, in units
+# of four cycles) x 4 / (4 SIMDs x SQ_BUSY_CU_CYCLES 1579185055): the share of SIMD cycles in which a VALU
+# instruction is in flight.  SQ_INSTS_VALU reads 1561788416 = 46.5 per wave-call.
+RNG_VALU_BUSY_COUNTER = 1561919488 / 1579185055
 
 
 # ---------------------------------------------------------------------------------------------- timing helpers
@@ -163,7 +162,7 @@ def valu_probe_ceiling(torch, rov, sync):
         ns[name] = min(ts) * 1e6 / (wave_insts / n_simd)          # ns per wave-instruction per SIMD
     add = ns["add"]
     mad, xor3, cmpw = ns["mad64_plus_add"] - add, ns["xor3"], ns["cmp_writelane_plus_add"] - add
-    ns_per_wave_call = 18 * mad + 15 * xor3 + 5 * add + 4 * cmpw + 4 * add
+    ns_per_wave_call = 18 * mad + 15 * xor3 + 5 * add + 4 * cmpw   # (a one-lane move priced as a lane write)
     gcalls = 64.0 * n_simd / ns_per_wave_call                     # 64 calls per wave-call, per ns -> Gcalls/s
     return {"ns_per_wave_instruction_per_simd": {"mad_u64_u32": mad, "bitop3_xor3": xor3, "add": add,
                                                  "cmp_plus_writelane": cmpw},
@@ -178,7 +177,7 @@ def rng_roofline(ncalls, t_ms, probe):
     return {"bound": "alu", "unit": "T int32 lane-instructions/s",
             "achieved": issued, "peak": PEAK_INT32_LANE_OPS, "frac": issued / PEAK_INT32_LANE_OPS,
             "peak_derivation": "peak = 256 CU x 4 SIMD x 32 lanes/clk x 2.4 GHz (the lane-instruction rate behind the "
-                               "published 157.3 TFLOP/s fp32); achieved = calls/s x 50.7 VALU instructions issued per call "
+                               "published 157.3 TFLOP/s fp32); achieved = calls/s x 46.5 VALU instructions issued per call "
                                "(SQ_INSTS_VALU per wave-call). Integer instructions cannot reach that peak on this chip "
                                "(measured: add 58 T/s, xor3 37 T/s, mad_u64_u32 28 T/s), so frac_of_probe_ceiling - the call "
                                "rate against what this kernel's own instruction mix costs at the probed issue rates - is "

@@ -9,8 +9,10 @@
 // call; the four compares of its output words are, as 64-lane ballots, exactly
 // the four mask words of the group (a mask word is the 64 lanes' bits for one
 // accumulator register of a 32 x 32 MFMA tile, see rov.h).
-// Each ballot is dropped into the lane that will store it (v_writelane), and
+// Each ballot is moved into the lane that will store it (park_words4), and
 // after 16 groups the wave issues one fully coalesced 512-byte store.
+// 46.5 vector instructions a call (SQ_INSTS_VALU; 50.6 while a ballot took two lane writes): 32 x 2048^2 bits 48.6 -> 46.1 us
+// = 730 Gcalls/s, launch included.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -37,12 +39,14 @@ std::atomic<int> g_rng_max_workgroups{0};
 std::atomic<int> g_rng_overlap_wgs_per_cu{0};   // 0 = by the register rule in mask_grid_cap
 
 // One chunk: 16 groups -> 64 mask words = 4 whole tiles of 32 x 32 elements; word 4*gi + r is
-// parked in lane 4*gi + r of (vhi:vlo).  RAGGED (S % 32 != 0): bits whose row or column lies
-// beyond S are cleared; (qt, kt) are the tile coordinates of the chunk's first tile.
+// parked in lane 4*gi + r of v.  RAGGED (S % 32 != 0): bits whose row or column lies
+// beyond S are cleared; (qt, kt) are the tile coordinates of the chunk's first tile.  (And the words are written lane by lane:
+// behind the clearing, park_words4's scalar chain shows where few waves are in flight, 8 x 639^2 bits 6.1 against 6.4 us.)
 template <int R, bool RAGGED, bool CARRY>
 __device__ __forceinline__ void mask_chunk(uint64_t base, uint32_t lane, uint32_t k0, uint32_t k1,
                                            uint32_t t_minus_1, uint32_t T, uint32_t S, uint32_t qt,
-                                           uint32_t kt, uint32_t& vlo, uint32_t& vhi) {
+                                           uint32_t kt, uint64_t& v) {
+    uint32_t vlo = 0u, vhi = 0u;
 #pragma unroll 2
     for (int gi = 0; gi < kGroupsPerChunk; ++gi) {
         uint64_t b[4];
@@ -54,22 +58,23 @@ __device__ __forceinline__ void mask_chunk(uint64_t base, uint32_t lane, uint32_
         }
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            uint32_t lo = (uint32_t)b[r], hi = (uint32_t)(b[r] >> 32);
             if (RAGGED) {
                 // word e = 4*(gi%4) + r: lanes 0-31 hold column 32*kt + 8*(gi%4) + r, lanes 32-63 that + 4
+                uint32_t lo = (uint32_t)b[r], hi = (uint32_t)(b[r] >> 32);
                 const uint32_t col = 32u * kt + 8u * ((uint32_t)gi & 3u) + (uint32_t)r;
                 lo = col < S ? (lo & row_mask) : 0u;
                 hi = col + 4u < S ? (hi & row_mask) : 0u;
+                vlo = write_lane(lo, 4u * (uint32_t)gi + (uint32_t)r, vlo);
+                vhi = write_lane(hi, 4u * (uint32_t)gi + (uint32_t)r, vhi);
             }
-            const uint32_t dst = 4u * (uint32_t)gi + (uint32_t)r;
-            vlo = write_lane(lo, dst, vlo);
-            vhi = write_lane(hi, dst, vhi);
         }
+        if (!RAGGED) park_words4(v, b, 4u * (uint32_t)gi);
         if (RAGGED && (gi & 3) == 3) {   // next tile
             kt = kt + 1u == T ? 0u : kt + 1u;
             if (kt == 0u) qt = qt + 1u == T ? 0u : qt + 1u;
         }
     }
+    if (RAGGED) v = ((uint64_t)vhi << 32) | vlo;
 }
 
 // lower_only: skip every chunk (4 consecutive tiles) none of whose tiles has key tile <= query
@@ -90,7 +95,7 @@ __global__ __launch_bounds__(kWavesPerBlock * 64) __attribute__((amdgpu_num_vgpr
     src.per = qper; src.batch = qbatch; src.lane = lane;
     for (bool more = src.first(chunk0 + (uint64_t)blockIdx.x * kWavesPerBlock + wave); more; more = src.next()) {
         const uint64_t chunk = src.cur;
-        uint32_t vlo = 0u, vhi = 0u;
+        uint64_t v = 0u;
         uint32_t qt = 0u, kt = 0u;   // tile coordinates of the chunk's first tile
         if (RAGGED || lower_only) {
             tile_coords(chunk * 4u, T, Tm, qt, kt);
@@ -102,12 +107,12 @@ __global__ __launch_bounds__(kWavesPerBlock * 64) __attribute__((amdgpu_num_vgpr
         // first call number of the chunk; its 1024 calls are base .. base + 1023
         const uint64_t base = offset + 64u * kGroupsPerChunk * chunk;
         if ((uint32_t)base <= 0xFFFFFFFFu - (64u * kGroupsPerChunk - 1u)) {
-            mask_chunk<R, RAGGED, false>(base, lane, k0, k1, t_minus_1, T, S, qt, kt, vlo, vhi);
+            mask_chunk<R, RAGGED, false>(base, lane, k0, k1, t_minus_1, T, S, qt, kt, v);
         } else {
-            mask_chunk<R, RAGGED, true>(base, lane, k0, k1, t_minus_1, T, S, qt, kt, vlo, vhi);
+            mask_chunk<R, RAGGED, true>(base, lane, k0, k1, t_minus_1, T, S, qt, kt, v);
         }
         const uint64_t widx = chunk * 64u + lane;
-        if (widx < words) out[widx] = ((uint64_t)vhi << 32) | vlo;
+        if (widx < words) out[widx] = v;
     }
 }
 
@@ -138,27 +143,30 @@ __global__ __launch_bounds__(kWavesPerBlock * 64) void mask_rows_kernel(
         const uint64_t gw = seg * seg_stride + seg_first + lc * 64u;   // first global word (multiple of 16)
         uint32_t kt, qt;
         tile_coords(gw >> 4, T, Tm, qt, kt);
-        uint32_t vlo = 0u, vhi = 0u;
+        uint64_t v = 0u;
         const uint64_t base = offset + 16u * gw;   // 64 calls per 4 words
         if ((uint32_t)base <= 0xFFFFFFFFu - (64u * kGroupsPerChunk - 1u)) {
-            mask_chunk<R, RAGGED, false>(base, lane, k0, k1, t_minus_1, T, S, qt, kt, vlo, vhi);
+            mask_chunk<R, RAGGED, false>(base, lane, k0, k1, t_minus_1, T, S, qt, kt, v);
         } else {
-            mask_chunk<R, RAGGED, true>(base, lane, k0, k1, t_minus_1, T, S, qt, kt, vlo, vhi);
+            mask_chunk<R, RAGGED, true>(base, lane, k0, k1, t_minus_1, T, S, qt, kt, v);
         }
         const uint64_t lw = lc * 64u + lane;
-        if (lw < seg_words) out[seg * seg_words + lw] = ((uint64_t)vhi << 32) | vlo;
+        if (lw < seg_words) out[seg * seg_words + lw] = v;
     }
 }
 
 // Narrow-threshold chunk: BITS (8 or 16) random bits per element.  One Philox call per lane now
 // serves E = 4 * 32/BITS mask words: field s of output word r decides word E*gi + 4*s + r of the
 // chunk.  A chunk is still 64 words = 4 tiles; tile t of the chunk has coordinates (qts[t], kts[t]).
+// (Lane writes: with two or four times the words a call, park_words4's scalar chain shows where few waves are in flight,
+// 8 x 1170^2 elements at 16 bits 6.9 against 7.6 us.)
 template <int BITS, bool RAGGED, bool CARRY>
 __device__ __forceinline__ void mask_chunk_bits(uint64_t base, uint32_t lane, uint32_t k0, uint32_t k1,
                                                 uint32_t tb, uint32_t S, const uint32_t (&qts)[4],
-                                                const uint32_t (&kts)[4], uint32_t& vlo, uint32_t& vhi) {
+                                                const uint32_t (&kts)[4], uint64_t& v) {
     constexpr int NF = 32 / BITS;          // fields per output word
     constexpr int E = 4 * NF;              // mask words per group
+    uint32_t vlo = 0u, vhi = 0u;
 #pragma unroll
     for (int gi = 0; gi < 64 / E; ++gi) {
         const uint64_t b = base + 64u * (uint64_t)gi;
@@ -190,6 +198,7 @@ __device__ __forceinline__ void mask_chunk_bits(uint64_t base, uint32_t lane, ui
                 vhi = write_lane(hi, (uint32_t)dst, vhi);
             }
     }
+    v = ((uint64_t)vhi << 32) | vlo;
 }
 
 template <int BITS, bool RAGGED>
@@ -202,7 +211,7 @@ __global__ __launch_bounds__(kWavesPerBlock * 64) void mask_bits_kernel(
     const uint64_t stride = (uint64_t)gridDim.x * kWavesPerBlock;
     for (uint64_t chunk = (uint64_t)blockIdx.x * kWavesPerBlock + wave; chunk < nchunks;
          chunk += stride) {
-        uint32_t vlo = 0u, vhi = 0u;
+        uint64_t v = 0u;
         uint32_t qts[4] = {0u, 0u, 0u, 0u}, kts[4] = {0u, 0u, 0u, 0u};
         if (RAGGED) {
             uint32_t kt, qt;
@@ -217,12 +226,12 @@ __global__ __launch_bounds__(kWavesPerBlock * 64) void mask_bits_kernel(
         }
         const uint64_t base = offset + (uint64_t)kCallsPerChunk * chunk;
         if ((uint32_t)base <= 0xFFFFFFFFu - (kCallsPerChunk - 1u)) {
-            mask_chunk_bits<BITS, RAGGED, false>(base, lane, k0, k1, tb, S, qts, kts, vlo, vhi);
+            mask_chunk_bits<BITS, RAGGED, false>(base, lane, k0, k1, tb, S, qts, kts, v);
         } else {
-            mask_chunk_bits<BITS, RAGGED, true>(base, lane, k0, k1, tb, S, qts, kts, vlo, vhi);
+            mask_chunk_bits<BITS, RAGGED, true>(base, lane, k0, k1, tb, S, qts, kts, v);
         }
         const uint64_t widx = chunk * 64u + lane;
-        if (widx < words) out[widx] = ((uint64_t)vhi << 32) | vlo;
+        if (widx < words) out[widx] = v;
     }
 }
 

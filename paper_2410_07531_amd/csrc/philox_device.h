@@ -32,6 +32,25 @@ __device__ __forceinline__ uint32_t write_lane(uint32_t v, uint32_t dst, uint32_
     return rov_llvm_writelane_i32(v, dst, old);
 }
 
+// Puts four wave-uniform 64-bit words into lanes `first` .. `first` + 3 of v.  A move under an EXEC of that one lane takes one
+// vector instruction a word where v_writelane takes two; EXEC is set by the scalar unit, beside other waves' vector
+// instructions.  Every lane of the wave is active on entry (and again behind it).  The words come from vector compares: a
+// vector instruction may read a scalar register two wait states after another has written it (s_nop).
+__device__ __forceinline__ void park_words4(uint64_t& v, const uint64_t (&w)[4], uint32_t first) {
+    const uint64_t bit = 1ull << first;
+    asm volatile("s_nop 1\n\t"
+                 "s_mov_b64 exec, %5\n\t"
+                 "v_mov_b64 %0, %1\n\t"
+                 "s_lshl_b64 exec, %5, 1\n\t"
+                 "v_mov_b64 %0, %2\n\t"
+                 "s_lshl_b64 exec, %5, 2\n\t"
+                 "v_mov_b64 %0, %3\n\t"
+                 "s_lshl_b64 exec, %5, 3\n\t"
+                 "v_mov_b64 %0, %4\n\t"
+                 "s_mov_b64 exec, -1"
+                 : "+v"(v) : "s"(w[0]), "s"(w[1]), "s"(w[2]), "s"(w[3]), "s"(bit) : "scc");
+}
+
 // R rounds on counter (c0, c1, c2, c3) with key (k0, k1).
 template <int R>
 __device__ __forceinline__ void philox4x32(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3,

@@ -91,8 +91,9 @@ def philox_cycles_per_call(chip: Chip, rounds: int = 10, bits: int = 32) -> floa
     """VALU issue cycles one wave64 spends per Philox call, from the mask kernel's instruction mix:
     per round two 32x32->64 multiplies and two three-input xors (the first two rounds save two
     multiplies and use plain xors: the upper counter words are zero and one product is
-    wave-uniform); per output field one compare-to-ballot and two lane writes (both halves of the
-    64-bit ballot), plus a field extract when fields are narrower than a word."""
+    wave-uniform); per output field one compare-to-ballot and the ballot's way into the lane that stores
+    it, priced as two lane writes (the kernel's one 64-bit move under a one-lane EXEC costs about 5 %
+    of the call less than that), plus a field extract when fields are narrower than a word."""
     mads = 2 * rounds - 2
     xors = 2 * rounds - 5
     simple = 4 + 1                                     # plain xors of the first rounds, counter add
