@@ -187,8 +187,9 @@ __global__ __launch_bounds__(64 * WM * WN * KS) void gemm_ring_kernel(const Ring
     // Load q of this wave is load q * NW + wave of the slot: part by part, A's rows, then W's, 1 KiB of LDS each (a load whose
     // operand differs between the waves selects its resource).  voff: the lane's byte offset from the panel's start at
     // slot 0; lane_k: its position in the slot's k (the row for a [K, N] tile).
-    // Rows past the edge and, in the last slot, k >= K lie outside the resource and read as zeros.
-    uint32_t voff[L];
+    // Rows past the edge and, in the last slot, k >= K lie outside the resource and read as zeros (vend: the offset there.  Kept, not
+    // worked out where it is used: that had become a branch at each load, 0.45 us of a product of one slot).
+    uint32_t voff[L], vend[L];
     // (all waves' loads q in one part, or of one operand: known when compiled)
     auto load_part = [&](int q) { return q * NW / QP == (q * NW + NW - 1) / QP ? q * NW / QP : (q * NW + wave) / QP; };
     auto load_in_part = [&](int q) { return q * NW - load_part(q) * QP + wave; };
@@ -213,6 +214,7 @@ __global__ __launch_bounds__(64 * WM * WN * KS) void gemm_ring_kernel(const Ring
         const uint32_t at = krow ? (uint32_t)(sub * KR1 + row) * ld_w + col
                                  : (uint32_t)row * (is_w ? ld_w : ld_a) + (uint32_t)(sub * kSlotRow) + col;
         voff[q] = ok ? at : (is_w ? bytes_w : bytes_a);
+        vend[q] = lane_k(q) < krem ? voff[q] : (is_w ? bytes_w : bytes_a);
     }
     // The slot being filled: its place in the ring, its position on the cyclic walk over k, and how many slots
     // of the walk are left.
@@ -231,8 +233,7 @@ __global__ __launch_bounds__(64 * WM * WN * KS) void gemm_ring_kernel(const Ring
         const uint32_t dst = lds_base + (uint32_t)(f_slot * kSlot + (q * NW + wave) * 1024);
         i32x4 rs = is_w ? rsrc_w : rsrc_a;
         rs[2] = f_left > 0 ? rs[2] : 0;
-        uint32_t vo = voff[q];
-        if (ragged && f_st == ns - 1) vo = lane_k(q) < krem ? vo : (is_w ? bytes_w : bytes_a);
+        const uint32_t vo = ragged && f_st == ns - 1 ? vend[q] : voff[q];
         const uint32_t so = KN && is_w ? (uint32_t)f_st * (uint32_t)KR * ld_w : (uint32_t)f_st * (uint32_t)(SUB * kSlotRow);
         const int sdst = __builtin_amdgcn_readfirstlane((int)dst), sso = __builtin_amdgcn_readfirstlane((int)so);
 #pragma unroll
