@@ -187,8 +187,8 @@ __global__ __launch_bounds__(64 * WM * WN * KS) void gemm_ring_kernel(const Ring
     // Load q of this wave is load q * NW + wave of the slot: part by part, A's rows, then W's, 1 KiB of LDS each (a load whose
     // operand differs between the waves selects its resource).  voff: the lane's byte offset from the panel's start at
     // slot 0; lane_k: its position in the slot's k (the row for a [K, N] tile).
-    // Rows past the edge and, in the last slot, k >= K lie outside the resource and read as zeros (vend: the offset there.  Kept, not
-    // worked out where it is used: that had become a branch at each load, 0.45 us of a product of one slot).
+    // Rows past the edge and, in the last slot, k >= K lie outside the resource and read as zeros (vend: the offset there.  Kept for
+    // the first loads, not worked out at each behind a branch: 0.45 us of a product of one slot).
     uint32_t voff[L], vend[L];
     // (all waves' loads q in one part, or of one operand: known when compiled)
     auto load_part = [&](int q) { return q * NW / QP == (q * NW + NW - 1) / QP ? q * NW / QP : (q * NW + wave) / QP; };
@@ -228,12 +228,17 @@ __global__ __launch_bounds__(64 * WM * WN * KS) void gemm_ring_kernel(const Ring
     // the kernel places its vmcnt waits itself.  M0 is only set by compiled code right before its own uses.
     // Past the end of the walk the range is empty and the scalar offset zero (the check takes it off the size):
     // no memory access, and the counter's arithmetic holds.
-    auto issue = [&](int q) {
+    // In the loop of the fp32 and [K, N] forms the offset beyond k is worked out behind a branch: its edges keep the loads between the
+    // MFMAs where they were put (2764 x 392 x 4096 fp32 88.5 us, with a select 100; 1024 x 4096 x 4096 [K, N] 38.3, 38.8).
+    // The others are 0.5 to 2 % faster with the select.
+    auto issue = [&](int q, auto in_loop) __attribute__((always_inline)) {
         const bool is_w = load_is_w(q);
         const uint32_t dst = lds_base + (uint32_t)(f_slot * kSlot + (q * NW + wave) * 1024);
         i32x4 rs = is_w ? rsrc_w : rsrc_a;
         rs[2] = f_left > 0 ? rs[2] : 0;
-        const uint32_t vo = ragged && f_st == ns - 1 ? vend[q] : voff[q];
+        uint32_t vo = voff[q];
+        if (!decltype(in_loop)::value || (DT != ROV_F32 && !KN)) vo = ragged && f_st == ns - 1 ? vend[q] : vo;
+        else if (ragged && f_st == ns - 1) vo = lane_k(q) < krem ? vo : (is_w ? bytes_w : bytes_a);
         const uint32_t so = KN && is_w ? (uint32_t)f_st * (uint32_t)KR * ld_w : (uint32_t)f_st * (uint32_t)(SUB * kSlotRow);
         const int sdst = __builtin_amdgcn_readfirstlane((int)dst), sso = __builtin_amdgcn_readfirstlane((int)so);
 #pragma unroll
@@ -320,7 +325,7 @@ __global__ __launch_bounds__(64 * WM * WN * KS) void gemm_ring_kernel(const Ring
 #pragma unroll
     for (int s = 0; s < STAGES; ++s) {
 #pragma unroll
-        for (int q = 0; q < L; ++q) issue(q);
+        for (int q = 0; q < L; ++q) issue(q, std::false_type{});
         next_fill();
     }
     wait_loads(std::integral_constant<int, (STAGES - 1) * L <= 63 ? (STAGES - 1) * L : 63>{});
@@ -339,7 +344,7 @@ __global__ __launch_bounds__(64 * WM * WN * KS) void gemm_ring_kernel(const Ring
             if (pos0 >= 0) {
 #pragma unroll
                 for (int q = 0; q < L; ++q)
-                    if (q * UW * MU / L == pos0 + m) issue(q);
+                    if (q * UW * MU / L == pos0 + m) issue(q, std::true_type{});
             }
         }
     };
