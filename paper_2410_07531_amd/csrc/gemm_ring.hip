@@ -528,9 +528,9 @@ int launch_ring_depth(const void* A, const void* W, void* C, const void* R, int 
 // busy) in nanoseconds, measured with K = 4096 at 128 to 1024 workgroups; for bf16 and fp8 [N, K] weights, where the 256-row
 // kernels compete, adjusted so that none of 622 products of either type for which all forms were timed (16 to 4096 rows, 256 to
 // 14336 columns, K of 512 to 14336) runs more than 2 % slower than with the 256-row kernel: fp8 128 x 64 at 280 chose this
-// form where it was up to 28 % slower (700 x 8192 x 8192 68 us against 53, 300 x 14336 x 4096 36.5 against 30.5).  fp32 and rows on
-// 4 bytes, which have no other matrix-core kernel, are fitted to 200 to 300 products of each kind instead: the choice is under 1 % above
-// the best form on average.  Register counts leave room
+// form where it was up to 28 % slower (700 x 8192 x 8192 68 us against 53, 300 x 14336 x 4096 36.5 against 30.5).  Rows on
+// 4 bytes, which have no other matrix-core kernel, are fitted to 300 products of either layout instead (see kRingRow4), fp32 to 870 (see f32_tiles_ns).
+// Register counts leave room
 // for three 24-register RNG waves on every SIMD (a 256 x 128 tile with eight waves, 250 registers each, was up to
 // 8 % faster than the 256-row kernel at 2048 x 4096 x 4096, but its workgroups could not be placed beside an RNG
 // grid that arrived first).
@@ -559,14 +559,14 @@ const RingVariant kRing[] = {
     {ROV_FP8_E4M3, 0, 16, 1, 64, 64, 172.f, launch_ring<ROV_FP8_E4M3, 2, 2, 2, 2, 1, 1, false, 16, 4>},
     {ROV_FP8_E4M3, 0, 16, 1, 128, 64, 315.f, launch_ring<ROV_FP8_E4M3, 2, 2, 4, 2, 1, 1, false, 16, 6>},
     {ROV_FP8_E4M3, 0, 16, 1, 128, 128, 530.f, launch_ring<ROV_FP8_E4M3, 4, 2, 2, 4, 1, 1, false, 16, 4>},
-    {ROV_F32, 0, 16, 4, 32, 32, 153.f, launch_ring<ROV_F32, 1, 1, 1, 1, 4, 1, false, 16, 4>},
-    {ROV_F32, 0, 16, 2, 64, 64, 715.f, launch_ring<ROV_F32, 1, 1, 2, 2, 2, 1, false, 16, 3>},
-    {ROV_F32, 0, 4, 4, 32, 32, 131.f, launch_ring<ROV_F32, 1, 1, 1, 1, 4, 1, false, 4, 4>},
-    {ROV_F32, 0, 4, 2, 64, 64, 534.f, launch_ring<ROV_F32, 1, 1, 2, 2, 2, 1, false, 4, 4>},
-    {ROV_F32, 1, 16, 4, 32, 32, 144.f, launch_ring<ROV_F32, 1, 1, 1, 1, 4, 1, true, 16, 4>},
-    {ROV_F32, 1, 16, 2, 64, 64, 715.f, launch_ring<ROV_F32, 1, 1, 2, 2, 2, 1, true, 16, 3>},
-    {ROV_F32, 1, 4, 4, 32, 32, 180.f, launch_ring<ROV_F32, 1, 1, 1, 1, 4, 1, true, 4, 4>},
-    {ROV_F32, 1, 4, 2, 64, 64, 730.f, launch_ring<ROV_F32, 1, 1, 2, 2, 2, 1, true, 4, 4>},
+    {ROV_F32, 0, 16, 4, 32, 32, 140.f, launch_ring<ROV_F32, 1, 1, 1, 1, 4, 1, false, 16, 4>},
+    {ROV_F32, 0, 16, 2, 64, 64, 510.f, launch_ring<ROV_F32, 1, 1, 2, 2, 2, 1, false, 16, 3>},
+    {ROV_F32, 0, 4, 4, 32, 32, 148.f, launch_ring<ROV_F32, 1, 1, 1, 1, 4, 1, false, 4, 4>},
+    {ROV_F32, 0, 4, 2, 64, 64, 510.f, launch_ring<ROV_F32, 1, 1, 2, 2, 2, 1, false, 4, 4>},
+    {ROV_F32, 1, 16, 4, 32, 32, 142.f, launch_ring<ROV_F32, 1, 1, 1, 1, 4, 1, true, 16, 4>},
+    {ROV_F32, 1, 16, 2, 64, 64, 510.f, launch_ring<ROV_F32, 1, 1, 2, 2, 2, 1, true, 16, 3>},
+    {ROV_F32, 1, 4, 4, 32, 32, 154.f, launch_ring<ROV_F32, 1, 1, 1, 1, 4, 1, true, 4, 4>},
+    {ROV_F32, 1, 4, 2, 64, 64, 510.f, launch_ring<ROV_F32, 1, 1, 2, 2, 2, 1, true, 4, 4>},
 };
 constexpr int kRingVariants = (int)(sizeof(kRing) / sizeof(kRing[0]));
 
@@ -600,6 +600,16 @@ double gemm_tiles_ns(long long tiles, int slots, double slot_ns) {
     return (double)rounds * ((double)slots * slot_ns * (0.73 + 0.27 * use) + 1500.0);
 }
 
+// fp32: several workgroups share a compute unit, so that a tile's fill and output lie beside another's walk, and idle units leave the
+// others no clock (the matrix rate binds, not power): rounds of one tile per compute unit each take the walk and a little.  Measured a slot
+// and round, ns: 32 x 32 165 to 180 in a lone round, 140 to 150 from two on; 64 x 64 505 to 530, 500.  Of 870 products (16 to 4096 rows, columns and k, half of
+// them 300 and more) the choice is 0.02 % above the sooner form on average, 4 % at worst.  With the formula above and 64 x 64 at 715 ns, large products took
+// 32 x 32 tiles: 1497 x 4040 x 1796 [K, N] 210 us against 177, 2830 x 3188 x 1956 332 against 291.
+double f32_tiles_ns(long long tiles, int slots, double slot_ns, int rows) {
+    const long long ncu = device_cu_count(), rounds = (tiles + ncu - 1) / ncu;
+    return (double)rounds * ((double)slots * slot_ns + (rows == 32 ? 500.0 : 1500.0));
+}
+
 int ring_variant(int M, int N, int K, int dtype, int transB, bool same_order, double* ns) {
     const int esz = dtype == ROV_F32 ? 4 : dtype == ROV_BF16 ? 2 : 1;
     const bool kn = transB == 0;
@@ -622,7 +632,7 @@ int ring_variant(int M, int N, int K, int dtype, int transB, bool same_order, do
         if (r.dtype != dtype || (r.kn != 0) != kn || r.vec != vec || (r.kparts > 1 && !split)) continue;
         const long long tiles = (long long)((M + r.bm - 1) / r.bm) * ((N + r.bn - 1) / r.bn);
         if (tiles > 0x7FFFFFFFLL) continue;
-        const double t = gemm_tiles_ns(tiles, slots, r.slot_ns);
+        const double t = dtype == ROV_F32 ? f32_tiles_ns(tiles, slots, r.slot_ns, r.bm) : gemm_tiles_ns(tiles, slots, r.slot_ns);
         if (best < 0 || t < best_ns) { best = v; best_ns = t; }
     }
     if (ns != nullptr) *ns = best_ns;

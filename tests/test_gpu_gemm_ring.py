@@ -48,11 +48,11 @@ CASES = [
     ("f32", 1, 1, 1, True, (32, 32, 4, 4)),   # smallest
     ("f32", 1000, 1024, 260, True, (64, 64, 2, 16)),   # last slot of one chunk
     ("f32", 33, 47, 131, True, (32, 32, 4, 4)),
-    ("f32", 700, 1025, 513, True, (64, 64, 2, 4)),
+    ("f32", 900, 1025, 513, True, (64, 64, 2, 4)),
     ("f32", 100, 36, 68, False, (32, 32, 4, 16)),
     ("f32", 1024, 1024, 64, False, (64, 64, 2, 16)),
     ("f32", 65, 33, 35, False, (32, 32, 4, 4)),
-    ("f32", 1021, 1027, 67, False, (64, 64, 2, 4)),
+    ("f32", 957, 1027, 67, False, (64, 64, 2, 4)),
 ]
 
 
