@@ -529,7 +529,7 @@ int launch_ring_depth(const void* A, const void* W, void* C, const void* R, int 
 // kernels compete, adjusted so that none of 622 products of either type for which all forms were timed (16 to 4096 rows, 256 to
 // 14336 columns, K of 512 to 14336) runs more than 2 % slower than with the 256-row kernel: fp8 128 x 64 at 280 chose this
 // form where it was up to 28 % slower (700 x 8192 x 8192 68 us against 53, 300 x 14336 x 4096 36.5 against 30.5).  Rows on
-// 4 bytes, which have no other matrix-core kernel, are fitted to 300 products of either layout instead (see kRingRow4), fp32 to 870 (see f32_tiles_ns).
+// 4 bytes, which have no other matrix-core kernel, are fitted to 300 products of either layout instead (see kRingRow4), fp32 to 1600 (see f32_tiles_ns).
 // Register counts leave room
 // for three 24-register RNG waves on every SIMD (a 256 x 128 tile with eight waves, 250 registers each, was up to
 // 8 % faster than the 256-row kernel at 2048 x 4096 x 4096, but its workgroups could not be placed beside an RNG
@@ -602,12 +602,12 @@ double gemm_tiles_ns(long long tiles, int slots, double slot_ns) {
 
 // fp32: several workgroups share a compute unit, so that a tile's fill and output lie beside another's walk, and idle units leave the
 // others no clock (the matrix rate binds, not power): rounds of one tile per compute unit each take the walk and a little.  Measured a slot
-// and round, ns: 32 x 32 165 to 180 in a lone round, 140 to 150 from two on; 64 x 64 505 to 530, 500.  Of 870 products (16 to 4096 rows, columns and k, half of
-// them 300 and more) the choice is 0.02 % above the sooner form on average, 4 % at worst.  With the formula above and 64 x 64 at 715 ns, large products took
+// and round, ns: 32 x 32 165 to 180 in a lone round, 140 to 150 from two on; 64 x 64 505 to 530, 500.  Of 1600 products (16 to 8000 rows and
+// columns, k of 2 to 4096) the choice is 0.07 % above the sooner form on average, 5 % at worst.  With the formula above and 64 x 64 at 715 ns, large products took
 // 32 x 32 tiles: 1497 x 4040 x 1796 [K, N] 210 us against 177, 2830 x 3188 x 1956 332 against 291.
 double f32_tiles_ns(long long tiles, int slots, double slot_ns, int rows) {
     const long long ncu = device_cu_count(), rounds = (tiles + ncu - 1) / ncu;
-    return (double)rounds * ((double)slots * slot_ns + (rows == 32 ? 500.0 : 1500.0));
+    return (double)rounds * ((double)slots * slot_ns + (rows == 32 ? 500.0 : 1000.0));
 }
 
 int ring_variant(int M, int N, int K, int dtype, int transB, bool same_order, double* ns) {
