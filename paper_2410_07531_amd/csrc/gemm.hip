@@ -863,18 +863,21 @@ int best_tile_cols(int M, int N, int fixed = 1) {
 }
 
 // Is a sum of at most 128 terms done sooner by the any-shape kernel?  Its 64 x 64 tiles pay per 16 terms; the
-// small tiles move whole slots of k and then pay for the output, more so where columns are not stored four at a time (c[1]) and
-// where rows start on 4 bytes (c[2]).  Both estimates in us, fitted to 1120 products of 1 to 6000 rows and 2 to 4098 columns (fp8: bf16's, but for the output).  Any
-// shape / small tiles, us: bf16 1500 x 4098 x 2 12 / 27, 6000 x 4098 x 40 54 / 63, x 72 84 / 63; fp32 1500 x 4098 x 30
-// 21 / 35, 6000 x 4096 x 16 40 / 55, x 48 66 / 67, x 96 105 / 79.
+// small tiles move whole slots of k and then pay for the output, more so where columns are not stored four at a time
+// (c[1]: bf16 rows of an odd number of values, fp32 rows off 16 bytes) and where rows start on 4 bytes (c[2]).  Both estimates in us,
+// fitted to 1780 products of 20 to 6000 rows, 20 to 8000 columns and 2 to 200 terms (they scatter by 5 to 8 %): the choice is 0.1 to 0.25 % above
+// the sooner kernel on average, and 0.12 to 0.17 % over 2480 others.  Any shape / small tiles, us: bf16 1500 x 4098 x 2 13.7 / 15.7, 4154 x 3759 x 2 25.1 /
+// 43.4, 6000 x 4098 x 24 47.1 / 32.7; fp8 6000 x 1001 x 16 13.5 / 18.9; fp32 5000 x 6001 x 2 55.7 / 62.7, 6000 x 4096 x 16 42.5 / 38.3.
 bool any_shape_sooner(int M, int N, int K, int dtype, int vec) {
     if (K > 128 || (double)M * (double)N < 5e5) return false;   // (small outputs: at launch cost either way)
     const bool f32 = dtype == ROV_F32;
     const double tiles = (double)((M + 63) / 64) * (double)((N + 63) / 64), out = 1e-6 * (double)M * (double)N;
-    const double any_us = fmax(1.8, 2.1e-3 * tiles + 1.3) * ((K + 15) / 16) + 3.7 + (f32 ? 4.6e-3 : 2.25e-3) * tiles;
-    const double c[4] = {f32 ? 1.78 : dtype == ROV_BF16 ? 0.85 : 1.15, f32 ? 1.43 : 1.36, f32 ? 0.84 : 1.20, f32 ? 0.013 : 0.0};
-    const double small_us = (f32 ? 5.3 : 4.4) + out * (c[0] + (N % 4 != 0 ? c[1] : 0.0) + (vec < 16 ? c[2] : 0.0) + c[3] * K);
-    return any_us < 1.05 * small_us;   // (the estimates scatter by 7 and 9 %)
+    const double any_us = (2.0e-3 * tiles + 1.45) * ((K + 15) / 16) + 3.4 + (f32 ? 5.8e-3 : 3.5e-3) * tiles;
+    struct Cost { double fixed, c[4]; };
+    static const Cost cost[3] = {{4.5, {1.29, 0.15, 0.54, 0.0134}}, {4.1, {1.03, 1.18, 0.55, 0.0016}}, {3.7, {0.88, 1.44, 0.0, 0.0115}}};
+    const Cost& p = cost[f32 ? 0 : dtype == ROV_BF16 ? 1 : 2];
+    const bool narrow = N % (f32 ? 4 : 2) != 0;
+    return any_us < p.fixed + out * (p.c[0] + (narrow ? p.c[1] : 0.0) + (vec < 16 ? p.c[2] : 0.0) + p.c[3] * K);
 }
 
 // Products that the 256-row kernel takes in its form for rows off 128 bytes (RAGGED): bf16 [N, K] operands whose rows start on 16 bytes.

@@ -21,7 +21,7 @@ def test_which_products_take_it():
         assert tile(M, N, K) == (rov.GEMM_256_ROWS, 256, cols, 1, 16), (M, N, K)
     for args in ((6935, 8514, 5956), (6935, 8512, 5960, False), (300, 1000, 1000), (4554, 1024, 1000)):
         assert tile(*args)[0] == rov.GEMM_SMALL_TILES, args
-    assert tile(6000, 4098, 24)[0] == rov.GEMM_ANY_SHAPE
+    assert tile(6000, 4098, 24)[0] == rov.GEMM_256_ROWS and tile(6000, 4099, 8)[0] == rov.GEMM_ANY_SHAPE
 
 
 @pytest.mark.gpu
