@@ -39,13 +39,14 @@ std::atomic<int> g_rng_max_workgroups{0};
 std::atomic<int> g_rng_overlap_wgs_per_cu{0};   // 0 = by the register rule in mask_grid_cap
 
 // One chunk: 16 groups -> 64 mask words = 4 whole tiles of 32 x 32 elements; word 4*gi + r is
-// parked in lane 4*gi + r of v.  RAGGED (S % 32 != 0): bits whose row or column lies
-// beyond S are cleared; (qt, kt) are the tile coordinates of the chunk's first tile.  (And the words are written lane by lane:
-// behind the clearing, park_words4's scalar chain shows where few waves are in flight, 8 x 639^2 bits 6.1 against 6.4 us.)
-template <int R, bool RAGGED, bool CARRY>
+// parked in lane 4*gi + r of v, by one-lane moves (PARK) or two lane writes each (see park_ballots).  RAGGED (S % 32 != 0): bits whose row or
+// column lies beyond S are cleared; (qt, kt) are the tile coordinates of the chunk's first tile.  (No one-lane moves there: the
+// clearing keeps the scalar unit busy already, and at every size from 2 to 400000 chunks they cost 2 to 5 %.)
+template <int R, bool RAGGED, bool CARRY, bool PARK>
 __device__ __forceinline__ void mask_chunk(uint64_t base, uint32_t lane, uint32_t k0, uint32_t k1,
                                            uint32_t t_minus_1, uint32_t T, uint32_t S, uint32_t qt,
                                            uint32_t kt, uint64_t& v) {
+    static_assert(!(RAGGED && PARK), "see above");
     uint32_t vlo = 0u, vhi = 0u;
 #pragma unroll 2
     for (int gi = 0; gi < kGroupsPerChunk; ++gi) {
@@ -58,30 +59,40 @@ __device__ __forceinline__ void mask_chunk(uint64_t base, uint32_t lane, uint32_
         }
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
+            uint32_t lo = (uint32_t)b[r], hi = (uint32_t)(b[r] >> 32);
             if (RAGGED) {
                 // word e = 4*(gi%4) + r: lanes 0-31 hold column 32*kt + 8*(gi%4) + r, lanes 32-63 that + 4
-                uint32_t lo = (uint32_t)b[r], hi = (uint32_t)(b[r] >> 32);
                 const uint32_t col = 32u * kt + 8u * ((uint32_t)gi & 3u) + (uint32_t)r;
                 lo = col < S ? (lo & row_mask) : 0u;
                 hi = col + 4u < S ? (hi & row_mask) : 0u;
+            }
+            if (!PARK) {
                 vlo = write_lane(lo, 4u * (uint32_t)gi + (uint32_t)r, vlo);
                 vhi = write_lane(hi, 4u * (uint32_t)gi + (uint32_t)r, vhi);
             }
         }
-        if (!RAGGED) park_words4(v, b, 4u * (uint32_t)gi);
+        if (PARK) park_words4(v, b, 4u * (uint32_t)gi);
         if (RAGGED && (gi & 3) == 3) {   // next tile
             kt = kt + 1u == T ? 0u : kt + 1u;
             if (kt == 0u) qt = qt + 1u == T ? 0u : qt + 1u;
         }
     }
-    if (RAGGED) v = ((uint64_t)vhi << 32) | vlo;
+    if (!PARK) v = ((uint64_t)vhi << 32) | vlo;
+}
+
+// One-lane moves save 4 of 50.6 vector instructions a call, and their scalar chain is hidden by the other waves of the SIMD.  10 rounds
+// are long enough at any size (whole masks, 64 to 150000 chunks: 1.00 to 1.06 times as fast); fewer rounds, and the rows kernel's longer
+// scalar part, want two waves a SIMD (3 rounds four): times as fast below / above that 0.97 to 1.00 / 1.00 to 1.09 (7 rounds and 5), 0.96 to 0.99 / 1.00
+// to 1.07 (3), 0.97 to 0.99 / 1.01 to 1.05 (rows).
+bool park_ballots(uint64_t nchunks, int rounds, bool rows) {
+    return (rounds == 10 && !rows) || nchunks > (uint64_t)device_cu_count() * (rounds == 3 ? 16u : 8u);
 }
 
 // lower_only: skip every chunk (4 consecutive tiles) none of whose tiles has key tile <= query
 // tile, i.e. which causal attention never reads; what is written has the same bits either way.
 // (at most 24 vector registers for the 10-round kernel: three of its waves then fit on a SIMD beside
 // the GEMM kernels, see mask_grid_cap)
-template <int R, bool RAGGED>
+template <int R, bool RAGGED, bool PARK>
 __global__ __launch_bounds__(kWavesPerBlock * 64) __attribute__((amdgpu_num_vgpr(24))) void mask_kernel(
     uint64_t* __restrict__ out, uint64_t words, uint64_t nchunks, uint64_t offset, uint32_t k0,
     uint32_t k1, uint32_t t_minus_1, uint32_t T, uint32_t Tm, uint32_t S, int lower_only, int qslot, uint64_t qper,
@@ -107,9 +118,9 @@ __global__ __launch_bounds__(kWavesPerBlock * 64) __attribute__((amdgpu_num_vgpr
         // first call number of the chunk; its 1024 calls are base .. base + 1023
         const uint64_t base = offset + 64u * kGroupsPerChunk * chunk;
         if ((uint32_t)base <= 0xFFFFFFFFu - (64u * kGroupsPerChunk - 1u)) {
-            mask_chunk<R, RAGGED, false>(base, lane, k0, k1, t_minus_1, T, S, qt, kt, v);
+            mask_chunk<R, RAGGED, false, PARK>(base, lane, k0, k1, t_minus_1, T, S, qt, kt, v);
         } else {
-            mask_chunk<R, RAGGED, true>(base, lane, k0, k1, t_minus_1, T, S, qt, kt, v);
+            mask_chunk<R, RAGGED, true, PARK>(base, lane, k0, k1, t_minus_1, T, S, qt, kt, v);
         }
         const uint64_t widx = chunk * 64u + lane;
         if (widx < words) out[widx] = v;
@@ -120,7 +131,7 @@ __global__ __launch_bounds__(kWavesPerBlock * 64) __attribute__((amdgpu_num_vgpr
 // [B*H][nqt][T][16]: the bits are those of the full mask (call numbers come from the global word
 // index), only the destination differs.  One "segment" per (batch, head): seg_words = nqt*T*16
 // words in `out`, starting at global word seg*seg_stride + seg_first.
-template <int R, bool RAGGED>
+template <int R, bool RAGGED, bool PARK>
 __global__ __launch_bounds__(kWavesPerBlock * 64) void mask_rows_kernel(
     uint64_t* __restrict__ out, uint64_t seg_words, uint64_t chunks_per_seg, uint64_t nseg,
     uint64_t seg_stride, uint64_t seg_first, uint64_t offset, uint32_t k0, uint32_t k1,
@@ -146,9 +157,9 @@ __global__ __launch_bounds__(kWavesPerBlock * 64) void mask_rows_kernel(
         uint64_t v = 0u;
         const uint64_t base = offset + 16u * gw;   // 64 calls per 4 words
         if ((uint32_t)base <= 0xFFFFFFFFu - (64u * kGroupsPerChunk - 1u)) {
-            mask_chunk<R, RAGGED, false>(base, lane, k0, k1, t_minus_1, T, S, qt, kt, v);
+            mask_chunk<R, RAGGED, false, PARK>(base, lane, k0, k1, t_minus_1, T, S, qt, kt, v);
         } else {
-            mask_chunk<R, RAGGED, true>(base, lane, k0, k1, t_minus_1, T, S, qt, kt, v);
+            mask_chunk<R, RAGGED, true, PARK>(base, lane, k0, k1, t_minus_1, T, S, qt, kt, v);
         }
         const uint64_t lw = lc * 64u + lane;
         if (lw < seg_words) out[seg * seg_words + lw] = v;
@@ -158,14 +169,15 @@ __global__ __launch_bounds__(kWavesPerBlock * 64) void mask_rows_kernel(
 // Narrow-threshold chunk: BITS (8 or 16) random bits per element.  One Philox call per lane now
 // serves E = 4 * 32/BITS mask words: field s of output word r decides word E*gi + 4*s + r of the
 // chunk.  A chunk is still 64 words = 4 tiles; tile t of the chunk has coordinates (qts[t], kts[t]).
-// (Lane writes: with two or four times the words a call, park_words4's scalar chain shows where few waves are in flight,
-// 8 x 1170^2 elements at 16 bits 6.9 against 7.6 us.)
+// Whole masks take one-lane moves at any size (16 bits 1.00 to 1.11, 8 bits 1.00 to 1.18 times as fast as lane writes); ragged
+// ones, whose clearing keeps the scalar unit busy, lane writes (moves 0.87 to 0.96 times, 8 x 1170^2 elements at 16 bits 7.6 against 6.9 us).
 template <int BITS, bool RAGGED, bool CARRY>
 __device__ __forceinline__ void mask_chunk_bits(uint64_t base, uint32_t lane, uint32_t k0, uint32_t k1,
                                                 uint32_t tb, uint32_t S, const uint32_t (&qts)[4],
                                                 const uint32_t (&kts)[4], uint64_t& v) {
     constexpr int NF = 32 / BITS;          // fields per output word
     constexpr int E = 4 * NF;              // mask words per group
+    constexpr bool PARK = !RAGGED;
     uint32_t vlo = 0u, vhi = 0u;
 #pragma unroll
     for (int gi = 0; gi < 64 / E; ++gi) {
@@ -179,12 +191,13 @@ __device__ __forceinline__ void mask_chunk_bits(uint64_t base, uint32_t lane, ui
             philox4x32<10>(c0, bhi + (c0 < blo ? 1u : 0u), 0u, 0u, k0, k1, x);
         }
 #pragma unroll
-        for (int s = 0; s < NF; ++s)
+        for (int s = 0; s < NF; ++s) {
+            uint64_t w[4];
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const uint32_t field = (x[r] >> (BITS * s)) & ((1u << BITS) - 1u);
-                const uint64_t bal = __ballot(field < tb);
-                uint32_t lo = (uint32_t)bal, hi = (uint32_t)(bal >> 32);
+                w[r] = __ballot(field < tb);
+                uint32_t lo = (uint32_t)w[r], hi = (uint32_t)(w[r] >> 32);
                 const int dst = E * gi + 4 * s + r;            // word of the chunk
                 if (RAGGED) {
                     const int t = dst >> 4, ew = dst & 15;     // tile of the chunk, word of the tile
@@ -194,11 +207,15 @@ __device__ __forceinline__ void mask_chunk_bits(uint64_t base, uint32_t lane, ui
                     lo = col < S ? (lo & row_mask) : 0u;
                     hi = col + 4u < S ? (hi & row_mask) : 0u;
                 }
-                vlo = write_lane(lo, (uint32_t)dst, vlo);
-                vhi = write_lane(hi, (uint32_t)dst, vhi);
+                if (!PARK) {
+                    vlo = write_lane(lo, (uint32_t)dst, vlo);
+                    vhi = write_lane(hi, (uint32_t)dst, vhi);
+                }
             }
+            if (PARK) park_words4(v, w, (uint32_t)(E * gi + 4 * s));
+        }
     }
-    v = ((uint64_t)vhi << 32) | vlo;
+    if (!PARK) v = ((uint64_t)vhi << 32) | vlo;
 }
 
 template <int BITS, bool RAGGED>
@@ -315,13 +332,11 @@ int launch_mask_r(uint64_t* out, uint64_t words, uint64_t offset, uint32_t k0, u
     uint64_t qper = 0;
     uint32_t qbatch = 1;
     queue_geometry(nchunks, &qper, &qbatch);
-    if ((S & 31) == 0) {
-        hipLaunchKernelGGL((mask_kernel<R, false>), grid, block, 0, stream, out, words, nchunks,
-                           offset, k0, k1, t_minus_1, T, div_magic(T), (uint32_t)S, (int)lower_only, qslot, qper, qbatch, chunk0);
-    } else {
-        hipLaunchKernelGGL((mask_kernel<R, true>), grid, block, 0, stream, out, words, nchunks,
-                           offset, k0, k1, t_minus_1, T, div_magic(T), (uint32_t)S, (int)lower_only, qslot, qper, qbatch, chunk0);
-    }
+    const auto kern = (S & 31) != 0                              ? mask_kernel<R, true, false>
+                      : park_ballots(nchunks - chunk0, R, false) ? mask_kernel<R, false, true>
+                                                                 : mask_kernel<R, false, R == 10>;   // (10 rounds: not reached)
+    hipLaunchKernelGGL(kern, grid, block, 0, stream, out, words, nchunks,
+                       offset, k0, k1, t_minus_1, T, div_magic(T), (uint32_t)S, (int)lower_only, qslot, qper, qbatch, chunk0);
     ROV_LAUNCH_CHECK();
     return ROV_OK;
 }
@@ -494,13 +509,11 @@ int launch_mask_rows(uint64_t seed, uint64_t offset, int B, int H, int S, float 
     uint32_t qbatch = 1;
     queue_geometry(nseg * cps, &qper, &qbatch);
     const uint64_t seg_first = (uint64_t)(q_begin / 32) * T * 16u;
-    if ((S & 31) == 0) {
-        hipLaunchKernelGGL((mask_rows_kernel<10, false>), grid, block, 0, stream, out, seg_words, cps, nseg,
-                           T * T * 16u, seg_first, offset, k0, k1, tm1, (uint32_t)T, div_magic(T), div_magic(cps), (uint32_t)S, qslot, qper, qbatch);
-    } else {
-        hipLaunchKernelGGL((mask_rows_kernel<10, true>), grid, block, 0, stream, out, seg_words, cps, nseg,
-                           T * T * 16u, seg_first, offset, k0, k1, tm1, (uint32_t)T, div_magic(T), div_magic(cps), (uint32_t)S, qslot, qper, qbatch);
-    }
+    const auto kern = (S & 31) != 0                        ? mask_rows_kernel<10, true, false>
+                      : park_ballots(nseg * cps, 10, true) ? mask_rows_kernel<10, false, true>
+                                                           : mask_rows_kernel<10, false, false>;
+    hipLaunchKernelGGL(kern, grid, block, 0, stream, out, seg_words, cps, nseg,
+                       T * T * 16u, seg_first, offset, k0, k1, tm1, (uint32_t)T, div_magic(T), div_magic(cps), (uint32_t)S, qslot, qper, qbatch);
     ROV_LAUNCH_CHECK();
     return ROV_OK;
 }

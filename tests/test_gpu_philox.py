@@ -66,6 +66,24 @@ def test_mask_round_variants_bit_exact(rounds):
     assert np.array_equal(got, OP.dropout_mask(11, 3, 1, 3, 200, 0.2, rounds=rounds))
 
 
+@pytest.mark.parametrize("rounds", [3, 5, 7])
+@pytest.mark.parametrize("H,S", [(3, 192), (2, 2048), (2, 2112), (4, 2048), (4, 2080)])   # chunks: 27, 2048, 2178, 4096, 4225
+def test_mask_round_variants_of_whole_tiles_bit_exact(rounds, H, S):
+    # below and above the number of chunks from which ballots are moved one lane at a time (2048; 3 rounds: 4096); call numbers
+    # carry into the second counter word
+    print("mask rounds", rounds, H, S, flush=True)
+    got = _np_u64(rov.dropout_mask_generate(11, 2**32 - 70000, 1, H, S, 0.2, rounds=rounds))
+    assert np.array_equal(got, OP.dropout_mask(11, 2**32 - 70000, 1, H, S, 0.2, rounds=rounds))
+
+
+@pytest.mark.parametrize("B,H,S,q_begin,q_rows", [(1, 3, 192, 32, 64), (1, 2, 4096, 1024, 1024), (1, 2, 4096, 1024, 1088)])   # chunks: 9, 2048, 2176
+def test_mask_rows_of_whole_tiles_bit_exact(B, H, S, q_begin, q_rows):
+    print("mask rows", H, S, q_begin, q_rows, flush=True)
+    got = _np_u64(rov.dropout_mask_generate_rows(11, 2**32 - 70000, B, H, S, 0.2, q_begin, q_rows))
+    exp = OP.dropout_mask(11, 2**32 - 70000, B, H, S, 0.2)
+    assert np.array_equal(got, exp[:, :, q_begin // 32:(q_begin + q_rows) // 32])
+
+
 def test_mask_small_grid_matches_default_grid():
     # the result must not depend on the launch shape
     a = _np_u64(rov.dropout_mask_generate(5, 0, 1, 8, 512, 0.1))
