@@ -282,6 +282,11 @@ int rov_attention_fwd_dropout(const void *Q, const void *K, const void *V, void 
  * problem, every mode and every stream.  ROV_ERR_INVALID for other arguments. */
 int rov_attention_key_parts(int B, int H, int S, int d, int dtype, int causal);
 
+/* Query rows of a tile of the attention kernel that runs (host-side rule, no device work): 256, 128 or 64
+ * for bf16 with d = 64 or 128, 32 or 16 for fp32 on the matrix cores, 1 where the one-row-per-wave kernel runs (where
+ * rov_attention_key_parts is 0).  The same for every range of rows of a problem, every mode and every stream. */
+int rov_attention_tile_rows(int B, int H, int S, int d, int dtype, int causal);
+
 /* Same with a selectable Philox round count for the fused variant (paper Sec. 5.2): with
  * mask == NULL and p > 0 the kernel draws the bits of
  * rov_dropout_mask_generate_rounds(seed, offset, ..., rounds).  rounds in {3, 5, 7, 10}; with a

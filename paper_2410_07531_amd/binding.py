@@ -79,6 +79,7 @@ SIGNATURES = {
     "rov_gemm_tile": (_i, [_i, _i, _i, _i, _i, ctypes.POINTER(ctypes.c_int)]),
     "rov_gemm_swiglu_tile_cols": (_i, [_i, _i, _i, _i]),
     "rov_attention_key_parts": (_i, [_i, _i, _i, _i, _i, _i]),
+    "rov_attention_tile_rows": (_i, [_i, _i, _i, _i, _i, _i]),
     "rov_overlap_mask_chunks": (ctypes.c_int64, [ctypes.c_double, _i, _i, _i, _i, _i, _i]),
     "rov_set_rng_overlap_workgroups_per_cu": (_i, [_i]),
     "rov_trace_enable": (_i, [_i]),
@@ -225,6 +226,13 @@ def attention_key_parts(B, H, S, d, dtype, causal):
     r = load().rov_attention_key_parts(B, H, S, d, dtype, int(bool(causal)))
     if r < 0:
         raise RovError(r, "rov_attention_key_parts")
+    return r
+
+
+def attention_tile_rows(B, H, S, d, dtype, causal):
+    r = load().rov_attention_tile_rows(B, H, S, d, dtype, int(bool(causal)))
+    if r < 0:
+        raise RovError(r, "rov_attention_tile_rows")
     return r
 
 

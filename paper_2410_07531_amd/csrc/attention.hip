@@ -913,7 +913,7 @@ __global__ __launch_bounds__(NW * 64) void attn_f32_kernel(const AttnParams p) {
 // operand as they stand here too.  The keep word of register e is word 4 * (2 * (block % 2) + (l / 16) / 2) + e of the 32 x 32 tile, its
 // bit 32 * (l / 16 % 2) + query % 32: read as the lane's half word (stored mask) or drawn by the lane (same call, same field).
 // Each K and V byte is read by twice as many workgroups: see attn_f32_q16 for where that begins to cost more.
-// us, 32-query tiles -> this: 128 tokens x 2 heads x 64 features (stored mask) 8.1 -> 6.9; 400 x 2 x 128 27.2 -> 17.7; 2 x 359 x 8 x 64 causal,
+// us, 32-query tiles -> this: 128 tokens x 2 heads x 64 features (stored mask) 8.1 -> 6.5; 400 x 2 x 128 27.2 -> 17.7; 2 x 359 x 8 x 64 causal,
 // bits drawn here, 16.1 -> 11.7.
 template <int DP, int NW, int MODE, int BITS>
 __global__ __launch_bounds__(NW * 64) void attn_f32_q16_kernel(const AttnParams p) {
@@ -1357,10 +1357,15 @@ int attn_f32_waves(int B, int H, int S, int d) {
     return d <= 64 ? 8 : 4;
 }
 
-// fp32: query tiles of 16 instead of 32 rows?  Where those of 32 are at most three quarters of the compute units (timed at 120 problems of 64 to 1100
-// tokens, 2 to 16 heads, 32 to 128 features: 1.2 to 1.5 times as fast up to 128 tiles, 1.0 to 1.4 at up to 192, 0.83 to 1.2 at 256,
-// 0.82 to 0.97 from 512 on).  Only what all launches over one problem share decides, so that row ranges and modes agree.
-bool attn_f32_q16(int B, int H, int S) { return ceil(S / 32.0) * B * H <= 0.75 * device_cu_count(); }
+// fp32: query tiles of 16 instead of 32 rows?  Timed at 1400 problems of 24 to 320 tiles of 32 rows (40 to 6000 tokens, 1 to 64 heads, 8 to 128
+// features).  Every workgroup walks all keys, so without the causal mask what counts is whether the tiles of 16 are one round: 1.1 to 1.9
+// times as fast up to one per compute unit; above, 0.64 to 1.1 (3 heads x 1616 tokens x 128 features 100 us against 69), but for the short walks
+// of up to 200 tokens and 96 features, 1.06 on average (0.86 to 1.4).  Causal walks even out: 1.03 to 1.7 times as fast up to three quarters of a 32-query
+// tile per compute unit, 0.9 to 1.6 above.  Only what all launches over one problem share decides, so that row ranges and modes agree.
+bool attn_f32_q16(int B, int H, int S, int d, bool causal) {
+    const double heads = (double)B * H, ncu = device_cu_count();
+    return ceil(S / 32.0) * heads <= 0.75 * ncu && (causal || ceil(S / 16.0) * heads <= ncu || (S <= 200 && d <= 96));
+}
 
 template <int DP, int NW>
 int launch_f32(const AttnParams& prm, int mode, hipStream_t stream) {
@@ -1520,7 +1525,7 @@ int launch_attention_rows(const void* Q, const void* K, const void* V, void* O, 
         // K / V of one (batch, kv head) are addressed through a buffer resource: byte offsets below 2^31
         for (int t = 4; t <= 7; t += 3)
             ok = ok && strides[t] >= 0 && (uint64_t)(S + 31) * (uint64_t)strides[t] * 4u + 4u * (uint64_t)d < (1ull << 31);
-        if (ok && attn_f32_q16(B, H, S)) {
+        if (ok && attn_f32_q16(B, H, S, d, causal != 0)) {
             if (d <= 32) return launch_f32_q16<32, 8>(prm, mode, stream);
             if (d <= 64) return launch_f32_q16<64, 8>(prm, mode, stream);
             if (d <= 96) return launch_f32_q16<96, 4>(prm, mode, stream);
@@ -1543,6 +1548,13 @@ extern "C" int rov_attention_key_parts(int B, int H, int S, int d, int dtype, in
     if (dtype != ROV_F32 && dtype != ROV_BF16) return ROV_ERR_INVALID;
     if (dtype == ROV_F32) return rov::attn_f32_waves(B, H, S, d);
     return d == 64 || d == 128 ? rov::attn_key_parts(B, H, S, d, causal != 0) : 0;
+}
+
+extern "C" int rov_attention_tile_rows(int B, int H, int S, int d, int dtype, int causal) {
+    const int parts = rov_attention_key_parts(B, H, S, d, dtype, causal);
+    if (parts <= 0) return parts < 0 ? parts : 1;
+    if (dtype == ROV_F32) return rov::attn_f32_q16(B, H, S, d, causal != 0) ? 16 : 32;
+    return 256 / parts;
 }
 
 extern "C" int rov_attention_fwd_dropout_rows(const void* Q, const void* K, const void* V, void* O, int B,

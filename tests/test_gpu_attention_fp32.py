@@ -49,9 +49,11 @@ def test_fp32_matches_oracle(B, S, H, Hkv, d, waves, causal):
     assert _err(O["none"], OD.attention_dropout(*f64, None, 0.0, causal=causal)) <= TOL
 
 
+@pytest.mark.parametrize("H,rows", [(2, 16), (80, 32)])     # query tiles of either height
 @pytest.mark.parametrize("rounds,bits", [(7, 32), (3, 32), (10, 16), (10, 8)])
-def test_fp32_fused_variants_draw_the_mask_kernels_bits(rounds, bits):
-    B, S, H, d, p, seed, offset = 1, 90, 2, 64, 0.3, 77, 640
+def test_fp32_fused_variants_draw_the_mask_kernels_bits(rounds, bits, H, rows):
+    B, S, d, p, seed, offset = 1, 90, 64, 0.3, 77, 640
+    assert rov.attention_tile_rows(B, H, S, d, rov.F32, False) == rows
     Q, K, V = (torch.from_numpy(x).cuda() for x in wl.qkv(np.random.default_rng(1), B, S, H, H, d))
     if bits == 32:
         mask = rov.dropout_mask_generate(seed, offset, B, H, S, p, rounds=rounds)
@@ -62,9 +64,11 @@ def test_fp32_fused_variants_draw_the_mask_kernels_bits(rounds, bits):
     assert torch.equal(fused, rov.attention_fwd_dropout(Q, K, V, p, mask=mask))
 
 
-def test_fp32_strided_views():
+@pytest.mark.parametrize("H,rows", [(2, 16), (80, 32)])
+def test_fp32_strided_views(H, rows):
     # Q, K, V as slices of one projection output; a row stride that is no multiple of 4 takes the general kernel
-    B, S, H, d = 1, 70, 2, 64
+    B, S, d = 1, 70, 64
+    assert rov.attention_tile_rows(B, H, S, d, rov.F32, True) == rows
     for pad in (0, 1):
         x = torch.randn(B, S, 3 * H * d + pad, device="cuda", generator=torch.Generator("cuda").manual_seed(5))
         Q, K, V = (x[..., i * H * d:(i + 1) * H * d].unflatten(-1, (H, d)) for i in range(3))
@@ -74,10 +78,11 @@ def test_fp32_strided_views():
         assert _err(O, ref) <= TOL
 
 
-def test_fp32_causal_rows_never_see_later_values():
+@pytest.mark.parametrize("H,rows", [(1, 16), (80, 32)])
+def test_fp32_causal_rows_never_see_later_values(H, rows):
     # non-finite keys and values reach the rows that admit them and no other
-    B, S, H, d = 1, 96, 1, 64
-    assert rov.attention_key_parts(B, H, S, d, rov.F32, True) == 8
+    B, S, d = 1, 96, 64
+    assert rov.attention_key_parts(B, H, S, d, rov.F32, True) == 8 and rov.attention_tile_rows(B, H, S, d, rov.F32, True) == rows
     g = torch.Generator("cuda").manual_seed(9)
     Q, K, V = (torch.randn(B, S, H, d, device="cuda", generator=g) for _ in range(3))
     ref = rov.attention_fwd_dropout(Q, K, V, 0.0, causal=True)
@@ -86,11 +91,12 @@ def test_fp32_causal_rows_never_see_later_values():
     K2[0, 77, 0, 0] = float("nan")
     O = rov.attention_fwd_dropout(Q, K2, V2, 0.0, causal=True)
     torch.cuda.synchronize()
-    assert torch.allclose(O[0, :40], ref[0, :40], rtol=1e-5, atol=1e-6)
+    assert torch.allclose(O[0, :40, 0], ref[0, :40, 0], rtol=1e-5, atol=1e-6)
     assert bool((O[0, 40:77, 0, 3] == float("inf")).all())
     others = [i for i in range(d) if i != 3]
     assert torch.allclose(O[0, 40:77, 0, others], ref[0, 40:77, 0, others], rtol=1e-5, atol=1e-6)
-    assert bool(torch.isnan(O[0, 77:]).all())
+    assert bool(torch.isnan(O[0, 77:, 0]).all())
+    assert torch.equal(O[0, :, 1:], ref[0, :, 1:])
 
 
 @pytest.mark.parametrize("causal", [False, True])

@@ -17,18 +17,15 @@ pytestmark = pytest.mark.gpu
 TOL = 1e-4
 
 
-def _rows(B, H, S):
-    return 16 if -(-S // 32) * B * H <= 192 else 32     # three quarters of the 256 compute units
-
-
 @pytest.mark.parametrize("causal", [False, True])
 @pytest.mark.parametrize("B,S,H,Hkv,d,rows", [
-    (1, 65, 2, 1, 32, 16), (1, 79, 2, 2, 48, 16), (1, 80, 1, 1, 8, 16), (1, 81, 3, 3, 72, 16), (1, 113, 2, 1, 120, 16),
-    (2, 129, 4, 2, 128, 16), (1, 190, 6, 2, 88, 16), (1, 300, 2, 2, 64, 16), (4, 70, 32, 8, 64, 32), (2, 129, 32, 8, 96, 32), (3, 97, 20, 20, 128, 32),
+    (1, 65, 2, 1, 32, (16, 16)), (1, 79, 2, 2, 48, (16, 16)), (1, 80, 1, 1, 8, (16, 16)), (1, 81, 3, 3, 72, (16, 16)), (1, 113, 2, 1, 120, (16, 16)),
+    (2, 129, 4, 2, 128, (16, 16)), (1, 190, 6, 2, 88, (16, 16)), (1, 300, 2, 2, 64, (16, 16)), (4, 70, 32, 8, 64, (32, 32)), (2, 129, 32, 8, 96, (32, 32)),
+    (3, 97, 20, 20, 128, (32, 32)), (2, 128, 16, 4, 64, (16, 16)), (2, 129, 16, 4, 40, (16, 16)), (1, 257, 17, 17, 40, (32, 16)),   # 256, 288, 289 tiles of 16 rows
 ])
 def test_both_tile_heights_match_oracle(B, S, H, Hkv, d, rows, causal):
     print("attn fp32 q16", B, S, H, Hkv, d, causal, flush=True)
-    assert _rows(B, H, S) == rows and rov.attention_key_parts(B, H, S, d, rov.F32, causal) in (4, 8)
+    assert rov.attention_tile_rows(B, H, S, d, rov.F32, causal) == rows[causal]
     p, seed, offset = 0.2, wl.SEED, 2**32 - 200
     q, k, v = wl.qkv(np.random.default_rng(S + d), B, S, H, Hkv, d)
     Q, K, V = (torch.from_numpy(x).cuda() for x in (q, k, v))
@@ -49,9 +46,10 @@ def test_both_tile_heights_match_oracle(B, S, H, Hkv, d, rows, causal):
 
 
 @pytest.mark.parametrize("bits", [8, 16])
-@pytest.mark.parametrize("rounds", [10])
-def test_narrow_fields_are_the_mask_kernels(bits, rounds):
-    B, S, H, d, p, seed, offset = 1, 83, 2, 40, 0.3, 77, 640
+@pytest.mark.parametrize("H,rows", [(2, 16), (80, 32)])
+def test_narrow_fields_are_the_mask_kernels(bits, H, rows):
+    B, S, d, p, seed, offset = 1, 83, 40, 0.3, 77, 640
+    assert rov.attention_tile_rows(B, H, S, d, rov.F32, False) == rows
     Q, K, V = (torch.from_numpy(x).cuda() for x in wl.qkv(np.random.default_rng(1), B, S, H, H, d))
     mask = rov.dropout_mask_generate_bits(seed, offset, B, H, S, p, bits)
     a = rov.attention_fwd_dropout(Q, K, V, p, mask=mask)
