@@ -1340,23 +1340,6 @@ int attn_key_parts(int B, int H, int S, int d, bool causal) {
     return best;
 }
 
-// Waves of a workgroup of the fp32 kernel: eight at up to 64 features, four above (their registers); 0: the one-row-per-wave
-// kernel runs, for a head dimension that this one does not take, for more workgroups than a grid holds, or because it is done
-// sooner.  That is so for a few rows: its waves have one key a lane, where the matrix kernel is one chain of load, 32-key
-// products and merge whatever S is.  Both times in us, fitted to 3360 problems of 1 to 96 tokens, 1 to 512 heads and 8 to 128
-// features (one row a wave / matrix kernel, no dropout, d = 128: 1 head x 33 tokens 7.9 / 11.0, 32 x 16 6.4 / 10.2, 32 x 64 15.3 / 10.7,
-// 512 x 8 9.4 / 19.1, 512 x 32 63 / 20; d = 64: 1 x 33 5.4 / 7.3, 32 x 33 6.7 / 8.0, 32 x 64 9.2 / 7.3).
-// Only what all launches over one problem share decides, so that row ranges and modes agree.
-int attn_f32_waves(int B, int H, int S, int d) {
-    const double heads = (double)B * H, tiles = ceil(S / 32.0) * heads;
-    if (d % 8 != 0 || d > 128 || tiles > 0x7FFFFFFF) return 0;
-    const double f = d <= 64 ? 1.0 : 2.0;
-    const double row_us = 2.5 + 0.06 * f * S + 1e-3 * heads * S * f * (1.0 + 0.01 * S);
-    const double mfma_us = (4.0 + 0.06 * ((d + 31) / 32 * 32)) * (0.2 + 0.8 * ceil(tiles / device_cu_count()));
-    if (S <= 64 && row_us < mfma_us) return 0;   // (beyond 64 tokens a lane has a second key)
-    return d <= 64 ? 8 : 4;
-}
-
 // fp32: query tiles of 16 instead of 32 rows?  Timed at 1400 problems of 24 to 320 tiles of 32 rows (40 to 6000 tokens, 1 to 64 heads, 8 to 128
 // features).  Every workgroup walks all keys, so without the causal mask what counts is whether the tiles of 16 are one round: 1.1 to 1.9
 // times as fast up to one per compute unit; above, 0.64 to 1.1 (3 heads x 1616 tokens x 128 features 100 us against 69), but for the short walks
@@ -1365,6 +1348,26 @@ int attn_f32_waves(int B, int H, int S, int d) {
 bool attn_f32_q16(int B, int H, int S, int d, bool causal) {
     const double heads = (double)B * H, ncu = device_cu_count();
     return ceil(S / 32.0) * heads <= 0.75 * ncu && (causal || ceil(S / 16.0) * heads <= ncu || (S <= 200 && d <= 96));
+}
+
+// Waves of a workgroup of the fp32 kernels: eight at up to 64 features, four above (their registers); 0: the one-row-per-wave
+// kernel runs, for a head dimension that these do not take, for more workgroups than a grid holds, or because it is done
+// sooner: its waves have one key a lane, where a matrix kernel is one chain of load, products and merge whatever S is.  Against tiles
+// of 32 rows both times are estimated, in us, fitted to 3360 problems of 1 to 96 tokens, 1 to 512 heads and 8 to 128
+// features (one row a wave / matrix kernel, d = 128: 512 heads x 8 tokens 9.4 / 19.1, 256 x 8 8.4 / 12.2, 512 x 32 63 / 20; d = 64: 256 x 9
+// 6.4 / 7.5, 512 x 9 9.3 / 12.6).  Tiles of 16 rows have a quarter of the chain: over 610 problems of up to 64 tokens they are even with the row
+// kernel up to 4 tokens (0.94 to 1.2 times as fast) and 1.02 to 3.8 times as fast from 5 on (1 x 16 x 64 4.7 against 5.2, 1 x 37 x 128 6.2 against 8.7,
+// 32 x 57 x 96 6.3 against 13.6).
+// Only what all launches over one problem share decides, so that row ranges and modes agree.
+int attn_f32_waves(int B, int H, int S, int d, bool causal) {
+    const double heads = (double)B * H, tiles = ceil(S / 32.0) * heads;
+    if (d % 8 != 0 || d > 128 || tiles > 0x7FFFFFFF) return 0;
+    const double f = d <= 64 ? 1.0 : 2.0;
+    const double row_us = 2.5 + 0.06 * f * S + 1e-3 * heads * S * f * (1.0 + 0.01 * S);
+    const double mfma_us = (4.0 + 0.06 * ((d + 31) / 32 * 32)) * (0.2 + 0.8 * ceil(tiles / device_cu_count()));
+    const int longest = attn_f32_q16(B, H, S, d, causal) ? 4 : 64;   // (beyond 64 tokens a lane has a second key)
+    if (S <= longest && row_us < mfma_us) return 0;
+    return d <= 64 ? 8 : 4;
 }
 
 template <int DP, int NW>
@@ -1518,7 +1521,7 @@ int launch_attention_rows(const void* Q, const void* K, const void* V, void* O, 
             return launch_bf16<64, 1, 8, 1>(prm, mode, stream);
         }
     }
-    if (dtype == ROV_F32 && attn_f32_waves(B, H, S, d) != 0) {
+    if (dtype == ROV_F32 && attn_f32_waves(B, H, S, d, causal != 0) != 0) {
         // 16-byte accesses to rows of Q, K and O
         bool ok = aligned(Q, 16) && aligned(K, 16) && aligned(O, 16);
         for (int i = 0; i < 12; ++i) ok = ok && (i / 3 == 2 || strides[i] % 4 == 0);
@@ -1546,7 +1549,7 @@ int launch_attention_rows(const void* Q, const void* K, const void* V, void* O, 
 extern "C" int rov_attention_key_parts(int B, int H, int S, int d, int dtype, int causal) {
     if (B <= 0 || H <= 0 || S <= 0 || d <= 0 || d > 256) return ROV_ERR_INVALID;
     if (dtype != ROV_F32 && dtype != ROV_BF16) return ROV_ERR_INVALID;
-    if (dtype == ROV_F32) return rov::attn_f32_waves(B, H, S, d);
+    if (dtype == ROV_F32) return rov::attn_f32_waves(B, H, S, d, causal != 0);
     return d == 64 || d == 128 ? rov::attn_key_parts(B, H, S, d, causal != 0) : 0;
 }
 

@@ -24,7 +24,8 @@ def _err(got, ref):
 
 @pytest.mark.parametrize("causal", [False, True])
 @pytest.mark.parametrize("B,S,H,Hkv,d,waves", [
-    (1, 1, 1, 1, 8, 0), (1, 33, 2, 1, 32, 0), (1, 40, 2, 2, 128, 0),       # few rows: one row a wave
+    (1, 1, 1, 1, 8, 0), (1, 4, 2, 1, 32, 0), (2, 9, 128, 32, 40, 0), (2, 12, 100, 50, 128, 0),   # few rows: one row a wave
+    (1, 5, 1, 1, 8, 8), (1, 33, 2, 1, 32, 8), (1, 40, 2, 2, 128, 4),       # tiles of 16 rows
     (8, 20, 64, 16, 8, 8), (4, 33, 16, 4, 32, 8), (8, 32, 32, 32, 128, 4),  # one or two key tiles, many heads
     (2, 65, 8, 4, 40, 8), (1, 300, 4, 2, 64, 8), (1, 97, 3, 3, 80, 4), (1, 70, 2, 2, 96, 4), (2, 129, 2, 1, 128, 4), (1, 100, 2, 2, 104, 4),
 ])
