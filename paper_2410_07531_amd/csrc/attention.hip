@@ -228,7 +228,7 @@ __global__ __launch_bounds__(NW * 64) void attn_bf16_kernel(const AttnParams p) 
     // Workgroup ids are dealt round-robin to the 8 XCDs.  All query blocks of one (batch, head)
     // go to the same XCD, so its K and V are fetched into one L2 only; within an XCD the order
     // is query block first, then head, so co-resident workgroups walk the same K/V in step.
-    // Causal: heaviest query blocks first.  Where two workgroups share a compute unit and all of them are resident at once, the
+    // Causal: heaviest query blocks first.  Where workgroups share a compute unit, the
     // order decides who shares: the first round of workgroups comes in reversed order then (see attn_turn), so that its lightest
     // get the second round's heaviest beside them.
     int qblk, bh;
@@ -1267,12 +1267,14 @@ __global__ __launch_bounds__(256) void attn_generic_kernel(const AttnParams p) {
 
 // Workgroups of an XCD that come in reversed order (causal, d = 64; at d = 128 a compute unit holds one workgroup, and the next goes
 // wherever one ends).  Heaviest first throughout, compute units got the heaviest of either round together: 24 units of work on some and
-// 10 on others at 2 x 1000 tokens x 16 heads (bits drawn in the kernel 22.3 us, now 20.0), 17 on each now; 2 x 427 x 32 heads 13.6 -> 11.1, stored
-// mask 9.8 -> 8.9.  Timed at 70 problems of 256 to 1100 workgroups: 1.0 to 1.2 times as fast up to 2.6 per compute unit, 0.96 to 1.04 above.
-int attn_turn(long long nblocks, int d, int ks, int mode) {
+// 10 on others at 2 x 1000 tokens x 16 heads (bits drawn in the kernel 20.0 us, now 17.5), 17 on each now; 2 x 427 x 32 heads 13.6 -> 11.1, stored
+// mask 9.8 -> 8.9.  Timed at 800 problems of 270 to 770 workgroups: up to two per compute unit, all resident at once, 1.0 to 1.2 times as fast.  Up to
+// 2.6 the third ones go where a unit is done first: from 1000 tokens on (bits drawn in the kernel: 600) 1.03 (1.08) on average, 0.98 (0.97) at
+// worst; with shorter sequences 0.92 to 1.06.  Above 2.6 1.02 (0.96 to 1.07), where it is not taken.
+int attn_turn(long long nblocks, int S, int d, int ks, int mode) {
     const long long ncu = device_cu_count();
     const bool shared = d == 64 && (ks > 1 || mode != MODE_FUSED);   // (the unsplit fused form's registers fill a compute unit)
-    return shared && ncu % 8 == 0 && 10 * nblocks > 11 * ncu && 10 * nblocks <= 26 * ncu ? (int)(ncu / 8) : 0;
+    return shared && ncu % 8 == 0 && 10 * nblocks > 11 * ncu && 10 * nblocks <= (S >= (mode == MODE_FUSED ? 600 : 1000) ? 26 : 20) * ncu ? (int)(ncu / 8) : 0;
 }
 
 template <int D, int NQ, int NW, int KS>
@@ -1282,7 +1284,7 @@ int launch_bf16(const AttnParams& prm, int mode, hipStream_t stream) {
     prm2.nq = (prm.q_end - prm.q_begin + bq - 1) / bq;
     const long long nblocks = (long long)prm2.nq * prm.H * prm.B;
     if (nblocks > 0x7FFFFFFFLL) return ROV_ERR_UNSUPPORTED;
-    prm2.turn = prm.causal ? attn_turn(nblocks, D, KS, mode) : 0;
+    prm2.turn = prm.causal ? attn_turn(nblocks, prm.S, D, KS, mode) : 0;
     const dim3 grid((unsigned)nblocks), block(NW * 64);
     const int lds_bytes = 2 * Tile<D, KS == 1 ? 64 : 32 * KS>::kStage;   // two K/V stages
     void (*kern)(const AttnParams) = mode == MODE_NONE ? attn_bf16_kernel<D, NQ, NW, KS, MODE_NONE>
