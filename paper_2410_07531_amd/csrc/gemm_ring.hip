@@ -529,7 +529,7 @@ int launch_ring_depth(const void* A, const void* W, void* C, const void* R, int 
 // kernels compete, adjusted so that none of 622 products of either type for which all forms were timed (16 to 4096 rows, 256 to
 // 14336 columns, K of 512 to 14336) runs more than 2 % slower than with the 256-row kernel: fp8 128 x 64 at 280 chose this
 // form where it was up to 28 % slower (700 x 8192 x 8192 68 us against 53, 300 x 14336 x 4096 36.5 against 30.5).  Rows on
-// 4 bytes, which have no other matrix-core kernel, are fitted to 300 products of either layout instead (see kRingRow4), fp32 to 1600 (see f32_tiles_ns).
+// 4 bytes, which have no other matrix-core kernel, are fitted to 300 products of either layout instead (see there), fp32 to 1600 (see f32_tiles_ns).
 // Register counts leave room
 // for three 24-register RNG waves on every SIMD (a 256 x 128 tile with eight waves, 250 registers each, was up to
 // 8 % faster than the 256-row kernel at 2048 x 4096 x 4096, but its workgroups could not be placed beside an RNG
@@ -539,7 +539,9 @@ struct RingVariant {
     int bm, bn;
     float slot_ns;
     int (*launch)(const void*, const void*, void*, const void*, int, int, int, float, hipStream_t);
+    int min_slots;                // taken from this many slots of k on
 };
+constexpr int kRow4Slots = 8;
 const RingVariant kRing[] = {
     //                                                                TM TN WM WN KS SUB KN   VEC ST
     {ROV_BF16, 0, 16, 4, 64, 32, 125.f, launch_ring_depth<ROV_BF16, 4, 2, 1, 1, 4, 2, false, 16, 5, 3>},
@@ -567,27 +569,21 @@ const RingVariant kRing[] = {
     {ROV_F32, 1, 16, 2, 64, 64, 510.f, launch_ring<ROV_F32, 1, 1, 2, 2, 2, 1, true, 16, 3>},
     {ROV_F32, 1, 4, 4, 32, 32, 154.f, launch_ring<ROV_F32, 1, 1, 1, 1, 4, 1, true, 4, 4>},
     {ROV_F32, 1, 4, 2, 64, 64, 510.f, launch_ring<ROV_F32, 1, 1, 2, 2, 2, 1, true, 4, 4>},
+    // Rows on 4 bytes, longer sums: with 16-byte loads there too (see VEC) they take the larger tiles as well, from kRow4Slots slots of k on
+    // (shorter sums are the output's time: the 64 x 64 tiles above).  Slot times fitted, with those of the 4-byte rows above, to 300 products of
+    // either layout (32 to 6000 rows, 32 to 8000 columns, K of 2 to 14336): the choice is 0.4 % (0.7 % [K, N]) above the best
+    // form on average, 15 % at worst.  With 4-byte loads and 64 x 64 tiles alone the same products took 1.56 (1.48) times as long:
+    // 770 x 4090 x 14336 [K, N] 274 -> 107 us, 1000 x 2002 x 2002 28 -> 19, 200 x 1000 x 4090 26 -> 11.
+    {ROV_BF16, 0, 4, 4, 64, 32, 245.f, launch_ring_depth<ROV_BF16, 4, 2, 1, 1, 4, 2, false, 4, 5, 3>, kRow4Slots},
+    {ROV_BF16, 0, 4, 2, 128, 64, 545.f, launch_ring<ROV_BF16, 4, 2, 2, 2, 2, 2, false, 4, 3>, kRow4Slots},
+    {ROV_BF16, 0, 4, 2, 128, 128, 869.f, launch_ring<ROV_BF16, 4, 4, 2, 2, 2, 1, false, 4, 4>, kRow4Slots},
+    {ROV_BF16, 0, 4, 2, 192, 128, 1130.f, launch_ring<ROV_BF16, 6, 4, 2, 2, 2, 1, false, 4, 4>, kRow4Slots},
+    {ROV_BF16, 1, 4, 4, 64, 64, 340.f, launch_ring<ROV_BF16, 4, 2, 1, 2, 4, 2, true, 4, 4>, kRow4Slots},
+    {ROV_BF16, 1, 4, 2, 128, 64, 575.f, launch_ring_depth<ROV_BF16, 4, 2, 2, 2, 2, 1, true, 4, 6, 3>, kRow4Slots},
+    {ROV_BF16, 1, 4, 2, 128, 128, 750.f, launch_ring<ROV_BF16, 4, 4, 2, 2, 2, 1, true, 4, 4>, kRow4Slots},
+    {ROV_BF16, 1, 4, 2, 192, 128, 1016.f, launch_ring<ROV_BF16, 6, 4, 2, 2, 2, 1, true, 4, 4>, kRow4Slots},
 };
 constexpr int kRingVariants = (int)(sizeof(kRing) / sizeof(kRing[0]));
-
-// bf16 products whose rows start on 4 bytes only: with 16-byte loads there too (see VEC) they take the larger tiles as well, from
-// kRow4Slots slots of k on (shorter sums are the output's time: the 64 x 64 tiles above).  Slot times fitted, with those of the 4-byte rows
-// above, to 300 products of either layout (32 to 6000 rows, 32 to 8000 columns, K of 2 to 14336): the choice is 0.4 % (0.7 % [K, N]) above the best
-// form on average, 15 % at worst.  With 4-byte loads and 64 x 64 tiles alone the same products took 1.56 (1.48) times as long:
-// 770 x 4090 x 14336 [K, N] 274 -> 107 us, 1000 x 2002 x 2002 28 -> 19, 200 x 1000 x 4090 26 -> 11.
-constexpr int kRow4Slots = 8;
-const RingVariant kRingRow4[] = {
-    {ROV_BF16, 0, /* rows on */ 4, 4, 64, 32, 245.f, launch_ring_depth<ROV_BF16, 4, 2, 1, 1, 4, 2, false, 4, 5, 3>},
-    {ROV_BF16, 0, /* rows on */ 4, 2, 128, 64, 545.f, launch_ring<ROV_BF16, 4, 2, 2, 2, 2, 2, false, 4, 3>},
-    {ROV_BF16, 0, /* rows on */ 4, 2, 128, 128, 869.f, launch_ring<ROV_BF16, 4, 4, 2, 2, 2, 1, false, 4, 4>},
-    {ROV_BF16, 0, /* rows on */ 4, 2, 192, 128, 1130.f, launch_ring<ROV_BF16, 6, 4, 2, 2, 2, 1, false, 4, 4>},
-    {ROV_BF16, 1, /* rows on */ 4, 4, 64, 64, 340.f, launch_ring<ROV_BF16, 4, 2, 1, 2, 4, 2, true, 4, 4>},
-    {ROV_BF16, 1, /* rows on */ 4, 2, 128, 64, 575.f, launch_ring_depth<ROV_BF16, 4, 2, 2, 2, 2, 1, true, 4, 6, 3>},
-    {ROV_BF16, 1, /* rows on */ 4, 2, 128, 128, 750.f, launch_ring<ROV_BF16, 4, 4, 2, 2, 2, 1, true, 4, 4>},
-    {ROV_BF16, 1, /* rows on */ 4, 2, 192, 128, 1016.f, launch_ring<ROV_BF16, 6, 4, 2, 2, 2, 1, true, 4, 4>},
-};
-constexpr int kRingAll = kRingVariants + (int)(sizeof(kRingRow4) / sizeof(kRingRow4[0]));
-inline const RingVariant& ring_form(int v) { return v < kRingVariants ? kRing[v] : kRingRow4[v - kRingVariants]; }
 
 }  // namespace
 
@@ -627,9 +623,9 @@ int ring_variant(int M, int N, int K, int dtype, int transB, bool same_order, do
     const bool split = !same_order || K >= 2048;
     int best = -1;
     double best_ns = 0.0;
-    for (int v = 0; v < (slots >= kRow4Slots ? kRingAll : kRingVariants); ++v) {
-        const RingVariant& r = ring_form(v);
-        if (r.dtype != dtype || (r.kn != 0) != kn || r.vec != vec || (r.kparts > 1 && !split)) continue;
+    for (int v = 0; v < kRingVariants; ++v) {
+        const RingVariant& r = kRing[v];
+        if (slots < r.min_slots || r.dtype != dtype || (r.kn != 0) != kn || r.vec != vec || (r.kparts > 1 && !split)) continue;
         const long long tiles = (long long)((M + r.bm - 1) / r.bm) * ((N + r.bn - 1) / r.bn);
         if (tiles > 0x7FFFFFFFLL) continue;
         const double t = dtype == ROV_F32 ? f32_tiles_ns(tiles, slots, r.slot_ns, r.bm) : gemm_tiles_ns(tiles, slots, r.slot_ns);
@@ -640,13 +636,13 @@ int ring_variant(int M, int N, int K, int dtype, int transB, bool same_order, do
 }
 
 void ring_variant_tile(int variant, int tile[4]) {
-    const RingVariant& r = ring_form(variant);
+    const RingVariant& r = kRing[variant];
     tile[0] = r.bm; tile[1] = r.bn; tile[2] = r.kparts; tile[3] = r.vec;
 }
 
 int launch_gemm_ring(int variant, const void* A, const void* W, void* C, const void* R, int M, int N, int K, float alpha,
                      hipStream_t stream) {
-    if (variant < 0 || variant >= kRingAll) return ROV_ERR_INVALID;
-    return ring_form(variant).launch(A, W, C, R, M, N, K, alpha, stream);
+    if (variant < 0 || variant >= kRingVariants) return ROV_ERR_INVALID;
+    return kRing[variant].launch(A, W, C, R, M, N, K, alpha, stream);
 }
 }  // namespace rov

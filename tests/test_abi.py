@@ -102,18 +102,19 @@ def test_kernel_choice_queries():
 
 
 def test_small_tile_cases_reach_every_form():
-    # every row of the small-tile GEMM's parity test names the tile that it reaches (the test asserts it); together they are
+    # every row of the small-tile GEMM's parity tests names the tile that it reaches (the tests assert it); together they are
     # all the forms that the launch chooses from
     import test_gpu_gemm_ring as T
+    import test_gpu_gemm_row4 as T4
     seen = set()
-    for dtype, M, N, K, transB, tile in T.CASES:
+    for dtype, M, N, K, transB, tile in T.CASES + [("bf16",) + case for case in T4.CASES]:
         assert binding.gemm_tile(M, N, K, T.DTYPES[dtype], transB) == (binding.GEMM_SMALL_TILES,) + tile, (dtype, M, N, K)
         seen.add((dtype, transB) + tile)
     src = open(os.path.join(ROOT, "paper_2410_07531_amd", "csrc", "gemm_ring.hip")).read()
     table = re.findall(r"^\s*\{ROV_(BF16|FP8_E4M3|F32), (\d), (\d+), (\d), (\d+), (\d+), ", src, flags=re.M)
     forms = {({"BF16": "bf16", "FP8_E4M3": "fp8", "F32": "f32"}[t], kn == "0", int(bm), int(bn), int(ks), int(vec))
              for t, kn, vec, ks, bm, bn in table}
-    assert len(forms) == len(table) == 25 and seen == forms, seen ^ forms
+    assert len(forms) == len(table) == 33 and seen == forms, seen ^ forms
 
 
 def test_small_tiles_only_where_they_are_sooner():

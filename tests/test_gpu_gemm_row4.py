@@ -38,7 +38,7 @@ def test_row4_cases_reach_every_form():
         assert rov.gemm_tile(M, N, K, rov.BF16, transB) == (rov.GEMM_SMALL_TILES,) + tile, (M, N, K, transB)
         seen.add((transB,) + tile)
     src = open(os.path.join(ROOT, "paper_2410_07531_amd", "csrc", "gemm_ring.hip")).read()
-    table = re.findall(r"^\s*\{ROV_BF16, (\d), /\* rows on \*/ (\d+), (\d), (\d+), (\d+), ", src, flags=re.M)
+    table = re.findall(r"^\s*\{ROV_BF16, (\d), (\d+), (\d), (\d+), (\d+), .*, kRow4Slots\},$", src, flags=re.M)
     forms = {(kn == "0", int(bm), int(bn), int(ks), int(row)) for kn, row, ks, bm, bn in table}
     assert len(forms) == len(table) == 8 and seen == forms, seen ^ forms
 
@@ -61,6 +61,7 @@ def _behind(t, fill, n=4096):
 @pytest.mark.parametrize("M,N,K,transB,tile", CASES)
 def test_row4_tiles_match_oracle(M, N, K, transB, tile):
     print("gemm row4", M, N, K, transB, tile, flush=True)
+    assert rov.gemm_tile(M, N, K, rov.BF16, transB) == (rov.GEMM_SMALL_TILES,) + tile
     A, W = _operands(M, N, K, transB)
     frame = torch.full((M * N + 128,), 3.0, dtype=torch.bfloat16, device="cuda")
     C = frame[64:64 + M * N].view(M, N)
