@@ -228,16 +228,17 @@ __global__ __launch_bounds__(64 * WM * WN * KS) void gemm_ring_kernel(const Ring
     // the kernel places its vmcnt waits itself.  M0 is only set by compiled code right before its own uses.
     // Past the end of the walk the range is empty and the scalar offset zero (the check takes it off the size):
     // no memory access, and the counter's arithmetic holds.
-    // In the loop of the fp32 and [K, N] forms the offset beyond k is worked out behind a branch: its edges keep the loads between the
-    // MFMAs where they were put (2764 x 392 x 4096 fp32 88.5 us, with a select 100; 1024 x 4096 x 4096 [K, N] 38.3, 38.8).
-    // The others are 0.5 to 2 % faster with the select.
+    // In the loop of the fp32 forms and the widest [K, N] ones the offset beyond k is worked out behind a branch: its edges keep the loads
+    // between the MFMAs where they were put (2764 x 392 x 4096 fp32 88.5 us, with a select 100; [K, N] 128 x 128 tiles 1 to 2 % sooner).
+    // The others are up to 2.5 % faster with the select (timed at 750 products, weights in L2 and from HBM).
+    constexpr bool kBranch = DT == ROV_F32 || (KN && VEC == 16 && BN == 128);
     auto issue = [&](int q, auto in_loop) __attribute__((always_inline)) {
         const bool is_w = load_is_w(q);
         const uint32_t dst = lds_base + (uint32_t)(f_slot * kSlot + (q * NW + wave) * 1024);
         i32x4 rs = is_w ? rsrc_w : rsrc_a;
         rs[2] = f_left > 0 ? rs[2] : 0;
         uint32_t vo = voff[q];
-        if (!decltype(in_loop)::value || (DT != ROV_F32 && !KN)) vo = ragged && f_st == ns - 1 ? vend[q] : vo;
+        if (!decltype(in_loop)::value || !kBranch) vo = ragged && f_st == ns - 1 ? vend[q] : vo;
         else if (ragged && f_st == ns - 1) vo = lane_k(q) < krem ? vo : (is_w ? bytes_w : bytes_a);
         const uint32_t so = KN && is_w ? (uint32_t)f_st * (uint32_t)KR * ld_w : (uint32_t)f_st * (uint32_t)(SUB * kSlotRow);
         const int sdst = __builtin_amdgcn_readfirstlane((int)dst), sso = __builtin_amdgcn_readfirstlane((int)so);
