@@ -134,9 +134,11 @@ def trace_by_kind(rov):
 # ---------------------------------------------------------------------------------------------- RNG ceiling
 def valu_probe_ceiling(torch, rov, sync):
     """Issue cost (ns per wave64 instruction per SIMD, 8 waves per SIMD) of the instruction kinds the
-    mask kernel is made of, measured now on this device, and the call rate its instruction mix could
-    reach at those costs: 18 wide multiply-adds, 15 three-input xors, 4 + 1 simple ops, 4 compare +
-    lane-write pairs and 4 more lane writes (priced as a simple op each) per call."""
+    mask kernel is made of, measured now on this device, and the call rate that the sum of its instruction
+    mix at those costs gives: 18 wide multiply-adds, 15 three-input xors, 4 + 1 simple ops and 4 compares,
+    each with the one-lane move of its ballot (priced as the probed compare + lane write), per call.  An
+    estimate, no bound: in the kernel the scalar unit and the multiplier overlap work that the
+    single-class streams serialise."""
     L = rov.load()
     props = torch.cuda.get_device_properties(0)
     n_simd = props.multi_processor_count * 4
@@ -162,7 +164,7 @@ def valu_probe_ceiling(torch, rov, sync):
         ns[name] = min(ts) * 1e6 / (wave_insts / n_simd)          # ns per wave-instruction per SIMD
     add = ns["add"]
     mad, xor3, cmpw = ns["mad64_plus_add"] - add, ns["xor3"], ns["cmp_writelane_plus_add"] - add
-    ns_per_wave_call = 18 * mad + 15 * xor3 + 5 * add + 4 * cmpw   # (a one-lane move priced as a lane write)
+    ns_per_wave_call = 18 * mad + 15 * xor3 + 5 * add + 4 * cmpw
     gcalls = 64.0 * n_simd / ns_per_wave_call                     # 64 calls per wave-call, per ns -> Gcalls/s
     return {"ns_per_wave_instruction_per_simd": {"mad_u64_u32": mad, "bitop3_xor3": xor3, "add": add,
                                                  "cmp_plus_writelane": cmpw},
@@ -179,9 +181,10 @@ def rng_roofline(ncalls, t_ms, probe):
             "peak_derivation": "peak = 256 CU x 4 SIMD x 32 lanes/clk x 2.4 GHz (the lane-instruction rate behind the "
                                "published 157.3 TFLOP/s fp32); achieved = calls/s x 46.5 VALU instructions issued per call "
                                "(SQ_INSTS_VALU per wave-call). Integer instructions cannot reach that peak on this chip "
-                               "(measured: add 58 T/s, xor3 37 T/s, mad_u64_u32 28 T/s), so frac_of_probe_ceiling - the call "
-                               "rate against what this kernel's own instruction mix costs at the probed issue rates - is "
-                               "the figure that says how close the kernel is to the hardware",
+                               "(measured: add 58 T/s, xor3 37 T/s, mad_u64_u32 28 T/s).  frac_of_probe_ceiling is the call "
+                               "rate against the sum of this kernel's own instruction mix at the probed issue rates: an "
+                               "estimate, above 1 where the kernel overlaps classes that the probes run one by one; "
+                               "valu_busy_counter says how full the issue slots are",
             "frac_of_probe_ceiling": (calls_s / 1e9) / probe["ceiling_gcalls_s"] if probe else None,
             "probe": probe,
             "valu_busy_counter": RNG_VALU_BUSY_COUNTER,

@@ -14,7 +14,7 @@ Chip properties used (`Chip`), with where each comes from:
   * matrix-instruction passes (16 cycles for MFMA 16x16x32 bf16, 32 for 32x32x16 bf16 and for the
     fp8 16x16x128: the published peak divided by the flops of one instruction);
   * the cycles a 16-byte-per-lane LDS-DMA load keeps its wave from issuing matrix instructions
-    (18; loads aimed outside their buffer, zero operands, round-1 measurement);
+    (18; loads aimed outside their buffer, zero operands);
   * the clock the chip holds: 2.21 GHz under VALU-only load and 0.62 GHz less per unit of
     matrix-core duty (the board's power limit; GRBM_GUI_ACTIVE / duration of the RNG kernel, the
     8192^3 GEMM and the fused attention kernel), never above 2.4 GHz;
@@ -91,14 +91,14 @@ def philox_cycles_per_call(chip: Chip, rounds: int = 10, bits: int = 32) -> floa
     """VALU issue cycles one wave64 spends per Philox call, from the mask kernel's instruction mix:
     per round two 32x32->64 multiplies and two three-input xors (the first two rounds save two
     multiplies and use plain xors: the upper counter words are zero and one product is
-    wave-uniform); per output field one compare-to-ballot and the ballot's way into the lane that stores
-    it, priced as two lane writes (the kernel's one 64-bit move under a one-lane EXEC costs about 5 %
-    of the call less than that), plus a field extract when fields are narrower than a word."""
+    wave-uniform); per output field one compare-to-ballot and one 64-bit move of the ballot into the lane
+    that stores it, priced as the probe's pair of compare and lane write, plus a field extract when fields
+    are narrower than a word.  (Masks whose last tiles are cut take two lane writes in place of the move.)"""
     mads = 2 * rounds - 2
     xors = 2 * rounds - 5
     simple = 4 + 1                                     # plain xors of the first rounds, counter add
     fields = 4 * (32 // bits)
-    per_field = chip.cyc_cmp_writelane + chip.cyc_simple + (chip.cyc_simple if bits < 32 else 0.0)
+    per_field = chip.cyc_cmp_writelane + (chip.cyc_simple if bits < 32 else 0.0)
     return mads * chip.cyc_mad64 + xors * chip.cyc_xor3 + simple * chip.cyc_simple + fields * per_field
 
 
@@ -187,8 +187,8 @@ def t_attention(chip: Chip, B: int, H: int, S: int, d: int, mode: str = "mask", 
     d = 128 kernel's counts per 64-key tile and wave (32 query rows): 32 MFMA 32x32x16; 33 exp2, 32
     multiply-adds into the exponent, 32 adds into the row sum, 16 three-input maxima, 16 packs to
     bf16 and 12 others; mode "mask": 32 selects more and the uncovered part of the scalar keep-word
-    loads' latency; mode "fused": 8 Philox calls per lane with a plain compare per element in place of
-    ballot and lane writes.  Each wave reads the K and V tile (32 KB) from LDS."""
+    loads' latency; mode "fused": 8 Philox calls per lane, each with its own 64-bit call number (4 simple
+    operations), and a plain compare per element in place of ballots and moves.  Each wave reads the K and V tile (32 KB) from LDS."""
     tiles = float(B) * H * (S / 32.0) * (S / 64.0) * (0.5 + 0.5 / max(S // 256, 1) if causal else 1.0)
     scale = d / 128.0
     mfma = 32.0 * scale * chip.cyc_mfma_32x32x16_bf16
@@ -198,7 +198,7 @@ def t_attention(chip: Chip, B: int, H: int, S: int, d: int, mode: str = "mask", 
         valu += 32 * chip.cyc_simple
         stall = chip.cyc_keep_word_stall / 2.0
     elif mode == "fused":
-        valu += 8 * (philox_cycles_per_call(chip, 10, 32) - 4.0 * chip.cyc_cmp_writelane) + 32 * 2 * chip.cyc_simple
+        valu += 8 * (philox_cycles_per_call(chip, 10, 32) - 4.0 * chip.cyc_cmp_writelane + 4.0 * chip.cyc_simple) + 32 * 2 * chip.cyc_simple
     per_tile = mfma + valu + stall                       # the two pipes do not overlap (see module text)
     f = clock_hz(chip, mfma / per_tile)
     simd = tiles * per_tile / (_simd_count(chip) * f)
@@ -278,23 +278,24 @@ def region(chip: Chip, B: int, H: int, S: int, d: int, hidden: int, ffn: int) ->
 
 def validation(chip: Chip = MI355X) -> Dict[str, Tuple[float, float]]:
     """(model ms, measured ms) for the kernels and blocks measured on one box in one bench.py run
-    (stand-alone kernels and the S = 16384 Llama-3-8B block).  None of these shapes entered a chip
+    (stand-alone kernels and the S = 16384 Llama-3-8B block; the 2048-token mask back to back in a
+    loop of its own).  None of these shapes entered a chip
     constant; the interference pair was calibrated on the S = 2048 layer step."""
     ms = 1e3
     b = block(chip, 1, 16384, 32, 8, 128, 4096, 14336)
     return {
-        "rng 32x16384^2 bits": (t_rng(chip, 1, 32, 16384)["time"] * ms, 2.80),
-        "rng 32x2048^2 bits": (t_rng(chip, 1, 32, 2048)["time"] * ms, 0.0495),
-        "attention S=16384 none": (t_attention(chip, 1, 32, 16384, 128, "none")["time"] * ms, 3.72),
-        "attention S=16384 mask": (t_attention(chip, 1, 32, 16384, 128, "mask")["time"] * ms, 4.40),
-        "attention S=16384 fused": (t_attention(chip, 1, 32, 16384, 128, "fused")["time"] * ms, 7.05),
-        "gemm 16384x6144x4096": (t_gemm(chip, 16384, 6144, 4096)["time"] * ms, 0.64),
-        "gemm 16384x4096x4096": (t_gemm(chip, 16384, 4096, 4096)["time"] * ms, 0.455),
-        "gemm swiglu 16384x14336x4096": (t_gemm(chip, 16384, 14336, 4096, dual=True)["time"] * ms, 2.67),
-        "gemm 16384x4096x14336": (t_gemm(chip, 16384, 4096, 14336)["time"] * ms, 1.40),
-        "gemm 2048x14336x4096": (t_gemm(chip, 2048, 14336, 4096)["time"] * ms, 0.185),
-        "gemm fp8 8192x8192x8192": (t_gemm(chip, 8192, 8192, 8192, esz=1)["time"] * ms, 0.385),
-        "block S=16384 sequential": (b["baseline"] * ms, 13.17),
-        "block S=16384 fused": (b["fusion"] * ms, 12.73),
-        "block S=16384 overlap": (b["overlap"] * ms, 10.85),
+        "rng 32x16384^2 bits": (t_rng(chip, 1, 32, 16384)["time"] * ms, 2.61),
+        "rng 32x2048^2 bits": (t_rng(chip, 1, 32, 2048)["time"] * ms, 0.0462),
+        "attention S=16384 none": (t_attention(chip, 1, 32, 16384, 128, "none")["time"] * ms, 3.67),
+        "attention S=16384 mask": (t_attention(chip, 1, 32, 16384, 128, "mask")["time"] * ms, 4.29),
+        "attention S=16384 fused": (t_attention(chip, 1, 32, 16384, 128, "fused")["time"] * ms, 7.25),
+        "gemm 16384x6144x4096": (t_gemm(chip, 16384, 6144, 4096)["time"] * ms, 0.633),
+        "gemm 16384x4096x4096": (t_gemm(chip, 16384, 4096, 4096)["time"] * ms, 0.457),
+        "gemm swiglu 16384x14336x4096": (t_gemm(chip, 16384, 14336, 4096, dual=True)["time"] * ms, 2.64),
+        "gemm 16384x4096x14336": (t_gemm(chip, 16384, 4096, 14336)["time"] * ms, 1.37),
+        "gemm 2048x14336x4096": (t_gemm(chip, 2048, 14336, 4096)["time"] * ms, 0.177),
+        "gemm fp8 8192x8192x8192": (t_gemm(chip, 8192, 8192, 8192, esz=1)["time"] * ms, 0.450),
+        "block S=16384 sequential": (b["baseline"] * ms, 12.76),
+        "block S=16384 fused": (b["fusion"] * ms, 12.62),
+        "block S=16384 overlap": (b["overlap"] * ms, 10.58),
     }
