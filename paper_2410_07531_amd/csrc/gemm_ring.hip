@@ -228,10 +228,11 @@ __global__ __launch_bounds__(64 * WM * WN * KS) void gemm_ring_kernel(const Ring
     // the kernel places its vmcnt waits itself.  M0 is only set by compiled code right before its own uses.
     // Past the end of the walk the range is empty and the scalar offset zero (the check takes it off the size):
     // no memory access, and the counter's arithmetic holds.
-    // In the loop of the fp32 forms and the widest [K, N] ones the offset beyond k is worked out behind a branch: its edges keep the loads
-    // between the MFMAs where they were put (2764 x 392 x 4096 fp32 88.5 us, with a select 100; [K, N] 128 x 128 tiles 1 to 2 % sooner).
-    // The others are up to 2.5 % faster with the select (timed at 750 products, weights in L2 and from HBM).
-    constexpr bool kBranch = DT == ROV_F32 || (KN && VEC == 16 && BN == 128);
+    // In the loop of the fp32 forms, the widest [K, N] ones and fp8's 128 x 64 the offset beyond k is worked out behind a branch: its edges
+    // keep the loads between the MFMAs where they were put (2764 x 392 x 4096 fp32 88.5 us, with a select 100; [K, N] 128 x 128 tiles 1 to 2 %
+    // sooner; fp8 92 x 10240 x 14336 34.1 us, with a select 34.8).  The others are up to 2.5 % faster with the select (timed at 750
+    // products, weights in L2 and from HBM; bf16 64 x 32 tiles at 280: 1 to 2 % at short sums, level from K = 2048 on).
+    constexpr bool kBranch = DT == ROV_F32 || (KN && VEC == 16 && BN == 128) || (DT == ROV_FP8_E4M3 && BM == 128 && BN == 64);
     auto issue = [&](int q, auto in_loop) __attribute__((always_inline)) {
         const bool is_w = load_is_w(q);
         const uint32_t dst = lds_base + (uint32_t)(f_slot * kSlot + (q * NW + wave) * 1024);
