@@ -173,7 +173,7 @@ def valu_probe_ceiling(torch, rov, sync):
 
 def rng_roofline(ncalls, t_ms, probe):
     """The VALU roofline of the stand-alone mask kernel in three forms: issued instructions against the nominal
-    lane-instruction peak, the call rate against the probed instruction-mix ceiling, and the counter reading."""
+    lane-instruction peak, the call rate against the sum of its mix at the probed costs, and the counter reading."""
     calls_s = ncalls / (t_ms * 1e-3)
     issued = calls_s * VALU_INSTS_PER_CALL / 1e12
     return {"bound": "alu", "unit": "T int32 lane-instructions/s",
@@ -194,7 +194,7 @@ def rng_roofline(ncalls, t_ms, probe):
             "traffic": TRAFFIC["mask_kernel"]}
 
 
-# ---------------------------------------------------------------------------------------------- block (configs[4])
+# ---------------------------------------------------------------------------------------------- block (8B-shaped, 16384 tokens)
 class Block:
     """The Llama-3-8B block workload on the device: weights, input, two mask buffers, workspace."""
 
