@@ -311,13 +311,20 @@ __global__ __launch_bounds__(64 * WM * WN * KS) void gemm_ring_kernel(const Ring
         __syncthreads();
     };
 
-    typename TR::acc_t acc[TN][TM];
+    // fp32 with two parts of k: every other unit has its own sums, so that a chain of additions is as long as with four parts (relative
+    // error against 64 bits at K = 3887: 5.6e-7, that of the 32 x 32 tiles; with one set 7.9e-7).  16 registers more, 0.07 us a product.
+    constexpr int NACC = DT == ROV_F32 && KS == 2 ? 2 : 1;
+    static_assert(NACC == 1 || UW % 2 == 0, "a slot's units alternate");
+    typename TR::acc_t accs[NACC][TN][TM];
 #pragma unroll
-    for (int j = 0; j < TN; ++j)
+    for (int a = 0; a < NACC; ++a)
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
+        for (int j = 0; j < TN; ++j)
 #pragma unroll
-            for (int e = 0; e < ACC; ++e) acc[j][i][e] = 0.0f;
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int e = 0; e < ACC; ++e) accs[a][j][i][e] = 0.0f;
+    auto& acc = accs[0];
 
     // vmcnt(n) alone
     auto wait_loads = [](auto n) {
@@ -342,7 +349,7 @@ __global__ __launch_bounds__(64 * WM * WN * KS) void gemm_ring_kernel(const Ring
 #pragma unroll
         for (int m = 0; m < MU; ++m) {
             const int j = m / TM, i = m % TM;
-            acc[j][i] = mfma(fw[par][j], fa[par][i], acc[j][i]);
+            accs[par % NACC][j][i] = mfma(fw[par][j], fa[par][i], accs[par % NACC][j][i]);
             if (pos0 >= 0) {
 #pragma unroll
                 for (int q = 0; q < L; ++q)
@@ -402,6 +409,12 @@ __global__ __launch_bounds__(64 * WM * WN * KS) void gemm_ring_kernel(const Ring
         }
     }
     wait_loads(std::integral_constant<int, 0>{});   // no LDS load may outlive the loop
+    if constexpr (NACC == 2) {
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int i = 0; i < TM; ++i) acc[j][i] += accs[1][j][i];
+    }
 
     // Block (i, j), register group g: the lane holds row fr of the block's A rows and four consecutive output
     // columns.  WHOLE: every row starts on four values, and its columns come in whole groups of four.

@@ -176,6 +176,23 @@ def test_fp32_product_keeps_infinities_and_nan_in_their_rows():
     assert torch.equal(torch.nan_to_num(C, nan=-1.0), torch.nan_to_num(exp, nan=-1.0))
 
 
+@pytest.mark.parametrize("K", [3840, 3842])
+@pytest.mark.parametrize("transB", [True, False])
+def test_fp32_tiles_of_both_sizes_round_alike(K, transB):
+    # The error of a long sum grows with the root of its chain of additions: k / 4 terms with either tile.  Over 65536 results and more its norm
+    # scatters by under 2 %; chains of k / 2 would show as a ratio of 1.41.
+    err = {}
+    for M, N, tile in ((256, 256, (32, 32, 4)), (2048, 2048, (64, 64, 2))):
+        assert rov.gemm_tile(M, N, K, rov.F32, transB)[1:4] == tile
+        g = torch.Generator("cuda").manual_seed(K + M)
+        A = torch.randn(M, K, device="cuda", generator=g)
+        W = torch.randn(*((N, K) if transB else (K, N)), device="cuda", generator=g)
+        ref = A.double() @ (W.double().t().contiguous() if transB else W.double())
+        C = rov.gemm(A, W, transB=transB)
+        err[tile[0]] = float((C.double() - ref).norm() / ref.norm())
+    assert err[64] <= 1.15 * err[32], err
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "fp8"])
 @pytest.mark.parametrize("M,N,K", [
     (300, 14336, 128),       # ragged rows
